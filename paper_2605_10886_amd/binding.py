@@ -1,9 +1,14 @@
-"""Thin ctypes binding of libloka.so (the C ABI declared in include/loka.h).
+"""Thin binding of libloka.so (the C ABI declared in include/loka.h).
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  PyTorch is used for device memory and the current HIP stream.  There is
 no CPU fallback: if the shared library is missing or was not built, every call
 raises.
+
+The per-step calls (quantize, GEMM + norm in its forms, BF16 reference, probe,
+tracker) marshal in native code (csrc/host_binding.cpp, module _host): a small
+layer's two launches take less GPU time than the same marshalling through ctypes.
+Queries, the dispatcher and the test aids go through ctypes (lib()).
 """
 from __future__ import annotations
 
@@ -118,6 +123,20 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def _host():
+    """The native marshalling module (built beside libloka.so, which it links)."""
+    global _native
+    if _native is None:
+        lib()
+        from . import _host as m
+        m.set_error(LokaError)
+        _native = m
+    return _native
+
+
 def status_string(status: int) -> str:
     return lib().loka_status_string(int(status)).decode()
 
@@ -145,18 +164,7 @@ def loka_scale_count(mode: int, rows: int, cols: int) -> int:
 
 def loka_quantize(x: torch.Tensor, mode: int, transpose_out: bool = False):
     """x bf16 [rows, cols] (device) -> (codes uint8 [rows, cols] or [cols, rows], scales fp32)."""
-    assert x.dtype == torch.bfloat16 and x.dim() == 2 and x.stride(1) == 1
-    rows, cols = x.shape
-    n = loka_scale_count(mode, rows, cols)
-    if n < 0:
-        raise LokaError(LOKA_ERR_SHAPE, "loka_scale_count")
-    q = torch.empty((cols, rows) if transpose_out else (rows, cols), dtype=torch.uint8, device=x.device)
-    s = torch.empty(n, dtype=torch.float32, device=x.device)
-    nws = lib().loka_quantize_workspace(mode, rows, cols, int(transpose_out))
-    ws = _ws(nws, x.device)
-    _check(lib().loka_quantize(_ptr(x), rows, cols, x.stride(0), mode, int(transpose_out), _ptr(q), _ptr(s), _ptr(ws),
-                               ws.numel(), _stream()), "loka_quantize")
-    return q, s
+    return (_native or _host()).quantize(x, mode, transpose_out)
 
 
 def loka_e4m3_from_f32(t: torch.Tensor) -> torch.Tensor:
@@ -208,49 +216,19 @@ def loka_default_variant(desc: GemmDesc) -> int:
 def loka_fp8_gemm_norm(desc: GemmDesc, xq, sx, wq, sw, gamma=None, beta=None, want_y: bool = False, out=None, y=None,
                        workspace=None):
     """Returns (O bf16 [batch*M, N], Y fp32 [batch*M, N] or None)."""
-    rows = desc.batch * desc.M
-    dev = xq.device
-    if out is None:
-        out = torch.empty((rows, desc.N), dtype=torch.bfloat16, device=dev)
-    if want_y and y is None:
-        y = torch.empty((rows, desc.N), dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = _ws(lib().loka_fp8_gemm_norm_workspace(byref(desc)), dev)
-    _check(lib().loka_fp8_gemm_norm(byref(desc), _ptr(xq), _ptr(sx), _ptr(wq), _ptr(sw), _ptr(gamma), _ptr(beta),
-                                    _ptr(out), _ptr(y), _ptr(workspace), workspace.numel(), _stream()),
-           "loka_fp8_gemm_norm")
-    return out, y
+    return (_native or _host()).gemm_norm(desc, xq, sx, wq, sw, gamma, beta, want_y, out, y, workspace)
 
 
 def loka_fp8_linear_norm(desc: GemmDesc, x, wq, sw, gamma=None, beta=None, want_y: bool = False, want_sx: bool = False,
                          out=None):
     """Rowwise quantization of bf16 x fused into the GEMM + norm.  Returns (O bf16, Y fp32 or None, sx or None)."""
-    rows = desc.batch * desc.M
-    dev = x.device
-    if out is None:
-        out = torch.empty((rows, desc.N), dtype=torch.bfloat16, device=dev)
-    y = torch.empty((rows, desc.N), dtype=torch.float32, device=dev) if want_y else None
-    sx = torch.empty(rows, dtype=torch.float32, device=dev) if want_sx else None
-    _check(lib().loka_fp8_linear_norm(byref(desc), _ptr(x), _ptr(wq), _ptr(sw), _ptr(gamma), _ptr(beta), _ptr(out), _ptr(y),
-                                      _ptr(sx), _stream()), "loka_fp8_linear_norm")
-    return out, y, sx
+    return (_native or _host()).linear_norm(desc, x, wq, sw, gamma, beta, want_y, want_sx, out)
 
 
 def loka_fp8_linear_norm_xq(desc: GemmDesc, x, wq, sw, gamma=None, beta=None, want_y: bool = False, out=None, xq=None, sx=None):
     """One launch: every workgroup quantizes the rows it consumes (rowwise), then GEMM + norm.  Returns (O bf16, Y fp32 or
     None, xq codes, sx row scales)."""
-    rows = desc.batch * desc.M
-    dev = x.device
-    if out is None:
-        out = torch.empty((rows, desc.N), dtype=torch.bfloat16, device=dev)
-    if xq is None:
-        xq = torch.empty((rows, desc.K), dtype=torch.uint8, device=dev)
-    if sx is None:
-        sx = torch.empty(rows, dtype=torch.float32, device=dev)
-    y = torch.empty((rows, desc.N), dtype=torch.float32, device=dev) if want_y else None
-    _check(lib().loka_fp8_linear_norm_xq(byref(desc), _ptr(x), _ptr(xq), _ptr(sx), _ptr(wq), _ptr(sw), _ptr(gamma), _ptr(beta),
-                                         _ptr(out), _ptr(y), _stream()), "loka_fp8_linear_norm_xq")
-    return out, y, xq, sx
+    return (_native or _host()).linear_norm_xq(desc, x, wq, sw, gamma, beta, want_y, out, xq, sx)
 
 
 def loka_fp8_gemm_norm_check(desc: GemmDesc, workspace) -> int:
@@ -280,51 +258,17 @@ def loka_test_set_spin_limit(polls: int) -> None:
 def loka_fp8_gemm_norm_fp8out(desc: GemmDesc, xq, sx, wq, sw, gamma=None, beta=None, want_y: bool = False, oq=None,
                               so=None, y=None, workspace=None):
     """Returns (codes uint8 [batch*M, N], row scales fp32 [batch*M], Y fp32 or None)."""
-    rows = desc.batch * desc.M
-    dev = xq.device
-    if oq is None:
-        oq = torch.empty((rows, desc.N), dtype=torch.uint8, device=dev)
-    if so is None:
-        so = torch.empty(rows, dtype=torch.float32, device=dev)
-    if want_y and y is None:
-        y = torch.empty((rows, desc.N), dtype=torch.float32, device=dev)
-    need = int(lib().loka_fp8_gemm_norm_fp8out_workspace(byref(desc)))
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    _check(lib().loka_fp8_gemm_norm_fp8out(byref(desc), _ptr(xq), _ptr(sx), _ptr(wq), _ptr(sw), _ptr(gamma), _ptr(beta),
-                                           _ptr(oq), _ptr(so), _ptr(y), _ptr(workspace),
-                                           0 if workspace is None else workspace.numel(), _stream()),
-           "loka_fp8_gemm_norm_fp8out")
-    return oq, so, y
+    return (_native or _host()).gemm_norm_fp8out(desc, xq, sx, wq, sw, gamma, beta, want_y, oq, so, y, workspace)
 
 
 def loka_bf16_gemm(desc: GemmDesc, x, w, yref=None, workspace=None):
     """x bf16 [batch*M, K], w bf16 [batch*K or K, N] -> Yref fp32 [batch*M, N]."""
-    dev = x.device
-    if yref is None:
-        yref = torch.empty((desc.batch * desc.M, desc.N), dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = _ws(lib().loka_bf16_gemm_workspace(byref(desc)), dev)
-    d = GemmDesc(desc.M, desc.N, desc.K, desc.batch, desc.strideX, desc.K * desc.N if desc.strideW else 0,
-                 desc.strideO, desc.x_mode, desc.w_mode, desc.norm, desc.eps, desc.variant)
-    _check(lib().loka_bf16_gemm(byref(d), _ptr(x), _ptr(w), _ptr(yref), _ptr(workspace), workspace.numel(), _stream()),
-           "loka_bf16_gemm")
-    return yref
+    return (_native or _host()).bf16_gemm(desc, x, w, yref, workspace)
 
 
 def loka_probe_error(y, yref, stats=None, rowmax=None, workspace=None, sync: bool = True):
     """Returns (stats dict [or the device tensor when sync=False], rowmax fp32 [M])."""
-    assert y.dtype == torch.float32 and yref.dtype == torch.float32 and y.shape == yref.shape
-    M, N = y.shape
-    dev = y.device
-    if stats is None:
-        stats = torch.empty(5, dtype=torch.float64, device=dev)
-    if rowmax is None:
-        rowmax = torch.empty(M, dtype=torch.float32, device=dev)
-    if workspace is None:
-        workspace = _ws(lib().loka_probe_error_workspace(M, N), dev)
-    _check(lib().loka_probe_error(_ptr(y), _ptr(yref), M, N, y.stride(0), _ptr(stats), _ptr(rowmax), _ptr(workspace),
-                                  workspace.numel(), _stream()), "loka_probe_error")
+    stats, rowmax = (_native or _host()).probe_error(y, yref, stats, rowmax, workspace)
     if not sync:
         return stats, rowmax
     v = stats.cpu().tolist()
@@ -333,12 +277,7 @@ def loka_probe_error(y, yref, stats=None, rowmax=None, workspace=None, sync: boo
 
 def loka_tracker_update(x: torch.Tensor, n_old: int, mu: torch.Tensor, sigma: torch.Tensor, workspace=None) -> int:
     """Merges the batch x [B, K] bf16 into (n_old, mu [K], sigma [K, K]) in place; returns the new row count."""
-    B, K = x.shape
-    need = int(lib().loka_tracker_update_workspace(B, K))
-    ws = workspace if workspace is not None else _ws(need, x.device)
-    _check(lib().loka_tracker_update(_ptr(x), B, K, x.stride(0), int(n_old), _ptr(mu), _ptr(sigma), _ptr(ws), ws.numel(),
-                                     _stream()), "loka_tracker_update")
-    return int(n_old) + B
+    return (_native or _host()).tracker_update(x, int(n_old), mu, sigma, workspace)
 
 
 def loka_dispatch_select(usec, err, budget: float, min_speedup: float = 0.0, usec_bf16: float = 0.0) -> int:

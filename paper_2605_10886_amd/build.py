@@ -1,9 +1,10 @@
-"""Builds paper_2605_10886_amd/libloka.so from csrc/*.hip with hipcc for gfx950.
+"""Builds paper_2605_10886_amd/libloka.so from csrc/*.hip with hipcc for gfx950, and the
+Python module _host.so (csrc/host_binding.cpp, host code only) that marshals into it.
 
     python -m paper_2605_10886_amd.build
 
-Objects go to _build/ at the repository root (git-ignored); the shared library is
-written next to this file so it travels with the tree.  hipcc cross-compiles, no
+Objects go to _build/ at the repository root (git-ignored); the shared libraries are
+written next to this file so they travel with the tree.  hipcc cross-compiles, no
 GPU is needed to build.
 """
 from __future__ import annotations
@@ -18,6 +19,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libloka.so")
+HOST = os.path.join(HERE, "_host.so")
 SOURCES = ["api.hip", "quantize.hip", "gemm.hip", "gemm_panel32.hip", "gemm_wreg.hip", "gemm_strip.hip", "probe.hip", "dispatch.hip", "tracker.hip", "ceiling.hip"]
 
 # -packed-fp32-ops off: packed fp32 VALU forms are kept out of the generated code.
@@ -54,16 +56,49 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _compile_host() -> str:
+    import sysconfig
+
+    import torch
+
+    t = os.path.dirname(torch.__file__)
+    obj = os.path.join(OBJ, "host_binding.o")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", os.path.join(t, "include"), "-isystem", os.path.join(t, "include", "torch", "csrc", "api", "include"),
+           "-isystem", "/opt/rocm/include", "-isystem", sysconfig.get_paths()["include"], "-Wall",
+           "-c", os.path.join(CSRC, "host_binding.cpp"), "-o", obj]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on host_binding.cpp:\n{r.stderr}")
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+    return obj
+
+
+def _link_host(obj: str) -> None:
+    import torch
+
+    tl = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = ["g++", "-shared", "-o", HOST, obj, "-L" + tl, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_hip", "-ltorch_python",
+           "-L" + HERE, "-lloka", "-Wl,-rpath,$ORIGIN"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("link of _host.so failed:\n" + r.stderr)
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ, exist_ok=True)
-    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        host = ex.submit(_compile_host)
         objs = list(ex.map(_compile, SOURCES))
+        host_obj = host.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stderr)
+    _link_host(host_obj)
     if verbose:
-        print("built", LIB)
+        print("built", LIB, HOST)
     return LIB
 
 

@@ -1,0 +1,40 @@
+"""The native marshalling of the per-step calls: what it rejects before anything is allocated (no GPU), and, on the GPU,
+that given outputs and workspaces are the ones written and that a failed call raises with the library's status."""
+import pytest
+import torch
+
+from paper_2605_10886_amd import binding as B
+
+
+def test_rejects_before_allocating():
+    with pytest.raises(AssertionError):
+        B.loka_quantize(torch.zeros(8, 16), B.SCALE_ROW)                          # not bf16
+    with pytest.raises(AssertionError):
+        B.loka_quantize(torch.zeros(16, 8, dtype=torch.bfloat16).t(), B.SCALE_ROW)   # columns strided
+    with pytest.raises(B.LokaError) as e:
+        B.loka_quantize(torch.zeros(16, 200, dtype=torch.bfloat16), B.SCALE_BLOCK_1x128)
+    assert e.value.status == B.LOKA_ERR_SHAPE
+    with pytest.raises(Exception):
+        B.loka_fp8_gemm_norm(object(), *(torch.zeros(1),) * 4)                    # not a descriptor
+    with pytest.raises(AssertionError):
+        B.loka_probe_error(torch.zeros(4, 8), torch.zeros(8, 4))
+
+
+@pytest.mark.gpu
+def test_given_outputs_and_errors():
+    M, K, N = 96, 128, 256
+    x = torch.randn(M, K, device="cuda").bfloat16()
+    wq, sw = B.loka_quantize((torch.randn(K, N, device="cuda") / 11).bfloat16(), B.SCALE_COL, transpose_out=True)
+    xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+    d = B.make_desc(M, N, K)
+    ref, none = B.loka_fp8_gemm_norm(d, xq, sx, wq, sw)
+    out, y = torch.empty_like(ref), torch.empty(M, N, device="cuda")
+    o2, y2 = B.loka_fp8_gemm_norm(d, xq, sx, wq, sw, want_y=True, out=out, y=y)
+    assert none is None and o2.data_ptr() == out.data_ptr() and y2.data_ptr() == y.data_ptr()
+    assert torch.equal(out.view(torch.int16), ref.view(torch.int16))
+    ws = torch.empty(16, dtype=torch.uint8, device="cuda")
+    wide = B.make_desc(M, 2048, K, norm=B.NORM_LAYERNORM, variant=B.variant_id("panel32_256x256"))
+    with pytest.raises(B.LokaError) as e:
+        B.loka_fp8_gemm_norm(wide, xq, sx, torch.zeros(2048, K, dtype=torch.uint8, device="cuda"),
+                             torch.ones(2048, device="cuda"), workspace=ws)
+    assert e.value.status == B.LOKA_ERR_WORKSPACE
