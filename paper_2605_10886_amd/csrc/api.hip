@@ -8,6 +8,7 @@
 
 namespace loka {
 // quantize.hip
+size_t quantize_workspace_bytes(loka_scale_mode, int64_t, int64_t);
 loka_status quantize_launch(const void*, int64_t, int64_t, int64_t, loka_scale_mode, int, uint8_t*, float*, void*,
                             hipStream_t);
 loka_status e4m3_from_f32_launch(const float*, uint8_t*, int64_t, hipStream_t);
@@ -127,9 +128,8 @@ int64_t loka_scale_count(loka_scale_mode mode, int64_t rows, int64_t cols) {
 size_t loka_quantize_workspace(loka_scale_mode mode, int64_t rows, int64_t cols, int transpose_out) {
     if (!transpose_out && (mode == LOKA_SCALE_ROW || is_block_x(mode))) return 0;
     if (is_block_w(mode) || mode == LOKA_SCALE_BLOCK_128x1) return 0;      // groups that fit a workgroup: one pass
-    const int64_t ng = loka_scale_count(mode, rows, cols);
-    if (ng < 0) return 0;
-    return static_cast<size_t>(ng) * 8;       // amax bits + quantization factors
+    if (loka_scale_count(mode, rows, cols) < 0) return 0;
+    return quantize_workspace_bytes(mode, rows, cols);       // partial maxima
 }
 
 loka_status loka_quantize(const void* x_bf16, int64_t rows, int64_t cols, int64_t ld, loka_scale_mode mode,

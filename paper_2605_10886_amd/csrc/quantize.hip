@@ -3,10 +3,11 @@
 // ROW and BLOCK_1x128 scaling are single-pass: the lanes that share a scale group
 // keep their elements in registers between the amax reduction and the cast, so the
 // matrix is read once (2 B/elem) and the codes written once (1 B/elem).
-// TENSOR, COL and BLOCK_128x128 scaling need every row of a group before the first
-// cast: an amax pass (atomic max on the bit pattern of non-negative floats), a tiny
-// finalize kernel (scale = amax/448, inv = 448/amax, one division each), and a cast
-// pass that can also write the transposed layout used for weights.
+// The modes whose groups fit a 128 x 128 tile are single-pass as well (quant_tile128_kernel).
+// TENSOR and COL scaling need every row of a group before the first cast: an amax pass that
+// leaves partial maxima in the workspace, and the tile kernel, whose workgroups fold the
+// partials of their columns, take scale = amax/448 and inv = 448/amax (one division each),
+// cast, and write plain or transposed (the layout used for weights).
 #include "common.h"
 
 namespace loka {
@@ -88,8 +89,15 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restr
     }
 }
 
-// Rows longer than the register-resident kernel covers: one workgroup per row, two
-// sweeps over the row (the second one hits the cache).
+__device__ __forceinline__ float chunk_amax(const u32x4 w) {
+    float a = fmaxf(fabsf(bf16_lo(w.x)), fabsf(bf16_hi(w.x)));
+    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y))));
+    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))));
+    return fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
+}
+
+// Rows longer than the register-resident kernels cover: one workgroup per row, two
+// sweeps over the row (one for 1x128 groups, which need no sweep of their own).
 template <bool BLOCK128>
 __global__ __launch_bounds__(256) void quant_long_rows_kernel(const uint16_t* __restrict__ x, int64_t rows,
                                                               int64_t cols, int64_t ld, uint8_t* __restrict__ q,
@@ -143,165 +151,113 @@ __global__ __launch_bounds__(256) void quant_long_rows_kernel(const uint16_t* __
 }
 
 // ---------------------------------------------------------------------------------
-// Multi-pass path.  Workspace layout: uint32 amax_bits[ng] followed by float inv[ng].
-__global__ void fill_u32_kernel(uint32_t* p, int64_t n, uint32_t v) {
-    int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
+// TENSOR and COL, first pass: partial maxima, parts[part][group] (group = column, or the one group of TENSOR).  Plain
+// stores of one value per workgroup (or column) instead of atomics: nothing has to be cleared first, and the pass that
+// casts folds the few partials itself, so the two passes are the whole call (with a clearing kernel, atomics and a
+// kernel for the scales in between it was four, and the atomics alone took 21 - 31 us at 256 x 1024).
+constexpr int kMaxParts = 64;              // row ranges of a COL pass: what every tile of the cast folds per column
+constexpr int kTensorParts = 1024;         // workgroups of a TENSOR pass
 
-__device__ __forceinline__ float chunk_amax(const u32x4 w) {
-    float a = fmaxf(fabsf(bf16_lo(w.x)), fabsf(bf16_hi(w.x)));
-    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y))));
-    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))));
-    return fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
-}
-
-// TENSOR: grid-stride over all chunks, one atomic per workgroup.
 __global__ __launch_bounds__(256) void amax_tensor_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                          int64_t ld, uint32_t* __restrict__ amax_bits) {
+                                                          int64_t ld, float* __restrict__ parts) {
     __shared__ float red[4];
-    const int64_t chunks = cols >> 3;
-    const int64_t total = rows * chunks;
+    const int64_t chunks = cols >> 3, total = rows * chunks, step = static_cast<int64_t>(gridDim.x) * 256;
+    const bool flat = ld == cols;          // (no division per chunk then)
     float a = 0.f;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < total;
-         i += static_cast<int64_t>(gridDim.x) * 256) {
-        const int64_t r = i / chunks, c = i - r * chunks;
-        a = fmaxf(a, chunk_amax(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + r * ld + c * 8))));
+    for (int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i0 < total; i0 += 4 * step) {
+        u32x4 w[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t i = i0 + u * step;
+            w[u] = u32x4{0u, 0u, 0u, 0u};
+            if (i < total) {
+                const int64_t r = flat ? 0 : i / chunks, c = flat ? i : i - r * chunks;
+                w[u] = *reinterpret_cast<const u32x4*>(x + r * ld + c * 8);       // (plain: the cast reads it again)
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) a = fmaxf(a, chunk_amax(w[u]));
     }
     for (int m = 1; m < 64; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        a = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-        atomicMax(amax_bits, __float_as_uint(a));
-    }
+    if (threadIdx.x == 0) parts[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
 }
 
-// COL: a workgroup owns 2048 columns x ROWS_PER_BLOCK rows; each thread keeps the
-// maxima of its 8 columns and publishes them with 8 atomics.
-constexpr int kColRowsPerBlock = 64;
+// A workgroup takes 64 columns (128-byte runs) of one row range: 8 chunk columns x 32 rows at a time.
 __global__ __launch_bounds__(256) void amax_col_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                       int64_t ld, uint32_t* __restrict__ amax_bits) {
-    const int64_t c = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;      // chunk column
-    if (c >= (cols >> 3)) return;
-    const int64_t r0 = static_cast<int64_t>(blockIdx.y) * kColRowsPerBlock;
-    const int64_t r1 = r0 + kColRowsPerBlock < rows ? r0 + kColRowsPerBlock : rows;
+                                                       int64_t ld, int64_t rows_per_part, float* __restrict__ parts) {
+    __shared__ float red[4][64];
+    const int cc = threadIdx.x & 7, rr = threadIdx.x >> 3, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t c = static_cast<int64_t>(blockIdx.x) * 64 + cc * 8;
+    const int64_t r0 = static_cast<int64_t>(blockIdx.y) * rows_per_part;
+    const int64_t r1 = r0 + rows_per_part < rows ? r0 + rows_per_part : rows;
     float a[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (int64_t r = r0; r < r1; ++r) {
-        const u32x4 w = *reinterpret_cast<const u32x4*>(x + r * ld + c * 8);
-        a[0] = fmaxf(a[0], fabsf(bf16_lo(w.x))); a[1] = fmaxf(a[1], fabsf(bf16_hi(w.x)));
-        a[2] = fmaxf(a[2], fabsf(bf16_lo(w.y))); a[3] = fmaxf(a[3], fabsf(bf16_hi(w.y)));
-        a[4] = fmaxf(a[4], fabsf(bf16_lo(w.z))); a[5] = fmaxf(a[5], fabsf(bf16_hi(w.z)));
-        a[6] = fmaxf(a[6], fabsf(bf16_lo(w.w))); a[7] = fmaxf(a[7], fabsf(bf16_hi(w.w)));
-    }
+    for (int64_t r = r0 + rr; r < r1; r += 128) {
+        u32x4 w[4];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) atomicMax(amax_bits + c * 8 + j, __float_as_uint(a[j]));
-}
-
-__global__ void finalize_scales_kernel(const uint32_t* __restrict__ amax_bits, float* __restrict__ inv,
-                                       float* __restrict__ scales, int64_t ng, const int pow2) {
-    int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g < ng) {
-        float s, i;
-        group_scale_any(pow2, __uint_as_float(amax_bits[g]), s, i);
-        scales[g] = s;
-        inv[g] = i;
-    }
-}
-
-// Cast pass.  MODE selects how a chunk finds its factor(s); TRANSPOSE writes q[c, r].
-template <int MODE>
-__device__ __forceinline__ void load_inv8(const float* __restrict__ inv, int64_t r, int64_t c8, int64_t cols,
-                                          float (&f)[8]) {
-    if (MODE == LOKA_SCALE_TENSOR) {
-        const float v = inv[0];
+        for (int u = 0; u < 4; ++u) {
+            w[u] = u32x4{0u, 0u, 0u, 0u};
+            if (c < cols && r + 32 * u < r1) w[u] = *reinterpret_cast<const u32x4*>(x + (r + 32 * u) * ld + c);
+        }
 #pragma unroll
-        for (int j = 0; j < 8; ++j) f[j] = v;
-    } else {
-        const float4 a = *reinterpret_cast<const float4*>(inv + c8);
-        const float4 b = *reinterpret_cast<const float4*>(inv + c8 + 4);
-        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
-    }
-}
-
-template <int MODE>
-__global__ __launch_bounds__(256) void cast_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                   int64_t ld, const float* __restrict__ inv,
-                                                   uint8_t* __restrict__ q) {
-    const int64_t chunks = cols >> 3;
-    const int64_t total = rows * chunks;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < total;
-         i += static_cast<int64_t>(gridDim.x) * 256) {
-        const int64_t r = i / chunks, c = i - r * chunks;
-        const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + r * ld + c * 8));
-        float f[8];
-        load_inv8<MODE>(inv, r, c * 8, cols, f);
-        u32x2 o;
-        o.x = e4m3x4(bf16_lo(w.x) * f[0], bf16_hi(w.x) * f[1], bf16_lo(w.y) * f[2], bf16_hi(w.y) * f[3]);
-        o.y = e4m3x4(bf16_lo(w.z) * f[4], bf16_hi(w.z) * f[5], bf16_lo(w.w) * f[6], bf16_hi(w.w) * f[7]);
-        *reinterpret_cast<u32x2*>(q + r * cols + c * 8) = o;   // plain store: the consumer reads the codes next
-    }
-}
-
-// 64 x 64 tile through LDS; rows % 16 == 0 and cols % 16 == 0, so 16-row / 8-column
-// pieces are either fully inside or fully outside the matrix.
-template <int MODE>
-__global__ __launch_bounds__(256) void cast_transpose_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
-                                                             int64_t ld, const float* __restrict__ inv,
-                                                             uint8_t* __restrict__ q) {
-    __shared__ uint8_t tile[64][64 + 16];        // [c][r], padded rows keep 16-byte alignment
-    const int64_t r0 = static_cast<int64_t>(blockIdx.y) * 64, c0 = static_cast<int64_t>(blockIdx.x) * 64;
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-        const int idx = threadIdx.x + s * 256;   // 512 chunks: 64 rows x 8 chunks
-        const int rr = idx >> 3, cc = (idx & 7) * 8;
-        const int64_t r = r0 + rr, c = c0 + cc;
-        if (r < rows && c < cols) {
-            const u32x4 w = *reinterpret_cast<const u32x4*>(x + r * ld + c);
-            float f[8];
-            load_inv8<MODE>(inv, r, c, cols, f);
-            const uint32_t lo = e4m3x4(bf16_lo(w.x) * f[0], bf16_hi(w.x) * f[1], bf16_lo(w.y) * f[2], bf16_hi(w.y) * f[3]);
-            const uint32_t hi = e4m3x4(bf16_lo(w.z) * f[4], bf16_hi(w.z) * f[5], bf16_lo(w.w) * f[6], bf16_hi(w.w) * f[7]);
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                tile[cc + j][rr] = static_cast<uint8_t>(lo >> (8 * j));
-                tile[cc + 4 + j][rr] = static_cast<uint8_t>(hi >> (8 * j));
-            }
+        for (int u = 0; u < 4; ++u) {
+            a[0] = fmaxf(a[0], fabsf(bf16_lo(w[u].x))); a[1] = fmaxf(a[1], fabsf(bf16_hi(w[u].x)));
+            a[2] = fmaxf(a[2], fabsf(bf16_lo(w[u].y))); a[3] = fmaxf(a[3], fabsf(bf16_hi(w[u].y)));
+            a[4] = fmaxf(a[4], fabsf(bf16_lo(w[u].z))); a[5] = fmaxf(a[5], fabsf(bf16_hi(w[u].z)));
+            a[6] = fmaxf(a[6], fabsf(bf16_lo(w[u].w))); a[7] = fmaxf(a[7], fabsf(bf16_hi(w[u].w)));
         }
     }
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int m = 8; m < 64; m <<= 1) a[j] = fmaxf(a[j], wave_shfl_xor(a[j], m));
+    if (lane < 8) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) red[wave][cc * 8 + j] = a[j];
+    }
     __syncthreads();
-    const int cc = threadIdx.x >> 2, rr = (threadIdx.x & 3) * 16;
-    const int64_t c = c0 + cc, r = r0 + rr;
-    if (c < cols && r < rows)
-        *reinterpret_cast<u32x4*>(q + c * rows + r) = *reinterpret_cast<const u32x4*>(&tile[cc][rr]);
+    const int t = static_cast<int>(threadIdx.x);
+    const int64_t col = static_cast<int64_t>(blockIdx.x) * 64 + t;
+    if (t < 64 && col < cols)
+        parts[static_cast<int64_t>(blockIdx.y) * cols + col] = fmaxf(fmaxf(red[0][t], red[1][t]), fmaxf(red[2][t], red[3][t]));
 }
 
-// Single-pass quantization of the modes whose scale groups fit one workgroup: a workgroup takes a 128 x 128 tile
-// (8 sweeps of 16 rows x 16 chunks of 8 elements: 32 registers per thread), finds the amax of its groups on chip,
+// A workgroup takes a 128 x 128 tile (8 rows x 8 columns per thread: 32 registers), finds the factors of its groups,
 // scales, casts and stores - every element is read once and written once (3 bytes per element).
-//   COLGROUPS == false: the whole tile is one group (BLOCK_128x128 and its power-of-two form); scales [rows/128][cols/128]
-//   COLGROUPS == true:  every column of the tile is a group (BLOCK_128x1); scales [cols][rows/128]
-//   TRANSPOSE: codes leave as [cols, rows] through an LDS tile (64-byte runs per output row)
-// rows % 128 == 0; cols % 16 == 0 (COLGROUPS) or % 128 == 0: chunks past the last column are skipped.
-template <bool COLGROUPS, bool TRANSPOSE>
+//   G_TILE:    the whole tile is one group (BLOCK_128x128 and its power-of-two form); scales [rows/128][cols/128]
+//   G_COL128:  every column of the tile is a group (BLOCK_128x1); scales [cols][rows/128]
+//   G_COL:     a group is a whole column (COL), G_TENSOR: the whole matrix: the workgroup folds the partial maxima of
+//              its groups that the amax pass left (parts[nparts][groups]); the first row of tiles writes the scales
+//   TRANSPOSE: codes leave as [cols, rows] through an LDS tile (128-byte runs per output row)
+// rows % 128 == 0 for G_TILE and G_COL128; rows % 16 == 0 with TRANSPOSE; any rows else.  cols % 16 == 0 (% 128 for G_TILE).
+// Measured (us, whole call with the amax pass; before: clearing, atomics, scales and a cast through a byte-wise LDS tile,
+// four kernels): COL transposed 256 x 1024 22.5 -> 7.9, 4096 x 4096 44.8 -> 19.3, 123200 x 1024 423 -> 129; TENSOR
+// 16384 x 512 57 -> 10.4, 65536 x 1024 95 -> 58, 32768 x 4096 136 -> 120.
+enum { G_TILE, G_COL128, G_COL, G_TENSOR };
+template <int GROUPS, bool TRANSPOSE>
 __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                             int64_t ld, uint8_t* __restrict__ q, float* __restrict__ scales,
-                                                            const int pow2) {
-    __shared__ float red[4 * 128];                      // per wave: column maxima (COLGROUPS) or one value
+                                                            const int pow2, const float* __restrict__ parts, const int nparts) {
+    constexpr bool ROW_TAIL = GROUPS == G_COL || GROUPS == G_TENSOR;   // rows need not fill the last tile
+    __shared__ float red[4 * 128];                      // per wave: column maxima (G_COL128) or one value
     __shared__ float inv_s[128];
     __shared__ __attribute__((aligned(16))) uint8_t tile[TRANSPOSE ? 128 * (128 + 16) : 16];   // [c][r], rows padded to 144 bytes
     const int t = static_cast<int>(threadIdx.x), lane = t & 63, wave = t >> 6;
     const int cc = t & 15, rr = t >> 4;                 // chunk column; the thread's 8 consecutive rows are rr * 8 + [0, 8)
-    const int64_t r0 = static_cast<int64_t>(blockIdx.y) * 128, c0 = static_cast<int64_t>(blockIdx.x) * 128;
+    const unsigned tiles_c = static_cast<unsigned>((cols + 127) >> 7);
+    const unsigned by = blockIdx.x / tiles_c, bx = blockIdx.x - by * tiles_c;
+    const int64_t r0 = static_cast<int64_t>(by) * 128, c0 = static_cast<int64_t>(bx) * 128;
     const bool live = c0 + cc * 8 < cols;
     u32x4 w[8];
 #pragma unroll
     for (int sw = 0; sw < 8; ++sw) {
         w[sw] = u32x4{0u, 0u, 0u, 0u};
-        if (live) w[sw] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + (r0 + rr * 8 + sw) * ld + c0 + cc * 8));
+        if (live && (!ROW_TAIL || r0 + rr * 8 + sw < rows))
+            w[sw] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + (r0 + rr * 8 + sw) * ld + c0 + cc * 8));
     }
     float inv8[8];
-    if (COLGROUPS) {
+    if (GROUPS == G_COL128) {
         float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int sw = 0; sw < 8; ++sw) {
@@ -326,21 +282,54 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
             float sc, iv;
             group_scale_any(pow2 != 0, am, sc, iv);
             inv_s[t] = iv;
-            if (c0 + t < cols) scales[(c0 + t) * (rows >> 7) + blockIdx.y] = sc;
+            if (c0 + t < cols) scales[(c0 + t) * (rows >> 7) + by] = sc;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) inv8[j] = inv_s[cc * 8 + j];
+    } else if (GROUPS == G_COL) {
+        // two threads per column fold half of the partials each (loads of 128 consecutive floats, eight in flight)
+        const int col = t & 127, half = t >> 7;
+        float am = 0.f;
+        if (c0 + col < cols) {
+            const float* src = parts + c0 + col;
+            for (int k0 = half; k0 < nparts; k0 += 16) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = k0 + 2 * u < nparts ? src[static_cast<int64_t>(k0 + 2 * u) * cols] : 0.f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) am = fmaxf(am, v[u]);
+            }
+        }
+        red[half * 128 + col] = am;
+        __syncthreads();
+        if (t < 128) {
+            float sc, iv;
+            group_scale(fmaxf(red[t], red[128 + t]), sc, iv);
+            inv_s[t] = iv;
+            if (by == 0 && c0 + t < cols) scales[c0 + t] = sc;
         }
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < 8; ++j) inv8[j] = inv_s[cc * 8 + j];
     } else {
         float a = 0.f;
+        if (GROUPS == G_TENSOR) {
+            for (int k = t; k < nparts; k += 256) a = fmaxf(a, parts[k]);
+        } else {
 #pragma unroll
-        for (int sw = 0; sw < 8; ++sw) a = fmaxf(a, chunk_amax(w[sw]));
+            for (int sw = 0; sw < 8; ++sw) a = fmaxf(a, chunk_amax(w[sw]));
+        }
         for (int m = 1; m < 64; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
         if (lane == 0) red[wave] = a;
         __syncthreads();
         float sc, iv;
         group_scale_any(pow2 != 0, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])), sc, iv);
-        if (t == 0) scales[blockIdx.y * (cols >> 7) + blockIdx.x] = sc;
+        if (GROUPS == G_TENSOR) {
+            if (t == 0 && blockIdx.x == 0) scales[0] = sc;
+        } else if (t == 0) {
+            scales[by * static_cast<int64_t>(tiles_c) + bx] = sc;
+        }
 #pragma unroll
         for (int j = 0; j < 8; ++j) inv8[j] = iv;
     }
@@ -349,7 +338,8 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
     for (int sw = 0; sw < 8; ++sw) {
         lo[sw] = e4m3x4(bf16_lo(w[sw].x) * inv8[0], bf16_hi(w[sw].x) * inv8[1], bf16_lo(w[sw].y) * inv8[2], bf16_hi(w[sw].y) * inv8[3]);
         hi[sw] = e4m3x4(bf16_lo(w[sw].z) * inv8[4], bf16_hi(w[sw].z) * inv8[5], bf16_lo(w[sw].w) * inv8[6], bf16_hi(w[sw].w) * inv8[7]);
-        if (!TRANSPOSE && live) *reinterpret_cast<u32x2*>(q + (r0 + rr * 8 + sw) * cols + c0 + cc * 8) = u32x2{lo[sw], hi[sw]};
+        if (!TRANSPOSE && live && (!ROW_TAIL || r0 + rr * 8 + sw < rows))
+            *reinterpret_cast<u32x2*>(q + (r0 + rr * 8 + sw) * cols + c0 + cc * 8) = u32x2{lo[sw], hi[sw]};
     }
     if (TRANSPOSE) {
         // the thread's 8 x 8 block of codes is transposed in registers (byte permutes on 4 x 4 sub-blocks), so that each
@@ -382,7 +372,8 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
             const int col = j * 32 + (t >> 3), key = col >> 3;           // the row's runs 2 chunk, 2 chunk + 1 sit at ^ key
             u32x4 v = *reinterpret_cast<const u32x4*>(tile + col * 144 + ((chunk ^ (key >> 1)) << 4));
             if (key & 1) v = u32x4{v.z, v.w, v.x, v.y};
-            if (c0 + col < cols) *reinterpret_cast<u32x4*>(q + (c0 + col) * rows + r0 + chunk * 16) = v;
+            if (c0 + col < cols && (!ROW_TAIL || r0 + chunk * 16 < rows))
+                *reinterpret_cast<u32x4*>(q + (c0 + col) * rows + r0 + chunk * 16) = v;
         }
     }
 }
@@ -416,18 +407,23 @@ static void launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t l
 #undef LOKA_QR
 }
 
-template <int MODE>
-static void launch_cast(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld, const float* inv, uint8_t* q,
-                        int transpose_out, hipStream_t s) {
-    if (transpose_out) {
-        dim3 g(static_cast<unsigned>((cols + 63) / 64), static_cast<unsigned>((rows + 63) / 64));
-        cast_transpose_kernel<MODE><<<g, 256, 0, s>>>(x, rows, cols, ld, inv, q);
-    } else {
-        const int64_t total = rows * (cols / 8);
-        int64_t blocks = (total + 255) / 256;
-        if (blocks > 256 * 64) blocks = 256 * 64;
-        cast_kernel<MODE><<<dim3(static_cast<unsigned>(blocks)), 256, 0, s>>>(x, rows, cols, ld, inv, q);
-    }
+// Row ranges of a COL amax pass: 128 rows each (four rows per thread) as long as the cast has few partials to fold.
+static int64_t col_rows_per_part(int64_t rows) {
+    const int64_t per = (rows + kMaxParts - 1) / kMaxParts;
+    return ((per < 128 ? 128 : per) + 31) / 32 * 32;
+}
+
+// Workgroups of a TENSOR amax pass: four chunks per thread as long as the cast has few partials to fold.
+static int64_t tensor_parts(int64_t rows, int64_t cols) {
+    const int64_t want = (rows * (cols / 8) + 1023) / 1024;
+    return want < kTensorParts ? want : kTensorParts;
+}
+
+// (at least the two values per group that callers of the smallest shapes have always been asked for)
+size_t quantize_workspace_bytes(loka_scale_mode mode, int64_t rows, int64_t cols) {
+    const int64_t groups = mode == LOKA_SCALE_TENSOR ? 1 : cols, per = col_rows_per_part(rows);
+    const int64_t parts = mode == LOKA_SCALE_TENSOR ? tensor_parts(rows, cols) : (rows + per - 1) / per;
+    return static_cast<size_t>(groups) * (parts < 2 ? 2 : parts) * sizeof(float);
 }
 
 loka_status quantize_launch(const void* x_bf16, int64_t rows, int64_t cols, int64_t ld, loka_scale_mode mode,
@@ -442,32 +438,28 @@ loka_status quantize_launch(const void* x_bf16, int64_t rows, int64_t cols, int6
         else launch_rows<true>(x, rows, cols, ld, q, scales, pow2, s);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
+    const dim3 tiles(static_cast<unsigned>(((cols + 127) / 128) * ((rows + 127) / 128)));
     if (mode == LOKA_SCALE_BLOCK_128x128 || mode == LOKA_SCALE_BLOCK_128x1) {
         // groups that fit a workgroup: one pass
-        const dim3 g(static_cast<unsigned>((cols + 127) / 128), static_cast<unsigned>(rows / 128));
-        if (mode == LOKA_SCALE_BLOCK_128x1) quant_tile128_kernel<true, true><<<g, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0);
-        else if (transpose_out) quant_tile128_kernel<false, true><<<g, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2);
-        else quant_tile128_kernel<false, false><<<g, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2);
+        if (mode == LOKA_SCALE_BLOCK_128x1) quant_tile128_kernel<G_COL128, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, nullptr, 0);
+        else if (transpose_out) quant_tile128_kernel<G_TILE, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, nullptr, 0);
+        else quant_tile128_kernel<G_TILE, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, nullptr, 0);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
-    const int64_t ng = loka_scale_count(mode, rows, cols);
-    uint32_t* amax_bits = static_cast<uint32_t*>(workspace);
-    float* inv = reinterpret_cast<float*>(amax_bits + ng);
+    float* parts = static_cast<float*>(workspace);
     if (mode == LOKA_SCALE_TENSOR) {
-        fill_u32_kernel<<<1, 64, 0, s>>>(amax_bits, 1, 0u);
-        const int64_t total = rows * (cols / 8);
-        int64_t blocks = (total + 255) / 256;
-        if (blocks > 256 * 16) blocks = 256 * 16;
-        amax_tensor_kernel<<<dim3(static_cast<unsigned>(blocks)), 256, 0, s>>>(x, rows, cols, ld, amax_bits);
-    } else if (mode == LOKA_SCALE_COL) {
-        fill_u32_kernel<<<dim3(static_cast<unsigned>((ng + 255) / 256)), 256, 0, s>>>(amax_bits, ng, 0u);
-        dim3 g(static_cast<unsigned>((cols / 8 + 255) / 256),
-               static_cast<unsigned>((rows + kColRowsPerBlock - 1) / kColRowsPerBlock));
-        amax_col_kernel<<<g, 256, 0, s>>>(x, rows, cols, ld, amax_bits);
+        const int n = static_cast<int>(tensor_parts(rows, cols));
+        amax_tensor_kernel<<<dim3(static_cast<unsigned>(n)), 256, 0, s>>>(x, rows, cols, ld, parts);
+        if (transpose_out) quant_tile128_kernel<G_TENSOR, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
+        else quant_tile128_kernel<G_TENSOR, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
+    } else {
+        const int64_t per = col_rows_per_part(rows);
+        const int n = static_cast<int>((rows + per - 1) / per);
+        const dim3 g(static_cast<unsigned>((cols + 63) / 64), static_cast<unsigned>(n));
+        amax_col_kernel<<<g, 256, 0, s>>>(x, rows, cols, ld, per, parts);
+        if (transpose_out) quant_tile128_kernel<G_COL, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
+        else quant_tile128_kernel<G_COL, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
     }
-    finalize_scales_kernel<<<dim3(static_cast<unsigned>((ng + 255) / 256)), 256, 0, s>>>(amax_bits, inv, scales, ng, pow2);
-    if (mode == LOKA_SCALE_TENSOR) launch_cast<LOKA_SCALE_TENSOR>(x, rows, cols, ld, inv, q, transpose_out, s);
-    else launch_cast<LOKA_SCALE_COL>(x, rows, cols, ld, inv, q, transpose_out, s);
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }
 
