@@ -96,6 +96,65 @@ __device__ __forceinline__ float chunk_amax(const u32x4 w) {
     return fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
 }
 
+// Rows too long for one wave (8192 < cols <= 131072): a workgroup of 16 waves holds the whole row in registers (CPL chunks
+// of 8 elements per thread, 64 registers at 131072 columns: 256 KB of a CU's register file) between the amax and the
+// cast, so the row is read once.  The workgroups are persistent: the register a chunk leaves at its cast takes the same
+// chunk of the workgroup's next row, so the next row streams in while this one is cast and stored, and the memory never
+// idles between a CU's rows.  Bound by HBM (3 B per element).  2048 x 123200: 230 us with two sweeps over the row (the
+// second one misses: the rows in flight are larger than the last-level cache) -> 125 us = 6.06 TB/s; 8192 x 32768 208 -> 126,
+// 2048 x 24576 37 -> 27.
+template <int CPL>
+__global__ __launch_bounds__(1024) void quant_wide_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
+                                                               int64_t ld, uint8_t* __restrict__ q, float* __restrict__ scales) {
+    __shared__ float red[2][16];           // (two sets: a row's maxima are written while slow waves still read the last row's)
+    const int t = static_cast<int>(threadIdx.x);
+    u32x4 v[CPL];
+    // buffer accesses relative to the row: one 32-bit offset per thread, chunks past the end of the row read as zeros and
+    // are not stored (64-bit addresses per chunk would not fit beside the row: 114 registers spilled at CPL = 16)
+    auto row_rsrc = [&](int64_t r) __attribute__((always_inline)) {
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(x + (r < rows ? r : 0) * ld), 0,
+                                                 r < rows ? static_cast<int>(cols) * 2 : 0, 0x00020000);
+    };
+    auto load = [&](const __amdgpu_buffer_rsrc_t& rs, int j) __attribute__((always_inline)) {
+        v[j] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, t * 16, j * 16384, 2));   // (2: streamed)
+    };
+    int64_t r = blockIdx.x;
+    {
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(r);
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) load(rs, j);
+    }
+    for (int it = 0; r < rows; it ^= 1) {
+        float a = chunk_amax(v[0]);
+#pragma unroll
+        for (int j = 1; j < CPL; ++j) a = fmaxf(a, chunk_amax(v[j]));
+#pragma unroll
+        for (int m = 1; m < 64; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+        if ((t & 63) == 0) red[it][t >> 6] = a;
+        __syncthreads();
+        a = red[it][t & 15];
+#pragma unroll
+        for (int m = 1; m < 16; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+        float scale, inv;
+        group_scale(a, scale, inv);
+        if (t == 0) scales[r] = scale;
+        const __amdgpu_buffer_rsrc_t rs = row_rsrc(r + gridDim.x);
+        const __amdgpu_buffer_rsrc_t qs = __builtin_amdgcn_make_buffer_rsrc(q + r * cols, 0, static_cast<int>(cols), 0x00020000);
+#pragma unroll
+        for (int j = 0; j < CPL; ++j) {
+            u32x4 w = v[j];
+            asm volatile("; row chunk" : "+v"(w));     // (opaque: the values widened for the amax are not kept for the cast)
+            u32x2 o;
+            o.x = e4m3x4(bf16_lo(w.x) * inv, bf16_hi(w.x) * inv, bf16_lo(w.y) * inv, bf16_hi(w.y) * inv);
+            o.y = e4m3x4(bf16_lo(w.z) * inv, bf16_hi(w.z) * inv, bf16_lo(w.w) * inv, bf16_hi(w.w) * inv);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2i, o), qs, t * 8, j * 8192, 0);
+            load(rs, j);
+            __builtin_amdgcn_sched_barrier(0);     // (a chunk's cast, its store, its reload: in this order no second row's registers)
+        }
+        r += gridDim.x;
+    }
+}
+
 // Rows longer than the register-resident kernels cover: one workgroup per row, two
 // sweeps over the row (one for 1x128 groups, which need no sweep of their own).
 template <bool BLOCK128>
@@ -403,7 +462,15 @@ static void launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t l
     else if (chunks <= 256) LOKA_QR(64, 4, 2);
     else if (chunks <= 512) LOKA_QR(64, 8, 1);
     else if (chunks <= 1024) LOKA_QR(64, 16, 1);
-    else quant_long_rows_kernel<B128><<<dim3(static_cast<unsigned>(rows)), 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2);
+    else if (!B128 && chunks <= 16384) {
+        // as many workgroups as stay resident: 2 per CU (2048 threads) while a thread's row share is small
+        const int64_t slots = chunks <= 4096 ? 512 : 256;
+        const dim3 g(static_cast<unsigned>(rows < slots ? rows : slots));
+        if (chunks <= 2048) quant_wide_rows_kernel<2><<<g, 1024, 0, s>>>(x, rows, cols, ld, q, scales);
+        else if (chunks <= 4096) quant_wide_rows_kernel<4><<<g, 1024, 0, s>>>(x, rows, cols, ld, q, scales);
+        else if (chunks <= 8192) quant_wide_rows_kernel<8><<<g, 1024, 0, s>>>(x, rows, cols, ld, q, scales);
+        else quant_wide_rows_kernel<16><<<g, 1024, 0, s>>>(x, rows, cols, ld, q, scales);
+    } else quant_long_rows_kernel<B128><<<dim3(static_cast<unsigned>(rows)), 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2);
 #undef LOKA_QR
 }
 
