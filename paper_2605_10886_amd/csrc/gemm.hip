@@ -76,29 +76,36 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
     const int l16 = lane & 15, q = lane >> 4;
 
-    // Tiles are enumerated (problem, m tile, n tile), n fastest.  The one-tile-per-workgroup schedules
-    // take tile blockIdx.x.  The panel-synchronous schedule is persistent: gridDim.x (a multiple of
-    // tiles_n, all co-resident) workgroups walk the tile list in rounds of gridDim.x tiles, so the
-    // tiles_n workgroups that share a row panel always run in the same round.  Workgroups are handed
-    // to the 8 XCDs round-robin; logical slot (id % 8) * (grid / 8) + id / 8 keeps a panel's
-    // workgroups (and the W tiles they stream) on one XCD's L2 when grid is a multiple of 8 * tiles_n.
+    // Every schedule hands each XCD one contiguous range of logical ids.  One-tile-per-workgroup schedules take the id's
+    // tile: problem by problem, in bands of 8 tile rows, and for split K range by range, so that an XCD's L2 serves the
+    // operand strips its workgroups share.  (In launch order the tiles of one strip land on all 8 XCDs and every XCD
+    // reads the whole of X: the traffic between the L2s and memory, not the matrix cores, was the bound.  Measured:
+    // split K at 2048 x 123200 x 1024 402 -> 364 us, as a weight gradient at 65536 x 256 x 1024 42.3 -> 36.7 us, the BF16
+    // reference at 16384 x 1024 x 1024 59.0 -> 51.6 us.)
+    // The panel-synchronous schedule is persistent: gridDim.x (a multiple of tiles_n, all co-resident) workgroups walk
+    // the tile list (n fastest) in rounds of gridDim.x tiles, so the tiles_n workgroups that share a row panel always
+    // run in the same round.
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
-    int tile_first = blockIdx.x, tile_stride = total_tiles;
+    const int id = xcd_contiguous(blockIdx.x, gridDim.x);
+    int tile_first = EPI == EPI_SPLITK ? id % total_tiles : id, tile_stride = total_tiles;
     if (EPI == EPI_PANEL_SYNC) {
-        const int G = gridDim.x;
-        tile_first = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
-        tile_stride = G;
+        tile_stride = gridDim.x;
         // the workspace remembers which launch used it last (a wait that runs out records the same value beside it)
         if (p.header && blockIdx.x == 0 && threadIdx.x == 0)
             __hip_atomic_store(p.header, p.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   for (int tile = tile_first; tile < total_tiles; tile += tile_stride) {
-    int t = tile;
-    const int tn = t % p.tiles_n; t /= p.tiles_n;
-    const int tm = t % p.tiles_m; t /= p.tiles_m;
-    // EPI_SPLITK: the launch has ksplit workgroups per output tile (blockIdx.y), each contracts its own range of K steps
-    const int g = t;
-    const int ks = EPI == EPI_SPLITK ? static_cast<int>(blockIdx.y) : 0;
+    const int g = tile / (p.tiles_m * p.tiles_n);
+    int tm, tn;
+    if (EPI == EPI_PANEL_SYNC) {
+        const int t = tile - g * p.tiles_m * p.tiles_n;
+        tm = t / p.tiles_n;
+        tn = t - tm * p.tiles_n;
+    } else {
+        banded_tile(tile - g * p.tiles_m * p.tiles_n, p.tiles_m, p.tiles_n, tm, tn);
+    }
+    // EPI_SPLITK: the launch has ksplit workgroups per output tile, each contracts its own range of K steps
+    const int ks = EPI == EPI_SPLITK ? id / total_tiles : 0;
     const int k_lo = ks * p.k_per_split;                       // first K step of this workgroup
     const int kb0 = k_lo * 128;
     const int m0 = tm * BM, n0 = tn * BN;
@@ -1393,7 +1400,7 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         splitk_plan(d, vi, &p.ksplit, &p.k_per_split);
         p.part = static_cast<float*>(workspace);
         p.y = nullptr;                                  // (the second kernel writes Y)
-        grid.y = static_cast<unsigned>(p.ksplit);
+        grid.x *= static_cast<unsigned>(p.ksplit);
         vi.launch(p, blockwise, grid, s);
         const int64_t rows = static_cast<int64_t>(d->batch) * d->M;
         // few rows (a weight gradient's K x N output): a workgroup per row, else a wave per row

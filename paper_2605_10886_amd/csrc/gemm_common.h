@@ -48,6 +48,23 @@ struct GemmParams {
 // lane writes full 64-byte runs per row.
 __host__ __device__ constexpr int coff_of(int ti) { return (ti >> 1) * 32 + (ti & 1) * 4; }
 
+// Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), and each XCD has an L2 of its own.  This
+// renumbers G blocks so that every XCD works on one contiguous range of logical ids (any G: the first G % 8 XCDs have one
+// more): neighbours in the id order, which share operands, then find them in the same L2.
+__device__ __forceinline__ int xcd_contiguous(int b, int G) {
+    const int x = b & 7, r = G & 7;
+    return x * (G >> 3) + (x < r ? x : r) + (b >> 3);
+}
+
+// Tile t of a tiles_m x tiles_n grid in bands of 8 tile rows, walked column by column inside a band: 64 neighbours in the
+// order cover an 8 x 8 block of tiles and read 8 + 8 operand strips, where plain row order would read 1 + 64.
+__device__ __forceinline__ void banded_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {
+    const int band = t / (8 * tiles_n), r = t - band * 8 * tiles_n;
+    const int rows = tiles_m - band * 8 < 8 ? tiles_m - band * 8 : 8;
+    tn = r / rows;
+    tm = band * 8 + r - tn * rows;
+}
+
 // Workgroup barrier that orders LDS traffic only: LDS reads/writes issued before it are complete, but
 // global loads (including the loads that stream the next stage into LDS) stay in flight across it.
 // Completion of those is awaited explicitly (s_waitcnt vmcnt) where a stage is about to be read.

@@ -150,9 +150,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
     int tile_first = blockIdx.x, tile_stride = total_tiles;
     if (EPI == EPI_PANEL_SYNC) {
-        const int G = gridDim.x;
-        tile_first = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
-        tile_stride = G;
+        tile_first = xcd_contiguous(blockIdx.x, gridDim.x);
+        tile_stride = gridDim.x;
         // the workspace remembers which launch used it last (a wait that runs out records the same value beside it)
         if (p.header && blockIdx.x == 0 && threadIdx.x == 0)
             __hip_atomic_store(p.header, p.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -113,9 +113,7 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
     const int wi = wave >> 2, wj = wave & 3;
     const int ldB = static_cast<int>(p.ld) * 2;
 
-    // consecutive logical ids sit on one XCD (the dispatcher deals workgroups round-robin over the 8 XCDs)
-    const int G = gridDim.x;
-    const int id = (G % 8 == 0) ? (blockIdx.x % 8) * (G / 8) + blockIdx.x / 8 : blockIdx.x;
+    const int id = xcd_contiguous(blockIdx.x, gridDim.x);                    // an XCD's workgroups share row ranges
     const int split = id / p.pairs, pair = id - split * p.pairs;
     const int64_t row_begin = static_cast<int64_t>(split) * p.rows_per_split;
     const int64_t row_end = row_begin + p.rows_per_split < p.B ? row_begin + p.rows_per_split : p.B;
