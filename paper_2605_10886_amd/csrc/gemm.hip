@@ -835,10 +835,10 @@ __global__ __launch_bounds__(256) void norm_rows_kernel(const float* __restrict_
 // few rows, as a weight gradient does) add the row's ksplit partial sums in a fixed order (repeatable bits; eight
 // partials are requested before the first is added, so the loads overlap while the additions keep their order), take
 // the row statistics of the sum in registers (two sweeps over the thread's values: no E[y^2] - mean^2 cancellation),
-// normalize and write bf16 O (and fp32 Y when asked).  N <= 8192: a thread holds N / (64 WPR) values.
+// normalize and write bf16 O (and fp32 Y when asked).  N <= 8192 = 256 WPR MAXC at most: a thread holds MAXC chunks of four values.
 // part: [ksplit][rows][N] fp32 with rows = batch * M; row r of problem g lies at g * strideO + m * N in O / Y.
 constexpr int kSplitkMaxN = 8192;
-template <int WPR>
+template <int WPR, int MAXC>
 __global__ __launch_bounds__(256) void splitk_norm_rows_kernel(const float* __restrict__ part, int ksplit, int64_t rows,
                                                                int M, int N, int64_t strideO, int norm, float eps,
                                                                const uint16_t* __restrict__ gamma,
@@ -849,7 +849,6 @@ __global__ __launch_bounds__(256) void splitk_norm_rows_kernel(const float* __re
     const int tr = threadIdx.x & (TPR - 1);
     const int64_t r = static_cast<int64_t>(blockIdx.x) * (256 / TPR) + threadIdx.x / TPR;
     if (WPR == 1 && r >= rows) return;               // (WPR == 4: one row per workgroup, the grid is exactly the rows)
-    constexpr int MAXC = kSplitkMaxN / (4 * TPR);    // float4 chunks per thread
     v4f v[MAXC];
     const int chunks = N >> 2;
     const int64_t slab = rows * static_cast<int64_t>(N);
@@ -929,19 +928,37 @@ __global__ __launch_bounds__(256) void splitk_norm_rows_kernel(const float* __re
     }
 }
 
-// [K, N] bf16 -> [N, K] bf16 (the reference GEMM reads K-contiguous operands like the FP8 one)
-__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ w, int K, int N,
+// [K, N] bf16 -> [N, K] bf16 (the reference GEMM reads K-contiguous operands like the FP8 one), problem blockIdx.z.
+// K % 8 == 0 and N % 16 == 0: both sides move whole 16-byte chunks, 128 bytes of a row per 8 lanes.  LDS rows of 33 words:
+// the 8 chunks x 8 columns a wave gathers from fall on distinct banks.  Latency bound (a few tiles per CU; 2-byte
+// accesses took 7.6 us at 1024 x 1024, this form 2.5).
+__global__ __launch_bounds__(256) void transpose_bf16_kernel(const uint16_t* __restrict__ w, int K, int N, int64_t strideW,
                                                              uint16_t* __restrict__ wt) {
-    __shared__ uint16_t tile[64][66];
+    __shared__ uint32_t tile[64][33];
+    w += blockIdx.z * strideW;
+    wt += static_cast<int64_t>(blockIdx.z) * K * N;
     const int k0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int kk = i >> 6, nn = i & 63;
-        if (k0 + kk < K && n0 + nn < N) tile[kk][nn] = w[static_cast<int64_t>(k0 + kk) * N + n0 + nn];
+    const int r = threadIdx.x >> 3, c = threadIdx.x & 7;
+    u32x4 in[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int k = k0 + r + 32 * j, n = n0 + c * 8;
+        in[j] = (k < K && n < N) ? *reinterpret_cast<const u32x4*>(w + static_cast<int64_t>(k) * N + n) : u32x4{0, 0, 0, 0};
     }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) tile[r + 32 * j][c * 4 + e] = in[j][e];
     __syncthreads();
-    for (int i = threadIdx.x; i < 64 * 64; i += 256) {
-        const int nn = i >> 6, kk = i & 63;
-        if (k0 + kk < K && n0 + nn < N) wt[static_cast<int64_t>(n0 + nn) * K + k0 + kk] = tile[kk][nn];
+    const uint16_t* t16 = reinterpret_cast<const uint16_t*>(&tile[0][0]);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int nn = r + 32 * j, n = n0 + nn, k = k0 + c * 8;
+        u32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            o[e] = t16[(c * 8 + 2 * e) * 66 + nn] | (static_cast<uint32_t>(t16[(c * 8 + 2 * e + 1) * 66 + nn]) << 16);
+        if (n < N && k < K) *reinterpret_cast<u32x4*>(wt + static_cast<int64_t>(n) * K + k) = o;
     }
 }
 
@@ -981,6 +998,7 @@ void strip_launch(const GemmParams& p, dim3 grid, hipStream_t s);
 static void launch_strip_any(const GemmParams& p, bool, dim3 grid, hipStream_t s) { strip_launch(p, grid, s); }
 static const char kStripName[] = "strip32";
 static const char kPanel32Name[] = "panel32_256x256";
+static const char kSplitk256Name[] = "splitk256x256";
 
 // gemm_panel32.hip
 const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro = false);
@@ -991,6 +1009,11 @@ void panel32_launch(const GemmParams& p, int bw, dim3 grid, hipStream_t s);
 static int panel32_bw(const GemmParams& p, bool blockwise) { return !blockwise ? 0 : scale_mode_is_pow2(p.x_mode) ? 2 : 1; }
 static void launch_panel32(const GemmParams& p, bool blockwise, dim3 grid, hipStream_t s) {
     panel32_launch(p, panel32_bw(p, blockwise), grid, s);
+}
+const void* panel32_part_fn(int bw, bool bf16);
+void panel32_part_launch(const GemmParams& p, int bw, bool bf16, dim3 grid, hipStream_t s);
+static void launch_splitk256(const GemmParams& p, bool blockwise, dim3 grid, hipStream_t s) {
+    panel32_part_launch(p, panel32_bw(p, blockwise), false, grid, s);
 }
 
 template <int BM, int BN_SUB, int NSPLIT, int WAVES_M, int WAVES_N, int EPI>
@@ -1043,6 +1066,8 @@ static const VariantInfo kVariants[] = {
     LOKA_VARIANT("panel256x256w8", 256, 256, 1, 2, 4, EPI_PANEL_SYNC),
     // the same schedule on 32x32x64 MFMAs: the throughput variant
     {kPanel32Name, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32, panel32_fn(0, false, false), panel32_fn(1, false, false)},
+    // split K on the same main loop, one workgroup per CU
+    {kSplitk256Name, 256, 256, 512, EPI_SPLITK, panel32_lds(), &launch_splitk256, panel32_part_fn(0, false), panel32_part_fn(1, false)},
 };
 constexpr int kMaxRowTiles = 256;     // shape limit of the panel-synchronous schedule (a row's tiles must be co-resident:
                                       // the launch checks them against the CU count of the device it runs on)
@@ -1128,7 +1153,7 @@ int variant_splitk_choice(const loka_gemm_desc* d) {
     int ring = -1, two = -1;
     for (int v = 0; v < kNumVariants; ++v) {
         if (kVariants[v].epi != EPI_SPLITK || !variant_supports(d, v)) continue;
-        if (kVariants[v].threads == 512) ring = v; else two = v;
+        if (kVariants[v].bm != 128) continue; if (kVariants[v].threads == 512) ring = v; else two = v;
     }
     if (ring < 0 || two < 0) return ring >= 0 ? ring : two;
     int ksplit = 1, per = 1;
@@ -1355,6 +1380,7 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
     const void* kfn = blockwise ? vi.fn_block : vi.fn_plain;
+    if (vi.name == kSplitk256Name) kfn = panel32_part_fn(panel32_bw(p, blockwise), false);
     if (vi.name == kPanel32Name) kfn = panel32_fn(panel32_bw(p, blockwise), outq != nullptr, panel32_affine(p), p.qpro != 0);
     if (!kfn) return LOKA_ERR_UNSUPPORTED;
     int per_cu = 0;
@@ -1404,12 +1430,14 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         vi.launch(p, blockwise, grid, s);
         const int64_t rows = static_cast<int64_t>(d->batch) * d->M;
         // few rows (a weight gradient's K x N output): a workgroup per row, else a wave per row
-        if (rows < 8192)
-            splitk_norm_rows_kernel<4><<<dim3(static_cast<unsigned>(rows)), 256, 0, s>>>(
-                p.part, p.ksplit, rows, p.M, p.N, p.strideO, d->norm, d->eps, p.gamma, p.beta, p.out, y);
-        else
-            splitk_norm_rows_kernel<1><<<dim3(static_cast<unsigned>((rows + 3) / 4)), 256, 0, s>>>(
-                p.part, p.ksplit, rows, p.M, p.N, p.strideO, d->norm, d->eps, p.gamma, p.beta, p.out, y);
+        auto norm_rows = [&](auto fn, int64_t wgs) {
+            fn<<<dim3(static_cast<unsigned>(wgs)), 256, 0, s>>>(p.part, p.ksplit, rows, p.M, p.N, p.strideO, d->norm, d->eps,
+                                                                p.gamma, p.beta, p.out, y);
+        };
+        if (p.N <= 256) norm_rows(&splitk_norm_rows_kernel<1, 1>, (rows + 3) / 4);
+        else if (p.N <= 1024) norm_rows(&splitk_norm_rows_kernel<4, 1>, rows);
+        else if (p.N <= 2048) norm_rows(&splitk_norm_rows_kernel<4, 2>, rows);
+        else norm_rows(&splitk_norm_rows_kernel<4, 8>, rows);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
     vi.launch(p, blockwise, grid, s);
@@ -1438,12 +1466,12 @@ loka_status bf16_gemm_launch(const loka_gemm_desc* d, const void* x, const void*
                              hipStream_t s, bool weights_ready) {
     uint16_t* wt = static_cast<uint16_t*>(workspace);
     const int64_t nw = d->strideW ? d->batch : 1;
-    for (int64_t g = 0; g < nw && !weights_ready; ++g) {
-        dim3 grid(static_cast<unsigned>((d->N + 63) / 64), static_cast<unsigned>((d->K + 63) / 64));
-        transpose_bf16_kernel<<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(w) + g * d->strideW,
-                                                   static_cast<int>(d->K), static_cast<int>(d->N), wt + g * d->K * d->N);
+    for (int64_t g = 0; g < nw && !weights_ready; g += 65535) {         // (grid.z holds 65535 problems, grid.y 65535 * 64 rows)
+        const int64_t ng = nw - g < 65535 ? nw - g : 65535;
+        dim3 grid(static_cast<unsigned>((d->N + 63) / 64), static_cast<unsigned>((d->K + 63) / 64), static_cast<unsigned>(ng));
+        transpose_bf16_kernel<<<grid, 256, 0, s>>>(static_cast<const uint16_t*>(w) + g * d->strideW, static_cast<int>(d->K),
+                                                   static_cast<int>(d->N), d->strideW, wt + g * d->K * d->N);
     }
-    constexpr int BM = 128, BN = 128;
     GemmParams p{};
     p.X = static_cast<const uint8_t*>(x); p.W = reinterpret_cast<const uint8_t*>(wt);
     p.M = static_cast<int>(d->M); p.N = static_cast<int>(d->N); p.KB = static_cast<int>(d->K * 2);
@@ -1451,15 +1479,25 @@ loka_status bf16_gemm_launch(const loka_gemm_desc* d, const void* x, const void*
     p.strideX = d->strideX * 2; p.strideW = d->strideW ? d->K * d->N * 2 : 0; p.strideO = d->strideO;
     p.y = yref;
     p.norm = LOKA_NORM_NONE;
-    p.tiles_m = static_cast<int>((d->M + BM - 1) / BM);
-    p.tiles_n = static_cast<int>((d->N + BN - 1) / BN);
-    auto fn = &gemm_kernel<BM, BN, 1, 2, 2, true, false, EPI_PARTIAL_STATS>;
-    constexpr size_t lds = 2 * (BM * 128 + BN * 128);
+    // 256 x 256 tiles on the panel kernel's main loop where they fill at least 80 % of the rounds of 256 workgroups they
+    // take, else 128 x 128 tiles, two workgroups per CU.  Measured, 256 against 128: 16384 x 1024 x 1024 (256 tiles) 42.0
+    // against 48.9 us, 8192 x 4096 x 4096 (512) 230 against 256, 32768 x 512 x 512 (256) 33.1 against 36.7; but
+    // 20000 x 1008 x 1008 (316) 77 against 71, 2048 x 4096 x 4096 (128) 99 against 83.
+    const int64_t tiles256 = ((d->M + 255) / 256) * ((d->N + 255) / 256) * d->batch;
+    const int64_t rounds256 = (tiles256 + 256 - 1) / 256;
+    const bool big = 10 * tiles256 >= 8 * rounds256 * 256 && 512 * d->K < (int64_t(1) << 31);
+    const int tile = big ? 256 : 128;
+    p.tiles_m = static_cast<int>((d->M + tile - 1) / tile);
+    p.tiles_n = static_cast<int>((d->N + tile - 1) / tile);
+    const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.batch;
+    auto fn = &gemm_kernel<128, 128, 1, 2, 2, true, false, EPI_PARTIAL_STATS>;
+    const size_t lds = big ? panel32_lds() : 2 * (128 * 128 + 128 * 128);
     int dev = 0, cus = 0;
-    if (device_cus(&dev, &cus) != LOKA_OK || prepare_fn(dev, reinterpret_cast<const void*>(fn), 256, lds, nullptr) != LOKA_OK)
+    if (device_cus(&dev, &cus) != LOKA_OK ||
+        prepare_fn(dev, big ? panel32_part_fn(0, true) : reinterpret_cast<const void*>(fn), big ? 512 : 256, lds, nullptr) != LOKA_OK)
         return LOKA_ERR_HIP;
-    const dim3 grid(static_cast<unsigned>(static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.batch));
-    fn<<<grid, 256, lds, s>>>(p);
+    if (big) panel32_part_launch(p, 0, true, dim3(static_cast<unsigned>(tiles < cus ? tiles : cus)), s);
+    else fn<<<dim3(static_cast<unsigned>(tiles)), 256, lds, s>>>(p);
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }
 

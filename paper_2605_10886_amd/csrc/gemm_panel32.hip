@@ -133,9 +133,16 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
     wait_vmcnt<0>();                             // codes and scales are in L2 before this wave passes the barrier
 }
 
-template <int EPI, int BW, int F8, bool QPRO = false>
+// Two forms leave as fp32 and normalize nothing (PART): EPI_SPLITK, one K range of one tile per workgroup, and BF16, the
+// reference GEMM (KB = 2 K bytes per row, two v_mfma_f32_32x32x16_bf16 in the place of each FP8 instruction: the same
+// bytes per fragment and the same matrix-pipe time per K step of 128 bytes, so the same main loop keeps the pipe full).
+// RAGK: K need not be a multiple of the 128-byte step: in the last step the lanes whose 16-byte chunk lies past the end
+// of the row read zeros, in both operands.
+template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0>
 __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     constexpr bool FP8OUT = F8 != 0;
+    constexpr bool SPLITK = EPI == EPI_SPLITK, PART = SPLITK || BF16;
+    static_assert(!PART || (!FP8OUT && !QPRO), "partial sums and the reference GEMM leave as fp32");
     constexpr bool BLOCKWISE = BW != 0;
     constexpr int BM = 256, BN = 256, NW = 8, WM = 128, WN = 64, MI = 4, NI = 2;
     constexpr int ES = 256 * 128;           // one ring entry: 256 rows x 128 bytes of X or of W
@@ -148,18 +155,23 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     const int l32 = lane & 31, hk = lane >> 5;
 
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
-    int tile_first = blockIdx.x, tile_stride = total_tiles;
+    // (split K: ids run range by range, so an XCD's workgroups contract the same K range of neighbouring tiles)
+    const int id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int tile_first = SPLITK ? id % total_tiles : id, tile_stride = SPLITK ? total_tiles : gridDim.x;
+    const int ks = SPLITK ? id / total_tiles : 0, k_lo = SPLITK ? ks * p.k_per_split : 0, kb0 = k_lo * 128;
     if (EPI == EPI_PANEL_SYNC) {
-        tile_first = xcd_contiguous(blockIdx.x, gridDim.x);
-        tile_stride = gridDim.x;
         // the workspace remembers which launch used it last (a wait that runs out records the same value beside it)
         if (p.header && blockIdx.x == 0 && threadIdx.x == 0)
             __hip_atomic_store(p.header, p.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // loop-invariant lane offsets
     const int ld_row = lane >> 3, ld_pos = lane & 7;
-    const int x_lane_off = ld_row * p.KB + (((ld_pos ^ (ld_row >> 1)) << 4) ^ ((wave & 1) << 6));
-    const int w_lane_off = ld_row * p.KB + (((ld_pos ^ ((ld_row >> 1) & 3)) << 4) ^ (((wave >> 1) & 1) << 6));
+    const int x_chunk = ((ld_pos ^ (ld_row >> 1)) << 4) ^ ((wave & 1) << 6);
+    const int w_chunk = ((ld_pos ^ ((ld_row >> 1) & 3)) << 4) ^ (((wave >> 1) & 1) << 6);
+    const int x_lane_off = ld_row * p.KB + x_chunk;
+    const int w_lane_off = ld_row * p.KB + w_chunk;
+    // chunks that exist in a ragged last K step
+    const bool x_in = !RAGK || x_chunk < (p.KB & 127), w_in = !RAGK || w_chunk < (p.KB & 127);
     // fragment read offsets inside a stage: K half s uses chunks 4s + 2hk, 4s + 2hk + 1
     const int xrow = wave_m * WM + l32;                                    // + 32 mi
     const int xkey = (xrow >> 1) & 7;
@@ -168,16 +180,26 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     const int wrow = wave_n * WN + wperm;                                  // + 32 ni
     const int wkey = ((wrow >> 1) & 1) | (((wrow >> 2) & 1) << 1) | (((wrow >> 4) & 1) << 2);
     const int w_off0 = wrow * 128 + (((2 * hk) ^ wkey) << 4), w_off1 = wrow * 128 + (((2 * hk + 1) ^ wkey) << 4);
-    const int ksteps = p.KB / 128;
+    const int ksteps_all = RAGK ? (p.KB + 127) / 128 : p.KB / 128;
+    const int ksteps = SPLITK && ksteps_all - k_lo > p.k_per_split ? p.k_per_split : ksteps_all - k_lo;
 
+    // n fastest where the tiles of a row panel run together, else in bands
+    auto locate = [&](int t, int& tm_, int& tn_, int& g_) __attribute__((always_inline)) {
+        g_ = t / (p.tiles_m * p.tiles_n);
+        t -= g_ * p.tiles_m * p.tiles_n;
+        if (PART) {
+            banded_tile(t, p.tiles_m, p.tiles_n, tm_, tn_);
+        } else {
+            tm_ = t / p.tiles_n;
+            tn_ = t - tm_ * p.tiles_n;
+        }
+    };
     // buffer descriptors of the tile whose operands are being streamed (bounds = the rows that exist: rows
     // past the end of X or W read as zeros)
     __amdgpu_buffer_rsrc_t x_rsrc, w_rsrc;
     auto set_rsrc = [&](int tile_id) __attribute__((always_inline)) {
-        int t = tile_id;
-        const int tn_ = t % p.tiles_n; t /= p.tiles_n;
-        const int tm_ = t % p.tiles_m;
-        const int g_ = t / p.tiles_m;
+        int tm_, tn_, g_;
+        locate(tile_id, tm_, tn_, g_);
         const int m0_ = tm_ * BM, n0_ = tn_ * BN;
         const int x_rows = p.M - m0_ < BM ? p.M - m0_ : BM, w_rows = p.N - n0_ < BN ? p.N - n0_ : BN;
         x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -196,10 +218,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     }
 
   for (int tile = tile_first; tile < total_tiles; tile += tile_stride) {
-    int t = tile;
-    const int tn = t % p.tiles_n; t /= p.tiles_n;
-    const int tm = t % p.tiles_m;
-    const int g = t / p.tiles_m;
+    int tm, tn, g;
+    locate(tile, tm, tn, g);
     const int m0 = tm * BM, n0 = tn * BN;
     const float* sxg = p.sx + static_cast<int64_t>(g) * p.strideSx;
     const float* swg = p.sw + static_cast<int64_t>(g) * p.strideSw;
@@ -209,14 +229,14 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     auto issue_x1 = [&](int slot, int kb, int j) __attribute__((always_inline)) {
         const int grp = wave + j * NW;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            x_rsrc, (__attribute__((address_space(3))) void*)(smem + slot * ES + grp * 1024), 16, x_lane_off,
-            grp * 8 * p.KB + kb, 0, 0);
+            x_rsrc, (__attribute__((address_space(3))) void*)(smem + slot * ES + grp * 1024), 16,
+            !RAGK || kb + kb0 + 128 <= p.KB || x_in ? x_lane_off : 0x7FFFFFFF, grp * 8 * p.KB + kb + kb0, 0, 0);
     };
     auto issue_w1 = [&](int slot, int kb, int j) __attribute__((always_inline)) {
         const int grp = wave + j * NW;
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            w_rsrc, (__attribute__((address_space(3))) void*)(smem + slot * ES + grp * 1024), 16, w_lane_off,
-            grp * 8 * p.KB + kb, 0, 0);
+            w_rsrc, (__attribute__((address_space(3))) void*)(smem + slot * ES + grp * 1024), 16,
+            !RAGK || kb + kb0 + 128 <= p.KB || w_in ? w_lane_off : 0x7FFFFFFF, grp * 8 * p.KB + kb + kb0, 0, 0);
     };
     auto issue_x = [&](int slot, int kb) __attribute__((always_inline)) {
 #pragma unroll
@@ -254,7 +274,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // (K a multiple of 512) a lane fetches four K blocks at once, every fourth step.
     float s_cur[MI], r_sc[MI], sx_nx[MI], sw_nx = 0.f;
     v4f sx_q[MI];
-    const bool quad = BLOCKWISE && (ksteps & 3) == 0;
+    const bool quad = BLOCKWISE && (ksteps & 3) == 0 && (ksteps_all & 3) == 0 && (k_lo & 3) == 0;
     auto pick = [](const v4f& v, int j) __attribute__((always_inline)) {
         return j == 0 ? v[0] : j == 1 ? v[1] : j == 2 ? v[2] : v[3];
     };
@@ -262,7 +282,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     const int bw_nb = ((n0 + wave_n * WN < p.N ? n0 + wave_n * WN : p.N - 1) >> 7), bw_nblk = p.N >> 7;
     auto bw_row = [&](int mi) __attribute__((always_inline)) {
         const int m = m0 + wave_m * WM + mi * 32 + l32;
-        return static_cast<int64_t>(m < p.M ? m : p.M - 1) * ksteps;
+        return static_cast<int64_t>(m < p.M ? m : p.M - 1) * ksteps_all + k_lo;
     };
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) {
@@ -270,7 +290,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
         sx_q[mi] = v4f{1.f, 1.f, 1.f, 1.f};
     }
     if (BLOCKWISE) {
-        const float sw0 = swg[bw_nb];
+        const float sw0 = swg[static_cast<int64_t>(k_lo) * bw_nblk + bw_nb];
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
             float sx0;
@@ -302,7 +322,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
             for (int mi = 0; mi < MI; ++mi) sc_x[mi] = static_cast<int>(__float_as_uint(sx_nx[mi]) >> 23);
         }
         if (k + 1 < ksteps) {
-            sw_nx = swg[static_cast<int64_t>(k + 1) * bw_nblk + bw_nb];
+            sw_nx = swg[static_cast<int64_t>(k_lo + k + 1) * bw_nblk + bw_nb];
             if (!quad) {
 #pragma unroll
                 for (int mi = 0; mi < MI; ++mi) sx_nx[mi] = sxg[bw_row(mi) + k + 1];
@@ -332,7 +352,13 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
         bx[mi] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
     };
     auto mfma_one = [&](int mi, int ni, int set) __attribute__((always_inline)) {
-        if (BW == 2)
+        if constexpr (BF16) {
+            const v8i a = aw[set][ni], b = bx[mi];
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, v4i{a[0], a[1], a[2], a[3]}),
+                                                                  __builtin_bit_cast(v8bf, v4i{b[0], b[1], b[2], b[3]}), acc[mi][ni], 0, 0, 0);
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, v4i{a[4], a[5], a[6], a[7]}),
+                                                                  __builtin_bit_cast(v8bf, v4i{b[4], b[5], b[6], b[7]}), acc[mi][ni], 0, 0, 0);
+        } else if (BW == 2)
             acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(aw[set][ni], bx[mi], acc[mi][ni], 0, 0, 0, sc_w, 0,
                                                                          sc_x[mi]);
         else
@@ -451,7 +477,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
         for (int a = 0; a < 4; ++a) {
-            if (BLOCKWISE) s4[ni][a] = v4f{1.f, 1.f, 1.f, 1.f};
+            if (BLOCKWISE || BF16) s4[ni][a] = v4f{1.f, 1.f, 1.f, 1.f};
             else if (tensor_w) { const float s = swg[0]; s4[ni][a] = v4f{s, s, s, s}; }
             else s4[ni][a] = ncol[ni] < p.N ? *reinterpret_cast<const v4f*>(swg + ncol[ni] + 4 * a) : v4f{0.f, 0.f, 0.f, 0.f};
         }
@@ -459,7 +485,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     for (int mi = 0; mi < MI; ++mi) {
         int m = m0 + wave_m * WM + mi * 32 + l32;
         m = m < p.M ? m : p.M - 1;
-        sxm[mi] = BW == 1 ? s_cur[mi] : BW == 2 ? 1.f : tensor_x ? sxg[0] : sxg[m];
+        sxm[mi] = BW == 1 ? s_cur[mi] : BW == 2 || BF16 ? 1.f : tensor_x ? sxg[0] : sxg[m];
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -482,12 +508,40 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     float* red2 = reinterpret_cast<float*>(smem + 16384);                          // [BM][4][2] (min, max) (FP8OUT); the
                                                                                    // transpose buffers take its place later
     const int64_t obase = static_cast<int64_t>(g) * p.strideO;
+    if (!BF16) {
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[mi][ni][i] *= s4[ni][i >> 2][i & 3] * sxm[mi];
+    }
+    if constexpr (PART) {
+        // fp32 tile: split K's share of this range (its scales are factors of every term) or the reference's Y.  Each
+        // wave passes a 32 x 32 sub-tile through 4 KB of its own LDS (128-byte rows, 16-byte chunk c of row r at position
+        // c ^ (r / 2 % 8)) and stores it with 8 lanes per row: whole 128-byte lines instead of 16 bytes in each of 64.
+        float* const dst = SPLITK ? p.part + (static_cast<int64_t>(ks) * p.batch + g) * p.M * p.N : p.y + obase;
+        uint8_t* const fbuf = smem + wave * 4096;
+        const int f_row = lane >> 3, f_c = lane & 7;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) acc[mi][ni][i] *= s4[ni][i >> 2][i & 3] * sxm[mi];
+            for (int ni = 0; ni < NI; ++ni) {
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+                    *reinterpret_cast<v4f*>(fbuf + l32 * 128 + (((4 * hk + a) ^ ((l32 >> 1) & 7)) << 4)) =
+                        v4f{acc[mi][ni][4 * a], acc[mi][ni][4 * a + 1], acc[mi][ni][4 * a + 2], acc[mi][ni][4 * a + 3]};
+                const int col = n0 + wave_n * WN + ni * 32 + f_c * 4;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 8 * j + f_row, m = m0 + wave_m * WM + mi * 32 + r;
+                    const v4f v = *reinterpret_cast<const v4f*>(fbuf + r * 128 + ((f_c ^ ((r >> 1) & 7)) << 4));
+                    if (m < p.M && col < p.N) *reinterpret_cast<v4f*>(dst + static_cast<int64_t>(m) * p.N + col) = v;
+                }
+            }
+        lds_barrier();
+        continue;
+    }
     if (p.y) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
@@ -930,6 +984,24 @@ const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro) {
     return bw == 2   ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0>)
            : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0>)
                      : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0>);
+}
+// a K that is no multiple of 128 (plain scales, bf16 output)
+const void* panel32_ragged_fn() { return reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, true>); }
+void panel32_ragged_launch(const GemmParams& p, dim3 grid, hipStream_t s) {
+    gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, true><<<grid, 512, kPanel32Lds, s>>>(p);
+}
+// split K (bw as above) and the BF16 reference GEMM: fp32 out
+const void* panel32_part_fn(int bw, bool bf16) {
+    return bf16      ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_ROW_IN_TILE, 0, 0, false, true>)
+           : bw == 2 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_SPLITK, 2, 0>)
+           : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_SPLITK, 1, 0>)
+                     : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_SPLITK, 0, 0>);
+}
+void panel32_part_launch(const GemmParams& p, int bw, bool bf16, dim3 grid, hipStream_t s) {
+    if (bf16) gemm_panel32_kernel<EPI_ROW_IN_TILE, 0, 0, false, true><<<grid, 512, kPanel32Lds, s>>>(p);
+    else if (bw == 2) gemm_panel32_kernel<EPI_SPLITK, 2, 0><<<grid, 512, kPanel32Lds, s>>>(p);
+    else if (bw == 1) gemm_panel32_kernel<EPI_SPLITK, 1, 0><<<grid, 512, kPanel32Lds, s>>>(p);
+    else gemm_panel32_kernel<EPI_SPLITK, 0, 0><<<grid, 512, kPanel32Lds, s>>>(p);
 }
 size_t panel32_lds() { return kPanel32Lds; }
 void panel32_launch(const GemmParams& p, int bw, dim3 grid, hipStream_t s) {
