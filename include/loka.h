@@ -182,8 +182,10 @@ int loka_variant_supports(const loka_gemm_desc* desc, int variant);
  *   gamma, beta: bf16 [N] or NULL (= 1 / 0), shared by all problems; beta is ignored by RMSNorm
  *   out_bf16 [batch][M, N] bf16 (required)
  *   y_fp32   [batch][M, N] fp32 pre-norm Y for the probe, or NULL to skip that store
- * Workspace: loka_fp8_gemm_norm_workspace(desc) bytes (non-zero only for variants whose row
- * statistics cross workgroups).  Returns LOKA_ERR_UNSUPPORTED when desc->variant cannot run
+ * Workspace: loka_fp8_gemm_norm_workspace(desc) bytes (non-zero for variants whose row statistics
+ * or partial sums cross workgroups).  With desc->variant < 0, layers with N <= 1024 or without a row norm also run with
+ * less, or with none, on the best kernel whose scratch fits (not those with at most 128 output tiles of 128 x 128 and
+ * K >= 2048, whose partial sums need the room).  Returns LOKA_ERR_UNSUPPORTED when desc->variant cannot run
  * the shape.  */
 size_t loka_fp8_gemm_norm_workspace(const loka_gemm_desc* desc);
 loka_status loka_fp8_gemm_norm(const loka_gemm_desc* desc, const uint8_t* xq, const float* sx, const uint8_t* wq,
@@ -206,9 +208,9 @@ loka_status loka_fp8_gemm_norm_check(const loka_gemm_desc* desc, const void* wor
  * owns (16 MiB per GPU the library runs on, held until the process ends) instead of from the caller.  Same arguments
  * otherwise, same kernels, same bits in out_bf16 / y_fp32.  The call allocates nothing and calls no allocating
  * routine; the first call on a device asks the runtime for the array's address on that device (set-up).
- *   - LOKA_ERR_WORKSPACE when the variant chosen for `desc` needs more scratch than
- *     LOKA_STATIC_SCRATCH_BYTES (loka_fp8_gemm_norm_workspace(desc) tells how much): use
- *     loka_fp8_gemm_norm with a caller-owned workspace for those.
+ *   - With desc->variant < 0 the library chooses among the kernels whose scratch fits LOKA_STATIC_SCRATCH_BYTES.
+ *     LOKA_ERR_WORKSPACE when none does, or when the variant named in `desc` needs more
+ *     (loka_fp8_gemm_norm_workspace(desc) tells how much): use loka_fp8_gemm_norm with a caller-owned workspace for those.
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap on one GPU (different streams, different
  *     threads) race on it and must be serialized by the caller.  Nothing in the array has to be cleared between
  *     calls (the kernels recognize stale contents), and no call relies on what an earlier one left there.

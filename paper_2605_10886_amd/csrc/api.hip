@@ -84,9 +84,33 @@ loka_status validate_desc(const loka_gemm_desc* d, bool fp8) {
     return LOKA_OK;
 }
 
+int variant_cheapest(const loka_gemm_desc* d, size_t max_ws);
+
 int resolve_variant(const loka_gemm_desc* d) {
     if (d->variant >= 0) return variant_supports(d, d->variant) ? d->variant : -1;
     return default_variant(d);
+}
+
+// The library's choice when it may use `ws_bytes` of scratch: the usual one where that fits, else the best of those that do
+// (-1: none, or the caller named the variant).
+static int variant_within(const loka_gemm_desc* d, int v, size_t ws_bytes) {
+    if (v < 0 || variant_workspace(d, v) <= ws_bytes) return v;
+    return d->variant >= 0 || d->norm == LOKA_NORM_BLOCKNORM ? -1 : variant_cheapest(d, ws_bytes);
+}
+
+// Layers that always run without scratch (loka.h): the kernels whose tile spans the row, or no row norm at all, unless few
+// output tiles meet a long K (split K, whose partial sums need room).
+static bool scratch_optional(const loka_gemm_desc* d) {
+    const int64_t t128 = ((d->M + 127) / 128) * ((d->N + 127) / 128) * d->batch;
+    return (d->N <= 1024 || d->norm == LOKA_NORM_NONE) && !(t128 <= 128 && d->K >= 2048);
+}
+
+// What loka_fp8_gemm_norm runs with this workspace (the workspace may still be too small for it).
+static int resolve_for_scratch(const loka_gemm_desc* d, const void* workspace, size_t ws_bytes) {
+    const int v = resolve_variant(d);
+    if (v < 0 || d->variant >= 0 || !scratch_optional(d)) return v;
+    const int fit = variant_within(d, v, workspace ? ws_bytes : 0);
+    return fit >= 0 ? fit : v;
 }
 
 }  // namespace loka
@@ -201,10 +225,11 @@ loka_status loka_fp8_gemm_norm_static(const loka_gemm_desc* desc, const uint8_t*
     if (!aligned16(xq) || !aligned16(wq) || !aligned16(sx) || !aligned16(sw) || !aligned16(out_bf16) ||
         !aligned16(y_fp32) || !aligned16(gamma_bf16) || !aligned16(beta_bf16))
         return LOKA_ERR_ALIGN;
-    const int v = resolve_variant(desc);
+    int v = resolve_variant(desc);
     if (v < 0) return LOKA_ERR_UNSUPPORTED;
+    v = variant_within(desc, v, kStaticScratchBytes);
+    if (v < 0) return LOKA_ERR_WORKSPACE;                           // beyond the array: use loka_fp8_gemm_norm with a workspace
     const size_t need = variant_workspace(desc, v);
-    if (need > kStaticScratchBytes) return LOKA_ERR_WORKSPACE;      // beyond the array: use loka_fp8_gemm_norm with a workspace
     void* ws = nullptr;
     if (need) {
         const loka_status sa = static_scratch_address(&ws);
@@ -229,7 +254,7 @@ loka_status loka_fp8_gemm_norm(const loka_gemm_desc* desc, const uint8_t* xq, co
     if (!aligned16(xq) || !aligned16(wq) || !aligned16(sx) || !aligned16(sw) || !aligned16(out_bf16) ||
         !aligned16(y_fp32) || !aligned16(gamma_bf16) || !aligned16(beta_bf16))
         return LOKA_ERR_ALIGN;
-    const int v = resolve_variant(desc);
+    const int v = resolve_for_scratch(desc, workspace, ws_bytes);
     if (v < 0) return LOKA_ERR_UNSUPPORTED;
     const size_t need = variant_workspace(desc, v);
     if (need && (!workspace || ws_bytes < need)) return LOKA_ERR_WORKSPACE;
@@ -295,7 +320,7 @@ loka_status loka_fp8_gemm_norm_check(const loka_gemm_desc* desc, const void* wor
     if (st != LOKA_OK) return st;
     // the variant loka_fp8_gemm_norm runs for desc, or (desc->variant < 0 only: the two choices can differ) the one
     // loka_fp8_gemm_norm_fp8out runs; every workspace with a bounded wait begins with the flag
-    int v = resolve_variant(desc);
+    int v = resolve_for_scratch(desc, workspace, ws_bytes);
     bool q = false;
     if (v < 0 || !variant_has_wait_flag(desc, v)) {
         const int vq = fp8out_variant(desc);

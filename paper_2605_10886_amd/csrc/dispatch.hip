@@ -15,13 +15,8 @@ namespace loka {
 int variant_count();
 const char* variant_name(int);
 bool variant_supports(const loka_gemm_desc*, int);
-int variant_epilogue(int);
 bool variant_is_streaming(int);
-bool variant_is_strip(int);
-bool variant_is_exact(int);
-int variant_bn(int);
-int variant_splitk_choice(const loka_gemm_desc*);
-int variant_bm(int);
+int variant_cheapest(const loka_gemm_desc*, size_t max_ws);
 loka_status validate_desc(const loka_gemm_desc* d, bool fp8);
 loka_status bf16_gemm_launch(const loka_gemm_desc*, const void*, const void*, float*, void*, hipStream_t, bool weights_ready);
 
@@ -62,9 +57,22 @@ struct DevBuf {
 
 }  // namespace
 
-// Static choice when nothing was profiled: the narrowest tile that still spans the row
-// (so the norm stays in the tile), taller tiles once M is large enough to fill the chip;
-// rows wider than every such tile go to the two-pass schedule.
+// The cheapest variant of a shape by the cost model, which is a pure function of the descriptor: a thread remembers the
+// last few shapes it asked for, because a call asks two or three times (workspace size, launch) and the model looks at
+// every variant (about 2 us; a small layer is a launch of 5).
+static int static_choice(const loka_gemm_desc* d) {
+    using Key = std::tuple<int64_t, int64_t, int64_t, int64_t, int, int, int>;
+    struct Slot { Key key; int variant; };
+    static thread_local Slot slots[16];
+    const Key key(d->M, d->N, d->K, d->batch, d->norm, d->x_mode, d->w_mode);
+    const uint64_t h = (static_cast<uint64_t>(d->M) * 0x9E3779B97F4A7C15ull) ^ (static_cast<uint64_t>(d->N) * 0xC2B2AE3D27D4EB4Full) ^
+                       (static_cast<uint64_t>(d->K) * 0x165667B19E3779F9ull) ^ (static_cast<uint64_t>(d->norm * 8 + d->x_mode) << 58);
+    Slot& s = slots[h >> 60];
+    if (s.key != key) s = Slot{key, variant_cheapest(d, SIZE_MAX)};        // (an empty slot holds M = 0: no valid shape)
+    return s.variant;
+}
+
+// The profiled choice where loka_dispatch has been run for the shape, else the static one.
 int default_variant(const loka_gemm_desc* d) {
     {
         const RecipeKey rk(d->M, d->N, d->K, d->batch, epilogue_of(d), d->x_mode, d->w_mode);
@@ -82,64 +90,7 @@ int default_variant(const loka_gemm_desc* d) {
                 if (variant_supports(d, v) && (pass == 1 || variant_is_streaming(v) == stream)) return v;
         return -1;
     }
-    // few output tiles and a long K (weight gradients; the widest layers at small batch): split K over several
-    // workgroups per tile (measured at 2048 x 123200 x 1024 with LayerNorm: see the variant's table entry)
-    {
-        const int64_t t128 = ((d->M + 127) / 128) * ((d->N + 127) / 128) * d->batch;
-        if (t128 <= 128 && d->K >= 2048) {
-            const int v = variant_splitk_choice(d);
-            if (v >= 0) return v;
-        }
-    }
-    // Measured on the skinny shapes (65536 x 1024 x 256, 65536 x 256 x 1024, 16384 x 512 x 512, 64 x 4096 x 256 x 256):
-    // with at least one 256 x 256 tile per CU the large-tile kernel wins when K is long and the row fits one
-    // tile (no cross-workgroup exchange then), and for blockwise scales, which the streaming kernel lacks.
-    const int64_t tiles256 = ((d->M + 255) / 256) * ((d->N + 255) / 256) * d->batch;
-    const bool blockwise = scale_mode_is_block(d->x_mode);
-    if (tiles256 >= 256 && d->N <= 1024 && (blockwise || (d->N <= 256 && d->K >= 1024))) {
-        for (int v = variant_count() - 1; v >= 0; --v)
-            if (variant_supports(d, v) && variant_epilogue(v) == 2) return v;
-    }
-    // small layers (K * N <= 128 KB, N <= 256) with enough rows: W in LDS, one row strip per wave (measured against
-    // the streaming kernel: 64 x (4096 x 256 x 256) 42.5 against 63 us, 65536 x 256 x 128 10.9 against 19.4 us,
-    // 65536 x 128 x 256 15.7 against 19.7 us, 65536 x 512 x 128 13.1 against 21.6 us)
-    // (only where W fits the LDS in one piece: the variant that streams K slabs of W is left to the profiler)
-    if (d->M * d->batch >= 8192 && (d->N <= 128 ? 128 : 256) * d->K <= 131072) {
-        for (int v = 0; v < variant_count(); ++v)
-            if (variant_is_strip(v) && variant_supports(d, v)) return v;
-    }
-    // skinny layers with enough rows to give every CU several row blocks: W in registers, X streamed
-    if (d->M * d->batch >= 8192) {
-        for (int v = 0; v < variant_count(); ++v)
-            if (variant_is_streaming(v) && variant_supports(d, v)) return v;
-    }
-    int best = -1;
-    int64_t best_bn = 0, best_bm = 0;
-    for (int v = 0; v < variant_count(); ++v) {
-        // (the exact-product forms of these tiles are never the static choice: they trade speed for accuracy)
-        if (variant_epilogue(v) != 0 || variant_is_streaming(v) || variant_is_strip(v) || variant_is_exact(v) || !variant_supports(d, v)) continue;
-        const int64_t bn = variant_bn(v), bm = variant_bm(v);
-        const int64_t tiles = ((d->M + bm - 1) / bm) * d->batch;
-        bool better;
-        if (best < 0) better = true;
-        else if (bn != best_bn) better = bn < best_bn;
-        else better = bm > best_bm && tiles >= 1024;     // taller tile only with >= 4 tiles per CU left
-        if (better) { best = v; best_bn = bn; best_bm = bm; }
-    }
-    if (best >= 0) return best;
-    // rows wider than a tile: the persistent panel-synchronous schedule once there is enough work to fill
-    // the chip for several rounds, the small two-pass tile otherwise
-    // (later table entries of a kind are the faster ones where they apply: 32x32x64 MFMAs for non-blockwise scales)
-    const bool big = d->M * d->N * d->batch >= (int64_t(1) << 24);
-    if (big) {
-        for (int v = variant_count() - 1; v >= 0; --v)
-            if (variant_supports(d, v) && variant_epilogue(v) == 2) return v;
-    }
-    for (int v = 0; v < variant_count(); ++v)
-        if (variant_supports(d, v) && variant_epilogue(v) == 1) return v;
-    for (int v = 0; v < variant_count(); ++v)
-        if (variant_supports(d, v)) return v;
-    return -1;
+    return static_choice(d);
 }
 
 }  // namespace loka

@@ -21,8 +21,12 @@
 // position): key(r) takes 8 values over the 8 same-parity rows of each operand's read pattern.
 #include "gemm_common.h"
 
+#include <algorithm>
+#include <array>
 #include <atomic>
 #include <chrono>
+#include <cmath>
+#include <cstring>
 #include <mutex>
 #include <vector>
 
@@ -45,9 +49,11 @@ __device__ __forceinline__ v8bf e4m3x8_to_bf16(int w0, int w1) {
 // Stages of 128 bytes per row kept in LDS, and the bytes a launch asks for: two stages (one in flight) everywhere but in
 // the eight-wave form of the split-K schedule, whose short chains of K steps need several loads in flight to hide the
 // memory latency (its ring also carries 1 KB of block scales per stage).
-constexpr int gemm_stages(int epi, int waves) { return (epi == EPI_SPLITK && waves == 8) ? 4 : 2; }
+constexpr int gemm_stages(int bm, int epi, int waves) {
+    return ((epi == EPI_SPLITK || epi == EPI_PANEL_SYNC) && bm == 128 && waves == 8) ? 4 : 2;
+}
 constexpr size_t gemm_lds_bytes(int bm, int bn_sub, int epi, int waves) {
-    return static_cast<size_t>(gemm_stages(epi, waves)) * (bm * 128 + bn_sub * 128 + (gemm_stages(epi, waves) > 2 ? 1024 : 0));
+    return static_cast<size_t>(gemm_stages(bm, epi, waves)) * (bm * 128 + bn_sub * 128 + (gemm_stages(bm, epi, waves) > 2 ? 1024 : 0));
 }
 
 template <int BM, int BN_SUB, int NSPLIT, int WAVES_M, int WAVES_N, bool IS_BF16, bool BLOCKWISE, int EPI, bool EXACT = false>
@@ -61,7 +67,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     constexpr int BN = BN_SUB * NSPLIT;
     constexpr int XS = BM * 128;               // bytes of one X stage
     constexpr int WS = BN_SUB * 128;           // bytes of one W stage
-    constexpr int NST = gemm_stages(EPI, NW);  // stages in LDS (split K with eight waves: a ring of 4, three in flight)
+    constexpr int NST = gemm_stages(BM, EPI, NW);  // stages in LDS (split K with eight waves: a ring of 4, three in flight)
     constexpr bool RING = NST > 2;
     static_assert(WM % 16 == 0 && WN % 16 == 0 && (NI == 2 || NI == 4 || NI == 8), "tile shape");
     static_assert(BM % 8 == 0 && BN_SUB % 8 == 0, "loader works on 8-row groups");
@@ -86,7 +92,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     // the tile list (n fastest) in rounds of gridDim.x tiles, so the tiles_n workgroups that share a row panel always
     // run in the same round.
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
-    const int id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int id = EPI == EPI_PANEL_SYNC && BM < 256 ? static_cast<int>(blockIdx.x) : xcd_contiguous(blockIdx.x, gridDim.x);
     int tile_first = EPI == EPI_SPLITK ? id % total_tiles : id, tile_stride = total_tiles;
     if (EPI == EPI_PANEL_SYNC) {
         tile_stride = gridDim.x;
@@ -95,6 +101,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
             __hip_atomic_store(p.header, p.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   for (int tile = tile_first; tile < total_tiles; tile += tile_stride) {
+    if (EPI == EPI_PANEL_SYNC) lds_barrier();              // the previous tile's epilogue is done with the LDS
     const int g = tile / (p.tiles_m * p.tiles_n);
     int tm, tn;
     if (EPI == EPI_PANEL_SYNC) {
@@ -127,12 +134,12 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     // Addressing: buffer loads straight into LDS.  One buffer descriptor per operand covers exactly the
     // tile's valid rows (scalar registers), one loop-invariant 32-bit per-lane offset per operand
     // (row-in-group * KB + swizzled chunk * 16; the group-dependent part of the swizzle key depends only
-    // on the wave, because NW and XG are multiples of 4), and a uniform scalar offset per entry (group
+    // on the wave, because NW is a multiple of 4), and a uniform scalar offset per entry (group
     // row offset + K offset).  Rows past the end of a ragged M or N tail fall outside the descriptor and
     // load zeros; their results are never stored.
     constexpr int XG = BM / 8, WGR = BN_SUB / 8;
-    static_assert(XG % NW == 0 && WGR % NW == 0 && NW % 4 == 0 && XG % 4 == 0, "loader split");
-    constexpr int XJ = XG / NW, JN = XJ + WGR / NW;
+    static_assert((XG % NW == 0 || XG < NW) && WGR % NW == 0 && NW % 4 == 0, "loader split");
+    constexpr int XJ = (XG + NW - 1) / NW, JN = XJ + WGR / NW;
     const int x_chunk = ((ld_pos ^ (ld_row >> 1)) << 4) ^ ((wave & 1) << 6);       // byte offset inside the 128-byte K step
     const int w_chunk = ((ld_pos ^ ((ld_row >> 1) & 1)) << 4) ^ ((wave & 3) << 5);
     const int x_lane_off = ld_row * p.KB + x_chunk;
@@ -152,7 +159,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
         kb += kb0;
         const bool tail = kb + 128 > p.KB;                    // uniform: the ragged last step
         if (j < XJ) {
-            if (with_x) {
+            if (with_x && (XG >= NW || wave < XG)) {
                 const int grp = wave + j * NW;                // uniform
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     x_rsrc, (__attribute__((address_space(3))) void*)(xbuf + stage_x * XS + grp * 1024), 16,
@@ -998,7 +1005,7 @@ void strip_launch(const GemmParams& p, dim3 grid, hipStream_t s);
 static void launch_strip_any(const GemmParams& p, bool, dim3 grid, hipStream_t s) { strip_launch(p, grid, s); }
 static const char kStripName[] = "strip32";
 static const char kPanel32Name[] = "panel32_256x256";
-static const char kSplitk256Name[] = "splitk256x256";
+static const char kPanel32RaggedName[] = "panel32_256x256_ragged";
 
 // gemm_panel32.hip
 const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro = false);
@@ -1010,11 +1017,11 @@ static int panel32_bw(const GemmParams& p, bool blockwise) { return !blockwise ?
 static void launch_panel32(const GemmParams& p, bool blockwise, dim3 grid, hipStream_t s) {
     panel32_launch(p, panel32_bw(p, blockwise), grid, s);
 }
+const void* panel32_ragged_fn();
+void panel32_ragged_launch(const GemmParams& p, dim3 grid, hipStream_t s);
 const void* panel32_part_fn(int bw, bool bf16);
 void panel32_part_launch(const GemmParams& p, int bw, bool bf16, dim3 grid, hipStream_t s);
-static void launch_splitk256(const GemmParams& p, bool blockwise, dim3 grid, hipStream_t s) {
-    panel32_part_launch(p, panel32_bw(p, blockwise), false, grid, s);
-}
+static void launch_panel32_ragged(const GemmParams& p, bool, dim3 grid, hipStream_t s) { panel32_ragged_launch(p, grid, s); }
 
 template <int BM, int BN_SUB, int NSPLIT, int WAVES_M, int WAVES_N, int EPI>
 static void launch_exact(const GemmParams& p, bool, dim3 grid, hipStream_t s) {
@@ -1040,6 +1047,11 @@ static const VariantInfo kVariants[] = {
     LOKA_VARIANT("row128x256", 128, 256, 1, 2, 4, EPI_ROW_IN_TILE),
     LOKA_VARIANT("row64x512", 64, 512, 1, 1, 8, EPI_ROW_IN_TILE),
     LOKA_VARIANT("row64x1024", 64, 512, 2, 1, 8, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row16x256", 16, 256, 1, 1, 4, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row32x256", 32, 256, 1, 1, 4, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row16x512", 16, 512, 1, 1, 8, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row32x512", 32, 512, 1, 1, 8, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row16x1024", 16, 512, 2, 1, 8, EPI_ROW_IN_TILE),
     // exact products: e4m3 operands widened to bf16 in registers and contracted on the BF16 matrix instruction (the
     // accuracy-first candidates of the non-blockwise recipes: fp32 Y agrees with exact arithmetic up to fp32 summation)
     LOKA_VARIANT_EXACT("exact64x256", 64, 256, 1, 1, 4, EPI_ROW_IN_TILE),
@@ -1058,16 +1070,22 @@ static const VariantInfo kVariants[] = {
     // split K: layers with few output tiles and a long K (weight gradients, the widest layers at small batch); ksplit
     // workgroups per tile contract a K range each into fp32 partial sums, a second kernel adds them and normalizes.
     // Two forms: eight waves on a ring of four LDS stages, one workgroup per CU (short ranges: a weight gradient), and
-    // four waves on two stages, two workgroups per CU (long ranges)
+    // the form for long ranges: four waves on two stages, two workgroups per CU, or 256 x 256 tiles on the panel kernel's
+    // main loop, one workgroup per CU, where the cost model below expects that to be faster
     LOKA_VARIANT("splitk128x128", 128, 128, 1, 2, 4, EPI_SPLITK),
     LOKA_VARIANT("splitk128x128s2", 128, 128, 1, 2, 2, EPI_SPLITK),
     // persistent, panel-synchronous: the tiles_n workgroups of a row panel exchange row statistics
     // through a few words of global memory and normalize their own tile in registers
     LOKA_VARIANT("panel256x256w8", 256, 256, 1, 2, 4, EPI_PANEL_SYNC),
+    // smaller tiles for layers that would leave CUs idle on 256 x 256 ones; two workgroups per CU (32 x 256, 64 x 256) or
+    // a ring of four stages (128 x 128)
+    LOKA_VARIANT("panel32x256", 32, 256, 1, 1, 4, EPI_PANEL_SYNC),
+    LOKA_VARIANT("panel64x256", 64, 256, 1, 1, 4, EPI_PANEL_SYNC),
+    LOKA_VARIANT("panel128x128", 128, 128, 1, 2, 4, EPI_PANEL_SYNC),
     // the same schedule on 32x32x64 MFMAs: the throughput variant
     {kPanel32Name, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32, panel32_fn(0, false, false), panel32_fn(1, false, false)},
-    // split K on the same main loop, one workgroup per CU
-    {kSplitk256Name, 256, 256, 512, EPI_SPLITK, panel32_lds(), &launch_splitk256, panel32_part_fn(0, false), panel32_part_fn(1, false)},
+    // ... for a K that is no multiple of the 128-byte step (non-blockwise recipes, bf16 output)
+    {kPanel32RaggedName, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32_ragged, panel32_ragged_fn(), nullptr},
 };
 constexpr int kMaxRowTiles = 256;     // shape limit of the panel-synchronous schedule (a row's tiles must be co-resident:
                                       // the launch checks them against the CU count of the device it runs on)
@@ -1076,7 +1094,6 @@ constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 int variant_count() { return kNumVariants; }
 const char* variant_name(int v) { return (v >= 0 && v < kNumVariants) ? kVariants[v].name : nullptr; }
-int variant_epilogue(int v) { return kVariants[v].epi; }
 bool variant_supports(const loka_gemm_desc* d, int v);
 // kernels that can take bf16 X and quantize it per row themselves (loka_fp8_linear_norm)
 bool variant_supports_fused(const loka_gemm_desc* d, int v) {
@@ -1125,40 +1142,142 @@ int variant_streaming_id() {
 bool variant_is_streaming(int v) { return kVariants[v].name == kWregName; }
 bool variant_is_strip(int v) { return kVariants[v].name == kStripName; }
 bool variant_is_panel32(int v) { return kVariants[v].name == kPanel32Name; }
-bool variant_is_exact(int v) { return kVariants[v].launch != nullptr && kVariants[v].name[0] == 'e' && kVariants[v].name[1] == 'x'; }
-int variant_bn(int v) { return kVariants[v].bn; }
-int variant_bm(int v) { return kVariants[v].bm; }
+// (the two instantiations of the 32 x 32 x 64 kernel that lay out the workspace its way)
+static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Name || vi.name == kPanel32RaggedName; }
 
-// Split K: the number of K ranges and their length in 128-byte steps.  The ring form: as many ranges as give an
-// MI355X's 256 CUs one workgroup each and no more (its stages fill a CU's LDS: a 257th workgroup would be a second
-// round).  The two-stage form: about two workgroups per CU.  At least 4 steps per range, at most 64 ranges.  (Fixed
-// figures, not the device's CU count: the workspace size follows from them and must not depend on the device.)
-static void splitk_plan(const loka_gemm_desc* d, const VariantInfo& vi, int* ksplit, int* per) {
-    const int64_t tiles = ((d->M + vi.bm - 1) / vi.bm) * ((d->N + vi.bn - 1) / vi.bn) * d->batch;
+// ---- expected time of a variant, in microseconds: what the static choice compares.
+// A launch is `start` plus, per round of workgroups (tiles over the slots of 256 CUs), `round` plus K steps of
+// `step` + `step_full` * (share of the slots in use: the last level caches and the power budget are shared), plus the
+// output at `mout` per million elements; kernels that exchange or re-read for a row norm add `norm` (per round; two-pass:
+// once per problem) and `norm_mout`.  Fitted (non-negative least squares on relative error) to every variant's time at 570
+// shapes, M 64 - 131072, N 64 - 4096, K 64 - 8192; the choice is within 1.4 % of the fastest variant in the geometric mean
+// over them (worst 1.48), where choosing by tile width and row count alone was at 30 % (2048 x 768 x 256: 64-row tiles
+// 17.5 us, 16-row tiles 8.6; 4096 x 1024 x 8192: 143 us, split K 52; 2048 x 3008 x 256: two-pass 27.6, panel 17.2).
+// Fixed figures for an MI355X, not the running device's: workspace sizes follow from the choice.
+struct CostRow { float start, round, step, step_full, mout, norm, norm_mout; };
+struct VariantCost { const char* name; int per_cu; CostRow plain, block; };
+constexpr int kPlanCus = 256;
+static const VariantCost kCosts[] = {
+    {"row32x128", 3, {3.62f, 0.f, .31f, .21f, .75f}, {3.37f, 0.f, .46f, .47f, .77f}},
+    {"row64x128", 3, {3.3f, .87f, .33f, .48f, .47f}, {3.75f, 0.f, .64f, .45f, .62f}},
+    {"row64x256", 2, {2.4f, 3.31f, .51f, .59f, .31f}, {.64f, 4.74f, 1.11f, .57f, .38f}},
+    {"row128x256", 1, {1.68f, 4.62f, .89f, .13f, .29f}, {0.f, 5.95f, 1.42f, .51f, .25f}},
+    {"row64x512", 1, {2.14f, 4.06f, .88f, .14f, .5f}, {1.78f, 4.73f, 1.52f, .33f, .12f}},
+    {"row64x1024", 1, {1.39f, 7.66f, 1.26f, .21f, .05f}, {2.17f, 7.04f, 2.23f, .08f, 0.f}},
+    {"row16x256", 2, {2.05f, 1.74f, .41f, .19f, .63f}, {.56f, 2.86f, .58f, .21f, .09f}},
+    {"row32x256", 2, {2.04f, 2.31f, .41f, .25f, .44f}, {2.82f, 1.13f, .76f, .22f, .63f}},
+    {"row16x512", 1, {1.68f, 2.31f, .62f, .12f, .64f}, {.7f, 3.11f, .82f, .2f, 0.f}},
+    {"row32x512", 1, {1.86f, 2.84f, .68f, .13f, .58f}, {.68f, 3.93f, 1.03f, .22f, 0.f}},
+    {"row16x1024", 1, {1.41f, 3.8f, .86f, .16f, 0.f}, {.75f, 4.3f, 1.22f, .05f, 0.f}},
+    // (W stays on the CU: a round is 32 rows per workgroup, `step` per 64 K of weights, `step_full` per million of X)
+    {kWregName, 1, {6.44f, .27f, .55f, .11f, .16f}, {}},
+    {kStripName, 1, {6.84f, 0.f, 1.21f, 0.f, 0.f}, {}},
+    {"twopass128x128", 2, {3.81f, 0.f, .47f, .42f, .44f, 6.41f, 1.7f}, {2.88f, 0.f, 1.07f, .31f, .51f, 6.02f, 1.68f}},
+    {"panel32x256", 2, {3.35f, 1.32f, .41f, .39f, .2f, 4.47f}, {3.57f, .08f, .79f, .23f, .51f, 4.26f}},
+    {"panel64x256", 2, {3.89f, 1.84f, .55f, .44f, .26f, 5.68f}, {4.19f, .19f, 1.16f, .31f, .41f, 5.05f}},
+    {"panel128x128", 1, {3.34f, 1.8f, .5f, .14f, .22f, 5.69f}, {3.55f, 1.26f, .66f, .11f, .34f, 5.53f}},
+    {kPanel32Name, 1, {2.55f, 6.65f, .98f, .25f, .11f, 4.3f}, {3.66f, 4.5f, 1.5f, .27f, .12f, 4.5f}},
+    {kPanel32RaggedName, 1, {.63f, 8.17f, 1.05f, .22f, .2f, 5.14f}, {}},
+    // split K: `mout` per million partial sums, `norm_mout` per million outputs
+    {"splitk128x128", 1, {10.5f, 0.f, 0.f, .59f, 1.79f}, {11.5f, 0.f, 0.f, .77f, 1.44f}},
+    {"splitk128x128s2", 2, {10.7f, 0.f, 0.f, .79f, 1.78f}, {12.f, 0.f, .12f, 1.13f, 1.37f, 0.f, .66f}},
+};
+static const VariantCost kCostSplitk256 = {"", 1, {15.8f, 0.f, .2f, 1.08f, 1.06f, 0.f, .27f}, {14.8f, 0.f, .66f, 1.38f, .85f, 0.f, .63f}};
+
+static const VariantCost* cost_entry(int v) {
+    static const auto table = [] {
+        std::array<const VariantCost*, kNumVariants> t{};
+        for (int i = 0; i < kNumVariants; ++i)
+            for (const VariantCost& c : kCosts)
+                if (std::strcmp(c.name, kVariants[i].name) == 0) t[i] = &c;
+        return t;
+    }();
+    return table[v];
+}
+
+// Split K: tile size, number of K ranges and their length in 128-byte steps.  The forms with one workgroup per CU: as
+// many ranges as give 256 CUs one workgroup each and no more (their stages fill a CU's LDS: a 257th workgroup would be a
+// second round).  The two-stage form: about two workgroups per CU.  At least 4 steps per range, at most 64 ranges.
+struct SplitkPlan { int tile, ksplit, per; double cost; };
+static SplitkPlan splitk_ranges(const loka_gemm_desc* d, int tile, bool two_per_cu, const VariantCost& vc) {
+    const int64_t tiles = ((d->M + tile - 1) / tile) * ((d->N + tile - 1) / tile) * d->batch;
     const int64_t steps = (d->K + 127) / 128;
-    int64_t want = vi.threads == 512 ? 256 / tiles : (512 + tiles - 1) / tiles;
+    int64_t want = two_per_cu ? (2 * kPlanCus + tiles - 1) / tiles : kPlanCus / tiles;
     if (want > 64) want = 64;
     if (want > steps / 4) want = steps / 4;
     if (want < 1) want = 1;
-    const int64_t len = (steps + want - 1) / want;
-    *per = static_cast<int>(len);
-    *ksplit = static_cast<int>((steps + len - 1) / len);
+    const int64_t len = (steps + want - 1) / want, ksplit = (steps + len - 1) / len;
+    const CostRow& c = scale_mode_is_block(d->x_mode) ? vc.block : vc.plain;
+    const double slots = kPlanCus * vc.per_cu, wgs = static_cast<double>(ksplit) * tiles;
+    const double rounds = std::ceil(wgs / slots), use = std::min(1.0, wgs / slots), out = 1e-6 * d->M * d->N * d->batch;
+    return {tile, static_cast<int>(ksplit), static_cast<int>(len),
+            c.start + rounds * len * (c.step + c.step_full * use) + ksplit * out * c.mout + out * c.norm_mout};
+}
+static bool splitk_is_ring(const VariantInfo& vi) { return vi.threads == 512; }
+static SplitkPlan splitk_plan(const loka_gemm_desc* d, int v) {
+    const SplitkPlan a = splitk_ranges(d, 128, !splitk_is_ring(kVariants[v]), *cost_entry(v));
+    if (splitk_is_ring(kVariants[v]) || 256 * d->K >= (int64_t(1) << 31)) return a;
+    const SplitkPlan b = splitk_ranges(d, 256, false, kCostSplitk256);
+    return b.ksplit >= 2 && (a.ksplit < 2 || b.cost < a.cost) ? b : a;
 }
 
 bool variant_supports(const loka_gemm_desc* d, int v);
 // the split-K form for the shape: the ring form unless its ranges would be long (measured: 65536 x 256 x 1024 as a weight
-// gradient, 32 steps per range, 43.5 us against 48.5 us for the two-stage form; 2048 x 123200 x 1024, 482 steps per range,
-// 437 us against 400 us), the other form where only one of them splits K at all
-int variant_splitk_choice(const loka_gemm_desc* d) {
+// gradient, 32 steps per range, 36.6 us against 41 us for the two-stage form; 2048 x 123200 x 1024, 482 steps per range:
+// 128 x 128 tiles 346 us, 256 x 256 tiles 242) or 256 x 256 tiles are expected to be faster; the other form where only one
+// of them splits K at all
+static int splitk_choice(const loka_gemm_desc* d) {
     int ring = -1, two = -1;
     for (int v = 0; v < kNumVariants; ++v) {
         if (kVariants[v].epi != EPI_SPLITK || !variant_supports(d, v)) continue;
-        if (kVariants[v].bm != 128) continue; if (kVariants[v].threads == 512) ring = v; else two = v;
+        if (splitk_is_ring(kVariants[v])) ring = v; else two = v;
     }
     if (ring < 0 || two < 0) return ring >= 0 ? ring : two;
-    int ksplit = 1, per = 1;
-    splitk_plan(d, kVariants[ring], &ksplit, &per);
-    return per <= 128 ? ring : two;
+    const SplitkPlan r = splitk_plan(d, ring), t = splitk_plan(d, two);
+    return r.per <= 128 && !(t.tile == 256 && t.cost < r.cost) ? ring : two;
+}
+
+// Expected time of variant v; negative where the static choice does not consider it (no row of the table above).
+static double variant_cost(const loka_gemm_desc* d, int v) {
+    const VariantInfo& vi = kVariants[v];
+    const VariantCost* vc = cost_entry(v);
+    if (!vc) return -1.0;
+    if (vi.epi == EPI_SPLITK) return splitk_plan(d, v).cost;
+    const CostRow& c = scale_mode_is_block(d->x_mode) ? vc->block : vc->plain;
+    const double out = 1e-6 * d->M * d->N * d->batch;
+    if (vi.name == kWregName || vi.name == kStripName) {
+        const double rounds = std::max(1.0, ((d->M + 31) / 32) * d->batch / static_cast<double>(kPlanCus * vc->per_cu));
+        return c.start + rounds * (c.round + c.step * d->K * d->N / 65536.0) + out * c.mout + c.step_full * 1e-6 * d->M * d->K * d->batch;
+    }
+    const int64_t tiles_n = (d->N + vi.bn - 1) / vi.bn, tiles = ((d->M + vi.bm - 1) / vi.bm) * tiles_n * d->batch;
+    int64_t slots = kPlanCus * vc->per_cu;
+    if (vi.epi == EPI_PANEL_SYNC) slots = slots / tiles_n * tiles_n;        // whole row panels at a time
+    // (one-tile workgroups: past a few rounds they drift apart and the last round no longer stands out)
+    const bool whole = vi.epi == EPI_PANEL_SYNC || tiles < 4 * slots;
+    const double rounds = whole ? static_cast<double>((tiles + slots - 1) / slots) : static_cast<double>(tiles) / slots;
+    const double steps = static_cast<double>((d->K + 127) / 128) * (vi.bn > 512 ? (d->N + 511) / 512 : 1);
+    double t = c.start + rounds * (c.round + steps * (c.step + c.step_full * std::min(1.0, static_cast<double>(tiles) / slots))) + out * c.mout;
+    if (d->norm != LOKA_NORM_NONE)
+        t += out * c.norm_mout + c.norm * (vi.epi == EPI_PANEL_SYNC ? rounds * (tiles_n > 1 ? 1.0 : 0.3) : static_cast<double>(d->batch));
+    return t;
+}
+
+size_t variant_workspace(const loka_gemm_desc* d, int v, bool fp8out);
+// The static choice among the variants whose workspace fits `max_ws`: the least expected time.  The streaming kernel only
+// from 4096 rows on (below, its set-up is most of the launch and the fit does not describe it).  -1: none.
+int variant_cheapest(const loka_gemm_desc* d, size_t max_ws) {
+    const int split = splitk_choice(d);
+    int best = -1;
+    double best_cost = 0.0;
+    for (int v = 0; v < kNumVariants; ++v) {
+        if (!variant_supports(d, v) || (kVariants[v].epi == EPI_SPLITK && v != split)) continue;
+        if (kVariants[v].name == kWregName && d->M * d->batch < 4096) continue;
+        const double c = variant_cost(d, v);
+        if (c < 0.0 || (best >= 0 && c >= best_cost) || (max_ws != SIZE_MAX && variant_workspace(d, v, false) > max_ws)) continue;
+        best = v;
+        best_cost = c;
+    }
+    return best;
 }
 
 bool variant_supports(const loka_gemm_desc* d, int v) {
@@ -1170,14 +1289,13 @@ bool variant_supports(const loka_gemm_desc* d, int v) {
     // a K that is not a multiple of 128 (the non-blockwise recipes allow any multiple of 16): the general tiled kernel
     // masks the tail of the last K step; the 32x32 panel kernel does not
     if (vi.name == kPanel32Name && d->K % 128) return false;
+    if (vi.name == kPanel32RaggedName && d->K % 128 == 0) return false;
     // BlockNorm (groups of 256 columns) is built into the kernels whose tile is 256 columns wide
     if (d->norm == LOKA_NORM_BLOCKNORM && vi.launch != &launch_panel32) return false;
     if ((scale_mode_is_block(d->x_mode) ? vi.fn_block : vi.fn_plain) == nullptr) return false;
     if (vi.epi == EPI_SPLITK) {
         // (offered where K actually gets split: with a single range it is the two-pass schedule with more traffic)
-        int ksplit = 1, per = 1;
-        splitk_plan(d, vi, &ksplit, &per);
-        if (d->N > kSplitkMaxN || d->norm == LOKA_NORM_BLOCKNORM || ksplit < 2) return false;
+        if (d->N > kSplitkMaxN || d->norm == LOKA_NORM_BLOCKNORM || splitk_plan(d, v).ksplit < 2) return false;
     }
     if (vi.epi == EPI_ROW_IN_TILE && d->N > vi.bn) return false;
     if (vi.epi == EPI_PANEL_SYNC && (d->N + vi.bn - 1) / vi.bn > kMaxRowTiles) return false;
@@ -1195,7 +1313,7 @@ bool variant_supports(const loka_gemm_desc* d, int v) {
 static bool panel_exchanges(const loka_gemm_desc* d, const VariantInfo& vi, bool fp8out = false) {
     if (vi.epi != EPI_PANEL_SYNC || d->norm == LOKA_NORM_NONE) return false;
     if (d->norm == LOKA_NORM_BLOCKNORM && !(fp8out && vi.name == kPanel32Name)) return false;
-    return !(vi.name == kPanel32Name && d->N <= vi.bn);
+    return !(panel32_layout(vi) && d->N <= vi.bn);
 }
 
 bool variant_has_wait_flag(const loka_gemm_desc* d, int v, bool fp8out) { return panel_exchanges(d, kVariants[v], fp8out); }
@@ -1204,15 +1322,13 @@ bool variant_has_wait_flag(const loka_gemm_desc* d, int v, bool fp8out) { return
 // exchange of its FP8-output form
 static size_t panel_flag_bytes(const loka_gemm_desc* d, const VariantInfo& vi) {
     const int64_t panels = d->batch * ((d->M + vi.bm - 1) / vi.bm), tiles_n = (d->N + vi.bn - 1) / vi.bn;
-    return (static_cast<size_t>(panels) * tiles_n * 8 * (vi.name == kPanel32Name ? 2 : 1) + 255) & ~size_t(255);
+    return (static_cast<size_t>(panels) * tiles_n * 8 * (panel32_layout(vi) ? 2 : 1) + 255) & ~size_t(255);
 }
 
 size_t variant_workspace(const loka_gemm_desc* d, int v, bool fp8out) {
     const VariantInfo& vi = kVariants[v];
     if (vi.epi == EPI_SPLITK) {
-        int ksplit = 1, per = 1;
-        splitk_plan(d, vi, &ksplit, &per);
-        return static_cast<size_t>(ksplit) * d->batch * d->M * d->N * sizeof(float);
+        return static_cast<size_t>(splitk_plan(d, v).ksplit) * d->batch * d->M * d->N * sizeof(float);
     }
     if (vi.epi == EPI_ROW_IN_TILE || d->norm == LOKA_NORM_NONE) return 0;
     if (d->norm == LOKA_NORM_BLOCKNORM && !panel_exchanges(d, vi, fp8out)) return 0;
@@ -1220,7 +1336,7 @@ size_t variant_workspace(const loka_gemm_desc* d, int v, bool fp8out) {
     size_t stats = static_cast<size_t>(d->batch) * d->M * tiles_n * 2 * sizeof(float);
     // the 32x32 panel kernel keeps a record for every row of every 256-row panel, and its FP8-output form exchanges
     // the row minimum and maximum as well
-    if (vi.name == kPanel32Name) stats = static_cast<size_t>(d->batch) * ((d->M + vi.bm - 1) / vi.bm) * vi.bm * tiles_n * 2 * sizeof(float) * 2;
+    if (panel32_layout(vi)) stats = static_cast<size_t>(d->batch) * ((d->M + vi.bm - 1) / vi.bm) * vi.bm * tiles_n * 2 * sizeof(float) * 2;
     stats = (stats + 255) & ~size_t(255);
     if (vi.epi == EPI_PANEL_SYNC) {
         if (!panel_exchanges(d, vi, fp8out)) return 0;
@@ -1357,8 +1473,15 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         return LOKA_ERR_UNSUPPORTED;
     }
     p.norm = d->norm; p.eps = d->eps; p.block_n = d->block_n; p.act = d->act;
-    p.tiles_m = static_cast<int>((d->M + vi.bm - 1) / vi.bm);
-    p.tiles_n = static_cast<int>((d->N + vi.bn - 1) / vi.bn);
+    int bm = vi.bm, bn = vi.bn;
+    if (vi.epi == EPI_SPLITK) {
+        const SplitkPlan pl = splitk_plan(d, v);
+        bm = bn = pl.tile;
+        p.ksplit = pl.ksplit;
+        p.k_per_split = pl.per;
+    }
+    p.tiles_m = static_cast<int>((d->M + bm - 1) / bm);
+    p.tiles_n = static_cast<int>((d->N + bn - 1) / bn);
     const bool two_pass = vi.epi == EPI_PARTIAL_STATS && d->norm != LOKA_NORM_NONE && d->norm != LOKA_NORM_BLOCKNORM;
     if (two_pass) {
         size_t stats = static_cast<size_t>(d->batch) * d->M * p.tiles_n * 2 * sizeof(float);
@@ -1380,15 +1503,16 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
     const void* kfn = blockwise ? vi.fn_block : vi.fn_plain;
-    if (vi.name == kSplitk256Name) kfn = panel32_part_fn(panel32_bw(p, blockwise), false);
+    const bool splitk256 = vi.epi == EPI_SPLITK && bm == 256;
+    if (splitk256) kfn = panel32_part_fn(panel32_bw(p, blockwise), false);
     if (vi.name == kPanel32Name) kfn = panel32_fn(panel32_bw(p, blockwise), outq != nullptr, panel32_affine(p), p.qpro != 0);
     if (!kfn) return LOKA_ERR_UNSUPPORTED;
     int per_cu = 0;
-    if (prepare_fn(dev, kfn, vi.threads, vi.lds, &per_cu) != LOKA_OK) return LOKA_ERR_HIP;
+    if (prepare_fn(dev, kfn, splitk256 ? 512 : vi.threads, splitk256 ? panel32_lds() : vi.lds, &per_cu) != LOKA_OK) return LOKA_ERR_HIP;
     dim3 grid(static_cast<unsigned>(static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.batch));
     if (vi.epi == EPI_PANEL_SYNC) {
         // persistent grid: a multiple of tiles_n workgroups, all resident at once (one per CU)
-        const int64_t slots = static_cast<int64_t>(cus) * (per_cu > 0 ? 1 : 0);
+        const int64_t slots = static_cast<int64_t>(cus) * (per_cu > 2 ? 2 : per_cu);
         int64_t g = (slots / p.tiles_n) * p.tiles_n;
         if (g <= 0) return LOKA_ERR_UNSUPPORTED;
         if (g > grid.x) g = (static_cast<int64_t>(grid.x) / p.tiles_n) * p.tiles_n;   // fewer tiles than slots
@@ -1423,11 +1547,11 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         }
     }
     if (vi.epi == EPI_SPLITK) {
-        splitk_plan(d, vi, &p.ksplit, &p.k_per_split);
         p.part = static_cast<float*>(workspace);
         p.y = nullptr;                                  // (the second kernel writes Y)
         grid.x *= static_cast<unsigned>(p.ksplit);
-        vi.launch(p, blockwise, grid, s);
+        if (splitk256) panel32_part_launch(p, panel32_bw(p, blockwise), false, grid, s);
+        else vi.launch(p, blockwise, grid, s);
         const int64_t rows = static_cast<int64_t>(d->batch) * d->M;
         // few rows (a weight gradient's K x N output): a workgroup per row, else a wave per row
         auto norm_rows = [&](auto fn, int64_t wgs) {
@@ -1484,8 +1608,8 @@ loka_status bf16_gemm_launch(const loka_gemm_desc* d, const void* x, const void*
     // against 48.9 us, 8192 x 4096 x 4096 (512) 230 against 256, 32768 x 512 x 512 (256) 33.1 against 36.7; but
     // 20000 x 1008 x 1008 (316) 77 against 71, 2048 x 4096 x 4096 (128) 99 against 83.
     const int64_t tiles256 = ((d->M + 255) / 256) * ((d->N + 255) / 256) * d->batch;
-    const int64_t rounds256 = (tiles256 + 256 - 1) / 256;
-    const bool big = 10 * tiles256 >= 8 * rounds256 * 256 && 512 * d->K < (int64_t(1) << 31);
+    const int64_t rounds256 = (tiles256 + kPlanCus - 1) / kPlanCus;
+    const bool big = 10 * tiles256 >= 8 * rounds256 * kPlanCus && 512 * d->K < (int64_t(1) << 31);
     const int tile = big ? 256 : 128;
     p.tiles_m = static_cast<int>((d->M + tile - 1) / tile);
     p.tiles_n = static_cast<int>((d->N + tile - 1) / tile);

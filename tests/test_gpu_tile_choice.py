@@ -1,0 +1,104 @@
+"""The static choice between tile sizes and schedules: shapes at the edges of the smaller tiles, rounds of workgroups past
+one per slot, the 256 x 256 split-K and BF16 forms with ragged edges, and calls with less scratch than the choice wants."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_10886_amd import binding as B
+from paper_2605_10886_amd import synth
+from test_gpu_gemm_norm import RECIPES, _run_case
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _rows(M, n=24):
+    return np.unique(np.concatenate([np.arange(2), np.linspace(0, M - 1, n).round().astype(int), [M - 2, M - 1]]))
+
+
+@pytest.mark.parametrize("variant,shape,recipe", [
+    ("panel32x256", (9001, 256, 528), "row"),          # more tiles than two per CU: several rounds of row panels
+    ("panel64x256", (12321, 144, 784), "row"),
+    ("panel128x128", (6500, 256, 640), "block"),
+    ("panel32x256", (33, 128, 4096), "block"),         # the most tiles a row has at the widest layers, ragged last rows
+    ("panel128x128", (129, 272, 4096), "tensor"),
+    ("row16x1024", (4099, 400, 1008), "row"),          # 16-row tiles: more tiles than CUs, both halves of the columns ragged
+    ("row16x256", (9001, 128, 256), "block_pow2"),
+    ("row32x512", (8209, 80, 272), "row"),
+    ("panel32_256x256_ragged", (4500, 1200, 1040), "row"),   # ragged in all three, two rounds with a prefetched tile
+    ("panel32_256x256_ragged", (66000, 16, 240), "tensor"),  # K shorter than one step
+])
+@pytest.mark.parametrize("norm", ["layernorm", "none"])
+def test_tile_edges_and_rounds(orc, variant, shape, recipe, norm):
+    M, K, N = shape
+    x, wt = synth.student_t4(M, K, seed=M + N), synth.weight(K, N, seed=K)
+    gamma, beta = synth.affine(N, seed=6) if norm == "layernorm" else (None, None)
+    _run_case(orc, x, wt, recipe, norm, B.variant_id(variant), gamma, beta, rows=_rows(M), tag=f"{variant} {shape}")
+
+
+@pytest.mark.parametrize("shape,recipe", [((300, 24592, 2320), "row"), ((1000, 16384, 1920), "block"),
+                                          ((513, 32768, 1024), "block_pow2"), ((257, 65552, 272), "tensor")])
+def test_split_k_long_ranges(orc, shape, recipe):
+    # the long-range form of split K; the first three take 256 x 256 tiles (the workspace is theirs), ragged in M, N and K
+    M, K, N = shape
+    x, wt = synth.student_t4(M, K, seed=M), synth.weight(K, N, seed=N)
+    v = B.variant_id("splitk128x128s2")
+    desc = B.make_desc(M, N, K, 1, *RECIPES[recipe], B.NORM_RMSNORM, 1e-5, v)
+    ws = B.lib().loka_fp8_gemm_norm_workspace(ctypes.byref(desc))
+    tiles256 = -(-M // 256) * -(-N // 256)
+    if N > 512:
+        assert ws // (4 * M * N) <= 256 // tiles256            # one workgroup per CU at most
+    _run_case(orc, x, wt, recipe, "rmsnorm", v, rows=_rows(M, 12), tag=f"split-K {shape}")
+
+
+@pytest.mark.parametrize("shape", [(65536, 8, 16), (66000, 72, 144), (16500, 200, 1008), (65536, 1024, 256), (32768, 4096, 272),
+                                   (130, 40, 48)])
+@pytest.mark.parametrize("batch", [1, 3])
+def test_bf16_reference_tiles(shape, batch):
+    # 256 x 256 tiles where they fill the chip, 128 x 128 below; K from one 16-byte chunk up, ragged in M, N and K.
+    # fp32 accumulation of exact products against fp64: 2^-24 per addition, K additions at most, relative to sum |x w|
+    M, K, N = shape
+    if batch > 1 and M * K * N > 1 << 33:
+        pytest.skip("the single problem covers the size")
+    g = torch.Generator().manual_seed(M + K)
+    x = torch.randn(batch, M, K, generator=g).to(torch.bfloat16).to(DEV)
+    w = torch.randn(batch, K, N, generator=g).to(torch.bfloat16).to(DEV)
+    y = B.loka_bf16_gemm(B.make_desc(M, N, K, batch, norm=B.NORM_NONE), x.view(-1, K), w.view(-1, N)).view(batch, M, N)
+    for b in range(batch):
+        ref = x[b].double() @ w[b].double()
+        bound = x[b].double().abs() @ w[b].double().abs()
+        assert bool(((y[b].double() - ref).abs() <= K * 2.0 ** -24 * bound + 1e-30).all())
+
+
+@pytest.mark.parametrize("M,K,N,norm,recipe", [(256, 1008, 720, "layernorm", "row"), (2048, 1024, 1024, "rmsnorm", "block"),
+                                               (300, 1024, 2320, "none", "row"), (5013, 1008, 1008, "layernorm", "tensor")])
+def test_layers_that_need_no_scratch_run_with_any(M, K, N, norm, recipe):
+    # N <= 1024 or no row norm: no workspace, a byte less than the query and the query itself are all accepted, and give the
+    # same result up to the order of the sums
+    L = B.lib()
+    x, wt = synth.normal(M, K, seed=3).to(DEV), synth.weight(K, N, seed=4).to(DEV)
+    xm, wm = RECIPES[recipe]
+    xq, sx = B.loka_quantize(x, xm)
+    wq, sw = B.loka_quantize(wt, wm, transpose_out=True)
+    desc = B.make_desc(M, N, K, 1, xm, wm, B.NORMS[norm], 1e-5)
+    need = L.loka_fp8_gemm_norm_workspace(ctypes.byref(desc))
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    ws = torch.empty(max(need, 1), dtype=torch.uint8, device=DEV)
+    outs = []
+    for p, n in ((None, 0), (ws.data_ptr(), max(need - 1, 0)), (ws.data_ptr(), need)):
+        out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV)
+        y = torch.full((M, N), float("nan"), device=DEV)
+        assert L.loka_fp8_gemm_norm(ctypes.byref(desc), xq.data_ptr(), sx.data_ptr(), wq.data_ptr(), sw.data_ptr(), None, None,
+                                    out.data_ptr(), y.data_ptr(), p, n, sp) == B.LOKA_OK
+        if n and n == need:
+            assert L.loka_fp8_gemm_norm_check(ctypes.byref(desc), p, 1 << 30, sp) == B.LOKA_OK     # (the header alone is read)
+        outs.append((out, y))
+    static, _ = B.loka_fp8_gemm_norm_static(desc, xq, sx, wq, sw)
+    torch.cuda.synchronize()
+    # the variants differ by fp32 summation order (and, blockwise, one rounding per K block): 2^-23 K / 128 of sum |terms|
+    ref = outs[-1][1].double()
+    for out, y in outs:
+        assert float((y.double() - ref).norm() / ref.norm()) <= 2.0 ** -23 * (K / 128 + 8)
+        assert float((out.double() - static.double()).norm() / static.double().norm()) <= 1e-3
