@@ -560,9 +560,9 @@ int strip_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool bf1
     *fn = bf16_in ? w->fn_fused : fp8_out ? w->fn_q : w->fn;
     *lds = w->lds;
     const int64_t strips = batch * ((M + 31) / 32);
-    const int waves = bf16_in ? fused_waves(w->nb, w->ks) : 8;
-    const int64_t wgs = (strips + waves - 1) / waves;       // at least one strip per wave
-    return static_cast<int>(wgs < cus ? wgs : cus);
+    // (one strip per workgroup while CUs are free, though only one wave of it then works: measured with fused quantization,
+    // M x N x K: 1311 x 112 x 256 10.4 -> 7.2 us, 9815 x 112 x 128 8.6 -> 6.8, 32 x (1348 x 128 x 256) 17.9 -> 13.2)
+    return static_cast<int>(strips < cus ? strips : cus);
 }
 
 void strip_launch(const GemmParams& p, dim3 grid, hipStream_t s) {
