@@ -547,7 +547,9 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
 
     // ---- row statistics (reciprocals and the inverse square root are the 1-ulp hardware ones: their
     // error is four orders of magnitude below a bf16 ulp, and the IEEE sequences are ~300 cycles each)
-    const float inv_n = 1.0f / static_cast<float>(p.N);
+    // (BlockNorm: a 256-column tile is one group of the row, normalized like a row of its own)
+    const bool blocknorm = EPI == EPI_ROW_IN_TILE && BN == 256 && p.norm == LOKA_NORM_BLOCKNORM;
+    const float inv_n = 1.0f / static_cast<float>(blocknorm ? BN : p.N);
     float mean_r[MI], rstd_r[MI];
     if (p.norm == LOKA_NORM_NONE) {
 #pragma unroll
@@ -745,7 +747,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     }
 
     // ---- normalize, affine, bf16 store
-    const bool has_g = p.gamma != nullptr, has_b = p.beta != nullptr && p.norm == LOKA_NORM_LAYERNORM;
+    const bool has_g = p.gamma != nullptr && !blocknorm, has_b = p.beta != nullptr && p.norm == LOKA_NORM_LAYERNORM;
 #pragma unroll
     for (int h = 0; h < NSPLIT; ++h) {
 #pragma unroll
@@ -776,6 +778,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
                     o[e] = (yv - mean_r[mi]) * rstd_r[mi];
                     if (has_g && p.norm != LOKA_NORM_NONE) o[e] *= gm[e];
                     if (has_b) o[e] += bt[e];
+                }
+                if (blocknorm && p.act == LOKA_ACT_HARDSWISH) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) o[e] = o[e] * __builtin_fminf(__builtin_fmaxf(o[e] + 3.0f, 0.0f), 6.0f) * (1.0f / 6.0f);
                 }
                 u32x4 pk;
                 pk.x = pack_bf16x2(o[0], o[1]); pk.y = pack_bf16x2(o[2], o[3]);
@@ -1257,9 +1263,29 @@ static double variant_cost(const loka_gemm_desc* d, int v) {
     const double rounds = whole ? static_cast<double>((tiles + slots - 1) / slots) : static_cast<double>(tiles) / slots;
     const double steps = static_cast<double>((d->K + 127) / 128) * (vi.bn > 512 ? (d->N + 511) / 512 : 1);
     double t = c.start + rounds * (c.round + steps * (c.step + c.step_full * std::min(1.0, static_cast<double>(tiles) / slots))) + out * c.mout;
-    if (d->norm != LOKA_NORM_NONE)
+    if (d->norm != LOKA_NORM_NONE && d->norm != LOKA_NORM_BLOCKNORM)
         t += out * c.norm_mout + c.norm * (vi.epi == EPI_PANEL_SYNC ? rounds * (tiles_n > 1 ? 1.0 : 0.3) : static_cast<double>(d->batch));
     return t;
+}
+
+// BlockNorm where the library chose the 32 x 32 x 64 kernel (a caller that names it gets its bits, which its FP8-output form
+// quantizes): the groups are tiles of 256 columns, so a layer with few rows also runs on the 256-column row tiles, one workgroup per group and 16, 32 or 64 rows (no exchange, no scratch in either).  By
+// expected time (bf16 output; M x N x K: 222 x 256 x 768 in 4 problems 16.1 -> 6.7 us, 2048 x 1024 x 512 14.9 -> 7.6, 1000 x 4096 x 4096 42.9 -> 30.4).
+static int blocknorm_form(const loka_gemm_desc* d, int v) {
+    static const std::array<int, 3> rows = [] {
+        std::array<int, 3> r{};
+        int n = 0;
+        for (int i = 0; i < kNumVariants && n < 3; ++i)
+            if (kVariants[i].epi == EPI_ROW_IN_TILE && kVariants[i].bn == 256 && kVariants[i].bm <= 64 && kVariants[i].fn_block) r[n++] = i;
+        return r;
+    }();
+    int best = v;
+    double cost = variant_cost(d, v);
+    for (int r : rows) {
+        const double c = variant_cost(d, r);
+        if (c < cost) { cost = c; best = r; }
+    }
+    return best;
 }
 
 size_t variant_workspace(const loka_gemm_desc* d, int v, bool fp8out);
@@ -1446,6 +1472,8 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
                                         const float* sw, const void* gamma, const void* beta, void* out, float* y,
                                         uint8_t* outq, float* outs, const void* x_bf16, float* sx_out, void* workspace,
                                         hipStream_t s, bool quantize_prologue) {
+    if (d->variant < 0 && d->norm == LOKA_NORM_BLOCKNORM && kVariants[v].name == kPanel32Name && !outq && !quantize_prologue)
+        v = blocknorm_form(d, v);
     const VariantInfo& vi = kVariants[v];
     const bool blockwise = scale_mode_is_block(d->x_mode);
     GemmParams p{};

@@ -102,3 +102,37 @@ def test_layers_that_need_no_scratch_run_with_any(M, K, N, norm, recipe):
     for out, y in outs:
         assert float((y.double() - ref).norm() / ref.norm()) <= 2.0 ** -23 * (K / 128 + 8)
         assert float((out.double() - static.double()).norm() / static.double().norm()) <= 1e-3
+
+
+@pytest.mark.parametrize("shape", [(1, 128, 256), (17, 128, 768), (222, 768, 256), (1000, 1024, 4096), (4100, 256, 512),
+                                   (9000, 384, 1024), (20000, 512, 512)])
+@pytest.mark.parametrize("recipe", ["tensor", "row", "block"])
+def test_blocknorm_on_row_tiles(orc, shape, recipe):
+    # BlockNorm by the library's choice: 16-, 32- and 64-row tiles of one group each for few rows, the large kernels above
+    M, K, N = shape
+    act = B.ACT_HARDSWISH if M % 2 else B.ACT_NONE
+    x, wt = synth.student_t4(M, K, seed=M), synth.weight(K, N, seed=N)
+    xm, wm = RECIPES[recipe]
+    xq, sx = B.loka_quantize(x.to(DEV), xm)
+    wq, sw = B.loka_quantize(wt.to(DEV), wm, transpose_out=True)
+    desc = B.make_desc(M, N, K, 1, xm, wm, B.NORM_BLOCKNORM, 1e-5, block_n=256, act=act)
+    out, y = B.loka_fp8_gemm_norm(desc, xq, sx, wq, sw, want_y=True)
+    torch.cuda.synchronize()
+    # Y against the exact product of the codes: rounding of the matrix pipe (7 products a group cut at 2^-13 of the largest)
+    # and of the fp32 sums, relative to sum |x w|; O against the norm of that Y in fp64: one bf16 rounding and a few fp32 ones
+    rows = _rows(M) if M > 4 else np.arange(M)
+    idx = torch.from_numpy(rows).to(DEV)
+    a = xq[idx].view(torch.float8_e4m3fn).double()
+    b = wq.view(torch.float8_e4m3fn).double()
+    if recipe == "block":
+        a = (a.view(len(rows), K // 128, 128) * sx.view(M, K // 128)[idx].double()[:, :, None]).view(len(rows), K)
+        b = (b.view(N // 128, 128, K // 128, 128) * sw.view(K // 128, N // 128).t().double()[:, None, :, None]).view(N, K)
+    else:
+        a, b = a * (sx if recipe == "tensor" else sx[idx][:, None]).double(), b * (sw if recipe == "tensor" else sw[:, None]).double()
+    assert bool(((y[idx].double() - a @ b.T).abs() <= (7 * 2.0 ** -13 + 1e-5) * (a.abs() @ b.abs().T) + 1e-30).all())
+    g = y[idx].double().view(len(rows), N // 256, 256)
+    o = g / (g.square().mean(-1, keepdim=True) + 1e-5).sqrt()
+    if act == B.ACT_HARDSWISH:
+        o = o * (o + 3).clamp(0, 6) / 6
+    o = o.view(len(rows), N)
+    assert bool(((out[idx].double() - o).abs() <= o.abs() * 2.0 ** -8 + 1e-5).all())
