@@ -295,7 +295,8 @@ loka_status loka_fp8_linear_norm_xq(const loka_gemm_desc* desc, const void* x_bf
  * Analysis"; the paper's reference is TF32, this build's is BF16 operands with fp32
  * accumulate).  x [batch][M, K] bf16, w [batch][K, N] bf16 (strideW 0 = shared),
  * yref [batch][M, N] fp32.  Only M, N, K, batch and the strides of `desc` are read.
- * K % 8 == 0, N % 16 == 0.  Workspace: loka_bf16_gemm_workspace() bytes (a transposed copy of W). */
+ * K % 8 == 0, N % 16 == 0.  Workspace: loka_bf16_gemm_workspace() bytes (a transposed copy of W and,
+ * where K is split over workgroups, partial sums; with room for the copy of W alone, 2 K N bytes per weight, K is not split). */
 size_t loka_bf16_gemm_workspace(const loka_gemm_desc* desc);
 loka_status loka_bf16_gemm(const loka_gemm_desc* desc, const void* x_bf16, const void* w_bf16, float* yref_fp32,
                            void* workspace, size_t ws_bytes, void* hip_stream);

@@ -36,7 +36,8 @@ void test_set_spin_limit(long long);
 // ceiling.hip
 loka_status machine_ceiling(int, double, void*, size_t, double*, hipStream_t);
 size_t bf16_gemm_workspace_bytes(const loka_gemm_desc*);
-loka_status bf16_gemm_launch(const loka_gemm_desc*, const void*, const void*, float*, void*, hipStream_t, bool weights_ready = false);
+size_t bf16_gemm_min_workspace_bytes(const loka_gemm_desc*);
+loka_status bf16_gemm_launch(const loka_gemm_desc*, const void*, const void*, float*, void*, size_t, hipStream_t, bool weights_ready = false);
 // probe.hip
 size_t probe_workspace_bytes();
 loka_status probe_launch(const float*, const float*, int64_t, int64_t, int64_t, loka_probe_stats*, float*, void*,
@@ -384,10 +385,9 @@ loka_status loka_bf16_gemm(const loka_gemm_desc* desc, const void* x_bf16, const
     const loka_status st = validate_desc(desc, false);
     if (st != LOKA_OK) return st;
     if (!aligned16(x_bf16) || !aligned16(w_bf16) || !aligned16(yref_fp32)) return LOKA_ERR_ALIGN;
-    const size_t need = bf16_gemm_workspace_bytes(desc);
-    if (!workspace || ws_bytes < need) return LOKA_ERR_WORKSPACE;
+    if (!workspace || ws_bytes < bf16_gemm_min_workspace_bytes(desc)) return LOKA_ERR_WORKSPACE;
     if (!aligned16(workspace)) return LOKA_ERR_ALIGN;
-    return bf16_gemm_launch(desc, x_bf16, w_bf16, yref_fp32, workspace, static_cast<hipStream_t>(hip_stream));
+    return bf16_gemm_launch(desc, x_bf16, w_bf16, yref_fp32, workspace, ws_bytes, static_cast<hipStream_t>(hip_stream));
 }
 
 size_t loka_probe_error_workspace(int64_t M, int64_t N) {

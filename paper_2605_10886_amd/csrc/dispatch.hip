@@ -18,7 +18,7 @@ bool variant_supports(const loka_gemm_desc*, int);
 bool variant_is_streaming(int);
 int variant_cheapest(const loka_gemm_desc*, size_t max_ws);
 loka_status validate_desc(const loka_gemm_desc* d, bool fp8);
-loka_status bf16_gemm_launch(const loka_gemm_desc*, const void*, const void*, float*, void*, hipStream_t, bool weights_ready);
+loka_status bf16_gemm_launch(const loka_gemm_desc*, const void*, const void*, float*, void*, size_t, hipStream_t, bool weights_ready);
 
 namespace {
 
@@ -205,7 +205,7 @@ loka_status loka_dispatch(const loka_gemm_desc* shape, const void* x_bf16, const
     float usec_bf16 = 0.f;
     st = loka_bf16_gemm(&d, xb, wb, yref.as<float>(), ws_b.p, ws_bf16, s);
     if (st != LOKA_OK) return st;
-    st = time_region([&] { return bf16_gemm_launch(&d, xb, wb, yref.as<float>(), ws_b.p, s, true); }, &usec_bf16);
+    st = time_region([&] { return bf16_gemm_launch(&d, xb, wb, yref.as<float>(), ws_b.p, ws_bf16, s, true); }, &usec_bf16);
     if (st != LOKA_OK) return st;
 
     struct Recipe { int xm, wm; };

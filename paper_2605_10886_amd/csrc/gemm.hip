@@ -524,7 +524,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
             }
         }
     }
-    if (IS_BF16) continue;                 // reference GEMM: fp32 Y only
+    if (IS_BF16 && EPI != EPI_SPLITK) continue;                 // reference GEMM: fp32 Y only
     if (EPI == EPI_SPLITK) {
         // this K range's share of Y (scales applied: they are factors of every term) goes to the partial buffer; a second
         // kernel adds the ranges in a fixed order and normalizes the row
@@ -937,7 +937,7 @@ __global__ __launch_bounds__(256) void splitk_norm_rows_kernel(const float* __re
         }
         u32x2 pk;
         pk.x = pack_bf16x2(o[0], o[1]); pk.y = pack_bf16x2(o[2], o[3]);
-        *reinterpret_cast<u32x2*>(out + obase + 4 * c) = pk;
+        if (out) *reinterpret_cast<u32x2*>(out + obase + 4 * c) = pk;       // (the reference GEMM wants Y alone)
     }
 }
 
@@ -1468,6 +1468,19 @@ loka_status fp8_linear_norm_xq_launch(const loka_gemm_desc* d, int v, const void
                                  true);
 }
 
+// The second kernel of split K: a wave per row, or a workgroup when a row is longer than a wave holds at once
+static void launch_splitk_sum(const GemmParams& p, const loka_gemm_desc* d, float* y, hipStream_t s) {
+    const int64_t rows = static_cast<int64_t>(d->batch) * d->M;
+    auto sum = [&](auto fn, int64_t wgs) {
+        fn<<<dim3(static_cast<unsigned>(wgs)), 256, 0, s>>>(p.part, p.ksplit, rows, p.M, p.N, p.strideO, p.norm, d->eps,
+                                                            p.gamma, p.beta, p.out, y);
+    };
+    if (p.N <= 256) sum(&splitk_norm_rows_kernel<1, 1>, (rows + 3) / 4);
+    else if (p.N <= 1024) sum(&splitk_norm_rows_kernel<4, 1>, rows);
+    else if (p.N <= 2048) sum(&splitk_norm_rows_kernel<4, 2>, rows);
+    else sum(&splitk_norm_rows_kernel<4, 8>, rows);
+}
+
 static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const uint8_t* xq, const float* sx, const uint8_t* wq,
                                         const float* sw, const void* gamma, const void* beta, void* out, float* y,
                                         uint8_t* outq, float* outs, const void* x_bf16, float* sx_out, void* workspace,
@@ -1580,16 +1593,7 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         grid.x *= static_cast<unsigned>(p.ksplit);
         if (splitk256) panel32_part_launch(p, panel32_bw(p, blockwise), false, grid, s);
         else vi.launch(p, blockwise, grid, s);
-        const int64_t rows = static_cast<int64_t>(d->batch) * d->M;
-        // few rows (a weight gradient's K x N output): a workgroup per row, else a wave per row
-        auto norm_rows = [&](auto fn, int64_t wgs) {
-            fn<<<dim3(static_cast<unsigned>(wgs)), 256, 0, s>>>(p.part, p.ksplit, rows, p.M, p.N, p.strideO, d->norm, d->eps,
-                                                                p.gamma, p.beta, p.out, y);
-        };
-        if (p.N <= 256) norm_rows(&splitk_norm_rows_kernel<1, 1>, (rows + 3) / 4);
-        else if (p.N <= 1024) norm_rows(&splitk_norm_rows_kernel<4, 1>, rows);
-        else if (p.N <= 2048) norm_rows(&splitk_norm_rows_kernel<4, 2>, rows);
-        else norm_rows(&splitk_norm_rows_kernel<4, 8>, rows);
+        launch_splitk_sum(p, d, y, s);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
     vi.launch(p, blockwise, grid, s);
@@ -1606,16 +1610,47 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }
 
-// BF16 reference GEMM: 128 x 128 tiles, fp32 Y only.
-size_t bf16_gemm_workspace_bytes(const loka_gemm_desc* d) {
+// BF16 reference GEMM, fp32 Y only.  Tiles and K ranges by shape:
+// - 256 x 256 tiles on the panel kernel's main loop where they fill at least 80 % of the rounds of 256 workgroups they take
+//   (measured, 256 against 128: 16384 x 1024 x 1024 (256 tiles) 42.0 against 48.9 us, 8192 x 4096 x 4096 (512) 230 against
+//   256, 32768 x 512 x 512 (256) 33.1 against 36.7; but 20000 x 1008 x 1008 (316) 77 against 71, 2048 x 4096 x 4096 (128)
+//   99 against 83);
+// - else 128 x 128 tiles, two workgroups per CU; where that leaves CUs idle, K is split over several workgroups per tile (at
+//   least 4 steps of 64 each, 16 ranges, two workgroups per CU) as far as the steps saved, 0.6 us each, pay for the partial
+//   sums, 1.8 us per million, and the kernel that adds them, 5.5 us: 1000 x 128 x 4096 45.3 -> 15.7 us, 1014 x 192 x 1856
+//   23.7 -> 14.6; not 4096 x 1024 x 1024 (21.0, split in two 29.4).
+struct Bf16Plan { int tile, ksplit, per; };
+static Bf16Plan bf16_plan(const loka_gemm_desc* d) {
+    const int64_t steps = (2 * d->K + 127) / 128;
+    const int64_t tiles256 = ((d->M + 255) / 256) * ((d->N + 255) / 256) * d->batch;
+    const int64_t rounds256 = (tiles256 + kPlanCus - 1) / kPlanCus;
+    if (10 * tiles256 >= 8 * rounds256 * kPlanCus && 512 * d->K < (int64_t(1) << 31)) return {256, 1, static_cast<int>(steps)};
+    const int64_t tiles = ((d->M + 127) / 128) * ((d->N + 127) / 128) * d->batch;
+    const int64_t most = d->N <= kSplitkMaxN ? std::min<int64_t>({2 * kPlanCus / tiles, steps / 4, 16}) : 1;
+    Bf16Plan best{128, 1, static_cast<int>(steps)};
+    double best_cost = 0.6 * steps;
+    for (int64_t want = 2; want <= most; ++want) {
+        const int64_t per = (steps + want - 1) / want, ksplit = (steps + per - 1) / per;
+        const double cost = 0.6 * per + 5.5 + 1.8e-6 * ksplit * d->M * d->N * d->batch;
+        if (cost < best_cost) { best = {128, static_cast<int>(ksplit), static_cast<int>(per)}; best_cost = cost; }
+    }
+    return best;
+}
+// [transposed weights][partial sums]; the sums are left out of a workspace that has no room for them
+static size_t bf16_weight_bytes(const loka_gemm_desc* d) {
     const int64_t nw = d->strideW ? d->batch : 1;
     return static_cast<size_t>(nw) * d->K * d->N * 2;
+}
+size_t bf16_gemm_min_workspace_bytes(const loka_gemm_desc* d) { return bf16_weight_bytes(d); }
+size_t bf16_gemm_workspace_bytes(const loka_gemm_desc* d) {
+    const Bf16Plan pl = bf16_plan(d);
+    return bf16_weight_bytes(d) + (pl.ksplit > 1 ? static_cast<size_t>(pl.ksplit) * d->batch * d->M * d->N * sizeof(float) : 0);
 }
 
 // weights_ready: the workspace already holds the transposed weights of an earlier call with the same w (the
 // dispatcher times the reference with its weights prepared once, like the FP8 candidates' quantized weights)
 loka_status bf16_gemm_launch(const loka_gemm_desc* d, const void* x, const void* w, float* yref, void* workspace,
-                             hipStream_t s, bool weights_ready) {
+                             size_t ws_bytes, hipStream_t s, bool weights_ready) {
     uint16_t* wt = static_cast<uint16_t*>(workspace);
     const int64_t nw = d->strideW ? d->batch : 1;
     for (int64_t g = 0; g < nw && !weights_ready; g += 65535) {         // (grid.z holds 65535 problems, grid.y 65535 * 64 rows)
@@ -1631,25 +1666,29 @@ loka_status bf16_gemm_launch(const loka_gemm_desc* d, const void* x, const void*
     p.strideX = d->strideX * 2; p.strideW = d->strideW ? d->K * d->N * 2 : 0; p.strideO = d->strideO;
     p.y = yref;
     p.norm = LOKA_NORM_NONE;
-    // 256 x 256 tiles on the panel kernel's main loop where they fill at least 80 % of the rounds of 256 workgroups they
-    // take, else 128 x 128 tiles, two workgroups per CU.  Measured, 256 against 128: 16384 x 1024 x 1024 (256 tiles) 42.0
-    // against 48.9 us, 8192 x 4096 x 4096 (512) 230 against 256, 32768 x 512 x 512 (256) 33.1 against 36.7; but
-    // 20000 x 1008 x 1008 (316) 77 against 71, 2048 x 4096 x 4096 (128) 99 against 83.
-    const int64_t tiles256 = ((d->M + 255) / 256) * ((d->N + 255) / 256) * d->batch;
-    const int64_t rounds256 = (tiles256 + kPlanCus - 1) / kPlanCus;
-    const bool big = 10 * tiles256 >= 8 * rounds256 * kPlanCus && 512 * d->K < (int64_t(1) << 31);
-    const int tile = big ? 256 : 128;
-    p.tiles_m = static_cast<int>((d->M + tile - 1) / tile);
-    p.tiles_n = static_cast<int>((d->N + tile - 1) / tile);
+    Bf16Plan pl = bf16_plan(d);
+    if (ws_bytes < bf16_gemm_workspace_bytes(d)) { pl.per *= pl.ksplit; pl.ksplit = 1; }
+    p.tiles_m = static_cast<int>((d->M + pl.tile - 1) / pl.tile);
+    p.tiles_n = static_cast<int>((d->N + pl.tile - 1) / pl.tile);
     const int64_t tiles = static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.batch;
-    auto fn = &gemm_kernel<128, 128, 1, 2, 2, true, false, EPI_PARTIAL_STATS>;
-    const size_t lds = big ? panel32_lds() : 2 * (128 * 128 + 128 * 128);
     int dev = 0, cus = 0;
-    if (device_cus(&dev, &cus) != LOKA_OK ||
-        prepare_fn(dev, big ? panel32_part_fn(0, true) : reinterpret_cast<const void*>(fn), big ? 512 : 256, lds, nullptr) != LOKA_OK)
-        return LOKA_ERR_HIP;
-    if (big) panel32_part_launch(p, 0, true, dim3(static_cast<unsigned>(tiles < cus ? tiles : cus)), s);
-    else fn<<<dim3(static_cast<unsigned>(tiles)), 256, lds, s>>>(p);
+    if (device_cus(&dev, &cus) != LOKA_OK) return LOKA_ERR_HIP;
+    if (pl.tile == 256) {
+        if (prepare_fn(dev, panel32_part_fn(0, true), 512, panel32_lds(), nullptr) != LOKA_OK) return LOKA_ERR_HIP;
+        panel32_part_launch(p, 0, true, dim3(static_cast<unsigned>(tiles < cus ? tiles : cus)), s);
+        return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
+    }
+    constexpr size_t lds = 2 * (128 * 128 + 128 * 128);
+    auto fn = pl.ksplit > 1 ? &gemm_kernel<128, 128, 1, 2, 2, true, false, EPI_SPLITK> : &gemm_kernel<128, 128, 1, 2, 2, true, false, EPI_PARTIAL_STATS>;
+    if (prepare_fn(dev, reinterpret_cast<const void*>(fn), 256, lds, nullptr) != LOKA_OK) return LOKA_ERR_HIP;
+    if (pl.ksplit > 1) {
+        p.ksplit = pl.ksplit;
+        p.k_per_split = pl.per;
+        p.part = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + bf16_weight_bytes(d));
+        p.y = nullptr;
+    }
+    fn<<<dim3(static_cast<unsigned>(tiles * pl.ksplit)), 256, lds, s>>>(p);
+    if (pl.ksplit > 1) launch_splitk_sum(p, d, yref, s);
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }
 

@@ -54,10 +54,10 @@ def test_split_k_long_ranges(orc, shape, recipe):
 
 
 @pytest.mark.parametrize("shape", [(65536, 8, 16), (66000, 72, 144), (16500, 200, 1008), (65536, 1024, 256), (32768, 4096, 272),
-                                   (130, 40, 48)])
+                                   (130, 40, 48), (1000, 4104, 128), (300, 1864, 208), (2048, 4096, 528)])
 @pytest.mark.parametrize("batch", [1, 3])
 def test_bf16_reference_tiles(shape, batch):
-    # 256 x 256 tiles where they fill the chip, 128 x 128 below; K from one 16-byte chunk up, ragged in M, N and K.
+    # 256 x 256 tiles where they fill the chip, 128 x 128 below, K split where those are few; K from one 16-byte chunk up, ragged in M, N and K.
     # fp32 accumulation of exact products against fp64: 2^-24 per addition, K additions at most, relative to sum |x w|
     M, K, N = shape
     if batch > 1 and M * K * N > 1 << 33:
@@ -70,6 +70,16 @@ def test_bf16_reference_tiles(shape, batch):
         ref = x[b].double() @ w[b].double()
         bound = x[b].double().abs() @ w[b].double().abs()
         assert bool(((y[b].double() - ref).abs() <= K * 2.0 ** -24 * bound + 1e-30).all())
+    # a workspace with room for the transposed weights alone is enough (K is then not split)
+    L, d = B.lib(), B.make_desc(M, N, K, batch, norm=B.NORM_NONE)
+    small = batch * K * N * 2
+    assert small <= L.loka_bf16_gemm_workspace(ctypes.byref(d))
+    ws, y2 = torch.empty(small, dtype=torch.uint8, device=DEV), torch.full_like(y, float("nan"))
+    args = (ctypes.byref(d), x.data_ptr(), w.data_ptr(), y2.data_ptr(), ws.data_ptr())
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.loka_bf16_gemm(*args, small - 1, sp) == B.LOKA_ERR_WORKSPACE
+    assert L.loka_bf16_gemm(*args, small, sp) == B.LOKA_OK
+    assert bool(((y2[0].double() - y[0].double()).abs() <= K * 2.0 ** -24 * (x[0].double().abs() @ w[0].double().abs()) + 1e-30).all())
 
 
 @pytest.mark.parametrize("M,K,N,norm,recipe", [(256, 1008, 720, "layernorm", "row"), (2048, 1024, 1024, "rmsnorm", "block"),
