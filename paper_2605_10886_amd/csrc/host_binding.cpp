@@ -62,14 +62,16 @@ loka_gemm_desc desc_of(PyObject* o) {      // a ctypes structure: its bytes are 
     return d;
 }
 
-// the library call without the interpreter lock (a launch can block while the hardware queue is full)
+// the library call without the interpreter lock (a launch can block while the hardware queue is full); a tensor without
+// storage throws where its pointer is taken, and the lock has to be back before that becomes a Python exception
+struct LockReleased {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~LockReleased() { PyEval_RestoreThread(state); }
+};
 template <class F>
 loka_status unlocked(F&& f) {
-    loka_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
-    return st;
+    const LockReleased released;
+    return f();
 }
 
 PyObject* wrap(const at::Tensor& t) {

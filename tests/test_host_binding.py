@@ -38,3 +38,16 @@ def test_given_outputs_and_errors():
         B.loka_fp8_gemm_norm(wide, xq, sx, torch.zeros(2048, K, dtype=torch.uint8, device="cuda"),
                              torch.ones(2048, device="cuda"), workspace=ws)
     assert e.value.status == B.LOKA_ERR_WORKSPACE
+
+
+@pytest.mark.gpu
+def test_tensor_without_storage_raises():
+    # a batched view has a shape and a device but no address of its own: the error leaves the call as a Python exception
+    x = torch.randn(2, 32, 128, device="cuda").bfloat16()
+    with pytest.raises(RuntimeError):
+        torch.vmap(lambda t: B.loka_quantize(t, B.SCALE_ROW)[0])(x)
+    y = torch.zeros(2, 32, 128, device="cuda")
+    with pytest.raises(RuntimeError):
+        torch.vmap(lambda t: B.loka_probe_error(t, t, sync=False)[1])(y)
+    codes, _ = B.loka_quantize(x[0], B.SCALE_ROW)                                 # and the next call runs
+    assert codes.shape == (32, 128)
