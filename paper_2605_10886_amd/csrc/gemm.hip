@@ -92,7 +92,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     // the tile list (n fastest) in rounds of gridDim.x tiles, so the tiles_n workgroups that share a row panel always
     // run in the same round.
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
-    const int id = EPI == EPI_PANEL_SYNC && BM < 256 ? static_cast<int>(blockIdx.x) : xcd_contiguous(blockIdx.x, gridDim.x);
+    const int id = EPI == EPI_PANEL_SYNC && (BM < 256 || !panels_may_spread(gridDim.x, p.tiles_n)) ? static_cast<int>(blockIdx.x)
+                                                                                                   : xcd_contiguous(blockIdx.x, gridDim.x);
     int tile_first = EPI == EPI_SPLITK ? id % total_tiles : id, tile_stride = total_tiles;
     if (EPI == EPI_PANEL_SYNC) {
         tile_stride = gridDim.x;

@@ -56,6 +56,12 @@ __device__ __forceinline__ int xcd_contiguous(int b, int G) {
     return x * (G >> 3) + (x < r ? x : r) + (b >> 3);
 }
 
+// Whether a persistent launch of G workgroups whose tiles_n neighbours wait for one another may be renumbered so.  Where a
+// range of ids ends inside a panel, the panel's first workgroups are dealt out last and its others among the first: while
+// another stream's kernel holds part of the CUs, those others wait on their CUs.  At most 7 tiles_n can, so with tiles_n <= 8 four
+// such launches at once still leave CUs that finish panels; wider rows keep launch order unless G is a multiple of 8.
+__device__ __forceinline__ bool panels_may_spread(int G, int tiles_n) { return G % 8 == 0 || tiles_n <= 8; }
+
 // Tile t of a tiles_m x tiles_n grid in bands of 8 tile rows, walked column by column inside a band: 64 neighbours in the
 // order cover an 8 x 8 block of tiles and read 8 + 8 operand strips, where plain row order would read 1 + 64.
 __device__ __forceinline__ void banded_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {

@@ -156,7 +156,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
 
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
     // (split K: ids run range by range, so an XCD's workgroups contract the same K range of neighbouring tiles)
-    const int id = xcd_contiguous(blockIdx.x, gridDim.x);
+    const int id = EPI == EPI_PANEL_SYNC && !panels_may_spread(gridDim.x, p.tiles_n) ? static_cast<int>(blockIdx.x)
+                                                                                     : xcd_contiguous(blockIdx.x, gridDim.x);
     const int tile_first = SPLITK ? id % total_tiles : id, tile_stride = SPLITK ? total_tiles : gridDim.x;
     const int ks = SPLITK ? id / total_tiles : 0, k_lo = SPLITK ? ks * p.k_per_split : 0, kb0 = k_lo * 128;
     if (EPI == EPI_PANEL_SYNC) {
