@@ -1054,11 +1054,6 @@ static const VariantInfo kVariants[] = {
     LOKA_VARIANT("row128x256", 128, 256, 1, 2, 4, EPI_ROW_IN_TILE),
     LOKA_VARIANT("row64x512", 64, 512, 1, 1, 8, EPI_ROW_IN_TILE),
     LOKA_VARIANT("row64x1024", 64, 512, 2, 1, 8, EPI_ROW_IN_TILE),
-    LOKA_VARIANT("row16x256", 16, 256, 1, 1, 4, EPI_ROW_IN_TILE),
-    LOKA_VARIANT("row32x256", 32, 256, 1, 1, 4, EPI_ROW_IN_TILE),
-    LOKA_VARIANT("row16x512", 16, 512, 1, 1, 8, EPI_ROW_IN_TILE),
-    LOKA_VARIANT("row32x512", 32, 512, 1, 1, 8, EPI_ROW_IN_TILE),
-    LOKA_VARIANT("row16x1024", 16, 512, 2, 1, 8, EPI_ROW_IN_TILE),
     // exact products: e4m3 operands widened to bf16 in registers and contracted on the BF16 matrix instruction (the
     // accuracy-first candidates of the non-blockwise recipes: fp32 Y agrees with exact arithmetic up to fp32 summation)
     LOKA_VARIANT_EXACT("exact64x256", 64, 256, 1, 1, 4, EPI_ROW_IN_TILE),
@@ -1084,14 +1079,21 @@ static const VariantInfo kVariants[] = {
     // persistent, panel-synchronous: the tiles_n workgroups of a row panel exchange row statistics
     // through a few words of global memory and normalize their own tile in registers
     LOKA_VARIANT("panel256x256w8", 256, 256, 1, 2, 4, EPI_PANEL_SYNC),
+    // the same schedule on 32x32x64 MFMAs: the throughput variant
+    {kPanel32Name, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32, panel32_fn(0, false, false), panel32_fn(1, false, false)},
+    // (an id is the place in this table, and callers keep ids: new entries go to the end)
+    // fewer rows per tile, for layers with few rows
+    LOKA_VARIANT("row16x256", 16, 256, 1, 1, 4, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row32x256", 32, 256, 1, 1, 4, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row16x512", 16, 512, 1, 1, 8, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row32x512", 32, 512, 1, 1, 8, EPI_ROW_IN_TILE),
+    LOKA_VARIANT("row16x1024", 16, 512, 2, 1, 8, EPI_ROW_IN_TILE),
     // smaller tiles for layers that would leave CUs idle on 256 x 256 ones; two workgroups per CU (32 x 256, 64 x 256) or
     // a ring of four stages (128 x 128)
     LOKA_VARIANT("panel32x256", 32, 256, 1, 1, 4, EPI_PANEL_SYNC),
     LOKA_VARIANT("panel64x256", 64, 256, 1, 1, 4, EPI_PANEL_SYNC),
     LOKA_VARIANT("panel128x128", 128, 128, 1, 2, 4, EPI_PANEL_SYNC),
-    // the same schedule on 32x32x64 MFMAs: the throughput variant
-    {kPanel32Name, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32, panel32_fn(0, false, false), panel32_fn(1, false, false)},
-    // ... for a K that is no multiple of the 128-byte step (non-blockwise recipes, bf16 output)
+    // the 32x32x64 kernel for a K that is no multiple of the 128-byte step (non-blockwise recipes, bf16 output)
     {kPanel32RaggedName, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32_ragged, panel32_ragged_fn(), nullptr},
 };
 constexpr int kMaxRowTiles = 256;     // shape limit of the panel-synchronous schedule (a row's tiles must be co-resident:

@@ -51,3 +51,11 @@ def test_tensor_without_storage_raises():
         torch.vmap(lambda t: B.loka_probe_error(t, t, sync=False)[1])(y)
     codes, _ = B.loka_quantize(x[0], B.SCALE_ROW)                                 # and the next call runs
     assert codes.shape == (32, 128)
+
+
+def test_variant_ids_keep_their_place():
+    # callers keep ids (a dispatch choice, a descriptor): entries are added at the end
+    names = ["row32x128", "row64x128", "row64x256", "row128x256", "row64x512", "row64x1024", "exact64x256", "exact64x512",
+             "exact64x1024", "wreg32", "strip32", "twopass128x128", "twopass256x256", "twopass256x256w8", "splitk128x128",
+             "splitk128x128s2", "panel256x256w8", "panel32_256x256"]
+    assert [B.variant_id(n) for n in names] == list(range(len(names)))
