@@ -1015,7 +1015,7 @@ static const char kPanel32Name[] = "panel32_256x256";
 static const char kPanel32RaggedName[] = "panel32_256x256_ragged";
 
 // gemm_panel32.hip
-const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro = false);
+const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro = false, bool want_y = true);
 bool panel32_affine(const GemmParams& p);
 size_t panel32_lds();
 void panel32_launch(const GemmParams& p, int bw, dim3 grid, hipStream_t s);
@@ -1549,7 +1549,7 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
     const void* kfn = blockwise ? vi.fn_block : vi.fn_plain;
     const bool splitk256 = vi.epi == EPI_SPLITK && bm == 256;
     if (splitk256) kfn = panel32_part_fn(panel32_bw(p, blockwise), false);
-    if (vi.name == kPanel32Name) kfn = panel32_fn(panel32_bw(p, blockwise), outq != nullptr, panel32_affine(p), p.qpro != 0);
+    if (vi.name == kPanel32Name) kfn = panel32_fn(panel32_bw(p, blockwise), outq != nullptr, panel32_affine(p), p.qpro != 0, p.y != nullptr);
     if (!kfn) return LOKA_ERR_UNSUPPORTED;
     int per_cu = 0;
     if (prepare_fn(dev, kfn, splitk256 ? 512 : vi.threads, splitk256 ? panel32_lds() : vi.lds, &per_cu) != LOKA_OK) return LOKA_ERR_HIP;

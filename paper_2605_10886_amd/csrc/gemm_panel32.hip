@@ -138,7 +138,9 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
 // bytes per fragment and the same matrix-pipe time per K step of 128 bytes, so the same main loop keeps the pipe full).
 // RAGK: K need not be a multiple of the 128-byte step: in the last step the lanes whose 16-byte chunk lies past the end
 // of the row read zeros, in both operands.
-template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0>
+// YOUT false: the caller wants no fp32 Y, and the code that would store it is left out (244 instead of 249 registers;
+// quantize + GEMM at 32768 x 4096 x 4096 549 -> 542 us, where 540 was measured before Y went through LDS).
+template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0, bool YOUT = true>
 __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     constexpr bool FP8OUT = F8 != 0;
     constexpr bool SPLITK = EPI == EPI_SPLITK, PART = SPLITK || BF16;
@@ -521,7 +523,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // a caller asked for.  Each wave passes a 32 x 32 sub-tile through 4 KB of its own LDS (128-byte rows, 16-byte chunk c
     // of row r at position c ^ (r / 2 % 8)) and stores it with 8 lanes per row: whole 128-byte lines instead of 16 bytes in
     // each of 64 (16384 x 1024 x 1024 with Y, 67 MB: 47.2 -> 36.3 us).
-    if (PART || p.y) {
+    if (PART || (YOUT && p.y)) {
         float* const dst = SPLITK ? p.part + (static_cast<int64_t>(ks) * p.batch + g) * p.M * p.N : p.y + obase;
         uint8_t* const fbuf = smem + wave * 4096;
         const int f_row = lane >> 3, f_c = lane & 7;
@@ -961,11 +963,15 @@ bool panel32_affine(const GemmParams& p) {
            p.norm == LOKA_NORM_BLOCKNORM || p.act != LOKA_ACT_NONE;
 }
 // bw: 0 plain scales, 1 block scales, 2 power-of-two block scales (see the kernel); fp8out with bw == 0 only
-const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro) {
+const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro, bool want_y) {
     if (qpro) return (bw != 0 || fp8out) ? nullptr : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, true>);
     if (fp8out) return bw != 0 ? nullptr
                        : affine ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 2>)
                                 : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 1>);
+    if (!want_y)
+        return bw == 2   ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0, false, false, false, false>)
+               : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0, false, false, false, false>)
+                         : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, false, false>);
     return bw == 2   ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0>)
            : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0>)
                      : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0>);
@@ -993,6 +999,9 @@ void panel32_launch(const GemmParams& p, int bw, dim3 grid, hipStream_t s) {
     if (p.qpro) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, true><<<grid, 512, kPanel32Lds, s>>>(p);
     else if (p.outq && panel32_affine(p)) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 2><<<grid, 512, kPanel32Lds, s>>>(p);
     else if (p.outq) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 1><<<grid, 512, kPanel32Lds, s>>>(p);
+    else if (!p.y && bw == 2) gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0, false, false, false, false><<<grid, 512, kPanel32Lds, s>>>(p);
+    else if (!p.y && bw == 1) gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0, false, false, false, false><<<grid, 512, kPanel32Lds, s>>>(p);
+    else if (!p.y) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, false, false><<<grid, 512, kPanel32Lds, s>>>(p);
     else if (bw == 2) gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0><<<grid, 512, kPanel32Lds, s>>>(p);
     else if (bw == 1) gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0><<<grid, 512, kPanel32Lds, s>>>(p);
     else gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0><<<grid, 512, kPanel32Lds, s>>>(p);
