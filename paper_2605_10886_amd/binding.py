@@ -290,7 +290,7 @@ def loka_dispatch_select(usec, err, budget: float, min_speedup: float = 0.0, use
 def loka_dispatch(desc: GemmDesc, x, w, err_budget: float, min_speedup: float = 0.0):
     """Returns (status, choice dict, candidate table list)."""
     choice = Choice()
-    cap = 64
+    cap = 4 * lib().loka_variant_count()          # four scale recipes, every variant
     table = (Candidate * cap)()
     n = c_int(0)
     st = lib().loka_dispatch(byref(desc), _ptr(x), _ptr(w), err_budget, min_speedup, byref(choice), table, cap,

@@ -146,3 +146,54 @@ def test_blocknorm_on_row_tiles(orc, shape, recipe):
         o = o * (o + 3).clamp(0, 6) / 6
     o = o.view(len(rows), N)
     assert bool(((out[idx].double() - o).abs() <= o.abs() * 2.0 ** -8 + 1e-5).all())
+
+
+@pytest.mark.parametrize("variant,shape", [("panel32x256", (1100, 272, 784)), ("panel64x256", (2100, 144, 784)), ("panel128x128", (1300, 256, 640)),
+                                           ("panel32_256x256_ragged", (900, 400, 784)), ("splitk128x128s2", (257, 16400, 528))])
+def test_new_forms_replay_from_a_graph(variant, shape):
+    # the calls of a training step and the split reference, captured once: every replay has new inputs, follows eager work and gives the eager bits
+    M, K, N = shape
+    desc = B.make_desc(M, N, K, 1, B.SCALE_ROW, B.SCALE_COL, B.NORM_LAYERNORM, 1e-5, B.variant_id(variant))
+    x, w = torch.empty(M, K, dtype=torch.bfloat16, device=DEV), torch.empty(K, N, dtype=torch.bfloat16, device=DEV)
+
+    def step():
+        wq, sw = B.loka_quantize(w, B.SCALE_COL, transpose_out=True)
+        xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+        out, _ = B.loka_fp8_gemm_norm(desc, xq, sx, wq, sw)
+        return wq, sw, xq, sx, out, B.loka_bf16_gemm(desc, x, w)
+
+    def inputs(seed):
+        x.copy_(synth.normal(M, K, seed=seed))
+        w.copy_(synth.weight(K, N, seed=seed + 1))
+
+    inputs(1)
+    step()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = step()
+    for seed in range(2, 6):
+        inputs(seed)
+        want = step()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
+def test_dispatch_table_lists_every_candidate():
+    # one row per recipe and variant that supports the shape, however many variants there are, the chosen one among them
+    M, K, N = 256, 128, 128
+    x, w = synth.normal(M, K, seed=1).to(DEV), synth.weight(K, N, seed=2).to(DEV)
+    B.loka_dispatch_clear()
+    st, ch, table = B.loka_dispatch(B.make_desc(M, N, K, norm=B.NORM_LAYERNORM), x, w, 0.1)
+    B.loka_dispatch_clear()
+    want = set()
+    for recipe in ("tensor", "row", "block", "block_pow2"):
+        xm, wm = RECIPES[recipe]
+        for v in range(B.lib().loka_variant_count()):
+            if B.loka_variant_supports(B.make_desc(M, N, K, 1, xm, wm, B.NORM_LAYERNORM, 1e-5), v):
+                want.add((xm, wm, v))
+    rows = [(r["x_mode"], r["w_mode"], r["variant"]) for r in table]
+    assert st == B.LOKA_OK and len(rows) == len(want) and set(rows) == want
+    assert (ch["x_mode"], ch["w_mode"], ch["variant"]) in want
