@@ -139,7 +139,8 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
 // RAGK: K need not be a multiple of the 128-byte step: in the last step the lanes whose 16-byte chunk lies past the end
 // of the row read zeros, in both operands.
 // YOUT false: the caller wants no fp32 Y, and the code that would store it is left out (244 instead of 249 registers;
-// quantize + GEMM at 32768 x 4096 x 4096 549 -> 542 us, where 540 was measured before Y went through LDS).
+// quantize + GEMM at 32768 x 4096 x 4096, beside a kernel that stored Y straight from registers: 1.1 and 0.5 % slower with the code in, 0.3 and
+// 0.4 % without it).
 template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0, bool YOUT = true>
 __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     constexpr bool FP8OUT = F8 != 0;
