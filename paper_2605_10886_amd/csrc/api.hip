@@ -2,6 +2,8 @@
 // forwarding to the kernel launchers.  See include/loka.h for the contract.
 #include "common.h"
 
+#include <algorithm>
+#include <cstdint>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
@@ -319,17 +321,15 @@ loka_status loka_fp8_gemm_norm_check(const loka_gemm_desc* desc, const void* wor
     if (!desc) return LOKA_ERR_NULL;
     const loka_status st = validate_desc(desc, true);
     if (st != LOKA_OK) return st;
-    // the variant loka_fp8_gemm_norm runs for desc, or (desc->variant < 0 only: the two choices can differ) the one
-    // loka_fp8_gemm_norm_fp8out runs; every workspace with a bounded wait begins with the flag
-    int v = resolve_for_scratch(desc, workspace, ws_bytes);
-    bool q = false;
-    if (v < 0 || !variant_has_wait_flag(desc, v)) {
-        const int vq = fp8out_variant(desc);
-        if (vq >= 0 && variant_has_wait_flag(desc, vq, true)) { v = vq; q = true; }
-    }
-    if (v < 0) return LOKA_ERR_UNSUPPORTED;
-    if (!variant_has_wait_flag(desc, v, q)) return LOKA_OK;
-    if (!workspace || ws_bytes < variant_workspace(desc, v, q)) return LOKA_ERR_WORKSPACE;
+    // `workspace` may belong to a loka_fp8_gemm_norm call or to a loka_fp8_gemm_norm_fp8out call, whose kernels (with
+    // desc->variant < 0) and sizes can differ either way: enough for one of the two that wait is enough.  Every workspace
+    // with a bounded wait begins with the same header.
+    const int v = resolve_for_scratch(desc, workspace, ws_bytes), vq = fp8out_variant(desc);
+    size_t need = SIZE_MAX;
+    if (v >= 0 && variant_has_wait_flag(desc, v)) need = variant_workspace(desc, v);
+    if (vq >= 0 && variant_has_wait_flag(desc, vq, true)) need = std::min(need, variant_workspace(desc, vq, true));
+    if (need == SIZE_MAX) return v < 0 ? LOKA_ERR_UNSUPPORTED : LOKA_OK;
+    if (!workspace || ws_bytes < need) return LOKA_ERR_WORKSPACE;
     // header of the workspace: [0] the nonce of the last launch that used it, [1] the nonce of the last launch in
     // which a wait ran out (0 in both: never used)
     unsigned long long hdr[2] = {0, 0};
