@@ -51,16 +51,22 @@ __host__ __device__ constexpr int coff_of(int ti) { return (ti >> 1) * 32 + (ti 
 // Workgroups are dealt to the 8 XCDs round-robin (block b runs on XCD b % 8), and each XCD has an L2 of its own.  This
 // renumbers G blocks so that every XCD works on one contiguous range of logical ids (any G: the first G % 8 XCDs have one
 // more): neighbours in the id order, which share operands, then find them in the same L2.
-__device__ __forceinline__ int xcd_contiguous(int b, int G) {
+__host__ __device__ constexpr int xcd_contiguous(int b, int G) {
     const int x = b & 7, r = G & 7;
     return x * (G >> 3) + (x < r ? x : r) + (b >> 3);
 }
 
-// Whether a persistent launch of G workgroups whose tiles_n neighbours wait for one another may be renumbered so.  Where a
-// range of ids ends inside a panel, the panel's first workgroups are dealt out last and its others among the first: while
-// another stream's kernel holds part of the CUs, those others wait on their CUs.  At most 7 tiles_n can, so with tiles_n <= 8 four
-// such launches at once still leave CUs that finish panels; wider rows keep launch order unless G is a multiple of 8.
-__device__ __forceinline__ bool panels_may_spread(int G, int tiles_n) { return G % 8 == 0 || tiles_n <= 8; }
+// Whether a persistent launch of G workgroups whose tiles_n neighbours wait for one another may be renumbered so.
+// An XCD starts its share of a launch in order, on 32 CUs.  Of a launch that it has not started in full it holds at most
+// tiles_n - 1 workgroups of an unfinished panel, so while L such launches share the chip and L (tiles_n - 1) < 32, XCD 0 gets
+// through its share, then XCD 1, whose first panel may begin on XCD 0, and so on: nobody's wait can fill an XCD.
+// That covers four launches up to 8 tiles and two up to 16 (there only without a panel on two XCDs: its workgroups would
+// start first on one and last on the other).  Wider rows keep launch order, which gives every XCD a few workgroups of each
+// panel and is the faster one there as well: 8192 x 8192 x 2048 (M x N x K) 167 -> 150 us, 4096 x 5120 x 2048 72.8 -> 67.9,
+// 8192 x 16384 x 512 193 -> 185; slowest the other way 3000 x 5120 x 512 22.3 -> 23.2, 3000 x 4096 x 512 19.8 -> 20.4.
+__host__ __device__ constexpr bool panels_may_spread(int G, int tiles_n) {
+    return tiles_n <= 8 || (tiles_n <= 16 && G % 8 == 0 && (G / 8) % tiles_n == 0);
+}
 
 // Tile t of a tiles_m x tiles_n grid in bands of 8 tile rows, walked column by column inside a band: 64 neighbours in the
 // order cover an 8 x 8 block of tiles and read 8 + 8 operand strips, where plain row order would read 1 + 64.

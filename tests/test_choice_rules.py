@@ -1,10 +1,14 @@
 """Host rules of the library: which kernel a call takes, and how much scratch it accepts (no GPU needed)."""
 import ctypes
+import os
+import random
+import subprocess
 
 import pytest
 import torch
 
 from paper_2605_10886_amd import binding as B
+from paper_2605_10886_amd import build
 
 
 def _check(desc, nbytes):
@@ -24,3 +28,68 @@ def test_wait_check_takes_the_workspace_of_either_call(M, N, K):
     sizes = [int(L.loka_fp8_gemm_norm_workspace(ctypes.byref(d))), int(L.loka_fp8_gemm_norm_fp8out_workspace(ctypes.byref(d)))]
     for n in sizes:
         assert _check(d, n) != B.LOKA_ERR_WORKSPACE, (sizes, n)
+
+
+@pytest.fixture(scope="module")
+def numbering(tmp_path_factory):
+    """(G, tiles_n) -> the order in which a panel launch takes its workgroups: logical id of every block, from the header
+    that the kernels compile.  None: launch order."""
+    d = tmp_path_factory.mktemp("numbering")
+    src = d / "numbering.hip"
+    src.write_text("""#include "gemm_common.h"
+#include <cstdio>
+int main() {
+    for (int tn = 1; tn <= 256; ++tn)
+        for (int G = tn; G <= 256; G += tn) {
+            std::printf("%d %d", G, tn);
+            if (loka::panels_may_spread(G, tn)) for (int b = 0; b < G; ++b) std::printf(" %d", loka::xcd_contiguous(b, G));
+            std::printf("\\n");
+        }
+}
+""")
+    exe = str(d / "numbering")
+    subprocess.run([build._hipcc(), "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(build.HERE, "csrc"), str(src), "-o", exe],
+                   check=True, capture_output=True)
+    rows = [[int(v) for v in line.split()] for line in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.splitlines()]
+    return {(r[0], r[1]): r[2:] or None for r in rows}
+
+
+def test_panels_are_spread_only_where_their_waits_cannot_fill_an_xcd(numbering):
+    assert len(numbering) == sum(256 // tn for tn in range(1, 257))
+    for (G, tn), ids in numbering.items():
+        if ids is None:
+            assert tn > 8
+            continue
+        assert sorted(ids) == list(range(G))
+        assert 2 * (tn - 1) < 32 and (tn > 8 or 4 * (tn - 1) < 32)
+        if tn > 8:                                                # no panel on two XCDs
+            homes = [{b % 8 for b in range(G) if ids[b] // tn == panel} for panel in range(G // tn)]
+            assert all(len(h) == 1 for h in homes), (G, tn)
+    assert numbering[256, 16] and numbering[255, 5]
+    assert not any(numbering[g] for g in ((240, 20), (240, 24), (240, 40), (256, 64), (256, 32), (64, 16)))
+
+
+@pytest.mark.parametrize("G,tn,launches", [(255, 5, 4), (256, 8, 4), (248, 8, 4), (256, 16, 2), (128, 16, 2), (252, 7, 4)])
+def test_launches_side_by_side_finish(numbering, G, tn, launches):
+    # 8 XCDs of 32 slots; each starts its share of every launch in order, the launches interleaved at random; a panel's
+    # workgroups leave once all of them are there.  Nobody may be left waiting.
+    ids = numbering[G, tn]
+    for seed in range(20):
+        rng = random.Random(seed)
+        todo = [[[ids[b] // tn for b in range(x, G, 8)] for x in range(8)] for _ in range(launches)]
+        held, arrived = [[] for _ in range(8)], {}
+        left = launches * G
+        while left:
+            moves = [(n, x) for x in range(8) if len(held[x]) < 32 for n in range(launches) if todo[n][x]]
+            assert moves, (G, tn, seed, "no slot is free and nobody can finish")
+            n, x = rng.choice(moves)
+            for _ in range(rng.randrange(1, 33)):                 # a run of one launch's workgroups on one XCD
+                if not todo[n][x] or len(held[x]) >= 32:
+                    break
+                key = (n, todo[n][x].pop(0))
+                held[x].append(key)
+                arrived[key] = arrived.get(key, 0) + 1
+                if arrived[key] == tn:
+                    for h in held:
+                        h[:] = [k for k in h if k != key]
+                    left -= tn
