@@ -68,6 +68,11 @@ __host__ __device__ constexpr bool panels_may_spread(int G, int tiles_n) {
     return tiles_n <= 8 || (tiles_n <= 16 && G % 8 == 0 && (G / 8) % tiles_n == 0);
 }
 
+// Loads of block scales that a wave of the 32 x 32 x 64 kernel requests at the start of K step k, for step k + 1: W's scale and
+// X's four, or (quad: a lane holds four K blocks' scales of X) W's alone in three steps of four.  What may stay in flight
+// where the step needs X(k + 1) and W(k + 1) is these and the 4 loads of X(k + 2), the only ones requested behind W(k + 1).
+__host__ __device__ constexpr int panel32_scale_loads(bool quad, int k) { return quad && ((k + 1) & 3) != 0 ? 1 : 5; }
+
 // Tile t of a tiles_m x tiles_n grid in bands of 8 tile rows, walked column by column inside a band: 64 neighbours in the
 // order cover an 8 x 8 block of tiles and read 8 + 8 operand strips, where plain row order would read 1 + 64.
 __device__ __forceinline__ void banded_tile(int t, int tiles_m, int tiles_n, int& tm, int& tn) {

@@ -439,9 +439,11 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
         const int ld_w_slot = e5, ld_w_kb = (k + 2) * 128;              // W(k + 2) -> the slot X(k) leaves
         bw_step(k);
         LOKA_HALF_STEP(e5, sw_cur, 1, 0, 1, 1);
-        // all but this step's newest loads: X(k + 2) (4) and, blockwise, the scales of block k + 1 (MI + 1)
-        if (ld_w) { if (BLOCKWISE) __builtin_amdgcn_s_waitcnt(0x0F79); else __builtin_amdgcn_s_waitcnt(0x0F74); }
-        else __builtin_amdgcn_s_waitcnt(0x0F70);
+        // all but this step's newest loads: X(k + 2) (4) and, blockwise, the scales of block k + 1 (1 or MI + 1)
+        if (!ld_w) __builtin_amdgcn_s_waitcnt(0x0F70);
+        else if (!BLOCKWISE) __builtin_amdgcn_s_waitcnt(0x0F74);
+        else if (panel32_scale_loads(quad, k) == 1) __builtin_amdgcn_s_waitcnt(0x0F75);
+        else __builtin_amdgcn_s_waitcnt(0x0F79);
         lds_barrier();                                          // (also waits for this wave's LDS reads)
         LOKA_HALF_STEP(sx_nxt, sw_nxt, 0, 1, 2, 0);
         e5 = sx_nxt;

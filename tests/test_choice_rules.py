@@ -93,3 +93,31 @@ def test_launches_side_by_side_finish(numbering, G, tn, launches):
                     for h in held:
                         h[:] = [k for k in h if k != key]
                     left -= tn
+
+
+def test_block_scales_leave_no_operand_in_flight(tmp_path):
+    # The block-scaled main loop, one wave's loads in the order they are requested (they return in it): X(0) W(0) X(1) W(1)
+    # X(2), then per step k the scales of block k + 1, X(k + 2) and, behind the wait, W(k + 2).  At the wait X(k + 1) and
+    # W(k + 1) have to be there, and no more than that is waited for.
+    src = tmp_path / "loads.hip"
+    src.write_text("""#include "gemm_common.h"
+#include <cstdio>
+int main() {
+    for (int quad = 0; quad < 2; ++quad)
+        for (int k = 0; k < 64; ++k) std::printf("%d ", loka::panel32_scale_loads(quad, k));
+}
+""")
+    exe = str(tmp_path / "loads")
+    subprocess.run([build._hipcc(), "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(build.HERE, "csrc"), str(src), "-o", exe],
+                   check=True, capture_output=True)
+    n = [int(v) for v in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.split()]
+    for quad, scales in ((False, n[:64]), (True, n[64:])):
+        for ksteps in (4, 5, 8, 16, 64) if not quad else (4, 8, 16, 64):
+            sent = [f"{m}{k}" for k in (0, 1) for m in "XW" for _ in range(4)] + ["X2"] * 4
+            for k in range(ksteps - 2):
+                fetch = 5 if not quad or (k + 1) % 4 == 0 else 1
+                sent += [f"s{k + 1}"] * fetch + ([f"X{k + 2}"] * 4 if k else [])
+                flying = sent[len(sent) - (4 + scales[k]):]
+                assert not {f"X{k + 1}", f"W{k + 1}"} & set(flying), (quad, ksteps, k)
+                assert sent[len(sent) - (4 + scales[k]) - 1] == f"W{k + 1}"
+                sent += [f"W{k + 2}"] * 4
