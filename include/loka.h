@@ -243,8 +243,8 @@ void loka_test_set_spin_limit(int64_t polls);
  *             row minimum and maximum, sent along with the row statistics in the one exchange between the row's
  *             workgroups, decide the row scale; with gamma / beta, under BlockNorm or with an activation the row
  *             amax of the result crosses the workgroups in a second exchange.  LOKA_NORM_NONE: unsupported.
- * desc->variant names one, or -1: the library's choice for the shape when it is one of the three, else the
- * streaming kernel where it covers the shape, else the panel kernel.  LOKA_ERR_UNSUPPORTED otherwise.
+ * desc->variant names one, or -1: the profiled choice for the shape when it is one of the three, else, of those that take
+ * the call, the one expected to be fastest.  LOKA_ERR_UNSUPPORTED otherwise.
  * Workspace: loka_fp8_gemm_norm_fp8out_workspace(desc) bytes (non-zero only for the panel kernel with rows wider
  * than 256 columns - also under BlockNorm, where loka_fp8_gemm_norm needs none -; NULL / 0 otherwise), device memory, 16-byte aligned, not shared with a call still running;
  * loka_fp8_gemm_norm_check reports the panel kernel's bounded wait on it as for loka_fp8_gemm_norm.
@@ -282,8 +282,8 @@ loka_status loka_fp8_linear_norm(const loka_gemm_desc* desc, const void* x_bf16,
  *   xq_out [batch][M, K] e4m3 codes and sx_out [batch][M] fp32 row scales: device memory, 16-byte aligned, written by
  *   the call, not to be read or written by anything else until the call's kernel has finished;
  *   wq, sw, gamma, beta, out_bf16, y_fp32 as in loka_fp8_gemm_norm.  desc->x_mode must be LOKA_SCALE_ROW;
- *   desc->variant names one of the two kernels, or is -1: the library's choice for the shape where that kernel has
- *   the prologue, else the other.  LOKA_ERR_UNSUPPORTED for shapes neither covers.
+ *   desc->variant names one of the two kernels, or is -1: the profiled choice for the shape where that kernel has
+ *   the prologue, else the one expected to be faster.  LOKA_ERR_UNSUPPORTED for shapes neither covers.
  * No workspace, no allocation. */
 loka_status loka_fp8_linear_norm_xq(const loka_gemm_desc* desc, const void* x_bf16, uint8_t* xq_out, float* sx_out,
                                     const uint8_t* wq, const float* sw, const void* gamma_bf16, const void* beta_bf16,

@@ -21,10 +21,8 @@ bool variant_supports(const loka_gemm_desc*, int);
 size_t variant_workspace(const loka_gemm_desc*, int, bool fp8out = false);
 loka_status fp8_gemm_norm_launch(const loka_gemm_desc*, int, const uint8_t*, const float*, const uint8_t*, const float*,
                                  const void*, const void*, void*, float*, uint8_t*, float*, void*, hipStream_t);
-int variant_streaming_id();
-bool variant_is_streaming(int);
-bool variant_is_strip(int);
-bool variant_is_panel32(int);
+bool variant_supports_fp8out(const loka_gemm_desc*, int);
+int variant_fp8out_default(const loka_gemm_desc*);
 bool variant_supports_fused(const loka_gemm_desc*, int);
 bool variant_supports_xq(const loka_gemm_desc*, int);
 int variant_xq_default(const loka_gemm_desc*);
@@ -299,22 +297,10 @@ loka_status loka_fp8_linear_norm_xq(const loka_gemm_desc* desc, const void* x_bf
                                      static_cast<hipStream_t>(hip_stream));
 }
 
-// The kernels with an FP8-output epilogue: the two that keep a whole output row inside one workgroup (streaming) or
-// one wave (strip), and the large-layer panel kernel (which sends the row extremes along with the row statistics).
-// The one the caller names, else the library's choice for the shape when it is one of the three, else the
-// streaming one where it can run the shape, else the panel kernel.  -1 when the named variant has no such epilogue
-// or cannot run the shape.
+// -1 when the named variant has no FP8-output epilogue or cannot run the shape.
 static int fp8out_variant(const loka_gemm_desc* desc) {
-    auto usable = [&](int v) {
-        return v >= 0 && (variant_is_streaming(v) || variant_is_strip(v) || variant_is_panel32(v)) && variant_supports(desc, v);
-    };
-    if (desc->variant >= 0) return usable(desc->variant) ? desc->variant : -1;
-    const int v = default_variant(desc);
-    if (usable(v)) return v;
-    if (usable(variant_streaming_id())) return variant_streaming_id();
-    for (int u = 0; u < variant_count(); ++u)             // the panel kernel takes every shape the two others do not
-        if (variant_is_panel32(u) && usable(u)) return u;
-    return -1;
+    if (desc->variant >= 0) return variant_supports_fp8out(desc, desc->variant) ? desc->variant : -1;
+    return variant_fp8out_default(desc);
 }
 
 loka_status loka_fp8_gemm_norm_check(const loka_gemm_desc* desc, const void* workspace, size_t ws_bytes, void* hip_stream) {

@@ -72,14 +72,18 @@ static int static_choice(const loka_gemm_desc* d) {
     return s.variant;
 }
 
-// The profiled choice where loka_dispatch has been run for the shape, else the static one.
+// The profiled choice where loka_dispatch has been run for the shape (it timed bf16 output), else -1.
+int profiled_variant(const loka_gemm_desc* d) {
+    const RecipeKey rk(d->M, d->N, d->K, d->batch, epilogue_of(d), d->x_mode, d->w_mode);
+    std::lock_guard<std::mutex> lk(g_mu);
+    auto it = g_best_variant.find(rk);
+    return it != g_best_variant.end() && variant_supports(d, it->second) ? it->second : -1;
+}
+
+// The profiled choice, else the static one.
 int default_variant(const loka_gemm_desc* d) {
-    {
-        const RecipeKey rk(d->M, d->N, d->K, d->batch, epilogue_of(d), d->x_mode, d->w_mode);
-        std::lock_guard<std::mutex> lk(g_mu);
-        auto it = g_best_variant.find(rk);
-        if (it != g_best_variant.end() && variant_supports(d, it->second)) return it->second;
-    }
+    const int prof = profiled_variant(d);
+    if (prof >= 0) return prof;
     if (d->norm == LOKA_NORM_BLOCKNORM) {
         // groups never leave a workgroup: the streaming kernel for skinny layers with many rows (unless K is
         // long and there is a 256 x 256 tile per CU), the large-tile kernel otherwise

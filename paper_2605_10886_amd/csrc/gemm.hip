@@ -1123,14 +1123,24 @@ bool variant_supports_xq(const loka_gemm_desc* d, int v) {
         return d->N <= 256 && (d->K == 512 || d->K == 1024 || d->K == 2048) && d->M * d->K < (int64_t(1) << 31);
     return false;
 }
-int default_variant(const loka_gemm_desc* d);
-// the library's choice for the shape when it has the prologue, else the first kernel that has it
+int profiled_variant(const loka_gemm_desc* d);
+// The kernel of loka_fp8_linear_norm_xq where the caller names none: the profiled choice where it has the prologue, else the one
+// that covers the shape.  Both do for N <= 256 and K of 512 or 1024: the large-tile kernel where its rounds of one tile per CU
+// are at least 7/8 full (each workgroup quantizes its 256 rows first; a tile more than fits is a second round), the
+// streaming kernel below.  Measured, streaming against large-tile, M x N x K: 60000 x 256 x 512 (235 of 256 tiles) 44.5 against
+// 39.3 us, 60000 x 64 x 1024 68 against 58, 131072 x 128 x 512 (512) 74 against 68; 49152 x 64 x 512 (192) 34 against 35,
+// 70000 x 256 x 1024 (274 of 512) 78 against 104, 98304 x 64 x 512 (384) 58 against 64.
 int variant_xq_default(const loka_gemm_desc* d) {
-    const int v0 = default_variant(d);
-    if (variant_supports_xq(d, v0)) return v0;
-    for (int v = 0; v < kNumVariants; ++v)
-        if (variant_supports_xq(d, v)) return v;
-    return -1;
+    const int prof = profiled_variant(d);
+    if (variant_supports_xq(d, prof)) return prof;
+    int wreg = -1, panel = -1;
+    for (int v = 0; v < kNumVariants; ++v) {
+        if (!variant_supports_xq(d, v)) continue;
+        (kVariants[v].name == kWregName ? wreg : panel) = v;
+    }
+    if (wreg < 0 || panel < 0) return wreg >= 0 ? wreg : panel;
+    const int64_t tiles = ((d->M + 255) / 256) * d->batch, rounds = (tiles + 255) / 256;
+    return 8 * tiles >= 7 * 256 * rounds ? panel : wreg;
 }
 // the kernel the fused entry point uses when the caller names none: the strip kernel where it applies (waves that
 // never synchronize, one strip each), else the streaming kernel
@@ -1143,14 +1153,7 @@ int variant_fused_default(const loka_gemm_desc* d) {
     }
     return wreg;
 }
-int variant_streaming_id() {
-    for (int v = 0; v < kNumVariants; ++v)
-        if (kVariants[v].name == kWregName) return v;
-    return -1;
-}
 bool variant_is_streaming(int v) { return kVariants[v].name == kWregName; }
-bool variant_is_strip(int v) { return kVariants[v].name == kStripName; }
-bool variant_is_panel32(int v) { return kVariants[v].name == kPanel32Name; }
 // (the two instantiations of the 32 x 32 x 64 kernel that lay out the workspace its way)
 static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Name || vi.name == kPanel32RaggedName; }
 
@@ -1287,6 +1290,50 @@ static int blocknorm_form(const loka_gemm_desc* d, int v) {
     for (int r : rows) {
         const double c = variant_cost(d, r);
         if (c < cost) { cost = c; best = r; }
+    }
+    return best;
+}
+
+// FP8 output: the kernels with that epilogue are the two that keep a whole output row inside one workgroup (streaming) or one
+// wave (strip), and the large-tile kernel (which sends the row extremes along with the row statistics).
+// The last of them only under a row norm and without block scales.
+bool variant_supports_fp8out(const loka_gemm_desc* d, int v) {
+    if (!variant_supports(d, v)) return false;
+    const char* name = kVariants[v].name;
+    if (name == kPanel32Name) return d->norm != LOKA_NORM_NONE && !scale_mode_is_block(d->x_mode);
+    return name == kWregName || name == kStripName;
+}
+// Expected time of that form, microseconds, N <= 256: fitted (as above) to its times at 252 shapes, M 512 - 131072, N 64 - 256,
+// K 128 - 2048; the choice is within 0.1 % of the fastest of the three in the geometric mean over them (worst 1.04), where
+// following the bf16 choice (and the streaming kernel where that has no such form) was at 17 % (worst 2.2).  W in LDS
+// (strip) costs by 128 or 256 columns, and only one phase of it is considered; the streaming kernel's blocks are taller for
+// K <= 256.
+static double fp8out_cost(const loka_gemm_desc* d, int v) {
+    const double x = 1e-6 * d->M * d->K * d->batch, out = 1e-6 * d->M * d->N * d->batch;
+    const double strips = static_cast<double>((d->M + 31) / 32) * d->batch;
+    if (kVariants[v].name == kStripName) {
+        const double wide = d->N > 128 ? 1.0 : 0.0, w = d->K * (128 + 128 * wide) / 65536.0;
+        return w > 2.0 ? 1e9 : 5.05 + 1.93 * wide + w * (1.87 + 1.62 * strips / 2048) + .17 * x + .28 * out;
+    }
+    if (kVariants[v].name == kWregName) {
+        const double rounds = std::max(1.0, strips / kPlanCus);
+        return 7.41 + (d->K <= 256 ? .93 : 0.0) + rounds * (.76 + .149 * d->K * d->N / 65536.0) + .24 * x + .185 * out;
+    }
+    const int64_t tiles = ((d->M + 255) / 256) * d->batch, rounds = (tiles + kPlanCus - 1) / kPlanCus, steps = (d->K + 127) / 128;
+    return 3.51 + rounds * (7.69 + steps * (1.0 + .61 * std::min(1.0, tiles / static_cast<double>(kPlanCus)))) + .07 * out;
+}
+// The kernel of loka_fp8_gemm_norm_fp8out where the caller names none: the profiled choice where it has the form, else the least
+// expected time.  Wider rows than 256: the streaming kernel where it covers the shape (M x N x K 2048 x 512 x 512 9.9 against
+// 18.7 us on the large-tile kernel, 65536 x 1024 x 128 44 against 55; 16384 x 1024 x 256 the same 18).
+int variant_fp8out_default(const loka_gemm_desc* d) {
+    const int prof = profiled_variant(d);
+    if (variant_supports_fp8out(d, prof)) return prof;
+    int best = -1;
+    double cost = 0.0;
+    for (int v = 0; v < kNumVariants; ++v) {
+        if (!variant_supports_fp8out(d, v)) continue;
+        const double c = d->N <= 256 ? fp8out_cost(d, v) : kVariants[v].name == kWregName ? 0.0 : 1.0;
+        if (best < 0 || c < cost) { best = v; cost = c; }
     }
     return best;
 }
@@ -1509,13 +1556,8 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
     // FP8 output: the row stays inside one workgroup (streaming kernel) or one wave (strip kernel), or - panel kernel -
     // the row amax crosses the workgroups: as the row's extreme pre-norm values along with the row statistics when
     // there is no gamma / beta (the normalized value then grows with the pre-norm value), else in a second exchange.
-    // The second exchange also serves BlockNorm (+ Hard-Swish), whose statistics never leave the tile.  A row norm is
-    // required; non-blockwise scales.
-    if (outq && vi.name == kPanel32Name) {
-        if (blockwise || d->norm == LOKA_NORM_NONE) return LOKA_ERR_UNSUPPORTED;
-    } else if (outq && vi.name != kWregName && vi.name != kStripName) {
-        return LOKA_ERR_UNSUPPORTED;
-    }
+    // The second exchange also serves BlockNorm (+ Hard-Swish), whose statistics never leave the tile.
+    if (outq && !variant_supports_fp8out(d, v)) return LOKA_ERR_UNSUPPORTED;
     p.norm = d->norm; p.eps = d->eps; p.block_n = d->block_n; p.act = d->act;
     int bm = vi.bm, bn = vi.bn;
     if (vi.epi == EPI_SPLITK) {

@@ -121,3 +121,33 @@ int main() {
                 assert not {f"X{k + 1}", f"W{k + 1}"} & set(flying), (quad, ksteps, k)
                 assert sent[len(sent) - (4 + scales[k]) - 1] == f"W{k + 1}"
                 sent += [f"W{k + 2}"] * 4
+
+
+def _chosen(form, M, N, K, norm=B.NORM_LAYERNORM, batch=1):
+    """Name of the kernel behind variant = -1 for a call of that form (the library's own rule, a C++ function of the descriptor)."""
+    fn = getattr(B.lib(), {"fp8out": "_ZN4loka22variant_fp8out_defaultEPK14loka_gemm_desc",
+                           "xq": "_ZN4loka18variant_xq_defaultEPK14loka_gemm_desc"}[form])
+    kw = dict(block_n=256) if norm == B.NORM_BLOCKNORM else {}
+    v = fn(ctypes.byref(B.make_desc(M, N, K, batch, norm=norm, **kw)))
+    return B.loka_variant_name(v) if v >= 0 else None
+
+
+# the kernel that was measured at least 10 % faster than the other two that have the form
+@pytest.mark.parametrize("form,M,N,K,want", [
+    ("fp8out", 2048, 64, 128, "strip32"), ("fp8out", 32768, 128, 128, "strip32"), ("fp8out", 65536, 112, 512, "strip32"),
+    ("fp8out", 131072, 128, 512, "strip32"), ("fp8out", 16384, 256, 1024, "wreg32"), ("fp8out", 8192, 256, 512, "wreg32"),
+    ("fp8out", 65536, 256, 1024, "panel32_256x256"), ("fp8out", 65536, 256, 512, "panel32_256x256"),
+    ("fp8out", 2048, 512, 512, "wreg32"), ("fp8out", 65536, 1024, 256, "wreg32"), ("fp8out", 2048, 2048, 512, "panel32_256x256"),
+    ("xq", 60000, 256, 512, "panel32_256x256"), ("xq", 60000, 64, 1024, "panel32_256x256"), ("xq", 70000, 256, 1024, "wreg32"),
+    ("xq", 80000, 64, 512, "wreg32"), ("xq", 32768, 128, 1024, "wreg32"), ("xq", 131072, 128, 256, "wreg32"),
+    ("xq", 4096, 128, 2048, "panel32_256x256")])
+def test_forms_choose_by_their_own_times(form, M, N, K, want):
+    assert _chosen(form, M, N, K) == want
+
+
+def test_fp8_output_without_a_row_norm_takes_a_kernel_that_has_it():
+    # the large-tile kernel needs a row norm; where it would be the fastest, the call still runs
+    for M, N, K in ((65536, 256, 512), (65536, 256, 1024), (131072, 256, 256)):
+        assert _chosen("fp8out", M, N, K, B.NORM_NONE) in ("wreg32", "strip32")
+        assert _chosen("fp8out", M, N, K, B.NORM_BLOCKNORM) in ("wreg32", "panel32_256x256")
+    assert _chosen("fp8out", 512, 4096, 4096, B.NORM_NONE) is None
