@@ -16,6 +16,7 @@ int variant_count();
 const char* variant_name(int);
 bool variant_supports(const loka_gemm_desc*, int);
 bool variant_is_streaming(int);
+bool variant_has_wait_flag(const loka_gemm_desc*, int, bool fp8out);
 int variant_cheapest(const loka_gemm_desc*, size_t max_ws);
 loka_status validate_desc(const loka_gemm_desc* d, bool fp8);
 loka_status bf16_gemm_launch(const loka_gemm_desc*, const void*, const void*, float*, void*, size_t, hipStream_t, bool weights_ready);
@@ -270,7 +271,8 @@ loka_status loka_dispatch(const loka_gemm_desc* shape, const void* x_bf16, const
             LOKA_HIP_TRY(hipStreamSynchronize(s));
             // a candidate whose cross-workgroup wait ran out (the device was not its alone) produced no result:
             // neither its time nor its error means anything
-            st = loka_fp8_gemm_norm_check(&t, ws_g.p, ws_gemm, s);
+            // (only where the bf16 call waits: under BlockNorm the FP8-output form alone does, on a workspace of its own)
+            st = variant_has_wait_flag(&t, v, false) ? loka_fp8_gemm_norm_check(&t, ws_g.p, ws_gemm, s) : LOKA_OK;
             if (st == LOKA_ERR_TIMEOUT) {
                 if (log_on()) std::fprintf(stderr, "[loka] %s: a bounded wait ran out, candidate dropped\n", variant_name(v));
                 continue;

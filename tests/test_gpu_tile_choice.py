@@ -197,3 +197,18 @@ def test_dispatch_table_lists_every_candidate():
     rows = [(r["x_mode"], r["w_mode"], r["variant"]) for r in table]
     assert st == B.LOKA_OK and len(rows) == len(want) and set(rows) == want
     assert (ch["x_mode"], ch["w_mode"], ch["variant"]) in want
+
+
+@pytest.mark.parametrize("shape", [(300, 1920, 1024), (130, 384, 4096), (8200, 256, 512)])
+def test_dispatch_of_wide_blocknorm_layers(shape):
+    # groups of 256 in rows of several tiles: bf16 output has no wait to report (FP8 output has), every recipe is a candidate
+    M, K, N = shape
+    x, w = synth.student_t4(M, K, seed=M).to(DEV), synth.weight(K, N, seed=N).to(DEV)
+    B.loka_dispatch_clear()
+    try:
+        desc = B.make_desc(M, N, K, 1, B.SCALE_ROW, B.SCALE_COL, B.NORM_BLOCKNORM, 1e-5, block_n=256, act=B.ACT_HARDSWISH)
+        st, ch, table = B.loka_dispatch(desc, x, w, 0.5)
+        assert st == B.LOKA_OK and {r["x_mode"] for r in table} == {RECIPES[r][0] for r in ("tensor", "row", "block", "block_pow2")}
+        assert ch["variant"] in [r["variant"] for r in table if r["x_mode"] == ch["x_mode"]]
+    finally:
+        B.loka_dispatch_clear()
