@@ -388,7 +388,9 @@ loka_status loka_dispatch(const loka_gemm_desc* shape, const void* x_bf16, const
 /* Forget every cached choice (host only). */
 void loka_dispatch_clear(void);
 /* Variant the library would run for desc with variant = -1 (cached dispatch choice for the
- * shape and recipe if there is one, else a static heuristic); -1 when nothing supports it. */
+ * shape and recipe if there is one, else a static heuristic); -1 when nothing supports it.
+ * BlockNorm without a cached choice: where this is "panel32_256x256", loka_fp8_gemm_norm with variant = -1 may run
+ * row tiles of 16, 32 or 64 rows in its place (few rows), whose fp32 sums are in another order; the id names the large tile. */
 int loka_default_variant(const loka_gemm_desc* desc);
 
 #ifdef __cplusplus

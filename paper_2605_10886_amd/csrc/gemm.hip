@@ -1274,9 +1274,11 @@ static double variant_cost(const loka_gemm_desc* d, int v) {
     return t;
 }
 
-// BlockNorm where the library chose the 32 x 32 x 64 kernel (a caller that names it gets its bits, which its FP8-output form
-// quantizes): the groups are tiles of 256 columns, so a layer with few rows also runs on the 256-column row tiles, one workgroup per group and 16, 32 or 64 rows (no exchange, no scratch in either).  By
-// expected time (bf16 output; M x N x K: 222 x 256 x 768 in 4 problems 16.1 -> 6.7 us, 2048 x 1024 x 512 14.9 -> 7.6, 1000 x 4096 x 4096 42.9 -> 30.4).
+// BlockNorm where the static choice is the 32 x 32 x 64 kernel (a caller that names it gets its bits, which its FP8-output form
+// quantizes, and so does a shape for which loka_dispatch timed and probed it): the groups are tiles of 256 columns, so a
+// layer with few rows also runs on the 256-column row tiles, one workgroup per group and 16, 32 or 64 rows (no exchange, no
+// scratch in either).  By expected time (bf16 output; M x N x K: 222 x 256 x 768 in 4 problems 16.1 -> 6.7 us,
+// 2048 x 1024 x 512 14.9 -> 7.6, 1000 x 4096 x 4096 42.9 -> 30.4).
 static int blocknorm_form(const loka_gemm_desc* d, int v) {
     static const std::array<int, 3> rows = [] {
         std::array<int, 3> r{};
@@ -1535,7 +1537,8 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
                                         const float* sw, const void* gamma, const void* beta, void* out, float* y,
                                         uint8_t* outq, float* outs, const void* x_bf16, float* sx_out, void* workspace,
                                         hipStream_t s, bool quantize_prologue) {
-    if (d->variant < 0 && d->norm == LOKA_NORM_BLOCKNORM && kVariants[v].name == kPanel32Name && !outq && !quantize_prologue)
+    if (d->variant < 0 && d->norm == LOKA_NORM_BLOCKNORM && kVariants[v].name == kPanel32Name && !outq && !quantize_prologue &&
+        profiled_variant(d) != v)
         v = blocknorm_form(d, v);
     const VariantInfo& vi = kVariants[v];
     const bool blockwise = scale_mode_is_block(d->x_mode);

@@ -148,6 +148,33 @@ def test_blocknorm_on_row_tiles(orc, shape, recipe):
     assert bool(((out[idx].double() - o).abs() <= o.abs() * 2.0 ** -8 + 1e-5).all())
 
 
+@pytest.mark.parametrize("shape", [(222, 768, 256), (300, 1920, 1024)])
+@pytest.mark.parametrize("recipe", ["row", "block"])
+def test_blocknorm_runs_the_kernel_that_was_profiled(shape, recipe):
+    # few rows: without a profile a row tile; after loka_dispatch the kernel that it timed and probed (K is one that the
+    # streaming kernel does not take: the large-tile kernel), with that kernel's bits
+    M, K, N = shape
+    x, w = synth.student_t4(M, K, seed=M).to(DEV), synth.weight(K, N, seed=N).to(DEV)
+    xm, wm = RECIPES[recipe]
+    xq, sx = B.loka_quantize(x, xm)
+    wq, sw = B.loka_quantize(w, wm, transpose_out=True)
+
+    def call(variant):
+        desc = B.make_desc(M, N, K, 1, xm, wm, B.NORM_BLOCKNORM, 1e-5, variant, block_n=256)
+        return (*B.loka_fp8_gemm_norm(desc, xq, sx, wq, sw, want_y=True), B.loka_default_variant(desc))
+
+    B.loka_dispatch_clear()
+    try:
+        st, _, table = B.loka_dispatch(B.make_desc(M, N, K, 1, xm, wm, B.NORM_BLOCKNORM, 1e-5, block_n=256), x, w, 0.5)
+        assert st == B.LOKA_OK
+        out, y, v = call(-1)
+        assert v in [r["variant"] for r in table if r["x_mode"] == xm]
+        named, named_y, _ = call(v)
+        assert torch.equal(out, named) and torch.equal(y, named_y)
+    finally:
+        B.loka_dispatch_clear()
+
+
 @pytest.mark.parametrize("variant,shape", [("panel32x256", (1100, 272, 784)), ("panel64x256", (2100, 144, 784)), ("panel128x128", (1300, 256, 640)),
                                            ("panel32_256x256_ragged", (900, 400, 784)), ("splitk128x128s2", (257, 16400, 528))])
 def test_new_forms_replay_from_a_graph(variant, shape):
