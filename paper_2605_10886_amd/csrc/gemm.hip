@@ -1576,7 +1576,10 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         size_t stats = static_cast<size_t>(d->batch) * d->M * p.tiles_n * 2 * sizeof(float);
         stats = (stats + 255) & ~size_t(255);
         p.part = static_cast<float*>(workspace);
-        if (!y) p.y = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + stats);
+        if (!y) {                                       // staged: [batch][M, N] without gaps, whatever the outputs' stride
+            p.y = reinterpret_cast<float*>(static_cast<uint8_t*>(workspace) + stats);
+            p.strideO = d->M * d->N;
+        }
     }
     int dev = 0, cus = 0;
     if (device_cus(&dev, &cus) != LOKA_OK) return LOKA_ERR_HIP;
@@ -1646,11 +1649,11 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
     }
     vi.launch(p, blockwise, grid, s);
     if (two_pass) {
-        // with a strided batch the rows of all problems are contiguous only when strideO == M*N
+        // with a strided batch the rows of all problems are contiguous only when strideO == M*N (the staged Y always is)
         for (int g = 0; g < p.batch; ++g) {
             const float* yg = p.y + static_cast<int64_t>(g) * p.strideO;
             const float* pg = p.part + static_cast<int64_t>(g) * d->M * p.tiles_n * 2;
-            uint16_t* og = p.out + static_cast<int64_t>(g) * p.strideO;
+            uint16_t* og = p.out + static_cast<int64_t>(g) * d->strideO;
             norm_rows_kernel<<<dim3(static_cast<unsigned>((d->M + 3) / 4)), 256, 0, s>>>(
                 yg, pg, d->M, p.N, p.tiles_n, vi.bn, d->norm, d->eps, p.gamma, p.beta, og);
         }

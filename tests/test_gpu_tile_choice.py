@@ -239,3 +239,31 @@ def test_dispatch_of_wide_blocknorm_layers(shape):
         assert ch["variant"] in [r["variant"] for r in table if r["x_mode"] == ch["x_mode"]]
     finally:
         B.loka_dispatch_clear()
+
+
+@pytest.mark.parametrize("variant", ["twopass128x128", "splitk128x128", "panel128x128", "panel64x256", "panel32_256x256"])
+@pytest.mark.parametrize("norm", ["layernorm", "none"])
+def test_strided_outputs_stay_inside_the_workspace(variant, norm):
+    # problems further apart than M * N in O: the bits of the contiguous call, nothing written between the problems, and
+    # nothing behind the workspace (the guard is long enough for an fp32 staging area with the outputs' stride)
+    M, K, N, batch = 130, 1024, 384, 3
+    stride = 2 * M * N + 128
+    L, v = B.lib(), B.variant_id(variant)
+    x, w = synth.normal(batch * M, K, seed=1).to(DEV), synth.weight(K, N, seed=2).to(DEV)
+    xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+    wq, sw = B.loka_quantize(w, B.SCALE_COL, transpose_out=True)
+    desc = B.make_desc(M, N, K, batch, B.SCALE_ROW, B.SCALE_COL, B.NORMS[norm], 1e-5, v)
+    desc.strideW = 0
+    want, _ = B.loka_fp8_gemm_norm(desc, xq, sx, wq, sw)
+    desc.strideO = stride
+    need = int(L.loka_fp8_gemm_norm_workspace(ctypes.byref(desc)))
+    guard = batch * stride * 4
+    ws = torch.full((need + guard,), 0xA5, dtype=torch.uint8, device=DEV)
+    out = torch.full((batch * stride,), 7.0, dtype=torch.bfloat16, device=DEV)
+    sp = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    assert L.loka_fp8_gemm_norm(ctypes.byref(desc), xq.data_ptr(), sx.data_ptr(), wq.data_ptr(), sw.data_ptr(), None, None,
+                                out.data_ptr(), None, ws.data_ptr(), need, sp) == B.LOKA_OK
+    torch.cuda.synchronize()
+    got = out.view(batch, stride)
+    assert torch.equal(got[:, :M * N].reshape(batch * M, N), want)
+    assert bool((got[:, M * N:] == 7.0).all()) and bool((ws[need:] == 0xA5).all())
