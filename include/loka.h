@@ -193,8 +193,12 @@ loka_status loka_fp8_gemm_norm(const loka_gemm_desc* desc, const uint8_t* xq, co
                                float* y_fp32, void* workspace, size_t ws_bytes, void* hip_stream);
 
 /* Variants whose row statistics cross workgroups inside one launch (rows wider than a tile) make every
- * workgroup wait for the other tiles of its row panel.  The wait is bounded: if it runs out (it never does when
- * the launch's workgroups are all resident, which the launch arranges on an otherwise idle device), the workgroup
+ * workgroup wait for the other tiles of its row panel.  Besides wide rows the library's choice (desc->variant < 0) runs
+ * layers of 128 < N <= 1024 that way where tiles that span the row would be slower; given no workspace, such a layer
+ * takes a kernel without the wait (see above).  The wait is bounded.  It never runs out when
+ * the launch's workgroups are all resident, which the launch arranges on an otherwise idle device, nor, with at most 8
+ * tiles per row, while up to four such launches share the device with kernels that hold a CU for less than the limit
+ * (about 0.2 s).  If it does run out, the workgroup
  * marks the launch in the workspace, writes the rows of its tile as NaN (FP8 output: a NaN row scale) so that
  * nothing downstream can take them for results, and goes on: the kernel always ends.  This call reports
  * the mark of the LAST loka_fp8_gemm_norm or loka_fp8_gemm_norm_fp8out call that used `workspace` with `desc`:

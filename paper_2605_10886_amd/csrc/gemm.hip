@@ -82,18 +82,20 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
     const int l16 = lane & 15, q = lane >> 4;
 
-    // Every schedule hands each XCD one contiguous range of logical ids.  One-tile-per-workgroup schedules take the id's
-    // tile: problem by problem, in bands of 8 tile rows, and for split K range by range, so that an XCD's L2 serves the
-    // operand strips its workgroups share.  (In launch order the tiles of one strip land on all 8 XCDs and every XCD
+    // One-tile-per-workgroup schedules hand each XCD one contiguous range of logical ids and take the id's tile: problem by
+    // problem, in bands of 8 tile rows, and for split K range by range, so that an XCD's L2 serves the operand strips its
+    // workgroups share.  (In launch order the tiles of one strip land on all 8 XCDs and every XCD
     // reads the whole of X: the traffic between the L2s and memory, not the matrix cores, was the bound.  Measured:
     // split K at 2048 x 123200 x 1024 402 -> 364 us, as a weight gradient at 65536 x 256 x 1024 42.3 -> 36.7 us, the BF16
     // reference at 16384 x 1024 x 1024 59.0 -> 51.6 us.)
     // The panel-synchronous schedule is persistent: gridDim.x (a multiple of tiles_n, all co-resident) workgroups walk
     // the tile list (n fastest) in rounds of gridDim.x tiles, so the tiles_n workgroups that share a row panel always
-    // run in the same round.
+    // run in the same round; its numberings keep a panel's workgroups together where rows are short (panels_may_spread,
+    // panel_per_xcd), else it takes launch order.
     const int total_tiles = p.tiles_m * p.tiles_n * p.batch;
-    const int id = EPI == EPI_PANEL_SYNC && (BM < 256 || !panels_may_spread(gridDim.x, p.tiles_n)) ? static_cast<int>(blockIdx.x)
-                                                                                                   : xcd_contiguous(blockIdx.x, gridDim.x);
+    int id = blockIdx.x;
+    if (EPI != EPI_PANEL_SYNC || (BM == 256 && panels_may_spread(gridDim.x, p.tiles_n))) id = xcd_contiguous(id, gridDim.x);
+    else if (BM < 256 && p.tiles_n <= 8) id = panel_per_xcd(id, gridDim.x, p.tiles_n);
     int tile_first = EPI == EPI_SPLITK ? id % total_tiles : id, tile_stride = total_tiles;
     if (EPI == EPI_PANEL_SYNC) {
         tile_stride = gridDim.x;
@@ -1603,7 +1605,8 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
     if (prepare_fn(dev, kfn, splitk256 ? 512 : vi.threads, splitk256 ? panel32_lds() : vi.lds, &per_cu) != LOKA_OK) return LOKA_ERR_HIP;
     dim3 grid(static_cast<unsigned>(static_cast<int64_t>(p.tiles_m) * p.tiles_n * p.batch));
     if (vi.epi == EPI_PANEL_SYNC) {
-        // persistent grid: a multiple of tiles_n workgroups, all resident at once (one per CU)
+        // persistent grid: a multiple of tiles_n workgroups, all resident at once on a device of their own (as many per CU
+        // as its registers and LDS hold, two at most: the 32 x 256 and 64 x 256 tiles; one in every other form)
         const int64_t slots = static_cast<int64_t>(cus) * (per_cu > 2 ? 2 : per_cu);
         int64_t g = (slots / p.tiles_n) * p.tiles_n;
         if (g <= 0) return LOKA_ERR_UNSUPPORTED;

@@ -68,6 +68,22 @@ __host__ __device__ constexpr bool panels_may_spread(int G, int tiles_n) {
     return tiles_n <= 8 || (tiles_n <= 16 && G % 8 == 0 && (G / 8) % tiles_n == 0);
 }
 
+// The numbering of the panel schedule's tiles below 256 x 256 (up to two workgroups per CU; rows of up to 8 tiles): a panel's
+// workgroups one behind the other on one XCD, the panels dealt to the XCDs in turn; fewer than 8 panels may be left, whose
+// workgroups follow in equal shares.  Of one launch an XCD then holds at most 7 workgroups that wait for others still to be
+// started: of a panel that it has begun, or, after the last whole panel, its share of those left (7 panels / 8).  So four
+// launches side by side (28 of at least 32 slots) always start in full; in launch order, where a panel lies on tiles_n
+// XCDs, two launches that two XCDs begin in different order can fill both with workgroups that wait for each other.
+// (A share of consecutive panels per XCD puts a last round that is partly full on a few XCDs: 3000 x 2048 x 512 on 32 x 256
+// tiles 22.0 -> 26.6 us.  Dealt in turn, geometric mean over 81 shapes against launch order: 32 x 256 0.995, 64 x 256 1.013,
+// 128 x 128 0.980.)
+__host__ __device__ constexpr int panel_per_xcd(int b, int G, int tiles_n) {
+    const int whole = G / (8 * tiles_n) * (8 * tiles_n);
+    if (b >= whole) return whole + xcd_contiguous(b - whole, G - whole);
+    const int i = b >> 3;
+    return ((i / tiles_n) * 8 + (b & 7)) * tiles_n + i % tiles_n;
+}
+
 // Loads of block scales that a wave of the 32 x 32 x 64 kernel requests at the start of K step k, for step k + 1: W's scale and
 // X's four, or (quad: a lane holds four K blocks' scales of X) W's alone in three steps of four.  What may stay in flight
 // where the step needs X(k + 1) and W(k + 1) is these and the 4 loads of X(k + 2), the only ones requested behind W(k + 1).

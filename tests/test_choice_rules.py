@@ -32,8 +32,8 @@ def test_wait_check_takes_the_workspace_of_either_call(M, N, K):
 
 @pytest.fixture(scope="module")
 def numbering(tmp_path_factory):
-    """(G, tiles_n) -> the order in which a panel launch takes its workgroups: logical id of every block, from the header
-    that the kernels compile.  None: launch order."""
+    """(form, G, tiles_n) -> the order in which a panel launch takes its workgroups: logical id of every block, from the header
+    that the kernels compile.  None: launch order.  Form 0: 256 x 256 tiles; form 1: smaller ones, up to two workgroups per CU."""
     d = tmp_path_factory.mktemp("numbering")
     src = d / "numbering.hip"
     src.write_text("""#include "gemm_common.h"
@@ -41,8 +41,14 @@ def numbering(tmp_path_factory):
 int main() {
     for (int tn = 1; tn <= 256; ++tn)
         for (int G = tn; G <= 256; G += tn) {
-            std::printf("%d %d", G, tn);
+            std::printf("0 %d %d", G, tn);
             if (loka::panels_may_spread(G, tn)) for (int b = 0; b < G; ++b) std::printf(" %d", loka::xcd_contiguous(b, G));
+            std::printf("\\n");
+        }
+    for (int tn = 1; tn <= 8; ++tn)
+        for (int G = tn; G <= 512; G += tn) {
+            std::printf("1 %d %d", G, tn);
+            for (int b = 0; b < G; ++b) std::printf(" %d", loka::panel_per_xcd(b, G, tn));
             std::printf("\\n");
         }
 }
@@ -51,12 +57,13 @@ int main() {
     subprocess.run([build._hipcc(), "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(build.HERE, "csrc"), str(src), "-o", exe],
                    check=True, capture_output=True)
     rows = [[int(v) for v in line.split()] for line in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.splitlines()]
-    return {(r[0], r[1]): r[2:] or None for r in rows}
+    return {tuple(r[:3]): r[3:] or None for r in rows}
 
 
 def test_panels_are_spread_only_where_their_waits_cannot_fill_an_xcd(numbering):
-    assert len(numbering) == sum(256 // tn for tn in range(1, 257))
-    for (G, tn), ids in numbering.items():
+    large = {k[1:]: v for k, v in numbering.items() if k[0] == 0}
+    assert len(large) == sum(256 // tn for tn in range(1, 257))
+    for (G, tn), ids in large.items():
         if ids is None:
             assert tn > 8
             continue
@@ -65,26 +72,43 @@ def test_panels_are_spread_only_where_their_waits_cannot_fill_an_xcd(numbering):
         if tn > 8:                                                # no panel on two XCDs
             homes = [{b % 8 for b in range(G) if ids[b] // tn == panel} for panel in range(G // tn)]
             assert all(len(h) == 1 for h in homes), (G, tn)
-    assert numbering[256, 16] and numbering[255, 5]
-    assert not any(numbering[g] for g in ((240, 20), (240, 24), (240, 40), (256, 64), (256, 32), (64, 16)))
+    assert large[256, 16] and large[255, 5]
+    assert not any(large[g] for g in ((240, 20), (240, 24), (240, 40), (256, 64), (256, 32), (64, 16)))
 
 
-@pytest.mark.parametrize("G,tn,launches", [(255, 5, 4), (256, 8, 4), (248, 8, 4), (256, 16, 2), (128, 16, 2), (252, 7, 4)])
-def test_launches_side_by_side_finish(numbering, G, tn, launches):
-    # 8 XCDs of 32 slots; each starts its share of every launch in order, the launches interleaved at random; a panel's
+def test_small_tiles_keep_a_panel_on_one_xcd(numbering):
+    # every id once; all panels but the last few (less than one per XCD) on one XCD, their workgroups one behind the other;
+    # of the rest an XCD has 7 at most, as many as it can have begun of a panel of 8
+    for (form, G, tn), ids in numbering.items():
+        if form == 0:
+            continue
+        assert sorted(ids) == list(range(G))
+        whole = G // (8 * tn) * 8
+        for x in range(8):
+            mine = [ids[b] for b in range(x, G, 8)]
+            panels = [i // tn for i in mine]
+            assert mine[:whole // 8 * tn] == [p * tn + t for p in range(x, whole, 8) for t in range(tn)], (G, tn, x)
+            assert all(p >= whole for p in panels[whole // 8 * tn:]) and len(mine) - whole // 8 * tn <= 7, (G, tn, x)
+
+
+@pytest.mark.parametrize("form,G,tn,launches,slots", [
+    (0, 255, 5, 4, 32), (0, 256, 8, 4, 32), (0, 248, 8, 4, 32), (0, 256, 16, 2, 32), (0, 128, 16, 2, 32), (0, 252, 7, 4, 32),
+    (1, 512, 4, 4, 64), (1, 510, 3, 4, 64), (1, 512, 8, 4, 64), (1, 511, 7, 4, 64), (1, 256, 8, 4, 32), (1, 252, 6, 4, 32)])
+def test_launches_side_by_side_finish(numbering, form, G, tn, launches, slots):
+    # 8 XCDs of 32 CUs; each starts its share of every launch in order, the launches interleaved at random; a panel's
     # workgroups leave once all of them are there.  Nobody may be left waiting.
-    ids = numbering[G, tn]
+    ids = numbering[form, G, tn]
     for seed in range(20):
         rng = random.Random(seed)
         todo = [[[ids[b] // tn for b in range(x, G, 8)] for x in range(8)] for _ in range(launches)]
         held, arrived = [[] for _ in range(8)], {}
         left = launches * G
         while left:
-            moves = [(n, x) for x in range(8) if len(held[x]) < 32 for n in range(launches) if todo[n][x]]
+            moves = [(n, x) for x in range(8) if len(held[x]) < slots for n in range(launches) if todo[n][x]]
             assert moves, (G, tn, seed, "no slot is free and nobody can finish")
             n, x = rng.choice(moves)
-            for _ in range(rng.randrange(1, 33)):                 # a run of one launch's workgroups on one XCD
-                if not todo[n][x] or len(held[x]) >= 32:
+            for _ in range(rng.randrange(1, slots + 1)):          # a run of one launch's workgroups on one XCD
+                if not todo[n][x] or len(held[x]) >= slots:
                     break
                 key = (n, todo[n][x].pop(0))
                 held[x].append(key)
