@@ -62,10 +62,10 @@ struct DevBuf {
 // last few shapes it asked for, because a call asks two or three times (workspace size, launch) and the model looks at
 // every variant (about 2 us; a small layer is a launch of 5).
 static int static_choice(const loka_gemm_desc* d) {
-    using Key = std::tuple<int64_t, int64_t, int64_t, int64_t, int, int, int>;
+    using Key = std::tuple<int64_t, int64_t, int64_t, int64_t, int, int, int, bool>;
     struct Slot { Key key; int variant; };
     static thread_local Slot slots[16];
-    const Key key(d->M, d->N, d->K, d->batch, d->norm, d->x_mode, d->w_mode);
+    const Key key(d->M, d->N, d->K, d->batch, d->norm, d->x_mode, d->w_mode, d->strideW != 0);
     const uint64_t h = (static_cast<uint64_t>(d->M) * 0x9E3779B97F4A7C15ull) ^ (static_cast<uint64_t>(d->N) * 0xC2B2AE3D27D4EB4Full) ^
                        (static_cast<uint64_t>(d->K) * 0x165667B19E3779F9ull) ^ (static_cast<uint64_t>(d->norm * 8 + d->x_mode) << 58);
     Slot& s = slots[h >> 60];

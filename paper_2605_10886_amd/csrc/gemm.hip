@@ -1160,79 +1160,128 @@ bool variant_is_streaming(int v) { return kVariants[v].name == kWregName; }
 static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Name || vi.name == kPanel32RaggedName; }
 
 // ---- expected time of a variant, in microseconds: what the static choice compares.
-// A launch is `start` plus, per round of workgroups (tiles over the slots of 256 CUs), `round` plus K steps of
-// `step` + `step_full` * (share of the slots in use: the last level caches and the power budget are shared), plus the
-// output at `mout` per million elements; kernels that exchange or re-read for a row norm add `norm` (per round; two-pass:
-// once per problem) and `norm_mout`.  Fitted (non-negative least squares on relative error) to every variant's time at 570
-// shapes, M 64 - 131072, N 64 - 4096, K 64 - 8192; the choice is within 1.4 % of the fastest variant in the geometric mean
-// over them (worst 1.48), where choosing by tile width and row count alone was at 30 % (2048 x 768 x 256: 64-row tiles
-// 17.5 us, 16-row tiles 8.6; 4096 x 1024 x 8192: 143 us, split K 52; 2048 x 3008 x 256: two-pass 27.6, panel 17.2).
+// A launch is `start` plus, per round of workgroups (tiles over the slots of 256 CUs), `round` plus K steps of `step` +
+// `full` * (share of the slots in use: the last level caches and the power budget are shared), `lng` more from the 17th
+// step on and `ragged` more where K is no multiple of a step, plus `ln` for the row statistics (RMSNorm: 0.4 of it); plus X, W and the output at `x`, `w` and `out` per million elements, `out32` more where rows of the output are no
+// whole number of 64-byte lines (the panel kernels' streaming stores).  Kernels that exchange or re-read for a row norm
+// add `norm` (per round; two-pass: per problem), two-pass also `once` and `norm_out` per million outputs.  Fitted
+// (non-negative least squares on relative error) to every variant's time at 5518 shapes, M 64 - 131072, N 64 - 16384, K 64 -
+// 131072; fitted to one half of them, the choice is within 0.8 % of the fastest variant in the geometric mean over the other
+// (worst 1.67).  profiles/variant_times.csv has the times of 2006 of them.  (A fit without `lng`, `ragged`, `x`, `w`, `ln`
+// and `out32` was at 2.1 %, worst 2.9: 101163 x 240 x 512 54 us on the 256 x 256 kernel, strip 30.  By tile width and row
+// count alone 25 %: 2048 x 768 x 256 17.5 us on 64-row tiles, 8.6 on 16-row tiles; 4096 x 1024 x 8192 143 us, split K 52.)
 // Fixed figures for an MI355X, not the running device's: workspace sizes follow from the choice.
-struct CostRow { float start, round, step, step_full, mout, norm, norm_mout; };
+struct CostRow { float start, round, step, full, lng, ragged, x, w, out, ln, norm, out32, once, norm_out; };
 struct VariantCost { const char* name; int per_cu; CostRow plain, block; };
 constexpr int kPlanCus = 256;
 static const VariantCost kCosts[] = {
-    {"row32x128", 3, {3.62f, 0.f, .31f, .21f, .75f}, {3.37f, 0.f, .46f, .47f, .77f}},
-    {"row64x128", 3, {3.3f, .87f, .33f, .48f, .47f}, {3.75f, 0.f, .64f, .45f, .62f}},
-    {"row64x256", 2, {2.4f, 3.31f, .51f, .59f, .31f}, {.64f, 4.74f, 1.11f, .57f, .38f}},
-    {"row128x256", 1, {1.68f, 4.62f, .89f, .13f, .29f}, {0.f, 5.95f, 1.42f, .51f, .25f}},
-    {"row64x512", 1, {2.14f, 4.06f, .88f, .14f, .5f}, {1.78f, 4.73f, 1.52f, .33f, .12f}},
-    {"row64x1024", 1, {1.39f, 7.66f, 1.26f, .21f, .05f}, {2.17f, 7.04f, 2.23f, .08f, 0.f}},
-    {"row16x256", 2, {2.05f, 1.74f, .41f, .19f, .63f}, {.56f, 2.86f, .58f, .21f, .09f}},
-    {"row32x256", 2, {2.04f, 2.31f, .41f, .25f, .44f}, {2.82f, 1.13f, .76f, .22f, .63f}},
-    {"row16x512", 1, {1.68f, 2.31f, .62f, .12f, .64f}, {.7f, 3.11f, .82f, .2f, 0.f}},
-    {"row32x512", 1, {1.86f, 2.84f, .68f, .13f, .58f}, {.68f, 3.93f, 1.03f, .22f, 0.f}},
-    {"row16x1024", 1, {1.41f, 3.8f, .86f, .16f, 0.f}, {.75f, 4.3f, 1.22f, .05f, 0.f}},
-    // (W stays on the CU: a round is 32 rows per workgroup, `step` per 64 K of weights, `step_full` per million of X)
-    {kWregName, 1, {6.44f, .27f, .55f, .11f, .16f}, {}},
-    {kStripName, 1, {6.84f, 0.f, 1.21f, 0.f, 0.f}, {}},
-    {"twopass128x128", 2, {3.81f, 0.f, .47f, .42f, .44f, 6.41f, 1.7f}, {2.88f, 0.f, 1.07f, .31f, .51f, 6.02f, 1.68f}},
-    {"panel32x256", 2, {3.35f, 1.32f, .41f, .39f, .2f, 4.47f}, {3.57f, .08f, .79f, .23f, .51f, 4.26f}},
-    {"panel64x256", 2, {3.89f, 1.84f, .55f, .44f, .26f, 5.68f}, {4.19f, .19f, 1.16f, .31f, .41f, 5.05f}},
-    {"panel128x128", 1, {3.34f, 1.8f, .5f, .14f, .22f, 5.69f}, {3.55f, 1.26f, .66f, .11f, .34f, 5.53f}},
-    {kPanel32Name, 1, {2.55f, 6.65f, .98f, .25f, .11f, 4.3f}, {3.66f, 4.5f, 1.5f, .27f, .12f, 4.5f}},
-    {kPanel32RaggedName, 1, {.63f, 8.17f, 1.05f, .22f, .2f, 5.14f}, {}},
-    // split K: `mout` per million partial sums, `norm_mout` per million outputs
-    {"splitk128x128", 1, {10.5f, 0.f, 0.f, .59f, 1.79f}, {11.5f, 0.f, 0.f, .77f, 1.44f}},
-    {"splitk128x128s2", 2, {10.7f, 0.f, 0.f, .79f, 1.78f}, {12.f, 0.f, .12f, 1.13f, 1.37f, 0.f, .66f}},
+    {"row32x128", 3, {2.85f, .469f, .211f, 0.f, .147f, .0222f, .146f, 0.f, .46f, 1.39f},
+     {3.04f, 0.f, .374f, .0472f, .212f, 0.f, .145f, 0.f, .492f, 1.44f}},
+    {"row64x128", 3, {2.26f, 1.64f, .237f, .1f, .177f, .0139f, .105f, 0.f, .32f, 1.4f},
+     {3.38f, .0158f, .375f, .42f, .239f, 0.f, .0513f, 9.51f, .422f, 1.39f}},
+    {"row64x256", 2, {2.37f, 3.22f, .421f, 0.f, .185f, .0318f, .142f, .0464f, .291f, 3.24f},
+     {3.f, 1.89f, .876f, .38f, .318f, 0.f, .0187f, 4.07f, .367f, 3.19f}},
+    {"row128x256", 1, {1.79f, 4.01f, .824f, 0.f, .0365f, .0326f, .0389f, .038f, .292f, 3.16f},
+     {2.54f, 2.41f, 1.21f, .333f, .316f, 0.f, 0.f, 3.05f, .273f, 3.1f}},
+    {"row64x512", 1, {1.92f, 3.19f, .728f, 0.f, .155f, .0492f, .111f, .154f, .382f, 4.35f},
+     {2.01f, 2.5f, 1.32f, .146f, .324f, 0.f, .0463f, 3.66f, .337f, 4.35f}},
+    {"row64x1024", 1, {2.06f, 4.57f, 1.34f, 0.f, 0.f, .0204f, .265f, 0.f, .118f, 4.91f},
+     {2.75f, 3.17f, 2.14f, 0.f, .526f, 0.f, .54f, 0.f, 0.f, 5.19f}},
+    {"row16x256", 2, {1.92f, 1.95f, .324f, 0.f, .127f, .0315f, .298f, .009f, .467f, .881f},
+     {1.91f, 1.61f, .382f, 0.f, .217f, 0.f, .31f, 3.5f, .369f, .972f}},
+    {"row32x256", 2, {2.05f, 2.4f, .327f, 0.f, .151f, .0291f, .197f, .0185f, .339f, 1.67f},
+     {2.03f, 1.94f, .559f, .0785f, .243f, 0.f, .103f, 3.17f, .377f, 1.66f}},
+    {"row16x512", 1, {1.8f, 2.f, .51f, 0.f, .182f, .0317f, .415f, .0663f, .485f, 1.22f},
+     {1.71f, 1.89f, .643f, 0.f, .271f, 0.f, .445f, 2.23f, .291f, 1.19f}},
+    {"row32x512", 1, {1.8f, 2.45f, .547f, 0.f, .206f, .0389f, .253f, .132f, .387f, 2.2f},
+     {1.73f, 2.12f, .842f, 0.f, .293f, 0.f, .257f, 2.88f, .275f, 2.16f}},
+    {"row16x1024", 1, {2.09f, 2.62f, .775f, 0.f, .206f, .0349f, 1.05f, 0.f, 0.f, 1.38f},
+     {2.42f, 2.12f, .934f, 0.f, .486f, 0.f, 1.43f, 0.f, 0.f, 1.42f}},
+    {"twopass128x128", 2, {3.82f, .338f, .362f, .369f, .245f, .0426f, .0474f, .152f, .403f, 1.86f, 2.67f, 0.f, 2.19f, 1.77f},
+     {3.55f, 0.f, .892f, .396f, .322f, 0.f, .0488f, .181f, .358f, 1.09f, 5.39f, 0.f, 0.f, 1.68f}},
+    {"panel32x256", 2, {3.43f, 1.32f, .303f, .365f, .211f, .0849f, .0251f, .348f, .295f, 3.54f, 1.64f, .104f},
+     {3.37f, .748f, .646f, .238f, .238f, 0.f, .00889f, .241f, .36f, 3.17f, 1.85f}},
+    {"panel64x256", 2, {4.28f, 1.47f, .433f, .392f, .224f, .0808f, .0272f, .239f, .325f, 4.94f, 1.83f, .249f},
+     {4.2f, .41f, .997f, .303f, .286f, 0.f, .013f, .167f, .366f, 4.59f, 2.06f}},
+    {"panel128x128", 1, {3.56f, 1.47f, .499f, .105f, 0.f, .0132f, .0146f, .059f, .265f, 4.49f, 2.25f, .0312f},
+     {3.49f, 1.26f, .662f, .087f, 0.f, 0.f, 0.f, .11f, .253f, 4.07f, 2.65f}},
+    {kPanel32Name, 1, {3.52f, 4.92f, 1.02f, .315f, 0.f, 0.f, 0.f, 0.f, .181f, 1.23f, 3.69f, .398f},
+     {4.43f, 3.2f, 1.53f, .255f, 0.f, 0.f, 0.f, .0737f, .238f, 1.24f, 3.86f}},
+    {kPanel32RaggedName, 1, {3.86f, 4.85f, 1.06f, .281f, 0.f, 0.f, 0.f, .0134f, .207f, 1.37f, 3.74f, .514f},
+     {}},
 };
-static const VariantCost kCostSplitk256 = {"", 1, {15.8f, 0.f, .2f, 1.08f, 1.06f, 0.f, .27f}, {14.8f, 0.f, .66f, 1.38f, .85f, 0.f, .63f}};
+// BlockNorm's choice between the large tile and the row tiles of its width (blocknorm_form), where rows are wider than a tile:
+// an earlier fit, of the first four terms and the output (taken from the table above, the choice was 4 % slower in the
+// geometric mean over 80 layers, 107 x 2048 x 256 in 4 problems 5.3 -> 12.0 us).
+static const VariantCost kBlocknormCosts[] = {
+    {"row16x256", 2, {2.05f, 1.74f, .41f, .19f, 0.f, 0.f, 0.f, 0.f, .63f}, {.56f, 2.86f, .58f, .21f, 0.f, 0.f, 0.f, 0.f, .09f}},
+    {"row32x256", 2, {2.04f, 2.31f, .41f, .25f, 0.f, 0.f, 0.f, 0.f, .44f}, {2.82f, 1.13f, .76f, .22f, 0.f, 0.f, 0.f, 0.f, .63f}},
+    {"row64x256", 2, {2.4f, 3.31f, .51f, .59f, 0.f, 0.f, 0.f, 0.f, .31f}, {.64f, 4.74f, 1.11f, .57f, 0.f, 0.f, 0.f, 0.f, .38f}},
+    {kPanel32Name, 1, {2.55f, 6.65f, .98f, .25f, 0.f, 0.f, 0.f, 0.f, .11f}, {3.66f, 4.5f, 1.5f, .27f, 0.f, 0.f, 0.f, 0.f, .12f}},
+};
+// split K: a launch is `start` plus, per round, K steps as above, plus `part` per million partial sums and `out` per
+// million outputs; rows of more than 2048 add `wide` and `wide_out`.  Tile 128 on the ring and on two stages, tile 256; plain
+// and block scales.
+struct SplitkCost { float start, step, full, part, out, wide, wide_out; };
+static const SplitkCost kSplitkCosts[3][2] = {
+    {{8.01f, .537f, 0.f, 2.39f, 0.f, 2.11f, 2.93f}, {8.6f, .698f, 0.f, 2.23f, 0.f, .668f, 4.27f}},
+    {{7.63f, .591f, .355f, 2.07f, .467f, 2.06f, 3.49f}, {6.78f, 1.3f, 0.f, 2.19f, 0.f, 1.5f, 2.89f}},
+    {{15.f, .655f, .822f, .757f, .569f, 3.99f, 3.7f}, {16.f, 1.07f, .952f, .613f, .544f, 1.56f, 5.71f}}};
+// ... and what decides between tiles of 128 and 256 on the long-range form.  An earlier fit, kept: a caller that names the
+// variant gets the same tiles (the two fits differ at 8 of 364 shapes).
+static const SplitkCost kSplitkTileCosts[2][2] = {{{10.7f, 0.f, .79f, 1.78f}, {12.f, .12f, 1.13f, 1.37f, .66f}},
+                                                  {{15.8f, .2f, 1.08f, 1.06f, .27f}, {14.8f, .66f, 1.38f, .85f, .63f}}};
 
-static const VariantCost* cost_entry(int v) {
-    static const auto table = [] {
-        std::array<const VariantCost*, kNumVariants> t{};
-        for (int i = 0; i < kNumVariants; ++i)
+static const VariantCost* cost_entry(int v, bool blocknorm) {
+    using Table = std::array<const VariantCost*, kNumVariants>;
+    static const auto tables = [] {
+        std::array<Table, 2> t{};
+        for (int i = 0; i < kNumVariants; ++i) {
             for (const VariantCost& c : kCosts)
-                if (std::strcmp(c.name, kVariants[i].name) == 0) t[i] = &c;
+                if (std::strcmp(c.name, kVariants[i].name) == 0) t[0][i] = &c;
+            for (const VariantCost& c : kBlocknormCosts)
+                if (std::strcmp(c.name, kVariants[i].name) == 0) t[1][i] = &c;
+        }
         return t;
     }();
-    return table[v];
+    return tables[blocknorm ? 1 : 0][v];
 }
 
 // Split K: tile size, number of K ranges and their length in 128-byte steps.  The forms with one workgroup per CU: as
 // many ranges as give 256 CUs one workgroup each and no more (their stages fill a CU's LDS: a 257th workgroup would be a
 // second round).  The two-stage form: about two workgroups per CU.  At least 4 steps per range, at most 64 ranges.
-struct SplitkPlan { int tile, ksplit, per; double cost; };
-static SplitkPlan splitk_ranges(const loka_gemm_desc* d, int tile, bool two_per_cu, const VariantCost& vc) {
+struct SplitkPlan { int tile, ksplit, per; };
+static SplitkPlan splitk_ranges(const loka_gemm_desc* d, int tile, bool two_per_cu) {
     const int64_t tiles = ((d->M + tile - 1) / tile) * ((d->N + tile - 1) / tile) * d->batch;
     const int64_t steps = (d->K + 127) / 128;
     int64_t want = two_per_cu ? (2 * kPlanCus + tiles - 1) / tiles : kPlanCus / tiles;
     if (want > 64) want = 64;
     if (want > steps / 4) want = steps / 4;
     if (want < 1) want = 1;
-    const int64_t len = (steps + want - 1) / want, ksplit = (steps + len - 1) / len;
-    const CostRow& c = scale_mode_is_block(d->x_mode) ? vc.block : vc.plain;
-    const double slots = kPlanCus * vc.per_cu, wgs = static_cast<double>(ksplit) * tiles;
+    const int64_t len = (steps + want - 1) / want;
+    return {tile, static_cast<int>((steps + len - 1) / len), static_cast<int>(len)};
+}
+static double splitk_cost(const loka_gemm_desc* d, const SplitkPlan& pl, bool two_per_cu, const SplitkCost* costs) {
+    const SplitkCost& c = costs[scale_mode_is_block(d->x_mode) ? 1 : 0];
+    const int64_t tiles = ((d->M + pl.tile - 1) / pl.tile) * ((d->N + pl.tile - 1) / pl.tile) * d->batch;
+    const double slots = kPlanCus * (two_per_cu ? 2 : 1), wgs = static_cast<double>(pl.ksplit) * tiles;
     const double rounds = std::ceil(wgs / slots), use = std::min(1.0, wgs / slots), out = 1e-6 * d->M * d->N * d->batch;
-    return {tile, static_cast<int>(ksplit), static_cast<int>(len),
-            c.start + rounds * len * (c.step + c.step_full * use) + ksplit * out * c.mout + out * c.norm_mout};
+    return c.start + rounds * pl.per * (c.step + c.full * use) + pl.ksplit * out * c.part + out * c.out +
+           (d->N > 2048 ? c.wide + out * c.wide_out : 0.0);
 }
 static bool splitk_is_ring(const VariantInfo& vi) { return vi.threads == 512; }
 static SplitkPlan splitk_plan(const loka_gemm_desc* d, int v) {
-    const SplitkPlan a = splitk_ranges(d, 128, !splitk_is_ring(kVariants[v]), *cost_entry(v));
-    if (splitk_is_ring(kVariants[v]) || 256 * d->K >= (int64_t(1) << 31)) return a;
-    const SplitkPlan b = splitk_ranges(d, 256, false, kCostSplitk256);
-    return b.ksplit >= 2 && (a.ksplit < 2 || b.cost < a.cost) ? b : a;
+    const bool ring = splitk_is_ring(kVariants[v]);
+    const SplitkPlan a = splitk_ranges(d, 128, !ring);
+    if (ring || 256 * d->K >= (int64_t(1) << 31)) return a;
+    const SplitkPlan b = splitk_ranges(d, 256, false);
+    if (b.ksplit < 2) return a;
+    return a.ksplit < 2 || splitk_cost(d, b, false, kSplitkTileCosts[1]) < splitk_cost(d, a, true, kSplitkTileCosts[0]) ? b : a;
+}
+static double splitk_time(const loka_gemm_desc* d, int v) {
+    const SplitkPlan pl = splitk_plan(d, v);
+    const bool two = !splitk_is_ring(kVariants[v]) && pl.tile == 128;
+    return splitk_cost(d, pl, two, kSplitkCosts[pl.tile == 256 ? 2 : two ? 1 : 0]);
 }
 
 bool variant_supports(const loka_gemm_desc* d, int v);
@@ -1247,32 +1296,51 @@ static int splitk_choice(const loka_gemm_desc* d) {
         if (splitk_is_ring(kVariants[v])) ring = v; else two = v;
     }
     if (ring < 0 || two < 0) return ring >= 0 ? ring : two;
-    const SplitkPlan r = splitk_plan(d, ring), t = splitk_plan(d, two);
-    return r.per <= 128 && !(t.tile == 256 && t.cost < r.cost) ? ring : two;
+    const bool large = splitk_plan(d, two).tile == 256;
+    return splitk_plan(d, ring).per <= 128 && !(large && splitk_time(d, two) < splitk_time(d, ring)) ? ring : two;
 }
 
-// Expected time of variant v; negative where the static choice does not consider it (no row of the table above).
+// The two kernels that keep W on the CU (fitted like the table, with terms of their own): strips of 32 rows, W in LDS by 128 or
+// 256 columns in one piece or (K * 128 or K * 256 above 128 KB) in slabs; blocks of 32 rows, W in registers, loaded once
+// per workgroup and problem.
+static double strip_time(const loka_gemm_desc* d, double ln) {
+    const double wide = d->N > 128 ? 1.0 : 0.0, w = d->K * (128 + 128 * wide) / 65536.0;
+    const double strips = static_cast<double>((d->M + 31) / 32) * d->batch / 2048, rounds = std::max(1.0, strips);
+    const double x = 1e-6 * d->M * d->K * d->batch, out = 1e-6 * d->M * d->N * d->batch;
+    if (w > 2.0) return rounds * (8.8 + 1.09 * ln) + w * (.496 + .0163 * d->batch) + .229 * x + .374 * out;
+    return 4.17 + 1.05 * wide + w * (1.42 + 2.35 * strips + .018 * d->batch) + .706 * rounds * ln + .1 * x + .275 * out;
+}
+static double wreg_time(const loka_gemm_desc* d, double ln) {
+    const double w = d->K * d->N / 65536.0, rounds = std::max(1.0, static_cast<double>((d->M + 31) / 32) * d->batch / kPlanCus);
+    const double x = 1e-6 * d->M * d->K * d->batch, out = 1e-6 * d->M * d->N * d->batch;
+    return 6.36 + w * (.361 + .0239 * d->batch) + rounds * (.0688 + .0314 * w + .722 * ln) + .199 * x + .277 * out;
+}
+
+// Expected time of variant v; negative where the static choice does not consider it (no figures above).
 static double variant_cost(const loka_gemm_desc* d, int v) {
     const VariantInfo& vi = kVariants[v];
-    const VariantCost* vc = cost_entry(v);
+    const bool row_norm = d->norm == LOKA_NORM_LAYERNORM || d->norm == LOKA_NORM_RMSNORM;
+    const double ln = d->norm == LOKA_NORM_LAYERNORM ? 1.0 : d->norm == LOKA_NORM_RMSNORM ? 0.4 : 0.0;
+    if (vi.epi == EPI_SPLITK) return splitk_time(d, v);
+    if (vi.name == kWregName) return wreg_time(d, ln);
+    if (vi.name == kStripName) return strip_time(d, ln);
+    const VariantCost* vc = cost_entry(v, d->norm == LOKA_NORM_BLOCKNORM);
     if (!vc) return -1.0;
-    if (vi.epi == EPI_SPLITK) return splitk_plan(d, v).cost;
     const CostRow& c = scale_mode_is_block(d->x_mode) ? vc->block : vc->plain;
-    const double out = 1e-6 * d->M * d->N * d->batch;
-    if (vi.name == kWregName || vi.name == kStripName) {
-        const double rounds = std::max(1.0, ((d->M + 31) / 32) * d->batch / static_cast<double>(kPlanCus * vc->per_cu));
-        return c.start + rounds * (c.round + c.step * d->K * d->N / 65536.0) + out * c.mout + c.step_full * 1e-6 * d->M * d->K * d->batch;
-    }
+    const double problems = static_cast<double>(d->batch), out = 1e-6 * d->M * d->N * problems;
+    const bool panel = vi.epi == EPI_PANEL_SYNC;
     const int64_t tiles_n = (d->N + vi.bn - 1) / vi.bn, tiles = ((d->M + vi.bm - 1) / vi.bm) * tiles_n * d->batch;
     int64_t slots = kPlanCus * vc->per_cu;
-    if (vi.epi == EPI_PANEL_SYNC) slots = slots / tiles_n * tiles_n;        // whole row panels at a time
+    if (panel) slots = slots / tiles_n * tiles_n;        // whole row panels at a time
     // (one-tile workgroups: past a few rounds they drift apart and the last round no longer stands out)
-    const bool whole = vi.epi == EPI_PANEL_SYNC || tiles < 4 * slots;
+    const bool whole = panel || tiles < 4 * slots;
     const double rounds = whole ? static_cast<double>((tiles + slots - 1) / slots) : static_cast<double>(tiles) / slots;
     const double steps = static_cast<double>((d->K + 127) / 128) * (vi.bn > 512 ? (d->N + 511) / 512 : 1);
-    double t = c.start + rounds * (c.round + steps * (c.step + c.step_full * std::min(1.0, static_cast<double>(tiles) / slots))) + out * c.mout;
-    if (d->norm != LOKA_NORM_NONE && d->norm != LOKA_NORM_BLOCKNORM)
-        t += out * c.norm_mout + c.norm * (vi.epi == EPI_PANEL_SYNC ? rounds * (tiles_n > 1 ? 1.0 : 0.3) : static_cast<double>(d->batch));
+    const double step = c.step + c.full * std::min(1.0, static_cast<double>(tiles) / slots) + (d->K % 128 ? c.ragged : 0.f);
+    double t = c.start + rounds * (c.round + steps * step + c.lng * std::max(0.0, steps - 16) + c.ln * ln) +
+               1e-6 * d->K * (d->M * problems * c.x + d->N * (d->strideW ? problems : 1.0) * c.w) +
+               out * (c.out + (panel && d->N % 32 ? c.out32 : 0.f));
+    if (row_norm) t += panel ? c.norm * rounds * (tiles_n > 1 ? 1.0 : 0.3) : c.norm * problems + c.once + out * c.norm_out;
     return t;
 }
 
