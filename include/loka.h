@@ -165,6 +165,8 @@ typedef struct {
     int32_t norm;             /* loka_norm */
     float eps;
     int32_t variant;          /* kernel variant id (see loka_variant_name), or -1 = library's choice for the shape.
+                               * An id names a kernel and its schedule; how the work is split inside (split K: tile and
+                               * number of K ranges, by shape) is the library's and shows in the workspace size.
                                * The choice behind -1 is looked up at every call and a loka_dispatch (or
                                * loka_dispatch_clear) in between can change it: a caller that sizes a workspace, launches
                                * and checks in separate calls while another thread may dispatch should resolve it once
@@ -185,7 +187,8 @@ int loka_variant_supports(const loka_gemm_desc* desc, int variant);
  * Workspace: loka_fp8_gemm_norm_workspace(desc) bytes (non-zero for variants whose row statistics
  * or partial sums cross workgroups).  With desc->variant < 0, layers with N <= 1024 or without a row norm also run with
  * less, or with none, on the best kernel whose scratch fits (not those with at most 128 output tiles of 128 x 128 and
- * K >= 2048, whose partial sums need the room).  Returns LOKA_ERR_UNSUPPORTED when desc->variant cannot run
+ * K >= 2048, whose partial sums need the room); another kernel adds in another order, so the bits can differ from those
+ * with the full workspace.  Returns LOKA_ERR_UNSUPPORTED when desc->variant cannot run
  * the shape.  */
 size_t loka_fp8_gemm_norm_workspace(const loka_gemm_desc* desc);
 loka_status loka_fp8_gemm_norm(const loka_gemm_desc* desc, const uint8_t* xq, const float* sx, const uint8_t* wq,
@@ -210,9 +213,11 @@ loka_status loka_fp8_gemm_norm_check(const loka_gemm_desc* desc, const void* wor
 /* For callers that cannot allocate device memory (code under HIP graph capture, serving loops that must not call the
  * allocator, harnesses that forbid it): loka_fp8_gemm_norm with its workspace taken from a device array the LIBRARY
  * owns (16 MiB per GPU the library runs on, held until the process ends) instead of from the caller.  Same arguments
- * otherwise, same kernels, same bits in out_bf16 / y_fp32.  The call allocates nothing and calls no allocating
+ * otherwise; same kernels and same bits in out_bf16 / y_fp32 where the variant is named or the usual choice fits the
+ * array (with desc->variant < 0 and a choice that needs more, another kernel runs: see below).  The call allocates nothing and calls no allocating
  * routine; the first call on a device asks the runtime for the array's address on that device (set-up).
- *   - With desc->variant < 0 the library chooses among the kernels whose scratch fits LOKA_STATIC_SCRATCH_BYTES.
+ *   - With desc->variant < 0 the library chooses among the kernels whose scratch fits LOKA_STATIC_SCRATCH_BYTES: for a layer
+ *     whose usual choice needs more, the sums are added in another order than loka_fp8_gemm_norm's.
  *     LOKA_ERR_WORKSPACE when none does, or when the variant named in `desc` needs more
  *     (loka_fp8_gemm_norm_workspace(desc) tells how much): use loka_fp8_gemm_norm with a caller-owned workspace for those.
  *   - Every call on a GPU uses that GPU's one array: calls that may overlap on one GPU (different streams, different
@@ -235,7 +240,8 @@ void loka_test_set_spin_limit(int64_t polls);
 /* FP8 output for the next layer (Section 3.2, "Block-wise Normalization", Case 1: once a row is normalized
  * inside the kernel, the activation and the quantization for the next layer can join the same epilogue, before
  * anything is written to HBM).  Same computation as loka_fp8_gemm_norm, but instead of bf16 O the call
- * writes what loka_quantize(O_bf16, LOKA_SCALE_ROW) would produce from it, bit for bit:
+ * writes what loka_quantize(O_bf16, LOKA_SCALE_ROW) would produce from it, bit for bit where both calls run the same
+ * variant (the choices behind desc->variant < 0 can differ):
  *   oq [batch][M, N] e4m3 codes,  so [batch][M] fp32 row scales (amax of the row's bf16 values / 448).
  * The next layer's loka_fp8_gemm_norm takes (oq, so) as its (xq, sx) with x_mode = LOKA_SCALE_ROW.
  * Built into three kernels, non-blockwise input scales:

@@ -113,8 +113,10 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
     const int wi = wave >> 2, wj = wave & 3;
     const int ldB = static_cast<int>(p.ld) * 2;
 
-    // an XCD's workgroups share row ranges; where the ranges are short and the grid is no multiple of 8, launch order is the faster
-    // one (2191 x 2072, 5 ranges of 448 rows: 43.5 us, renumbered 44.2; 32768 x 1024, 25 of 1344: 67.9, renumbered 65.5)
+    // Renumbered, an XCD's workgroups share row ranges.  Where the grid is no multiple of 8 that pays from about 1000 rows per
+    // range on (launch order -> renumbered, batch x features: 53098 x 1240, ranges of 3136, 126.4 -> 115.3 us; 32768 x 1024,
+    // 1728, 72.5 -> 70.5; nothing either way from 830 to 1250: 8192 x 1024, 832, 38.9 -> 39.2); short ranges are faster in
+    // launch order (1593 x 1168, 320, 26.3 -> 28.6; 18786 x 456, 576, 32.3 -> 34.3).
     const bool spread = gridDim.x % 8 == 0 || p.rows_per_split >= 1024;
     const int id = spread ? xcd_contiguous(blockIdx.x, gridDim.x) : static_cast<int>(blockIdx.x);
     const int split = id / p.pairs, pair = id - split * p.pairs;

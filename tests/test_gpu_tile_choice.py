@@ -38,18 +38,16 @@ def test_tile_edges_and_rounds(orc, variant, shape, recipe, norm):
     _run_case(orc, x, wt, recipe, norm, B.variant_id(variant), gamma, beta, rows=_rows(M), tag=f"{variant} {shape}")
 
 
-@pytest.mark.parametrize("shape,recipe", [((300, 24592, 2320), "row"), ((1000, 16384, 1920), "block"),
-                                          ((513, 32768, 1024), "block_pow2"), ((257, 65552, 272), "tensor")])
-def test_split_k_long_ranges(orc, shape, recipe):
-    # the long-range form of split K; the first three take 256 x 256 tiles (the workspace is theirs), ragged in M, N and K
+@pytest.mark.parametrize("shape,recipe,ksplit", [((300, 24592, 2320), "row", 12), ((1000, 16384, 1920), "block", 8),
+                                                 ((513, 32768, 1024), "block_pow2", 20), ((257, 65552, 272), "tensor", 57)])
+def test_split_k_long_ranges(orc, shape, recipe, ksplit):
+    # the long-range form of split K, ragged in M, N and K; the first three take 256 x 256 tiles: the workspace holds their
+    # number of K ranges (128 x 128 tiles would give 9, 5 and 13)
     M, K, N = shape
     x, wt = synth.student_t4(M, K, seed=M), synth.weight(K, N, seed=N)
     v = B.variant_id("splitk128x128s2")
     desc = B.make_desc(M, N, K, 1, *RECIPES[recipe], B.NORM_RMSNORM, 1e-5, v)
-    ws = B.lib().loka_fp8_gemm_norm_workspace(ctypes.byref(desc))
-    tiles256 = -(-M // 256) * -(-N // 256)
-    if N > 512:
-        assert ws // (4 * M * N) <= 256 // tiles256            # one workgroup per CU at most
+    assert B.lib().loka_fp8_gemm_norm_workspace(ctypes.byref(desc)) == 4 * M * N * ksplit
     _run_case(orc, x, wt, recipe, "rmsnorm", v, rows=_rows(M, 12), tag=f"split-K {shape}")
 
 
