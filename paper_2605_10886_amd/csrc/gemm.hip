@@ -1017,7 +1017,8 @@ static const char kPanel32Name[] = "panel32_256x256";
 static const char kPanel32RaggedName[] = "panel32_256x256_ragged";
 
 // gemm_panel32.hip
-const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro = false, bool want_y = true);
+const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro = false, bool want_y = true, bool quad = false);
+bool panel32_quad(int KB, int k_per_split);
 bool panel32_affine(const GemmParams& p);
 size_t panel32_lds();
 void panel32_launch(const GemmParams& p, int bw, dim3 grid, hipStream_t s);
@@ -1028,7 +1029,7 @@ static void launch_panel32(const GemmParams& p, bool blockwise, dim3 grid, hipSt
 }
 const void* panel32_ragged_fn();
 void panel32_ragged_launch(const GemmParams& p, dim3 grid, hipStream_t s);
-const void* panel32_part_fn(int bw, bool bf16);
+const void* panel32_part_fn(int bw, bool bf16, bool quad);
 void panel32_part_launch(const GemmParams& p, int bw, bool bf16, dim3 grid, hipStream_t s);
 static void launch_panel32_ragged(const GemmParams& p, bool, dim3 grid, hipStream_t s) { panel32_ragged_launch(p, grid, s); }
 
@@ -1669,8 +1670,8 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
     }
     const void* kfn = blockwise ? vi.fn_block : vi.fn_plain;
     const bool splitk256 = vi.epi == EPI_SPLITK && bm == 256;
-    if (splitk256) kfn = panel32_part_fn(panel32_bw(p, blockwise), false);
-    if (vi.name == kPanel32Name) kfn = panel32_fn(panel32_bw(p, blockwise), outq != nullptr, panel32_affine(p), p.qpro != 0, p.y != nullptr);
+    if (splitk256) kfn = panel32_part_fn(panel32_bw(p, blockwise), false, panel32_quad(p.KB, p.k_per_split));
+    if (vi.name == kPanel32Name) kfn = panel32_fn(panel32_bw(p, blockwise), outq != nullptr, panel32_affine(p), p.qpro != 0, p.y != nullptr, panel32_quad(p.KB, 0));
     if (!kfn) return LOKA_ERR_UNSUPPORTED;
     int per_cu = 0;
     if (prepare_fn(dev, kfn, splitk256 ? 512 : vi.threads, splitk256 ? panel32_lds() : vi.lds, &per_cu) != LOKA_OK) return LOKA_ERR_HIP;
@@ -1799,7 +1800,7 @@ loka_status bf16_gemm_launch(const loka_gemm_desc* d, const void* x, const void*
     int dev = 0, cus = 0;
     if (device_cus(&dev, &cus) != LOKA_OK) return LOKA_ERR_HIP;
     if (pl.tile == 256) {
-        if (prepare_fn(dev, panel32_part_fn(0, true), 512, panel32_lds(), nullptr) != LOKA_OK) return LOKA_ERR_HIP;
+        if (prepare_fn(dev, panel32_part_fn(0, true, false), 512, panel32_lds(), nullptr) != LOKA_OK) return LOKA_ERR_HIP;
         panel32_part_launch(p, 0, true, dim3(static_cast<unsigned>(tiles < cus ? tiles : cus)), s);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }

@@ -21,6 +21,8 @@
 // {0,1} or {2,3} per 16 lanes: key = bits (1, 2, 4) of r.  Both give 16 lanes x 16 bytes on 64 distinct banks.
 #include "gemm_common.h"
 
+#include <type_traits>
+
 namespace loka {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -141,7 +143,7 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
 // YOUT false: the caller wants no fp32 Y, and the code that would store it is left out (244 instead of 249 registers;
 // quantize + GEMM at 32768 x 4096 x 4096, beside a kernel that stored Y straight from registers: 1.1 and 0.5 % slower with the code in, 0.3 and
 // 0.4 % without it).
-template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0, bool YOUT = true>
+template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0, bool YOUT = true, bool QUAD = false>
 __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     constexpr bool FP8OUT = F8 != 0;
     constexpr bool SPLITK = EPI == EPI_SPLITK, PART = SPLITK || BF16;
@@ -201,17 +203,23 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // buffer descriptors of the tile whose operands are being streamed (bounds = the rows that exist: rows
     // past the end of X or W read as zeros)
     __amdgpu_buffer_rsrc_t x_rsrc, w_rsrc;
+    uint8_t *x_base, *w_base;
+    int x_bytes, w_bytes;
     auto set_rsrc = [&](int tile_id) __attribute__((always_inline)) {
         int tm_, tn_, g_;
         locate(tile_id, tm_, tn_, g_);
         const int m0_ = tm_ * BM, n0_ = tn_ * BN;
         const int x_rows = p.M - m0_ < BM ? p.M - m0_ : BM, w_rows = p.N - n0_ < BN ? p.N - n0_ : BN;
-        x_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint8_t*>(p.X + static_cast<int64_t>(g_) * p.strideX + static_cast<int64_t>(m0_) * p.KB), 0,
-            x_rows * p.KB, 0x00020000);
-        w_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<uint8_t*>(p.W + static_cast<int64_t>(g_) * p.strideW + static_cast<int64_t>(n0_) * p.KB), 0,
-            w_rows * p.KB, 0x00020000);
+        x_base = const_cast<uint8_t*>(p.X + static_cast<int64_t>(g_) * p.strideX + static_cast<int64_t>(m0_) * p.KB);
+        w_base = const_cast<uint8_t*>(p.W + static_cast<int64_t>(g_) * p.strideW + static_cast<int64_t>(n0_) * p.KB);
+        x_bytes = x_rows * p.KB; w_bytes = w_rows * p.KB;
+        x_rsrc = __builtin_amdgcn_make_buffer_rsrc(x_base, 0, x_bytes, 0x00020000);
+        w_rsrc = __builtin_amdgcn_make_buffer_rsrc(w_base, 0, w_bytes, 0x00020000);
+    };
+    // ... or of nothing: what is requested then reads as zeros
+    auto limit_rsrc = [&](bool more) __attribute__((always_inline)) {
+        x_rsrc = __builtin_amdgcn_make_buffer_rsrc(x_base, 0, more ? x_bytes : 0, 0x00020000);
+        w_rsrc = __builtin_amdgcn_make_buffer_rsrc(w_base, 0, more ? w_bytes : 0, 0x00020000);
     };
     bool prefetched = false;        // ring entries X(0) W(0) X(1) W(1) of `tile` were requested during the previous epilogue
     if (QPRO) {
@@ -267,7 +275,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // 16 multiplies per tile and K step sit in front of the tile's first MFMA of the step (the vector ALU is idle
     // there).  One extra fp32 rounding of the running sum per K step (and a 1-ulp reciprocal in the ratio):
     // K / 128 * 2^-23 relative to sum |terms|, two orders below the matrix pipe's own truncation.
-    // The scales of block k + 1 are fetched at the start of step k.
+    // The scales of block k + 1 are fetched at the start of step k and used at its end.
     // Power-of-two block scales (BW == 2): every scale is 2^(e - 127) with e its fp32 exponent field, which is the
     // 8-bit scale format of the scaled MFMA: the instruction multiplies the products of a 32-element K run by
     // 2^(ea - 127) * 2^(eb - 127), ea / eb taken from the lane that holds the run.  A lane's X fragment is one
@@ -275,64 +283,73 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // for the wave).  The accumulators then hold the scaled sum itself and the epilogue multiplies by nothing.
     // X's block scales lie [row][K block]: a lane reading one value per K step touches a cache line of its own each
     // time (as many L2 requests per step as the operands themselves need).  When a row's scales are 16-byte aligned
-    // (K a multiple of 512) a lane fetches four K blocks at once, every fourth step.
+    // (K a multiple of 512) a lane fetches four K blocks at once, every fourth step (QUAD, an instantiation of its own: 541
+    // against 555 us at 32768 x 4096 x 4096, 488 against 523 with power-of-two scales).
     float s_cur[MI], r_sc[MI], sx_nx[MI], sw_nx = 0.f;
     v4f sx_q[MI];
-    const bool quad = BLOCKWISE && (ksteps & 3) == 0 && (ksteps_all & 3) == 0 && (k_lo & 3) == 0;
-    auto pick = [](const v4f& v, int j) __attribute__((always_inline)) {
-        return j == 0 ? v[0] : j == 1 ? v[1] : j == 2 ? v[2] : v[3];
-    };
     int sc_x[MI], sc_w = 127;
     const int bw_nb = ((n0 + wave_n * WN < p.N ? n0 + wave_n * WN : p.N - 1) >> 7), bw_nblk = p.N >> 7;
-    auto bw_row = [&](int mi) __attribute__((always_inline)) {
-        const int m = m0 + wave_m * WM + mi * 32 + l32;
-        return static_cast<int64_t>(m < p.M ? m : p.M - 1) * ksteps_all + k_lo;
+    const float* const sx_tile = sxg + static_cast<int64_t>(m0) * ksteps_all + k_lo;
+    unsigned sx_off[MI];                                     // this lane's rows in them, in bytes
+    auto load_sx1 = [&](int mi, int k) __attribute__((always_inline)) {
+        return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(sx_tile + k) + sx_off[mi]);
     };
-#pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-        s_cur[mi] = 1.f; r_sc[mi] = 1.f; sx_nx[mi] = 1.f; sc_x[mi] = 127;
-        sx_q[mi] = v4f{1.f, 1.f, 1.f, 1.f};
-    }
-    if (BLOCKWISE) {
+    auto load_sx4 = [&](int mi, int k) __attribute__((always_inline)) {
+        return *reinterpret_cast<const v4f*>(reinterpret_cast<const char*>(sx_tile + k) + sx_off[mi]);
+    };
+    // the first block's scales
+    auto bw_first = [&]() __attribute__((always_inline)) {
+        if (!BLOCKWISE) return;
         const float sw0 = swg[static_cast<int64_t>(k_lo) * bw_nblk + bw_nb];
+        float sx0[MI];
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-            float sx0;
-            if (quad) { sx_q[mi] = *reinterpret_cast<const v4f*>(sxg + bw_row(mi)); sx0 = sx_q[mi][0]; }
-            else sx0 = sxg[bw_row(mi)];
-            if (BW == 1) s_cur[mi] = sx0 * sw0;
-            else sc_x[mi] = static_cast<int>(__float_as_uint(sx0) >> 23);
+            const int r = wave_m * WM + mi * 32 + l32;
+            sx_off[mi] = static_cast<unsigned>(m0 + r < p.M ? r : p.M - 1 - m0) * static_cast<unsigned>(ksteps_all * 4);
+            if (QUAD) sx_q[mi] = load_sx4(mi, 0);
+            else sx0[mi] = load_sx1(mi, 0);
+        }
+        if (!prefetched && ksteps > 1) { issue_x(3, 128); issue_w(4, 128); }
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            if (QUAD) sx0[mi] = sx_q[mi][0];
+            if (BW == 1) { s_cur[mi] = sx0[mi] * sw0; r_sc[mi] = 1.f; }
+            else sc_x[mi] = static_cast<int>(__float_as_uint(sx0[mi]) >> 23);
         }
         if (BW == 2) sc_w = static_cast<int>(__float_as_uint(sw0) >> 23);
-    }
-    // ratio for the step that begins (its scales were fetched one step earlier), then the fetch for the next one
-    auto bw_step = [&](int k) __attribute__((always_inline)) {
+    };
+    // requests the scales of block k + 1 (panel32_scale_loads(QUAD, k) loads)
+    auto bw_fetch = [&](int k) __attribute__((always_inline)) {
         if (!BLOCKWISE) return;
-        if (k >= 1 && quad) {
+        sw_nx = swg[static_cast<int64_t>(k_lo + k + 1) * bw_nblk + bw_nb];
+        if (!QUAD) {
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) sx_nx[mi] = pick(sx_q[mi], k & 3);
+            for (int mi = 0; mi < MI; ++mi) sx_nx[mi] = load_sx1(mi, k + 1);
+        } else if (((k + 1) & 3) == 0) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) sx_q[mi] = load_sx4(mi, k + 1);
         }
-        if (k >= 1 && BW == 1) {
+    };
+    // takes them, at the end of step k: the ratio to the last step's, or the exponents
+    auto bw_use = [&](int k) __attribute__((always_inline)) {
+        if (!BLOCKWISE) return;
+        if (BW == 2) sc_w = static_cast<int>(__float_as_uint(sw_nx) >> 23);
+        const int j = (k + 1) & 3;
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const float s_new = sx_nx[mi] * sw_nx;
+        for (int mi = 0; mi < MI; ++mi) {
+            float sx;
+            if (QUAD) {
+                const float lo = j & 1 ? sx_q[mi][1] : sx_q[mi][0], hi = j & 1 ? sx_q[mi][3] : sx_q[mi][2];
+                sx = j & 2 ? hi : lo;
+            } else {
+                sx = sx_nx[mi];
+            }
+            if (BW == 1) {
+                const float s_new = sx * sw_nx;
                 r_sc[mi] = s_cur[mi] * __builtin_amdgcn_rcpf(s_new);
                 s_cur[mi] = s_new;
-            }
-        }
-        if (k >= 1 && BW == 2) {
-            sc_w = static_cast<int>(__float_as_uint(sw_nx) >> 23);
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi) sc_x[mi] = static_cast<int>(__float_as_uint(sx_nx[mi]) >> 23);
-        }
-        if (k + 1 < ksteps) {
-            sw_nx = swg[static_cast<int64_t>(k_lo + k + 1) * bw_nblk + bw_nb];
-            if (!quad) {
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi) sx_nx[mi] = sxg[bw_row(mi) + k + 1];
-            } else if (((k + 1) & 3) == 0) {
-#pragma unroll
-                for (int mi = 0; mi < MI; ++mi) sx_q[mi] = *reinterpret_cast<const v4f*>(sxg + bw_row(mi) + k + 1);
+            } else {
+                sc_x[mi] = static_cast<int>(__float_as_uint(sx) >> 23);
             }
         }
     };
@@ -390,14 +407,14 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
             }                                                                        \
             mfma_one(mi, 0, SET);                                                    \
             __builtin_amdgcn_sched_barrier(0);                                       \
-            if ((LD) == 1 && ld_x && !grp_b) issue_x1(ld_x_slot, ld_x_kb, mi);       \
-            if ((LD) == 2 && ld_w && !grp_b) issue_w1(ld_w_slot, ld_w_kb, mi);       \
+            if ((LD) == 1 && ld_x && (BLOCKWISE || !grp_b)) issue_x1(ld_x_slot, ld_x_kb, mi); \
+            if ((LD) == 2 && ld_w && (BLOCKWISE || !grp_b)) issue_w1(ld_w_slot, ld_w_kb, mi);       \
             __builtin_amdgcn_sched_barrier(0);                                       \
             mfma_one(mi, 1, SET);                                                    \
             __builtin_amdgcn_sched_barrier(0);                                       \
             read_x(SLOT_X, S_READ, mi);                                              \
-            if ((LD) == 1 && ld_x && grp_b) issue_x1(ld_x_slot, ld_x_kb, mi);        \
-            if ((LD) == 2 && ld_w && grp_b) issue_w1(ld_w_slot, ld_w_kb, mi);        \
+            if ((LD) == 1 && ld_x && !BLOCKWISE && grp_b) issue_x1(ld_x_slot, ld_x_kb, mi);        \
+            if ((LD) == 2 && ld_w && !BLOCKWISE && grp_b) issue_w1(ld_w_slot, ld_w_kb, mi);        \
         }                                                                            \
         __builtin_amdgcn_sched_barrier(0);                                           \
     } while (0)
@@ -414,10 +431,14 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     if (!prefetched) {
         issue_x(1, 0);
         issue_w(2, 0);
-        if (ksteps > 1) { issue_x(3, 128); issue_w(4, 128); }
+        if (!BLOCKWISE && ksteps > 1) { issue_x(3, 128); issue_w(4, 128); }
     }
-    if (ksteps > 2) issue_x(0, 256);
-    if (ksteps > 2) {
+    // (block scales: between the operands of the first two steps, which they would hold up by a round trip in front)
+    bw_first();
+    if (!BLOCKWISE && ksteps > 2) issue_x(0, 256);     // (block scales: in the first step)
+    if (BLOCKWISE) {
+        if (ksteps > 1) __builtin_amdgcn_s_waitcnt(0x0F78); else __builtin_amdgcn_s_waitcnt(0x0F70);
+    } else if (ksteps > 2) {
         // loads return in issue order, so "at most 4 (12) outstanding" covers X(0), W(0) whatever else (the
         // previous tile's stores) is still in flight
         if (prefetched) __builtin_amdgcn_s_waitcnt(0x0F74); else __builtin_amdgcn_s_waitcnt(0x0F7C);
@@ -434,24 +455,31 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // (the last K step is peeled: MFMAs under a condition inside the loop make the compiler copy accumulators)
     for (int k = 0; k + 1 < ksteps; ++k) {
         const int sw_cur = mod5(e5 + 1), sx_nxt = mod5(e5 + 2), sw_nxt = mod5(e5 + 3);
-        const bool ld_x = k >= 1 && k + 2 < ksteps, ld_w = k + 2 < ksteps;
+        // Block scales: every step requests the same loads in the same places (those past the last step read zeros into
+        // free slots, both waves of a SIMD use the same gap), so that the compiler can count how many are younger than a
+        // block's scales.  Under a condition it has to assume that none is, and waits for everything in flight at their
+        // use: the ring had no depth then.  32768 x 4096 x 4096 604 -> 541 us, power-of-two scales 550 -> 488; 8192 x 2048 x
+        // 2048 (one tile per CU) 47.5 -> 44 and 44.5 -> 40.3.
+        const bool more = k + 2 < ksteps;
+        const bool ld_x = BLOCKWISE || (k >= 1 && more), ld_w = BLOCKWISE || more;
         const int ld_x_slot = mod5(e5 + 4), ld_x_kb = (k + 2) * 128;    // X(k + 2) -> the slot W(k - 1) left
         const int ld_w_slot = e5, ld_w_kb = (k + 2) * 128;              // W(k + 2) -> the slot X(k) leaves
-        bw_step(k);
+        if (BLOCKWISE) limit_rsrc(more);
+        bw_fetch(k);
         LOKA_HALF_STEP(e5, sw_cur, 1, 0, 1, 1);
         // all but this step's newest loads: X(k + 2) (4) and, blockwise, the scales of block k + 1 (1 or MI + 1)
         if (!ld_w) __builtin_amdgcn_s_waitcnt(0x0F70);
         else if (!BLOCKWISE) __builtin_amdgcn_s_waitcnt(0x0F74);
-        else if (panel32_scale_loads(quad, k) == 1) __builtin_amdgcn_s_waitcnt(0x0F75);
+        else if (panel32_scale_loads(QUAD, k) == 1) __builtin_amdgcn_s_waitcnt(0x0F75);
         else __builtin_amdgcn_s_waitcnt(0x0F79);
         lds_barrier();                                          // (also waits for this wave's LDS reads)
         LOKA_HALF_STEP(sx_nxt, sw_nxt, 0, 1, 2, 0);
+        bw_use(k);
         e5 = sx_nxt;
     }
     {
         const bool ld_x = false, ld_w = false;
         const int ld_x_slot = 0, ld_x_kb = 0, ld_w_slot = 0, ld_w_kb = 0;
-        bw_step(ksteps - 1);
         LOKA_HALF_STEP(e5, mod5(e5 + 1), 1, 0, 0, 1);
         (void)ld_x; (void)ld_w; (void)ld_x_slot; (void)ld_x_kb; (void)ld_w_slot; (void)ld_w_kb;
     }
@@ -497,6 +525,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi) mfma_row(mi, 1);
 #undef LOKA_HALF_STEP
+    if (BLOCKWISE) wait_vmcnt<0>();                         // (the zeros requested past the last K step are in)
     __syncthreads();                                        // LDS is free for the epilogue
     // the next tile's first four ring entries stream in while this tile's statistics are exchanged
     prefetched = tile + tile_stride < total_tiles;
@@ -965,49 +994,42 @@ bool panel32_affine(const GemmParams& p) {
     return (p.gamma != nullptr && (ln || p.norm == LOKA_NORM_RMSNORM)) || (p.beta != nullptr && ln) ||
            p.norm == LOKA_NORM_BLOCKNORM || p.act != LOKA_ACT_NONE;
 }
+// X's block scales four K blocks at a time: a row's scales are whole 16-byte runs, and so are a K range's
+bool panel32_quad(int KB, int k_per_split) { return KB % 512 == 0 && k_per_split % 4 == 0; }
+namespace {
+using Panel32Fn = void (*)(GemmParams);
+template <int EPI, bool YOUT>
+Panel32Fn panel32_block_fn(int bw, bool quad) {
+    return bw == 2 ? (quad ? &gemm_panel32_kernel<EPI, 2, 0, false, false, false, YOUT, true> : &gemm_panel32_kernel<EPI, 2, 0, false, false, false, YOUT, false>)
+                   : (quad ? &gemm_panel32_kernel<EPI, 1, 0, false, false, false, YOUT, true> : &gemm_panel32_kernel<EPI, 1, 0, false, false, false, YOUT, false>);
+}
 // bw: 0 plain scales, 1 block scales, 2 power-of-two block scales (see the kernel); fp8out with bw == 0 only
-const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro, bool want_y) {
-    if (qpro) return (bw != 0 || fp8out) ? nullptr : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, true>);
-    if (fp8out) return bw != 0 ? nullptr
-                       : affine ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 2>)
-                                : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 1>);
-    if (!want_y)
-        return bw == 2   ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0, false, false, false, false>)
-               : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0, false, false, false, false>)
-                         : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, false, false>);
-    return bw == 2   ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0>)
-           : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0>)
-                     : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0>);
+Panel32Fn panel32_pick(int bw, bool fp8out, bool affine, bool qpro, bool want_y, bool quad) {
+    if (qpro) return (bw != 0 || fp8out) ? nullptr : &gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, true>;
+    if (fp8out) return bw != 0 ? nullptr : affine ? &gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 2> : &gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 1>;
+    if (bw) return want_y ? panel32_block_fn<EPI_PANEL_SYNC, true>(bw, quad) : panel32_block_fn<EPI_PANEL_SYNC, false>(bw, quad);
+    return want_y ? &gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0> : &gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, false, false>;
+}
+// split K and the BF16 reference GEMM: fp32 out
+Panel32Fn panel32_part_pick(int bw, bool bf16, bool quad) {
+    return bf16 ? &gemm_panel32_kernel<EPI_ROW_IN_TILE, 0, 0, false, true> : bw ? panel32_block_fn<EPI_SPLITK, true>(bw, quad) : &gemm_panel32_kernel<EPI_SPLITK, 0, 0>;
+}
+}  // namespace
+const void* panel32_fn(int bw, bool fp8out, bool affine, bool qpro, bool want_y, bool quad) {
+    return reinterpret_cast<const void*>(panel32_pick(bw, fp8out, affine, qpro, want_y, quad));
 }
 // a K that is no multiple of 128 (plain scales, bf16 output)
 const void* panel32_ragged_fn() { return reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, true>); }
 void panel32_ragged_launch(const GemmParams& p, dim3 grid, hipStream_t s) {
     gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, true><<<grid, 512, kPanel32Lds, s>>>(p);
 }
-// split K (bw as above) and the BF16 reference GEMM: fp32 out
-const void* panel32_part_fn(int bw, bool bf16) {
-    return bf16      ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_ROW_IN_TILE, 0, 0, false, true>)
-           : bw == 2 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_SPLITK, 2, 0>)
-           : bw == 1 ? reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_SPLITK, 1, 0>)
-                     : reinterpret_cast<const void*>(&gemm_panel32_kernel<EPI_SPLITK, 0, 0>);
-}
+const void* panel32_part_fn(int bw, bool bf16, bool quad) { return reinterpret_cast<const void*>(panel32_part_pick(bw, bf16, quad)); }
 void panel32_part_launch(const GemmParams& p, int bw, bool bf16, dim3 grid, hipStream_t s) {
-    if (bf16) gemm_panel32_kernel<EPI_ROW_IN_TILE, 0, 0, false, true><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (bw == 2) gemm_panel32_kernel<EPI_SPLITK, 2, 0><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (bw == 1) gemm_panel32_kernel<EPI_SPLITK, 1, 0><<<grid, 512, kPanel32Lds, s>>>(p);
-    else gemm_panel32_kernel<EPI_SPLITK, 0, 0><<<grid, 512, kPanel32Lds, s>>>(p);
+    panel32_part_pick(bw, bf16, panel32_quad(p.KB, p.k_per_split))<<<grid, 512, kPanel32Lds, s>>>(p);
 }
 size_t panel32_lds() { return kPanel32Lds; }
 void panel32_launch(const GemmParams& p, int bw, dim3 grid, hipStream_t s) {
-    if (p.qpro) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, true><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (p.outq && panel32_affine(p)) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 2><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (p.outq) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 1><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (!p.y && bw == 2) gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0, false, false, false, false><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (!p.y && bw == 1) gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0, false, false, false, false><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (!p.y) gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0, false, false, false, false><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (bw == 2) gemm_panel32_kernel<EPI_PANEL_SYNC, 2, 0><<<grid, 512, kPanel32Lds, s>>>(p);
-    else if (bw == 1) gemm_panel32_kernel<EPI_PANEL_SYNC, 1, 0><<<grid, 512, kPanel32Lds, s>>>(p);
-    else gemm_panel32_kernel<EPI_PANEL_SYNC, 0, 0><<<grid, 512, kPanel32Lds, s>>>(p);
+    panel32_pick(bw, p.outq != nullptr, panel32_affine(p), p.qpro != 0, p.y != nullptr, panel32_quad(p.KB, 0))<<<grid, 512, kPanel32Lds, s>>>(p);
 }
 
 }  // namespace loka

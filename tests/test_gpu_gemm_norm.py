@@ -210,6 +210,17 @@ def test_blockwise_ragged(orc, recipe):
         _run_case(orc, x, wt, recipe, "none", v, tag=f"{recipe} no norm {B.loka_variant_name(v)}")
 
 
+@pytest.mark.parametrize("recipe", ["block", "block_pow2"])
+@pytest.mark.parametrize("M,N,K", [(300, 384, 128), (300, 384, 256), (300, 384, 384), (257, 256, 512), (300, 640, 640), (40, 256, 1024),
+                                   (33280, 512, 512), (33280, 512, 384)])      # (260 tiles: workgroups with a second tile)
+def test_block_scales_of_the_large_tile_kernel(orc, recipe, M, N, K):
+    # one, two, three and more K steps, scales fetched one or four K blocks at a time
+    x, _ = synth.normal_outlier4(M, K, seed=M + K)
+    v = next(i for i in range(B.loka_variant_count()) if B.loka_variant_name(i) == "panel32_256x256")
+    rows = None if M < 1000 else np.r_[0:40, M // 2:M // 2 + 40, M - 300:M - 260, M - 40:M]
+    _run_case(orc, x, synth.weight(K, N, seed=N), recipe, "layernorm", v, rows=rows, tag=f"{recipe} {M}x{N}x{K}")
+
+
 def test_layernorm_rows_with_large_mean(orc):
     # rows whose mean is far larger than their spread: the fused statistics must not cancel
     M, K, N = 64, 128, 256
