@@ -203,9 +203,37 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     const float* sxg = p.sx + static_cast<int64_t>(g) * p.strideSx;
     const float* swg = p.sw + static_cast<int64_t>(g) * p.strideSw;
 
+    // The row's and the columns' scales are requested behind the first operands where registers allow it: asked for in the
+    // epilogue they are one more trip to memory at the end of a launch that may be no longer than a few of them.
+    constexpr bool EARLY_SCALES = !BLOCKWISE && !IS_BF16 && MI * NI * NSPLIT <= 16;
+    const bool tensor_x = p.x_mode == LOKA_SCALE_TENSOR, tensor_w = p.w_mode == LOKA_SCALE_TENSOR;
+    float sxv[MI];
+    v4f swv[NSPLIT][NI];
+    auto load_sx = [&](int mi) __attribute__((always_inline)) {
+        int m = m0 + wave_m * WM + mi * 16 + l16;
+        m = m < p.M ? m : p.M - 1;
+        return sxg[tensor_x ? 0 : m];
+    };
+    auto load_sw = [&](int h, int ti) __attribute__((always_inline)) {
+        const int n = n0 + h * BN_SUB + wave_n * WN + q * 8 + coff_of(ti);
+        if (tensor_w) {
+            const float t = swg[0];
+            return v4f{t, t, t, t};
+        }
+        return n < p.N ? *reinterpret_cast<const v4f*>(swg + n) : v4f{0.f, 0.f, 0.f, 0.f};
+    };
     if constexpr (!RING) {
 #pragma unroll
         for (int j = 0; j < JN; ++j) issue_j(j, 0, 0, 0, 0, true);   // stage 0, every wave's share
+    }
+
+    if constexpr (EARLY_SCALES) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) sxv[mi] = load_sx(mi);
+#pragma unroll
+        for (int h = 0; h < NSPLIT; ++h)
+#pragma unroll
+            for (int ti = 0; ti < NI; ++ti) swv[h][ti] = load_sw(h, ti);
     }
 
     // loads of the next stage are issued in the first ISSUE_STEPS tile steps of the running stage
@@ -306,7 +334,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
                         const v4f c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(aw, bx[mi], v4f{0.f, 0.f, 0.f, 0.f},
                                                                                         0, 0, 0, 0, 0, 0);
                         const float s = sxk[mi] * swk;
-                        acc[0][mi][ti] += c * s;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[0][mi][ti][e] = __builtin_fmaf(c[e], s, acc[0][mi][ti][e]);
                     } else {
                         acc[0][mi][ti] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(aw, bx[mi], acc[0][mi][ti],
                                                                                          0, 0, 0, 0, 0, 0);
@@ -374,6 +403,26 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
         }
         if (!grp_b) lds_barrier();
     } else {
+    // Block scales of an iteration are requested an iteration ahead, with the operands they belong to (asked for where they
+    // are used, every K step waited a second trip to memory behind the first: 8192 x 1024 x 512, M x K x N, 18.6 -> 15.4 us
+    // with the epilogue's share).
+    float sxn[MI], swn = 0.f;
+    auto load_block_scales = [&](int it) __attribute__((always_inline)) {
+        const int k = it / NSPLIT, h = it % NSPLIT;
+        if (h == 0) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) {
+                int m = m0 + wave_m * WM + mi * 16 + l16;
+                m = m < p.M ? m : p.M - 1;
+                sxn[mi] = sxg[static_cast<int64_t>(m) * ksteps_all + k_lo + k];
+            }
+        }
+        int nrun = n0 + h * BN_SUB + wave_n * WN + q * 8;
+        nrun = nrun < p.N ? nrun : p.N - 1;
+        swn = swg[static_cast<int64_t>(k_lo + k) * (p.N >> 7) + (nrun >> 7)];
+    };
+    if (BLOCKWISE) load_block_scales(0);
+    float sxk[MI];
     for (int it = 0; it < iters; ++it) {
         const int k = it / NSPLIT, h = it % NSPLIT;
         __builtin_amdgcn_s_waitcnt(0x0F70);                     // vmcnt(0): this wave's loads for stage `it` have landed
@@ -395,24 +444,18 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
                 xe[mi][2] = e4m3x8_to_bf16(hi[0], hi[1]); xe[mi][3] = e4m3x8_to_bf16(hi[2], hi[3]);
             }
         }
-        float sxk[MI];
+        float swk = 0.f;
         if (BLOCKWISE) {
+            if (h == 0) {
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                int m = m0 + wave_m * WM + mi * 16 + l16;
-                m = m < p.M ? m : p.M - 1;
-                sxk[mi] = sxg[static_cast<int64_t>(m) * ksteps_all + k_lo + k];
+                for (int mi = 0; mi < MI; ++mi) sxk[mi] = sxn[mi];
             }
+            swk = swn;
+            load_block_scales(more ? it + 1 : it);
         }
 #pragma unroll
         for (int hh = 0; hh < NSPLIT; ++hh) {
             if (hh != h) continue;
-            float swk = 0.f;
-            if (BLOCKWISE) {
-                int nrun = n0 + hh * BN_SUB + wave_n * WN + q * 8;
-                nrun = nrun < p.N ? nrun : p.N - 1;
-                swk = swg[static_cast<int64_t>(k_lo + k) * (p.N >> 7) + (nrun >> 7)];
-            }
             // W fragments are fetched one tile ahead of the MFMAs that consume them
             v4i lo = *reinterpret_cast<const v4i*>(ws + w_off0);
             v4i hi = *reinterpret_cast<const v4i*>(ws + w_off1);      // coff_of(0) == 0
@@ -456,7 +499,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
                             v4f c = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(aw, bx[mi], v4f{0.f, 0.f, 0.f, 0.f},
                                                                                      0, 0, 0, 0, 0, 0);
                             const float s = sxk[mi] * swk;
-                            acc[hh][mi][ti] += c * s;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[hh][mi][ti][e] = __builtin_fmaf(c[e], s, acc[hh][mi][ti][e]);
                         } else {
                             acc[hh][mi][ti] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(aw, bx[mi], acc[hh][mi][ti],
                                                                                                0, 0, 0, 0, 0, 0);
@@ -472,42 +516,45 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
 
     // ------------------------------------------------------------------ epilogue
     // lane owns row m (per mi) and, per N-part h and tile ti, columns ncol(h) + coff_of(ti) + [0, 4)
-    __syncthreads();                       // all waves are done reading the stages: LDS is free
-    float* red = reinterpret_cast<float*>(smem);   // [BM][WAVES_N][3]
+    const bool ln = p.norm == LOKA_NORM_LAYERNORM;
+    const bool blocknorm = EPI == EPI_ROW_IN_TILE && BN == 256 && p.norm == LOKA_NORM_BLOCKNORM;
+    const bool has_g = p.gamma != nullptr && !blocknorm && p.norm != LOKA_NORM_NONE, has_b = p.beta != nullptr && ln;
+    // gamma and beta of 8 columns (absent: ones, zeros); in flight during the statistics where registers allow it
+    constexpr bool EARLY_AFFINE = MI * NI * NSPLIT <= 16 && EPI != EPI_SPLITK && !IS_BF16;
+    u32x4 gw[NSPLIT][NI / 2], bw[NSPLIT][NI / 2];
+    auto load_affine = [&](int h, int tp) __attribute__((always_inline)) {
+        const int n = n0 + h * BN_SUB + wave_n * WN + q * 8 + coff_of(tp);
+        gw[h][tp / 2] = u32x4{0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+        bw[h][tp / 2] = u32x4{0u, 0u, 0u, 0u};
+        if (has_g && n < p.N) gw[h][tp / 2] = *reinterpret_cast<const u32x4*>(p.gamma + n);
+        if (has_b && n < p.N) bw[h][tp / 2] = *reinterpret_cast<const u32x4*>(p.beta + n);
+    };
+    if constexpr (EARLY_AFFINE) {
+#pragma unroll
+        for (int h = 0; h < NSPLIT; ++h)
+#pragma unroll
+            for (int tp = 0; tp < NI; tp += 2) load_affine(h, tp);
+    }
+    lds_barrier();                         // all waves are done reading the stages: LDS is free
     const int64_t obase = static_cast<int64_t>(g) * p.strideO;
-    const bool tensor_x = p.x_mode == LOKA_SCALE_TENSOR, tensor_w = p.w_mode == LOKA_SCALE_TENSOR;
 
     int ncol[NSPLIT];
-    float cnt_lane = 0.f;                  // valid columns this lane holds per row
 #pragma unroll
-    for (int h = 0; h < NSPLIT; ++h) {
-        ncol[h] = n0 + h * BN_SUB + wave_n * WN + q * 8;
-#pragma unroll
-        for (int ti = 0; ti < NI; ++ti)
-            if (ncol[h] + coff_of(ti) < p.N) cnt_lane += 4.f;
-    }
+    for (int h = 0; h < NSPLIT; ++h) ncol[h] = n0 + h * BN_SUB + wave_n * WN + q * 8;
 
     // apply scales in place
-    if (!BLOCKWISE && !IS_BF16) {
+    if constexpr (!BLOCKWISE && !IS_BF16) {
+        if constexpr (!EARLY_SCALES) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) sxv[mi] = load_sx(mi);
+        }
 #pragma unroll
         for (int h = 0; h < NSPLIT; ++h)
 #pragma unroll
             for (int ti = 0; ti < NI; ++ti) {
-                const int n = ncol[h] + coff_of(ti);
-                v4f s4;
-                if (tensor_w) {
-                    const float s = swg[0];
-                    s4 = v4f{s, s, s, s};
-                } else {
-                    s4 = (n < p.N) ? *reinterpret_cast<const v4f*>(swg + n) : v4f{0.f, 0.f, 0.f, 0.f};
-                }
+                if constexpr (!EARLY_SCALES) swv[h][ti] = load_sw(h, ti);
 #pragma unroll
-                for (int mi = 0; mi < MI; ++mi) {
-                    int m = m0 + wave_m * WM + mi * 16 + l16;
-                    m = m < p.M ? m : p.M - 1;
-                    const float sxm = tensor_x ? sxg[0] : sxg[m];
-                    acc[h][mi][ti] *= s4 * sxm;
-                }
+                for (int mi = 0; mi < MI; ++mi) acc[h][mi][ti] *= swv[h][ti] * sxv[mi];
             }
     }
 
@@ -551,93 +598,105 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     // ---- row statistics (reciprocals and the inverse square root are the 1-ulp hardware ones: their
     // error is four orders of magnitude below a bf16 ulp, and the IEEE sequences are ~300 cycles each)
     // (BlockNorm: a 256-column tile is one group of the row, normalized like a row of its own)
-    const bool blocknorm = EPI == EPI_ROW_IN_TILE && BN == 256 && p.norm == LOKA_NORM_BLOCKNORM;
+    // A lane takes (sum, centred sum of squares) of its values of a row; parts are combined by the sum of their sums and
+    // sum(m2 + n (mean_part - mean)^2): additions only, no branches, so the MI row sets of a wave overlap.  (A chain of
+    // pairwise merges, each with a reciprocal behind a branch, took 1.4 us of a 32 x 128 tile and 3.2 us of a 64 x 256 one.
+    // With it went the scales' trip to memory at the end of the launch.  Call, before -> after, M x K x N: 256 x 128 x 128
+    // 5.0 -> 4.2 us, 5013 x 1008 x 720 19.2 -> 17.5, 20000 x 640 x 512 on 64 x 512 tiles 31.0 -> 24.0.)
     const float inv_n = 1.0f / static_cast<float>(blocknorm ? BN : p.N);
-    float mean_r[MI], rstd_r[MI];
+    const int tile_cols = p.N - n0 < BN ? p.N - n0 : BN;
+    auto wave_cols = [&](int w) __attribute__((always_inline)) {      // columns of the tile that wave column w holds (uniform)
+        int c = 0;
+#pragma unroll
+        for (int h = 0; h < NSPLIT; ++h) {
+            const int r = tile_cols - h * BN_SUB - w * WN;
+            c += r < 0 ? 0 : r < WN ? r : WN;
+        }
+        return static_cast<float>(c);
+    };
+    auto rcp0 = [](float n) __attribute__((always_inline)) { return n > 0.f ? __builtin_amdgcn_rcpf(n) : 0.f; };
+    constexpr int RS = WAVES_N + 1;                                   // (one spare entry: rows on distinct banks)
+    float4* const red = reinterpret_cast<float4*>(smem);              // [BM][RS] (sum, mean, m2, count)
+    float mean_r[MI], rstd_r[MI];                                     // (rstd_r: m2 of the tile until the row is complete)
     if (p.norm == LOKA_NORM_NONE) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) { mean_r[mi] = 0.f; rstd_r[mi] = 1.f; }
     } else {
-        const bool ln = p.norm == LOKA_NORM_LAYERNORM;
+        float cnt_lane = 0.f;                                         // N % 16 == 0: a tile pair's 8 columns are inside or outside
+#pragma unroll
+        for (int h = 0; h < NSPLIT; ++h)
+#pragma unroll
+            for (int tp = 0; tp < NI; tp += 2) {
+                const bool in = ncol[h] + coff_of(tp) < p.N;
+                cnt_lane += in ? 8.f : 0.f;
+                if (tile_cols < BN) {                                 // (uniform) columns past N count as zeros below
+#pragma unroll
+                    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) acc[h][mi][tp + (e >> 2)][e & 3] = in ? acc[h][mi][tp + (e >> 2)][e & 3] : 0.f;
+                }
+            }
+        const float rc_lane = rcp0(cnt_lane), cnt_wave = wave_cols(wave_n), rc_wave = rcp0(cnt_wave);
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-            float n_ = cnt_lane, mean = 0.f, m2 = 0.f;
+            float s = 0.f, m2 = 0.f, mean_w = 0.f;
             if (ln) {
-                float s = 0.f;
+                float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int h = 0; h < NSPLIT; ++h)
 #pragma unroll
                     for (int ti = 0; ti < NI; ++ti)
-                        if (ncol[h] + coff_of(ti) < p.N)
-                            s += (acc[h][mi][ti][0] + acc[h][mi][ti][1]) + (acc[h][mi][ti][2] + acc[h][mi][ti][3]);
-                mean = n_ > 0.f ? s * __builtin_amdgcn_rcpf(n_) : 0.f;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) s4[e] += acc[h][mi][ti][e];
+                s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+                const float mean = s * rc_lane;
+                float q4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int h = 0; h < NSPLIT; ++h)
 #pragma unroll
-                    for (int ti = 0; ti < NI; ++ti)
-                        if (ncol[h] + coff_of(ti) < p.N) {
+                    for (int tp = 0; tp < NI; tp += 2) {
+                        const float mean_in = ncol[h] + coff_of(tp) < p.N ? mean : 0.f;
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                const float d = acc[h][mi][ti][e] - mean;
-                                m2 += d * d;
-                            }
+                        for (int e = 0; e < 8; ++e) {
+                            const float d = acc[h][mi][tp + (e >> 2)][e & 3] - mean_in;
+                            q4[e & 3] = __builtin_fmaf(d, d, q4[e & 3]);
                         }
-                // lanes l, l^16, l^32, l^48 hold the same row
-#pragma unroll
-                for (int msk = 16; msk < 64; msk <<= 1) {
-                    const float nb = wave_shfl_xor(n_, msk), mb = wave_shfl_xor(mean, msk), m2b = wave_shfl_xor(m2, msk);
-                    // symmetric form so both partners compute identical bits
-                    const float nn = n_ + nb;
-                    if (nn > 0.f) {
-                        const float d = mb - mean;
-                        const float rn = __builtin_amdgcn_rcpf(nn);
-                        const float newmean = (n_ * mean + nb * mb) * rn;
-                        m2 = m2 + m2b + d * d * (n_ * nb * rn);
-                        mean = newmean;
                     }
-                    n_ = nn;
-                }
+                m2 = (q4[0] + q4[1]) + (q4[2] + q4[3]);
+                s = row_lanes_sum(s);                                 // lanes l, l^16, l^32, l^48 hold the same row
+                mean_w = s * rc_wave;
+                const float d = mean - mean_w;
+                m2 = row_lanes_sum(__builtin_fmaf(cnt_lane * d, d, m2));
             } else {
+                float q4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int h = 0; h < NSPLIT; ++h)
 #pragma unroll
                     for (int ti = 0; ti < NI; ++ti)
-                        if (ncol[h] + coff_of(ti) < p.N) {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) m2 += acc[h][mi][ti][e] * acc[h][mi][ti][e];
-                        }
-                m2 += wave_shfl_xor(m2, 16);
-                m2 += wave_shfl_xor(m2, 32);
+                        for (int e = 0; e < 4; ++e) q4[e] = __builtin_fmaf(acc[h][mi][ti][e], acc[h][mi][ti][e], q4[e]);
+                m2 = row_lanes_sum((q4[0] + q4[1]) + (q4[2] + q4[3]));
             }
-            if (WAVES_N > 1) {
-                const int row = wave_m * WM + mi * 16 + l16;
-                if (q == 0) {
-                    float* r3 = red + (row * WAVES_N + wave_n) * 3;
-                    r3[0] = n_; r3[1] = mean; r3[2] = m2;
-                }
-            }
-            mean_r[mi] = mean; rstd_r[mi] = m2;        // rstd_r holds M2 / sumsq until finalized
-            if (WAVES_N == 1 && EPI == EPI_ROW_IN_TILE) {
-                rstd_r[mi] = __builtin_amdgcn_rsqf(m2 * inv_n + p.eps);
-            }
+            if (q == 0) red[(wave_m * WM + mi * 16 + l16) * RS + wave_n] = make_float4(s, mean_w, m2, cnt_wave);
         }
-        if (WAVES_N > 1) {
-            __syncthreads();
+        lds_barrier();
+        const float inv_cols = EPI == EPI_ROW_IN_TILE ? inv_n : __builtin_amdgcn_rcpf(static_cast<float>(tile_cols));
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const int row = wave_m * WM + mi * 16 + l16;
-                float n_ = 0.f, mean = 0.f, m2 = 0.f;
+        for (int mi = 0; mi < MI; ++mi) {
+            float4 r[WAVES_N];
 #pragma unroll
-                for (int w = 0; w < WAVES_N; ++w) {             // fixed order: every wave gets identical bits
-                    const float* r3 = red + (row * WAVES_N + w) * 3;
-                    if (ln) merge_stats(n_, mean, m2, r3[0], r3[1], r3[2]);
-                    else m2 += r3[2];
-                }
-                mean_r[mi] = mean; rstd_r[mi] = m2;
-                if (EPI == EPI_ROW_IN_TILE) {
-                    rstd_r[mi] = __builtin_amdgcn_rsqf(m2 * inv_n + p.eps);
-                }
+            for (int w = 0; w < WAVES_N; ++w) r[w] = red[(wave_m * WM + mi * 16 + l16) * RS + w];
+            float s = 0.f, m2 = 0.f;                                  // fixed order: every wave gets identical bits
+#pragma unroll
+            for (int w = 0; w < WAVES_N; ++w) s += r[w].x;
+            const float mean = s * inv_cols;                          // (without a mean the sums are zero)
+#pragma unroll
+            for (int w = 0; w < WAVES_N; ++w) {
+                const float d = r[w].y - mean;
+                m2 += __builtin_fmaf(r[w].w * d, d, r[w].z);
             }
+            mean_r[mi] = mean;
+            rstd_r[mi] = EPI == EPI_ROW_IN_TILE ? __builtin_amdgcn_rsqf(m2 * inv_n + p.eps) : m2;
         }
     }
 
@@ -670,25 +729,24 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
             for (int mi = 0; mi < MI; ++mi) {
                 const int m = m0 + wave_m * WM + mi * 16 + l16;
                 if (m < p.M) {
-                    float* dst = prow + static_cast<int64_t>(m) * (2 * p.tiles_n) + 2 * tn;
-                    // device-coherent (write-through) stores: no L2-wide write-back is needed to publish them
-                    __hip_atomic_store(dst, mean_r[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    __hip_atomic_store(dst + 1, rstd_r[mi], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    // device-coherent (write-through) store: no L2-wide write-back is needed to publish the pair
+                    const unsigned long long rec = (static_cast<unsigned long long>(__float_as_uint(rstd_r[mi])) << 32) | __float_as_uint(mean_r[mi]);
+                    __hip_atomic_store(reinterpret_cast<unsigned long long*>(prow + static_cast<int64_t>(m) * (2 * p.tiles_n) + 2 * tn), rec,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
             }
         }
-        int* lds_word = reinterpret_cast<int*>(smem) + BM * WAVES_N * 3 + 4;                  // between `red` and `fin`
+        int* lds_word = reinterpret_cast<int*>(smem) + BM * RS * 4 + 4;                        // between `red` and `fin`
         const bool arrived = panel_publish_and_wait(p, p.flags + static_cast<int64_t>(panel) * p.tiles_n, tn, p.tiles_n, lds_word);
-        const bool ln = p.norm == LOKA_NORM_LAYERNORM;
         // Merge: the workgroup's BM rows are spread over its threads (TPR threads per row, each folding a
         // contiguous share of the row's tiles_n entries in order, read with device-coherent 8-byte loads
-        // that bypass stale cache lines); shares are combined with the symmetric merge, the row's final
+        // that bypass stale cache lines); shares are combined like the parts of a tile, the row's final
         // (mean, rstd) goes through LDS to the lanes that own the row.  Every workgroup of the panel runs
         // the same procedure on the same words, so all of them normalize with identical statistics.
         {
             constexpr int T = NW * 64, TPR = T / BM >= 1 ? T / BM : 1;
             static_assert(T % BM == 0 || T < BM, "threads per row");
-            float2* fin = reinterpret_cast<float2*>(smem) + BM * WAVES_N * 3 / 2 + 8;   // after `red`
+            float2* fin = reinterpret_cast<float2*>(smem) + BM * RS * 2 + 8;            // after `red`
             for (int r0 = 0; r0 < BM; r0 += T / TPR) {
                 const int r = r0 + static_cast<int>(threadIdx.x) / TPR, sub = static_cast<int>(threadIdx.x) % TPR;
                 int m = m0 + r;
@@ -698,42 +756,39 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
                 float n_ = 0.f, mean = 0.f, m2 = 0.f;
                 for (int t0 = sub * TH; t0 < (sub + 1) * TH && t0 < p.tiles_n; t0 += 8) {
                     unsigned long long raw[8];
-#pragma unroll
-                    for (int u = 0; u < 8; ++u) {
-                        int tt = t0 + u;
-                        tt = tt < p.tiles_n ? tt : p.tiles_n - 1;
-                        raw[u] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src + 2 * tt),
-                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    }
+                    float wc[8], nb = 0.f, sb = 0.f, m2b = 0.f;
 #pragma unroll
                     for (int u = 0; u < 8; ++u) {
                         const int tt = t0 + u;
+                        raw[u] = 0;
+                        wc[u] = 0.f;
                         if (tt < (sub + 1) * TH && tt < p.tiles_n) {
-                            const float a = __uint_as_float(static_cast<unsigned>(raw[u]));
-                            const float b2 = __uint_as_float(static_cast<unsigned>(raw[u] >> 32));
-                            const int wcols = (tt + 1) * BN <= p.N ? BN : p.N - tt * BN;
-                            if (ln) merge_stats(n_, mean, m2, static_cast<float>(wcols), a, b2);
-                            else m2 += b2;
+                            raw[u] = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(src + 2 * tt),
+                                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                            wc[u] = static_cast<float>((tt + 1) * BN <= p.N ? BN : p.N - tt * BN);
                         }
                     }
-                }
 #pragma unroll
-                for (int msk = 1; msk < TPR; msk <<= 1) {
-                    const float nb = wave_shfl_xor(n_, msk), mb = wave_shfl_xor(mean, msk), m2b = wave_shfl_xor(m2, msk);
-                    if (ln) {
-                        const float nn = n_ + nb;
-                        if (nn > 0.f) {
-                            const float d = mb - mean;
-                            const float rn = __builtin_amdgcn_rcpf(nn);
-                            const float newmean = (n_ * mean + nb * mb) * rn;
-                            m2 = m2 + m2b + d * d * (n_ * nb * rn);
-                            mean = newmean;
-                        }
-                        n_ = nn;
-                    } else {
-                        m2 = m2 + m2b;
+                    for (int u = 0; u < 8; ++u) {
+                        nb += wc[u];
+                        sb = __builtin_fmaf(wc[u], __uint_as_float(static_cast<unsigned>(raw[u])), sb);
                     }
+                    const float mb = ln ? sb * rcp0(nb) : 0.f;
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        const float d = ln ? __uint_as_float(static_cast<unsigned>(raw[u])) - mb : 0.f;
+                        m2b += __builtin_fmaf(wc[u] * d, d, __uint_as_float(static_cast<unsigned>(raw[u] >> 32)));
+                    }
+                    merge_stats(n_, mean, m2, nb, mb, m2b);
                 }
+                float s = n_ * mean;
+#pragma unroll
+                for (int msk = 1; msk < TPR; msk <<= 1) s += wave_shfl_xor(s, msk);
+                const float row_mean = s * inv_n, dm = mean - row_mean;
+                m2 = __builtin_fmaf(n_ * dm, dm, m2);
+#pragma unroll
+                for (int msk = 1; msk < TPR; msk <<= 1) m2 += wave_shfl_xor(m2, msk);
+                mean = row_mean;
                 // (a wait that ran out: the row statistics are not to be trusted, the tile's rows leave as NaN)
                 if (sub == 0 && r < BM)
                     fin[r] = arrived ? make_float2(ln ? mean : 0.f, __builtin_amdgcn_rsqf(m2 * inv_n + p.eps))
@@ -750,7 +805,6 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
     }
 
     // ---- normalize, affine, bf16 store
-    const bool has_g = p.gamma != nullptr && !blocknorm, has_b = p.beta != nullptr && p.norm == LOKA_NORM_LAYERNORM;
 #pragma unroll
     for (int h = 0; h < NSPLIT; ++h) {
 #pragma unroll
@@ -758,29 +812,24 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
             const int n = ncol[h] + coff_of(tp);
             if (n >= p.N) continue;
             float gm[8], bt[8];
+            if constexpr (!EARLY_AFFINE) load_affine(h, tp);
+            const u32x4 gv = gw[h][tp / 2], bv = bw[h][tp / 2];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) { gm[e] = 1.f; bt[e] = 0.f; }
-            if (has_g && p.norm != LOKA_NORM_NONE) {
-                const u32x4 w = *reinterpret_cast<const u32x4*>(p.gamma + n);
-                gm[0] = bf16_lo(w.x); gm[1] = bf16_hi(w.x); gm[2] = bf16_lo(w.y); gm[3] = bf16_hi(w.y);
-                gm[4] = bf16_lo(w.z); gm[5] = bf16_hi(w.z); gm[6] = bf16_lo(w.w); gm[7] = bf16_hi(w.w);
-            }
-            if (has_b) {
-                const u32x4 w = *reinterpret_cast<const u32x4*>(p.beta + n);
-                bt[0] = bf16_lo(w.x); bt[1] = bf16_hi(w.x); bt[2] = bf16_lo(w.y); bt[3] = bf16_hi(w.y);
-                bt[4] = bf16_lo(w.z); bt[5] = bf16_hi(w.z); bt[6] = bf16_lo(w.w); bt[7] = bf16_hi(w.w);
+            for (int e = 0; e < 4; ++e) {
+                gm[2 * e] = bf16_lo(gv[e]); gm[2 * e + 1] = bf16_hi(gv[e]);
+                bt[2 * e] = bf16_lo(bv[e]); bt[2 * e + 1] = bf16_hi(bv[e]);
             }
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi) {
                 const int m = m0 + wave_m * WM + mi * 16 + l16;
                 if (m >= p.M) continue;
+                const float nmr = -mean_r[mi] * rstd_r[mi];
                 float o[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const float yv = acc[h][mi][tp + (e >> 2)][e & 3];
-                    o[e] = (yv - mean_r[mi]) * rstd_r[mi];
-                    if (has_g && p.norm != LOKA_NORM_NONE) o[e] *= gm[e];
-                    if (has_b) o[e] += bt[e];
+                    o[e] = __builtin_fmaf(yv, rstd_r[mi], nmr);
+                    if (has_g || has_b) o[e] = __builtin_fmaf(o[e], gm[e], bt[e]);
                 }
                 if (blocknorm && p.act == LOKA_ACT_HARDSWISH) {
 #pragma unroll
