@@ -1050,7 +1050,7 @@ static void launch_fp8(const GemmParams& p, bool blockwise, dim3 grid, hipStream
 // gemm_wreg.hip
 bool wreg_supports(int64_t M, int64_t N, int64_t K);
 bool wreg_supports_fused(int64_t M, int64_t N, int64_t K);
-int wreg_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool fp8_out, bool bf16_in, const void** fn, size_t* lds);
+int wreg_plan(const GemmParams& p, int64_t batch, int cus, const void** fn, size_t* lds);
 void wreg_launch(const GemmParams& p, dim3 grid, hipStream_t s);
 static void launch_wreg_any(const GemmParams& p, bool, dim3 grid, hipStream_t s) { wreg_launch(p, grid, s); }
 static const char kWregName[] = "wreg32";
@@ -1710,7 +1710,7 @@ static loka_status gemm_norm_launch_impl(const loka_gemm_desc* d, int v, const u
         const void* fn = nullptr;
         size_t lds = 0;
         const int wgs = vi.name == kWregName
-                            ? wreg_plan(d->M, d->N, d->K, d->batch, cus, p.outq != nullptr, p.xb != nullptr && !p.qpro, &fn, &lds)
+                            ? wreg_plan(p, d->batch, cus, &fn, &lds)
                             : strip_plan(d->M, d->N, d->K, d->batch, cus, p.xb != nullptr, p.outq != nullptr, &fn, &lds);
         if (wgs <= 0) return LOKA_ERR_UNSUPPORTED;
         if (prepare_fn(dev, fn, vi.threads, lds, nullptr) != LOKA_OK) return LOKA_ERR_HIP;

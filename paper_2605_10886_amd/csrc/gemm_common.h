@@ -116,14 +116,20 @@ __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt(0x0F70 | (N_ & 15) | ((N_ >> 4) << 14));
 }
 
-// Sum over lanes l, l ^ 16, l ^ 32, l ^ 48 (identical bits on all four), by the row and half swaps of the vector unit: no LDS
-// round trip, which a shuffle is.
-__device__ __forceinline__ float row_lanes_sum(float v) {
-    typedef unsigned u2 __attribute__((ext_vector_type(2)));
-    u2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = __uint_as_float(r.x) + __uint_as_float(r.y);
-    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+// Sums over lanes l, l ^ 32 and over l, l ^ 16, l ^ 32, l ^ 48 (identical bits on all of them), by the half and row swaps of the
+// vector unit: no LDS round trip, which a shuffle is.
+typedef unsigned u32_pair __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float half_lanes_sum(float v) {
+    const u32_pair r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r.x) + __uint_as_float(r.y);
+}
+__device__ __forceinline__ float half_lanes_max(float v) {
+    const u32_pair r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __builtin_fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+}
+__device__ __forceinline__ float row_lanes_sum(float v) {
+    const u32_pair r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return half_lanes_sum(__uint_as_float(r.x) + __uint_as_float(r.y));
 }
 
 // Chan's pairwise merge of (count, mean, M2).

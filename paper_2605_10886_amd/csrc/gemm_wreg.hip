@@ -47,7 +47,7 @@ struct WregCfg {
     static constexpr int OFF_SW = OFF_OB + OBYTES;        // [NT] fp32 column scales (0 beyond N)
     static constexpr int OFF_GM = OFF_SW + NT * 4;        // [NT] fp32 gamma (1 when absent)
     static constexpr int OFF_BT = OFF_GM + NT * 4;        // [NT] fp32 beta (0 when absent)
-    static constexpr int OFF_RED = OFF_BT + NT * 4;       // [RB][9] (count, mean, M2, -); 9: rows on distinct banks
+    static constexpr int OFF_RED = OFF_BT + NT * 4;       // [RB][9] (count, mean, M2, -), from the extremes (max, mean, M2, min); 9: rows on distinct banks
     static constexpr int LDS_RUN = OFF_RED + RB * 9 * 16;
     static constexpr int STAGE = NT * KB < 131072 ? NT * KB : 131072;   // W staging at the start of a problem (overlays the rest)
     static constexpr int LDS = LDS_RUN > STAGE ? LDS_RUN : STAGE;
@@ -196,9 +196,17 @@ struct QuantPrologue {
     }
 };
 
-template <int WNC, int KS, int RT, bool FP8OUT, bool BF16IN>
+// What leaves the kernel: bf16; e4m3 codes and row scales converted from the staged bf16 values once the row's amax is known;
+// the same codes with the amax taken from the row's extremes before normalization, wherever the normalized value is a
+// monotone function of the product (a row norm without gamma, beta and activation).  The extremes travel with the statistics,
+// so the codes are made in registers and staged as bytes: half the LDS traffic, one barrier and one pass over the staged
+// values less (65536 x 256 x 1024: 1.29 -> 1.11 times the bf16 call's time on the same card, 50 -> 43 us).
+enum { OUT_BF16 = 0, OUT_FP8 = 1, OUT_FP8_EXT = 2 };
+
+template <int WNC, int KS, int RT, int OUT, bool BF16IN>
 __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, const int blocks_per_problem) {
     using C = WregCfg<WNC, KS, RT>;
+    constexpr bool FP8OUT = OUT == OUT_FP8, FP8EXT = OUT == OUT_FP8_EXT;
     constexpr int NIW = C::NIW, KB = C::KB, NT = C::NT, RB = C::RB, NBUF = C::NBUF, LPW = C::LPW, LDW = C::LDW, SXL = C::SXL;
     constexpr int KEYMASK = C::SWIN - 1;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -444,7 +452,7 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
     // With FP8 output the deferred step also converts: a lane reads 16 staged bf16 values, scales them with the
     // row's quantization factor (left in LDS by the block's epilogue) and stores 16 codes.
     constexpr bool DEFER = !BF16IN;
-    constexpr int CPR = FP8OUT ? NT / 16 : NT / 8;                      // 16-byte output chunks per row
+    constexpr int CPR = FP8OUT || FP8EXT ? NT / 16 : NT / 8;                     // 16-byte output chunks per row
     constexpr int SW_ = DEFER ? 8 : 4;                                  // waves that store (deferred: all of them)
     constexpr int INSTR_ = RB * CPR / 64 / SW_;
     constexpr int INSTR = INSTR_ > 0 ? INSTR_ : 1;                      // store instructions per storing wave and block
@@ -478,6 +486,12 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
         // exists (rows past M are dropped by its bound, no compare and no branch), the per-lane offset is 32 bits wide
         // (a block is at most RB * N * 2 bytes), columns past N get an offset beyond the bound.
         const unsigned ur = static_cast<unsigned>(id) / CPR, uc = static_cast<unsigned>(id) % CPR;
+        if (FP8EXT) {                                                   // (a row of codes: NT staged bytes; fewer than a wave's share: ur past the block)
+            const u32x4 ck = *reinterpret_cast<const u32x4*>(smem + C::OFF_OB + (ur % RB) * NT + ((uc ^ (ur & 15)) << 4));
+            const unsigned qoff = uc * 16 < static_cast<unsigned>(p.N) && ur < RB ? ur * static_cast<unsigned>(p.N) + uc * 16 : 0xFFFFFFF0u;
+            __builtin_amdgcn_raw_buffer_store_b128(ck, pend_rsrc, static_cast<int>(qoff), 0, 2 /* streaming (nt) */);
+            return;
+        }
         const u32x4 pk = *reinterpret_cast<const u32x4*>(smem + C::OFF_OB + ur * (NT * 2) + ((uc ^ (ur & 15)) << 4));
         const unsigned voff = uc * 8 < static_cast<unsigned>(p.N) ? ur * (2u * static_cast<unsigned>(p.N)) + uc * 16 : 0xFFFFFFF0u;
         __builtin_amdgcn_raw_buffer_store_b128(pk, pend_rsrc, static_cast<int>(voff), 0, 2 /* streaming (nt) */);
@@ -485,6 +499,9 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
     // descriptor of block (sg, sm0) of the bf16 output: its rows that exist
     auto out_rsrc = [&](int sg, int sm0) __attribute__((always_inline)) {
         const int rows_here = p.M - sm0 < RB ? p.M - sm0 : RB;
+        if (FP8EXT)
+            return __builtin_amdgcn_make_buffer_rsrc(
+                p.outq + static_cast<int64_t>(sg) * p.strideO + static_cast<int64_t>(sm0) * p.N, 0, rows_here * p.N, 0x00020000);
         return __builtin_amdgcn_make_buffer_rsrc(
             p.out + static_cast<int64_t>(sg) * p.strideO + static_cast<int64_t>(sm0) * p.N, 0, rows_here * p.N * 2, 0x00020000);
     };
@@ -559,6 +576,10 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
             colbase[ni] = wave * WNC + ni * 32 + hk * 16;
             if (colbase[ni] < p.N) cnt_lane += 16.f;                    // N % 16 == 0
         }
+        const int wcols = p.N - wave * WNC;                             // columns that the wave holds
+        const float cnt_wave = static_cast<float>(wcols < 0 ? 0 : wcols < WNC ? wcols : WNC);
+        const float rc_lane = cnt_lane > 0.f ? __builtin_amdgcn_rcpf(cnt_lane) : 0.f;
+        const float rc_wave = cnt_wave > 0.f ? __builtin_amdgcn_rcpf(cnt_wave) : 0.f;
         uint8_t* const obuf = smem + C::OFF_OB;
         float4* const red = reinterpret_cast<float4*>(smem + C::OFF_RED);
 
@@ -641,48 +662,57 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
                     }
             }
             if (p.norm != LOKA_NORM_NONE) {
-                float n_ = cnt_lane, mean = 0.f, m2 = 0.f;
+                // (Branch-free, the halves of a row by the vector unit's half swap, no LDS shuffle and no merge with a reciprocal:
+                // LayerNorm at 65536 rows, K x N 256 x 512 25.6 -> 24.2 us, 512 x 512 31.7 -> 30.5.  Columns past N hold
+                // zeros: they add nothing to the sums, and their centred value is taken as zero.)
+                float mean = 0.f, m2 = 0.f;
                 if (ln) {
-                    float s = 0.f;
+                    float s4[4] = {0.f, 0.f, 0.f, 0.f}, q4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int ni = 0; ni < NIW; ++ni)
-                        if (colbase[ni] < p.N) {
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) s += acc[rt][ni][i];
-                        }
-                    mean = n_ > 0.f ? s * __builtin_amdgcn_rcpf(n_) : 0.f;
+                        for (int i = 0; i < 16; ++i) s4[i & 3] += acc[rt][ni][i];
+                    const float s = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+                    const float mean_l = s * rc_lane;
 #pragma unroll
-                    for (int ni = 0; ni < NIW; ++ni)
-                        if (colbase[ni] < p.N) {
+                    for (int ni = 0; ni < NIW; ++ni) {
+                        const float mean_in = colbase[ni] < p.N ? mean_l : 0.f;
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) { const float d = acc[rt][ni][i] - mean; m2 = __builtin_fmaf(d, d, m2); }
-                        }
-                    // lanes l and l ^ 32 hold the same row: symmetric merge, identical bits on both
-                    const float nb = wave_shfl_xor(n_, 32), mb = wave_shfl_xor(mean, 32), m2b = wave_shfl_xor(m2, 32);
-                    const float nn = n_ + nb;
-                    if (nn > 0.f) {
-                        const float d = mb - mean;
-                        const float rn = __builtin_amdgcn_rcpf(nn);
-                        const float newmean = (n_ * mean + nb * mb) * rn;
-                        m2 = m2 + m2b + d * d * (n_ * nb * rn);
-                        mean = newmean;
+                        for (int i = 0; i < 16; ++i) { const float d = acc[rt][ni][i] - mean_in; q4[i & 3] = __builtin_fmaf(d, d, q4[i & 3]); }
                     }
-                    n_ = nn;
+                    mean = half_lanes_sum(s) * rc_wave;
+                    const float d = mean_l - mean;
+                    m2 = half_lanes_sum(__builtin_fmaf(cnt_lane * d, d, (q4[0] + q4[1]) + (q4[2] + q4[3])));
                 } else {
+                    float q4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                     for (int ni = 0; ni < NIW; ++ni)
-                        if (colbase[ni] < p.N) {
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) m2 = __builtin_fmaf(acc[rt][ni][i], acc[rt][ni][i], m2);
-                        }
-                    m2 += wave_shfl_xor(m2, 32);
+                        for (int i = 0; i < 16; ++i) q4[i & 3] = __builtin_fmaf(acc[rt][ni][i], acc[rt][ni][i], q4[i & 3]);
+                    m2 = half_lanes_sum((q4[0] + q4[1]) + (q4[2] + q4[3]));
                 }
-                if (hk == 0) red[(rt * 32 + l32) * 9 + wave] = make_float4(n_, mean, m2, 0.f);
+                float hi = cnt_wave, lo = 0.f;
+                if (FP8EXT) {
+                    hi = -__builtin_inff();
+                    lo = __builtin_inff();
+#pragma unroll
+                    for (int ni = 0; ni < NIW; ++ni) {
+                        float h = acc[rt][ni][0], l = h;
+#pragma unroll
+                        for (int i = 1; i < 16; ++i) { h = __builtin_fmaxf(h, acc[rt][ni][i]); l = __builtin_fminf(l, acc[rt][ni][i]); }
+                        const bool in = colbase[ni] < p.N;
+                        hi = in ? __builtin_fmaxf(hi, h) : hi;
+                        lo = in ? __builtin_fminf(lo, l) : lo;
+                    }
+                    hi = half_lanes_max(hi);
+                    lo = -half_lanes_max(-lo);
+                }
+                if (hk == 0) red[(rt * 32 + l32) * 9 + wave] = make_float4(hi, mean, m2, lo);
             }
         }
-        float mean_r[RT], rstd_r[RT];
+        float mean_r[RT], rstd_r[RT], qf_r[RT];                         // (qf_r: the row's quantization factor, FP8 output from the extremes)
 #pragma unroll
-        for (int rt = 0; rt < RT; ++rt) { mean_r[rt] = 0.f; rstd_r[rt] = 1.f; }
+        for (int rt = 0; rt < RT; ++rt) { mean_r[rt] = 0.f; rstd_r[rt] = 1.f; qf_r[rt] = 1.f; }
         if (p.norm != LOKA_NORM_NONE) {
             lds_barrier();
             // The two lanes that hold a row (l and l ^ 32) take four waves' entries each and add their halves (a + b ==
@@ -696,12 +726,21 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
                 float4 r[4];
 #pragma unroll
                 for (int w = 0; w < 4; ++w) r[w] = red[(rt * 32 + l32) * 9 + 4 * hk + w];
+                float hi = -__builtin_inff(), lo = __builtin_inff();
+                if (FP8EXT) {
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        hi = __builtin_fmaxf(hi, r[w].x);
+                        lo = __builtin_fminf(lo, r[w].w);
+                        const int c = p.N - (4 * hk + w) * WNC;
+                        r[w].x = static_cast<float>(c < 0 ? 0 : c < WNC ? c : WNC);
+                    }
+                }
                 if (ln) {
                     float s1 = 0.f;
 #pragma unroll
                     for (int w = 0; w < 4; ++w) s1 = __builtin_fmaf(r[w].x, r[w].y, s1);
-                    s1 += wave_shfl_xor(s1, 32);
-                    tmean = s1 * inv_n;
+                    tmean = half_lanes_sum(s1) * inv_n;
 #pragma unroll
                     for (int w = 0; w < 4; ++w) {
                         const float d = r[w].y - tmean;
@@ -714,9 +753,22 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
                         if (!blocknorm || (4 * hk + w) / WPG == wave / WPG) tm2 += r[w].z;
                     }
                 }
-                tm2 += wave_shfl_xor(tm2, 32);
+                tm2 = half_lanes_sum(tm2);
                 mean_r[rt] = tmean;
                 rstd_r[rt] = __builtin_amdgcn_rsqf(tm2 * (blocknorm ? 1.0f / 256.0f : inv_n) + p.eps);
+                if (FP8EXT) {
+                    hi = half_lanes_max(hi);
+                    lo = -half_lanes_max(-lo);
+                    // the normalized extremes, rounded to bf16 like every value of the row; larger magnitude as bits
+                    const float nmr = -mean_r[rt] * rstd_r[rt];
+                    const uint32_t pk = pack_bf16x2(__builtin_fmaf(hi, rstd_r[rt], nmr), __builtin_fmaf(lo, rstd_r[rt], nmr)) & 0x7FFF7FFFu;
+                    const uint32_t amax = (pk & 0xFFFFu) > (pk >> 16) ? pk & 0xFFFFu : pk >> 16;
+                    float scale;
+                    group_scale(__uint_as_float(amax << 16), scale, qf_r[rt]);
+                    // (by a storer wave: a loader's memory counter must not hold a store this young)
+                    const int m = m0 + rt * 32 + l32;
+                    if (wave == 4 && hk == 0 && m < p.M) p.outs[static_cast<int64_t>(g) * p.M + m] = scale;
+                }
             }
         } else if (DEFER) {
             lds_barrier();      // every wave has read its part of the previous block out of the staging buffer
@@ -787,7 +839,26 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
                 }
             }
         };
-        if (affine) stage(std::true_type{}); else stage(std::false_type{});
+        if constexpr (FP8EXT) {
+            // 16 codes of a row per lane and tile, straight from the accumulators (row 32 rt + l32, NT bytes; 16-byte chunk c
+            // at position c ^ (row % 16))
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt) {
+                const float rstd = rstd_r[rt], nmr = -mean_r[rt] * rstd, qf = qf_r[rt];
+#pragma unroll
+                for (int ni = 0; ni < NIW; ++ni) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    u32x4 ck;
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const uint32_t p0 = pack_bf16x2(__builtin_fmaf(acc[rt][ni][4 * a], rstd, nmr), __builtin_fmaf(acc[rt][ni][4 * a + 1], rstd, nmr));
+                        const uint32_t p1 = pack_bf16x2(__builtin_fmaf(acc[rt][ni][4 * a + 2], rstd, nmr), __builtin_fmaf(acc[rt][ni][4 * a + 3], rstd, nmr));
+                        ck[a] = e4m3x4(bf16_lo(p0) * qf, bf16_hi(p0) * qf, bf16_lo(p1) * qf, bf16_hi(p1) * qf);
+                    }
+                    *reinterpret_cast<u32x4*>(obuf + (rt * 32 + l32) * NT + (((colbase[ni] >> 4) ^ (l32 & 15)) << 4)) = ck;
+                }
+            }
+        } else if (affine) stage(std::true_type{}); else stage(std::false_type{});
         if (FP8OUT) {
             // ---- FP8 output for the next layer: the staged bf16 values quantized per row exactly as the quantize
             // entry point would quantize the stored bf16 tensor (amax over the row of |bf16 value|, scale =
@@ -837,6 +908,7 @@ struct WregInst {
     int wnc, ks, rb;
     const void* fn;      // bf16 output
     const void* fn_q;    // e4m3 output
+    const void* fn_qx;   // e4m3 output from the row's extremes
     const void* fn_b;    // bf16 input, quantized in the kernel
     size_t lds;
     void (*launch)(const GemmParams&, int, dim3, hipStream_t);
@@ -848,24 +920,33 @@ struct WregInst {
 template <int WNC, int KS, int RT>
 constexpr bool kWregFused = WNC * KS < 512;
 
+// FP8 output from the row's extremes: the normalized value has to be a monotone function of the product
+bool wreg_from_extremes(const GemmParams& p) {
+    return (p.norm == LOKA_NORM_LAYERNORM || p.norm == LOKA_NORM_RMSNORM) && p.gamma == nullptr && p.beta == nullptr && p.act == LOKA_ACT_NONE;
+}
+
 template <int WNC, int KS, int RT>
 void launch_wreg(const GemmParams& p, int bpp, dim3 grid, hipStream_t s) {
+    using C = WregCfg<WNC, KS, RT>;
     if (p.xb && !p.qpro) {
         if constexpr (kWregFused<WNC, KS, RT>)
-            gemm_wreg_kernel<WNC, KS, RT, false, true><<<grid, 512, WregCfg<WNC, KS, RT>::LDS, s>>>(p, bpp);
-    } else if (p.outq) gemm_wreg_kernel<WNC, KS, RT, true, false><<<grid, 512, WregCfg<WNC, KS, RT>::LDS, s>>>(p, bpp);
-    else gemm_wreg_kernel<WNC, KS, RT, false, false><<<grid, 512, WregCfg<WNC, KS, RT>::LDS, s>>>(p, bpp);
+            gemm_wreg_kernel<WNC, KS, RT, OUT_BF16, true><<<grid, 512, C::LDS, s>>>(p, bpp);
+    } else if (p.outq) {
+        if (wreg_from_extremes(p)) gemm_wreg_kernel<WNC, KS, RT, OUT_FP8_EXT, false><<<grid, 512, C::LDS, s>>>(p, bpp);
+        else gemm_wreg_kernel<WNC, KS, RT, OUT_FP8, false><<<grid, 512, C::LDS, s>>>(p, bpp);
+    } else gemm_wreg_kernel<WNC, KS, RT, OUT_BF16, false><<<grid, 512, C::LDS, s>>>(p, bpp);
 }
 
 template <int WNC, int KS, int RT>
 const void* wreg_fused_fn() {
-    if constexpr (kWregFused<WNC, KS, RT>) return reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, false, true>);
+    if constexpr (kWregFused<WNC, KS, RT>) return reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, OUT_BF16, true>);
     else return nullptr;
 }
 
 #define LOKA_WREG(WNC, KS, RT)                                                                                   \
-    {WNC, KS, 32 * RT, reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, false, false>),               \
-     reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, true, false>),                                  \
+    {WNC, KS, 32 * RT, reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, OUT_BF16, false>),               \
+     reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, OUT_FP8, false>),                               \
+     reinterpret_cast<const void*>(&gemm_wreg_kernel<WNC, KS, RT, OUT_FP8_EXT, false>),                           \
      wreg_fused_fn<WNC, KS, RT>(), WregCfg<WNC, KS, RT>::LDS,                                                     \
      &launch_wreg<WNC, KS, RT>}
 
@@ -897,11 +978,13 @@ bool wreg_supports(int64_t M, int64_t N, int64_t K) {
 }
 
 // Workgroups to launch and the kernel's entry (for the dynamic-LDS attribute); 0 when unsupported.
-int wreg_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool fp8_out, bool bf16_in, const void** fn,
-              size_t* lds) {
-    const WregInst* w = wreg_pick(N, K);
+int wreg_plan(const GemmParams& p, int64_t batch, int cus, const void** fn, size_t* lds) {
+    const int64_t M = p.M;
+    const WregInst* w = wreg_pick(p.N, p.KB);
+    const bool bf16_in = p.xb && !p.qpro;
+    const int out = !p.outq ? OUT_BF16 : wreg_from_extremes(p) ? OUT_FP8_EXT : OUT_FP8;
     if (!w) return 0;
-    *fn = bf16_in ? w->fn_b : fp8_out ? w->fn_q : w->fn;
+    *fn = bf16_in ? w->fn_b : out == OUT_FP8_EXT ? w->fn_qx : out == OUT_FP8 ? w->fn_q : w->fn;
     *lds = w->lds;
     const int64_t blocks = batch * ((M + w->rb - 1) / w->rb);
     return static_cast<int>(blocks < cus ? blocks : cus);

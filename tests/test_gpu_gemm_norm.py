@@ -1158,3 +1158,29 @@ def test_fused_quantization_c4_full_size(orc, variant):
         ok, worst, _ = check_bf16_out(to_np_bits(o1[idx]), orc.norm(y_o, B.NORM_RMSNORM),
                                       abs_tol=propagated_abs_tol(y_o, err, B.NORM_RMSNORM, 1e-5))
         assert ok, f"group {g}: worst {worst} ulps"
+
+
+# the streaming kernel's FP8 output is the quantize entry point's result on its own bf16 output, byte for byte, both where the
+# row amax is taken from the row's extremes (no gamma) and where it is taken from the staged values; each instantiation, rows
+# and columns that do not fill a block or a wave, several problems, a zero row and a row whose scale is NaN
+@pytest.mark.parametrize("shape", [(260, 128, 128, 1), (517, 256, 256, 1), (333, 512, 240, 1), (129, 1024, 112, 1), (640, 128, 512, 2),
+                                   (900, 256, 400, 1), (77, 512, 512, 1), (97, 128, 1024, 1), (100, 256, 1024, 3), (31, 256, 784, 1)])
+@pytest.mark.parametrize("norm", ["layernorm", "rmsnorm"])
+@pytest.mark.parametrize("gamma", [False, True])
+def test_streaming_fp8_output_is_the_quantized_bf16_output(shape, norm, gamma):
+    M, K, N, batch = shape
+    x = synth.normal(batch * M, K, seed=61).to(DEV)
+    x[3] = 0
+    xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+    sx[5] = float("nan")
+    ws = [B.loka_quantize(synth.weight(K, N, seed=62 + b).to(DEV), B.SCALE_COL, transpose_out=True) for b in range(batch)]
+    wq, sw = torch.cat([q for q, _ in ws]), torch.cat([s for _, s in ws])
+    g = synth.normal(1, N, seed=70).to(DEV).reshape(N) if gamma else None
+    desc = B.make_desc(M, N, K, batch, norm=B.NORMS[norm], variant=B.variant_id("wreg32"))
+    out, _ = B.loka_fp8_gemm_norm(desc, xq, sx, wq, sw, g)
+    oq, so, _ = B.loka_fp8_gemm_norm_fp8out(desc, xq, sx, wq, sw, g)
+    q, s = B.loka_quantize(out, B.SCALE_ROW)
+    rows = torch.arange(batch * M, device=DEV) != 5
+    assert torch.isnan(so[5]) and torch.isnan(out[5].float()).all()
+    assert torch.equal(so[rows], s[rows])
+    assert torch.equal(oq.view(torch.uint8)[rows], q.view(torch.uint8)[rows])
