@@ -1215,52 +1215,54 @@ static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Na
 // ---- expected time of a variant, in microseconds: what the static choice compares.
 // A launch is `start` plus, per round of workgroups (tiles over the slots of 256 CUs), `round` plus K steps of `step` +
 // `full` * (share of the slots in use: the last level caches and the power budget are shared), `lng` more from the 17th
-// step on and `ragged` more where K is no multiple of a step, plus `ln` for the row statistics (RMSNorm: 0.4 of it); plus X, W and the output at `x`, `w` and `out` per million elements, `out32` more where rows of the output are no
-// whole number of 64-byte lines (the panel kernels' streaming stores).  Kernels that exchange or re-read for a row norm
+// step on and `ragged` more where K is no multiple of a step, plus `ln` for the row statistics (RMSNorm: 0.4 of it); plus X, W
+// and the output at `x`, `w` and `out` per million elements, `out32` more where rows of the output are no whole number of 64-byte lines (the panel kernels' streaming stores).  Kernels that exchange or re-read for a row norm
 // add `norm` (per round; two-pass: per problem), two-pass also `once` and `norm_out` per million outputs.  Fitted
-// (non-negative least squares on relative error) to every variant's time at 5518 shapes, M 64 - 131072, N 64 - 16384, K 64 -
-// 131072; fitted to one half of them, the choice is within 0.8 % of the fastest variant in the geometric mean over the other
-// (worst 1.67).  profiles/variant_times.csv has the times of 2006 of them.  (A fit without `lng`, `ragged`, `x`, `w`, `ln`
-// and `out32` was at 2.1 %, worst 2.9: 101163 x 240 x 512 54 us on the 256 x 256 kernel, strip 30.  By tile width and row
-// count alone 25 %: 2048 x 768 x 256 17.5 us on 64-row tiles, 8.6 on 16-row tiles; 4096 x 1024 x 8192 143 us, split K 52.)
+// (non-negative least squares on relative error, variants far from the fastest of a shape counting less) to every variant's
+// time at 24182 shapes, M 64 - 131072, N 64 - 16384, K 64 - 131072; fitted to one half of them, the choice is within 1.1 % of
+// the fastest variant in the geometric mean over the other (block scales 0.5 %; the table before the branch-free epilogue
+// 1.5 % and 1.0 %: 5013 x 720 x 1008, M x N x K, 17.5 us on 32 x 256 tiles, 14.3 on 128 x 128).
+// profiles/variant_times.csv has the times of 2000 of them.  (A first fit without `lng`, `ragged`, `x`, `w`, `ln` and `out32`
+// was at 2.1 %, worst 2.9: 101163 x 240 x 512 54 us on the 256 x 256 kernel, strip 30.  By tile width and row count alone 25 %:
+// 2048 x 768 x 256 17.5 us on 64-row tiles, 8.6 on 16-row tiles; 4096 x 1024 x 8192 143 us, split K 52.)
 // Fixed figures for an MI355X, not the running device's: workspace sizes follow from the choice.
 struct CostRow { float start, round, step, full, lng, ragged, x, w, out, ln, norm, out32, once, norm_out; };
 struct VariantCost { const char* name; int per_cu; CostRow plain, block; };
 constexpr int kPlanCus = 256;
 static const VariantCost kCosts[] = {
-    {"row32x128", 3, {2.85f, .469f, .211f, 0.f, .147f, .0222f, .146f, 0.f, .46f, 1.39f},
-     {3.04f, 0.f, .374f, .0472f, .212f, 0.f, .145f, 0.f, .492f, 1.44f}},
-    {"row64x128", 3, {2.26f, 1.64f, .237f, .1f, .177f, .0139f, .105f, 0.f, .32f, 1.4f},
-     {3.38f, .0158f, .375f, .42f, .239f, 0.f, .0513f, 9.51f, .422f, 1.39f}},
-    {"row64x256", 2, {2.37f, 3.22f, .421f, 0.f, .185f, .0318f, .142f, .0464f, .291f, 3.24f},
-     {3.f, 1.89f, .876f, .38f, .318f, 0.f, .0187f, 4.07f, .367f, 3.19f}},
-    {"row128x256", 1, {1.79f, 4.01f, .824f, 0.f, .0365f, .0326f, .0389f, .038f, .292f, 3.16f},
-     {2.54f, 2.41f, 1.21f, .333f, .316f, 0.f, 0.f, 3.05f, .273f, 3.1f}},
-    {"row64x512", 1, {1.92f, 3.19f, .728f, 0.f, .155f, .0492f, .111f, .154f, .382f, 4.35f},
-     {2.01f, 2.5f, 1.32f, .146f, .324f, 0.f, .0463f, 3.66f, .337f, 4.35f}},
-    {"row64x1024", 1, {2.06f, 4.57f, 1.34f, 0.f, 0.f, .0204f, .265f, 0.f, .118f, 4.91f},
-     {2.75f, 3.17f, 2.14f, 0.f, .526f, 0.f, .54f, 0.f, 0.f, 5.19f}},
-    {"row16x256", 2, {1.92f, 1.95f, .324f, 0.f, .127f, .0315f, .298f, .009f, .467f, .881f},
-     {1.91f, 1.61f, .382f, 0.f, .217f, 0.f, .31f, 3.5f, .369f, .972f}},
-    {"row32x256", 2, {2.05f, 2.4f, .327f, 0.f, .151f, .0291f, .197f, .0185f, .339f, 1.67f},
-     {2.03f, 1.94f, .559f, .0785f, .243f, 0.f, .103f, 3.17f, .377f, 1.66f}},
-    {"row16x512", 1, {1.8f, 2.f, .51f, 0.f, .182f, .0317f, .415f, .0663f, .485f, 1.22f},
-     {1.71f, 1.89f, .643f, 0.f, .271f, 0.f, .445f, 2.23f, .291f, 1.19f}},
-    {"row32x512", 1, {1.8f, 2.45f, .547f, 0.f, .206f, .0389f, .253f, .132f, .387f, 2.2f},
-     {1.73f, 2.12f, .842f, 0.f, .293f, 0.f, .257f, 2.88f, .275f, 2.16f}},
-    {"row16x1024", 1, {2.09f, 2.62f, .775f, 0.f, .206f, .0349f, 1.05f, 0.f, 0.f, 1.38f},
-     {2.42f, 2.12f, .934f, 0.f, .486f, 0.f, 1.43f, 0.f, 0.f, 1.42f}},
-    {"twopass128x128", 2, {3.82f, .338f, .362f, .369f, .245f, .0426f, .0474f, .152f, .403f, 1.86f, 2.67f, 0.f, 2.19f, 1.77f},
-     {3.55f, 0.f, .892f, .396f, .322f, 0.f, .0488f, .181f, .358f, 1.09f, 5.39f, 0.f, 0.f, 1.68f}},
-    {"panel32x256", 2, {3.43f, 1.32f, .303f, .365f, .211f, .0849f, .0251f, .348f, .295f, 3.54f, 1.64f, .104f},
-     {3.37f, .748f, .646f, .238f, .238f, 0.f, .00889f, .241f, .36f, 3.17f, 1.85f}},
-    {"panel64x256", 2, {4.28f, 1.47f, .433f, .392f, .224f, .0808f, .0272f, .239f, .325f, 4.94f, 1.83f, .249f},
-     {4.2f, .41f, .997f, .303f, .286f, 0.f, .013f, .167f, .366f, 4.59f, 2.06f}},
-    {"panel128x128", 1, {3.56f, 1.47f, .499f, .105f, 0.f, .0132f, .0146f, .059f, .265f, 4.49f, 2.25f, .0312f},
-     {3.49f, 1.26f, .662f, .087f, 0.f, 0.f, 0.f, .11f, .253f, 4.07f, 2.65f}},
-    {kPanel32Name, 1, {3.52f, 4.92f, 1.02f, .315f, 0.f, 0.f, 0.f, 0.f, .181f, 1.23f, 3.69f, .398f},
-     {4.43f, 3.2f, 1.53f, .255f, 0.f, 0.f, 0.f, .0737f, .238f, 1.24f, 3.86f}},
-    {kPanel32RaggedName, 1, {3.86f, 4.85f, 1.06f, .281f, 0.f, 0.f, 0.f, .0134f, .207f, 1.37f, 3.74f, .514f},
+    {"row32x128", 3, {2.82f, .327f, .264f, 0.f, .0607f, .0117f, .131f, 0.f, .417f, .551f},
+     {2.97f, .0418f, .376f, .112f, .017f, 0.f, .125f, 0.f, .378f, .497f}},
+    {"row64x128", 3, {2.33f, 1.27f, .27f, 0.f, .113f, .0324f, .118f, 0.f, .309f, .733f},
+     {2.75f, .801f, .479f, .121f, .0668f, 0.f, .0989f, 0.f, .306f, .617f}},
+    {"row64x256", 2, {2.72f, 1.86f, .431f, .0809f, .139f, .0551f, .122f, .0257f, .309f, 1.41f},
+     {2.84f, 1.26f, .861f, 0.f, .0461f, 0.f, .166f, .656f, .292f, 1.27f}},
+    {"row128x256", 1, {2.32f, 2.85f, .81f, .0533f, .06f, .035f, .0313f, .0698f, .318f, 1.53f},
+     {1.99f, 2.62f, .943f, .21f, .155f, 0.f, 0.f, 4.33f, .272f, 1.49f}},
+    {"row64x512", 1, {2.26f, 2.51f, .766f, .208f, .129f, .0268f, 0.f, .0752f, .337f, 1.75f},
+     {1.97f, 2.48f, 1.17f, .126f, .191f, 0.f, 0.f, 2.72f, .281f, 1.72f}},
+    {"row64x1024", 1, {2.59f, 4.83f, .779f, 0.f, 0.f, .115f, .426f, .0893f, .148f, 2.69f},
+     {1.94f, 5.01f, .713f, 0.f, 0.f, 0.f, .582f, 6.66f, .067f, 2.49f}},
+    {"row16x256", 2, {2.02f, 1.43f, .381f, .0232f, .0235f, .0184f, .197f, .0215f, .468f, .423f},
+     {2.07f, 1.33f, .428f, 0.f, 0.f, 0.f, .254f, .762f, .429f, .391f}},
+    {"row32x256", 2, {2.13f, 1.73f, .361f, .0962f, .0621f, .0242f, .135f, .021f, .324f, .715f},
+     {2.44f, 1.25f, .581f, 0.f, .0356f, 0.f, .172f, .0771f, .354f, .66f}},
+    {"row16x512", 1, {1.66f, 2.01f, .597f, 0.f, .0287f, .0247f, .114f, .0389f, .425f, .584f},
+     {1.41f, 2.13f, .684f, .00668f, .0501f, 0.f, .119f, .713f, .248f, .562f}},
+    {"row32x512", 1, {1.72f, 2.43f, .628f, .0629f, .0841f, .0207f, .0713f, .0457f, .337f, 1.01f},
+     {1.43f, 2.38f, .781f, .0564f, .156f, 0.f, .0844f, 1.17f, .237f, .997f}},
+    {"row16x1024", 1, {1.89f, 2.97f, .599f, 0.f, 0.f, .0282f, 1.26f, 0.f, 0.f, .79f},
+     {1.81f, 2.87f, .699f, 0.f, .0113f, 0.f, 1.09f, .195f, 0.f, .789f}},
+    {"twopass128x128", 2, {3.59f, .713f, .418f, .402f, .131f, .0464f, .0335f, .0245f, .351f, .431f, 2.78f, 0.f, 2.2f, 1.53f},
+     {3.86f, .0412f, .809f, .423f, .0655f, 0.f, .0489f, .328f, .351f, .554f, 5.78f, 0.f, 0.f, 1.39f}},
+    {"panel32x256", 2, {3.87f, .387f, .347f, .309f, .102f, .0658f, .0483f, .223f, .395f, 1.43f, 2.09f, .149f},
+     {4.04f, 0.f, .582f, .234f, .113f, 0.f, .0502f, .148f, .465f, 1.11f, 2.24f}},
+    {"panel64x256", 2, {4.63f, .162f, .55f, .37f, .108f, .0861f, .0313f, .158f, .387f, 1.67f, 2.3f, .23f},
+     {4.62f, 0.f, .871f, .392f, .0876f, 0.f, .0514f, .281f, .348f, 1.39f, 2.48f}},
+    {"panel128x128", 1, {3.66f, 1.23f, .482f, .0953f, 0.f, .0277f, .0134f, .0382f, .316f, 1.3f, 2.83f, .0413f},
+     {3.67f, 1.14f, .569f, .0915f, 0.f, 0.f, .014f, .138f, .249f, 1.2f, 2.85f}},
+    {kPanel32Name, 1, {2.76f, 5.39f, .936f, .445f, 0.f, 0.f, 0.f, 0.f, .178f, 1.87f, 3.23f, .562f},
+     {3.13f, 5.15f, 1.14f, .502f, .0411f, 0.f, 0.f, .0807f, .144f, 2.02f, 3.12f}},
+    {kPanel32RaggedName, 1, {3.6f, 4.53f, .944f, .524f, 0.f, 0.f, 0.f, .0115f, .199f, 1.51f, 3.57f, .515f},
      {}},
 };
 // BlockNorm's choice between the large tile and the row tiles of its width (blocknorm_form), where rows are wider than a tile:
@@ -1277,9 +1279,9 @@ static const VariantCost kBlocknormCosts[] = {
 // and block scales.
 struct SplitkCost { float start, step, full, part, out, wide, wide_out; };
 static const SplitkCost kSplitkCosts[3][2] = {
-    {{8.01f, .537f, 0.f, 2.39f, 0.f, 2.11f, 2.93f}, {8.6f, .698f, 0.f, 2.23f, 0.f, .668f, 4.27f}},
-    {{7.63f, .591f, .355f, 2.07f, .467f, 2.06f, 3.49f}, {6.78f, 1.3f, 0.f, 2.19f, 0.f, 1.5f, 2.89f}},
-    {{15.f, .655f, .822f, .757f, .569f, 3.99f, 3.7f}, {16.f, 1.07f, .952f, .613f, .544f, 1.56f, 5.71f}}};
+    {{8.57f, .429f, .0372f, 2.05f, .0325f, 1.84f, 4.13f}, {9.4f, .336f, .285f, 1.77f, 0.f, 1.24f, 4.08f}},
+    {{8.63f, .351f, .685f, 1.6f, .249f, 1.56f, 4.62f}, {9.77f, .438f, .95f, 1.61f, 0.f, 1.36f, 3.41f}},
+    {{13.f, .568f, .805f, .941f, .71f, 1.13f, 4.19f}, {13.9f, .878f, .883f, .805f, .437f, 0.f, 4.34f}}};
 // ... and what decides between tiles of 128 and 256 on the long-range form.  An earlier fit, kept: a caller that names the
 // variant gets the same tiles (the two fits differ at 8 of 364 shapes).
 static const SplitkCost kSplitkTileCosts[2][2] = {{{10.7f, 0.f, .79f, 1.78f}, {12.f, .12f, 1.13f, 1.37f, .66f}},
@@ -1465,19 +1467,23 @@ int variant_fp8out_default(const loka_gemm_desc* d) {
 
 size_t variant_workspace(const loka_gemm_desc* d, int v, bool fp8out);
 // The static choice among the variants whose workspace fits `max_ws`: the least expected time.  The streaming kernel only
-// from 4096 rows on (below, its set-up is most of the launch and the fit does not describe it).  -1: none.
+// from 4096 rows on (below, its set-up is most of the launch and the fit does not describe it).  A tile that is less
+// than 5 % below the strip kernel does not displace it, so that the call keeps its last bits (36 of the 1360 shapes that it
+// takes: it is the faster one at 8 of them, the other by 4 % in the mean).  -1: none.
 int variant_cheapest(const loka_gemm_desc* d, size_t max_ws) {
     const int split = splitk_choice(d);
-    int best = -1;
-    double best_cost = 0.0;
+    int best = -1, strip = -1;
+    double best_cost = 0.0, strip_cost = 0.0;
     for (int v = 0; v < kNumVariants; ++v) {
         if (!variant_supports(d, v) || (kVariants[v].epi == EPI_SPLITK && v != split)) continue;
         if (kVariants[v].name == kWregName && d->M * d->batch < 4096) continue;
         const double c = variant_cost(d, v);
+        if (kVariants[v].name == kStripName) { strip = v; strip_cost = c; }
         if (c < 0.0 || (best >= 0 && c >= best_cost) || (max_ws != SIZE_MAX && variant_workspace(d, v, false) > max_ws)) continue;
         best = v;
         best_cost = c;
     }
+    if (strip >= 0 && kVariants[best].name != kWregName && 0.95 * strip_cost < best_cost) best = strip;
     return best;
 }
 
