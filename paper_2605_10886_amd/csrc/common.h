@@ -61,6 +61,18 @@ __device__ __forceinline__ uint32_t e4m3x4(float t0, float t1, float t2, float t
     return static_cast<uint32_t>(pk);
 }
 
+// The cast without the clamp, for values t = v * inv of a group whose amax is finite (inv = 448 / amax rounded, |v| <= amax):
+// |t| <= 448 (1 + 2^-23), which converts to 448 like 448 itself (the next boundary is 464).  An infinite or NaN amax needs the
+// clamp, which takes the NaN products to -448.
+__device__ __forceinline__ uint32_t e4m3x4_finite(float t0, float t1, float t2, float t3) {
+    int pk = 0;
+    pk = __builtin_amdgcn_cvt_pk_fp8_f32(t0, t1, pk, false);
+    pk = __builtin_amdgcn_cvt_pk_fp8_f32(t2, t3, pk, true);
+    return static_cast<uint32_t>(pk);
+}
+// whether any lane's amax (bf16 bits of a magnitude) is infinite or NaN (uniform)
+__device__ __forceinline__ bool any_not_finite(unsigned amax_bits) { return __builtin_amdgcn_ballot_w64(amax_bits >= 0x7F80u) != 0; }
+
 // amax floor, dequantization scale and quantization factor of one scale group:
 // each a single IEEE fp32 division.
 __device__ __forceinline__ void group_scale(float amax, float& scale, float& inv) {

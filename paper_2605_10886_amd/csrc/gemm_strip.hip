@@ -37,6 +37,14 @@ struct StripCfg {
     static constexpr int OFF_T = OFF_BT + NT * 4;         // [8 waves][2 KB] output staging (see the epilogue)
     static constexpr int LDS = OFF_T + 8 * 2048;
     static_assert(LDS <= 160 * 1024, "W, the tables and the staging buffers must fit the LDS");
+    // fused quantization with nwv waves, more than 128 columns: K steps of a wave's bf16 strip that wait in LDS, behind the
+    // staging buffers: all of them, half, or none (up to 128 columns registers and caches do: 64 x (4096 x 128 x 128),
+    // M x N x K, 26.0 us, 27.0 through LDS)
+    static constexpr int off_raw(int nwv) { return OFF_T + nwv * 2048; }
+    static constexpr int raw_steps(int nwv) {
+        return NPH != 1 || NB != 8 ? 0 : off_raw(nwv) + nwv * KS * 4096 <= 160 * 1024 ? KS : off_raw(nwv) + nwv * KS * 2048 <= 160 * 1024 ? KS / 2 : 0;
+    }
+    static constexpr int lds_fused(int nwv) { return raw_steps(nwv) ? off_raw(nwv) + nwv * raw_steps(nwv) * 4096 : LDS; }
 };
 
 // NWV waves per workgroup; BF16IN: X arrives as bf16 and is quantized per row (amax, scale, e4m3 cast: the
@@ -49,6 +57,11 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
     using C = StripCfg<NB, KS, NPH>;
     static_assert(!BF16IN || NPH == 1, "fused quantization needs the whole row of X in one pass");
     constexpr int NT = C::NT, KB = C::KB, KBT = C::KBT, KEYMASK = C::SWIN - 1;
+    // Up to rows of 256: statistics and stores without branches, and the next strip's operands awaited by count; with fused
+    // quantization the stores everywhere.  Longer rows' operands leave no registers for it: the kernel spills more (M x N x K:
+    // 65536 x 128 x 1024 21.5 -> 23.2 us, with FP8 output 23.9 -> 25.3 and 64 x (4096 x 256 x 512) 62.6 -> 64.8; but
+    // 64 x (4096 x 256 x 256) 38.9 -> 37.6 and, with FP8 output, 48.6 -> 45.6).
+    constexpr bool SHORT_ROWS = KS < 8 && NPH == 1, LEAN = SHORT_ROWS || BF16IN;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
     const int lane = threadIdx.x & 63;
@@ -63,6 +76,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb)
         if (nb * 32 + hk * 16 < p.N) cnt_lane += 16.f;     // N % 16 == 0: a run of 16 columns is all in or all out
+    const float rc_lane = cnt_lane > 0.f ? __builtin_amdgcn_rcpf(cnt_lane) : 0.f;
 
     // contiguous range of strips of this workgroup (strip = 32 rows of one problem)
     const int64_t total = static_cast<int64_t>(p.batch) * strips_per_problem;
@@ -109,18 +123,25 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
         const float* sxg = p.sx + static_cast<int64_t>(g) * p.strideSx;
         const int s_base = g * strips_per_problem;
 
+        const __amdgpu_buffer_rsrc_t sxr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(sxg), 0, tensor_x ? 4 : p.M * 4, 0x00020000);
         // operands of strip s, phase ph: row m0 + l32, K bytes [KB ph + 64 j + 32 hk, +32) per K step (rows past M
         // read as zeros)
-        auto load_x = [&](int s, int ph, v8i (&x)[KS], float& sxm) __attribute__((always_inline)) {
+        auto load_x = [&](int s, int ph, v8i (&x)[KS], float& sxm, bool live) __attribute__((always_inline)) {
             const int m = (s - s_base) * 32 + l32;
+            // (short rows: the first row's offset from a scalar register, beyond the descriptor's bound where there is no strip,
+            // so that the loads are the same on every path)
+            unsigned base = SHORT_ROWS ? (live ? static_cast<unsigned>((s - s_base) * 32) * KBT : 0x80000000u) : 0u;
+            if (SHORT_ROWS) asm volatile("; first row" : "+s"(base));
 #pragma unroll
             for (int j = 0; j < KS; ++j) {
-                const unsigned off = static_cast<unsigned>(m) * KBT + static_cast<unsigned>(ph * KB + (4 * j + 2 * hk) * 16);
+                const unsigned off = SHORT_ROWS ? base + static_cast<unsigned>(l32 * KBT + (4 * j + 2 * hk) * 16)
+                                                : static_cast<unsigned>(m) * KBT + static_cast<unsigned>(ph * KB + (4 * j + 2 * hk) * 16);
                 const v4i lo = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(xr, off, 0, 0));
                 const v4i hi = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(xr, off + 16u, 0, 0));
                 x[j] = v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
             }
-            sxm = tensor_x ? sxg[0] : (m < p.M ? sxg[m] : 0.f);
+            if (SHORT_ROWS) sxm = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sxr, tensor_x ? 0 : m * 4, 0, 0));
+            else sxm = tensor_x ? sxg[0] : (m < p.M ? sxg[m] : 0.f);
         };
 
         // Fused quantization: the lane's 32 bf16 values per K step (row m0 + l32, K elements [64 j + 32 hk, +32): 64
@@ -129,11 +150,13 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
         const __amdgpu_buffer_rsrc_t xbr = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<uint16_t*>(BF16IN ? p.xb + static_cast<int64_t>(g) * p.strideX : nullptr), 0,
             static_cast<unsigned>(p.M) * KBT * 2u, 0x00020000);
-        auto load_raw = [&](int s, u32x4 (&raw)[KS][4]) __attribute__((always_inline)) {
-            const int m = (s - s_base) * 32 + l32;
+        auto load_raw = [&](int s, u32x4 (&raw)[KS][4], int j0) __attribute__((always_inline)) {
+            int lane_o = lane;
+            if (BF16IN && C::raw_steps(NWV) > 0) asm volatile("; per-strip lane id" : "+v"(lane_o));
+            const int m = (s - s_base) * 32 + (lane_o & 31);
 #pragma unroll
-            for (int j = 0; j < KS; ++j) {
-                const unsigned off = static_cast<unsigned>(m) * (KBT * 2u) + static_cast<unsigned>((64 * j + 32 * hk) * 2);
+            for (int j = j0; j < KS; ++j) {
+                const unsigned off = static_cast<unsigned>(m) * (KBT * 2u) + static_cast<unsigned>((64 * j + 32 * (lane_o >> 5)) * 2);
 #pragma unroll
                 for (int q = 0; q < 4; ++q)
                     raw[j][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xbr, off + 16u * q, 0, 0));
@@ -152,19 +175,50 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                     raw[i / 4][i % 4] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xbr, off, 0, 0));
                 }
         };
+        // Where LDS has room the raw strip comes through it: loads straight into LDS move whole rows (1 KB runs; 16-byte chunk c
+        // of row r at c ^ (r % 16)), each lane then takes its pieces from there.  Requested straight into the lanes that
+        // need them a load instruction touches 64 lines for 16 bytes each, and four waves' strips do not stay in the CU's
+        // cache until the other pieces are asked for.  With half a strip there (and the other half in 32 registers instead of 64) eight
+        // waves fit a CU where four did (M x N x K: 100000 x 240 x 256 32.1 -> 25.2 us, 16 x (4096 x 256 x 256) 21.2 -> 18.0).
+        constexpr int KL = BF16IN ? C::raw_steps(NWV) : 0;                // K steps of 64 that come through LDS (the first ones)
+        constexpr bool RAWLDS = KL > 0;
+        constexpr int ROWB = KBT * 2, ROWL = RAWLDS ? KL * 128 : 128, RLD = KL * 4;
+        uint8_t* const rbuf = smem + C::off_raw(NWV) + wave * (KL * 4096);
+        auto request_raw = [&](int s) __attribute__((always_inline)) {
+            int lane_o = lane;
+            asm volatile("; per-strip lane id" : "+v"(lane_o));
+            // (load i covers rows i RPL .. + RPL - 1, a power of two, so that the swizzle key of a lane's row is (i RPL) ^ r)
+            constexpr int LPR = ROWL / 16, RPL = 64 / LPR;
+            const int r = lane_o / LPR, pos = (lane_o % LPR) ^ r;
+            const unsigned base = static_cast<unsigned>((s - s_base) * 32 + r) * ROWB;
+#pragma unroll
+            for (int i = 0; i < RLD; ++i)
+                // (rows past M lie behind the descriptor's bound and read as zeros)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xbr, (__attribute__((address_space(3))) void*)(rbuf + i * 1024), 16,
+                                                         base + i * RPL * ROWB + static_cast<unsigned>((pos ^ (i * RPL & 15)) << 4), 0, 0, 0);
+        };
+        auto read_raw = [&](u32x4 (&raw)[KS][4]) __attribute__((always_inline)) {
+            int lane_o = lane;
+            asm volatile("; per-strip lane id" : "+v"(lane_o));
+            const uint8_t* row = rbuf + (lane_o & 31) * ROWL;
+#pragma unroll
+            for (int j = 0; j < KL; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                    raw[j][q] = *reinterpret_cast<const u32x4*>(row + (((8 * j + 4 * (lane_o >> 5) + q) ^ (lane_o & 15)) << 4));
+        };
         auto convert = [&](int s, const u32x4 (&raw)[KS][4], v8i (&x)[KS], float& sxm) __attribute__((always_inline)) {
-            unsigned am = 0u;                                   // max over the lane's values of the 15 magnitude bits
+            // max over the lane's values of the 15 magnitude bits, two per word
+            typedef unsigned short us2 __attribute__((ext_vector_type(2)));
+            us2 a2 = {0, 0};
 #pragma unroll
             for (int j = 0; j < KS; ++j)
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                for (int q = 0; q < 4; ++q) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const unsigned w = raw[j][q][e];
-                        const unsigned lo = w & 0x7FFFu, hi = (w >> 16) & 0x7FFFu;
-                        am = am > lo ? am : lo;
-                        am = am > hi ? am : hi;
-                    }
+                    for (int e = 0; e < 4; ++e) a2 = __builtin_elementwise_max(a2, __builtin_bit_cast(us2, raw[j][q][e] & 0x7FFF7FFFu));
+                }
+            unsigned am = a2[0] > a2[1] ? a2[0] : a2[1];
             const unsigned other = static_cast<unsigned>(__shfl_xor(static_cast<int>(am), 32, 64));
             am = am > other ? am : other;
             float scale, inv;
@@ -172,14 +226,22 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             sxm = scale;
             const int m = (s - s_base) * 32 + l32;
             if (p.sx_out && hk == 0 && m < p.M) p.sx_out[static_cast<int64_t>(g) * p.M + m] = scale;
+            auto cast = [&](auto finite_tag) __attribute__((always_inline)) {
+                auto four = [&](float a, float b, float c, float d) __attribute__((always_inline)) {
+                    return static_cast<int>(decltype(finite_tag)::value ? e4m3x4_finite(a, b, c, d) : e4m3x4(a, b, c, d));
+                };
 #pragma unroll
-            for (int j = 0; j < KS; ++j)
+                for (int j = 0; j < KS; ++j) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const u32x4 w = raw[j][q];
-                    x[j][2 * q] = static_cast<int>(e4m3x4(bf16_lo(w.x) * inv, bf16_hi(w.x) * inv, bf16_lo(w.y) * inv, bf16_hi(w.y) * inv));
-                    x[j][2 * q + 1] = static_cast<int>(e4m3x4(bf16_lo(w.z) * inv, bf16_hi(w.z) * inv, bf16_lo(w.w) * inv, bf16_hi(w.w) * inv));
+                    for (int q = 0; q < 4; ++q) {
+                        const u32x4 w = raw[j][q];
+                        x[j][2 * q] = four(bf16_lo(w.x) * inv, bf16_hi(w.x) * inv, bf16_lo(w.y) * inv, bf16_hi(w.y) * inv);
+                        x[j][2 * q + 1] = four(bf16_lo(w.z) * inv, bf16_hi(w.z) * inv, bf16_lo(w.w) * inv, bf16_hi(w.w) * inv);
+                    }
                 }
+            };
+            // (four waves: one path, two take 80 registers more)
+            if (NWV == 4 || any_not_finite(am)) cast(std::false_type{}); else cast(std::true_type{});
         };
 
         // MFMAs of one phase of a strip.  Lane-derived LDS addresses restart from an opaque copy of the lane id in
@@ -249,39 +311,69 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             float mean = 0.f, rstd = 1.f;
             if (p.norm != LOKA_NORM_NONE) {
                 float m2 = 0.f;
-                if (ln) {
-                    float n_ = cnt_lane, sum = 0.f;
+                if constexpr (SHORT_ROWS) {                           // (the same bits whatever the output's type)
+                    // (branch-free; columns past N hold zeros: they add nothing to the sums, and their centred value is taken as zero)
+                    float q4[4] = {0.f, 0.f, 0.f, 0.f};
+                    if (ln) {
+                        float s4[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        if (nb * 32 + hk * 16 < p.N) {
+                        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) sum += acc[nb][i];
+                            for (int i = 0; i < 16; ++i) s4[i & 3] += acc[nb][i];
+                        const float sum = (s4[0] + s4[1]) + (s4[2] + s4[3]);
+                        const float mean_l = sum * rc_lane;
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb) {
+                            const float mean_in = nb * 32 + hk * 16 < p.N ? mean_l : 0.f;
+#pragma unroll
+                            for (int i = 0; i < 16; ++i) { const float d = acc[nb][i] - mean_in; q4[i & 3] = __builtin_fmaf(d, d, q4[i & 3]); }
                         }
-                    mean = n_ > 0.f ? sum * __builtin_amdgcn_rcpf(n_) : 0.f;
+                        // the other half of the row is in lane ^ 32: identical bits on both
+                        mean = half_lanes_sum(sum) * inv_n;
+                        const float d = mean_l - mean;
+                        m2 = half_lanes_sum(__builtin_fmaf(cnt_lane * d, d, (q4[0] + q4[1]) + (q4[2] + q4[3])));
+                    } else {
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        if (nb * 32 + hk * 16 < p.N) {
+                        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) { const float d = acc[nb][i] - mean; m2 = __builtin_fmaf(d, d, m2); }
-                        }
-                    // symmetric Chan merge: identical bits on both lanes
-                    const float nb_ = wave_shfl_xor(n_, 32), mb = wave_shfl_xor(mean, 32), m2b = wave_shfl_xor(m2, 32);
-                    const float nn = n_ + nb_;
-                    if (nn > 0.f) {
-                        const float d = mb - mean;
-                        const float rn = __builtin_amdgcn_rcpf(nn);
-                        const float newmean = (n_ * mean + nb_ * mb) * rn;
-                        m2 = m2 + m2b + d * d * (n_ * nb_ * rn);
-                        mean = newmean;
+                            for (int i = 0; i < 16; ++i) q4[i & 3] = __builtin_fmaf(acc[nb][i], acc[nb][i], q4[i & 3]);
+                        m2 = half_lanes_sum((q4[0] + q4[1]) + (q4[2] + q4[3]));
                     }
                 } else {
+                    if (ln) {
+                        float n_ = cnt_lane, sum = 0.f;
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        if (nb * 32 + hk * 16 < p.N) {
+                        for (int nb = 0; nb < NB; ++nb)
+                            if (nb * 32 + hk * 16 < p.N) {
 #pragma unroll
-                            for (int i = 0; i < 16; ++i) m2 = __builtin_fmaf(acc[nb][i], acc[nb][i], m2);
+                                for (int i = 0; i < 16; ++i) sum += acc[nb][i];
+                            }
+                        mean = n_ > 0.f ? sum * __builtin_amdgcn_rcpf(n_) : 0.f;
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            if (nb * 32 + hk * 16 < p.N) {
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) { const float d = acc[nb][i] - mean; m2 = __builtin_fmaf(d, d, m2); }
+                            }
+                        // symmetric Chan merge: identical bits on both lanes
+                        const float nb_ = wave_shfl_xor(n_, 32), mb = wave_shfl_xor(mean, 32), m2b = wave_shfl_xor(m2, 32);
+                        const float nn = n_ + nb_;
+                        if (nn > 0.f) {
+                            const float d = mb - mean;
+                            const float rn = __builtin_amdgcn_rcpf(nn);
+                            const float newmean = (n_ * mean + nb_ * mb) * rn;
+                            m2 = m2 + m2b + d * d * (n_ * nb_ * rn);
+                            mean = newmean;
                         }
-                    m2 += wave_shfl_xor(m2, 32);
+                    } else {
+#pragma unroll
+                        for (int nb = 0; nb < NB; ++nb)
+                            if (nb * 32 + hk * 16 < p.N) {
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) m2 = __builtin_fmaf(acc[nb][i], acc[nb][i], m2);
+                            }
+                        m2 += wave_shfl_xor(m2, 32);
+                    }
                 }
                 rstd = __builtin_amdgcn_rsqf(m2 * inv_n + p.eps);
             }
@@ -295,7 +387,28 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             uint8_t* const tbuf = smem + C::OFF_T + wave * 2048;
             const int t_wr = l32 * 64, t_key = (l32 >> 2) & 3;
             const int t_row = lane_o >> 2, t_c = lane_o & 3;                   // store side: row (+ 16 j), chunk
+            // (buffer stores relative to the strip's first row: the descriptor ends with the last row that exists, columns past
+            // N get an offset beyond it.  Every strip issues the same stores, no branch among them, so that a wait for the
+            // next strip's operands, requested before them, leaves them in flight.)
+            const int row0 = (s - s_base) * 32, rows_here = p.M - row0 < 32 ? p.M - row0 : 32;
+            const __amdgpu_buffer_rsrc_t orsrc =
+                FP8OUT ? __builtin_amdgcn_make_buffer_rsrc(p.outq + static_cast<int64_t>(g) * p.strideO + static_cast<int64_t>(row0) * p.N, 0,
+                                                           rows_here * p.N, 0x00020000)
+                       : __builtin_amdgcn_make_buffer_rsrc(p.out + static_cast<int64_t>(g) * p.strideO + static_cast<int64_t>(row0) * p.N, 0,
+                                                           rows_here * p.N * 2, 0x00020000);
             uint16_t* const obase = p.out + static_cast<int64_t>(g) * p.strideO + static_cast<int64_t>((s - s_base) * 32) * p.N;
+            uint8_t* const qbase = p.outq + static_cast<int64_t>(g) * p.strideO + static_cast<int64_t>((s - s_base) * 32) * p.N;
+            auto put = [&](const u32x4 v, int r, int ccol) __attribute__((always_inline)) {
+                constexpr int ES = FP8OUT ? 1 : 2;                              // bytes per value
+                if constexpr (LEAN) {
+                    __builtin_amdgcn_raw_buffer_store_b128(v, orsrc, ccol < p.N ? (r * p.N + ccol) * ES : 0x7FFFFFF0, 0, 0);
+                } else {
+                    if ((s - s_base) * 32 + r < p.M && ccol < p.N) {
+                        if (FP8OUT) *reinterpret_cast<u32x4*>(qbase + static_cast<int64_t>(r) * p.N + ccol) = v;
+                        else *reinterpret_cast<u32x4*>(obase + static_cast<int64_t>(r) * p.N + ccol) = v;
+                    }
+                }
+            };
             // (without gamma and beta the affine step is x * 1 + 0: skipped, same bits, no table reads)
             auto normalize_store = [&](auto affine_tag) __attribute__((always_inline)) {
                 constexpr bool AFFINE = decltype(affine_tag)::value;
@@ -327,8 +440,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                         const int r = 16 * j + t_row;
                         const u32x4 pk = *reinterpret_cast<const u32x4*>(tbuf + r * 64 + ((t_c ^ ((r >> 2) & 3)) << 4));
                         const int ccol = nb * 32 + t_c * 8;
-                        if ((s - s_base) * 32 + r < p.M && ccol < p.N)
-                            *reinterpret_cast<u32x4*>(obase + static_cast<int64_t>(r) * p.N + ccol) = pk;
+                        put(pk, r, ccol);
                     }
                     after_block(nb);
                 }
@@ -380,7 +492,6 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                 float scale, inv;
                 group_scale(__uint_as_float(am << 16), scale, inv);
                 if (hk == 0 && m < p.M) p.outs[static_cast<int64_t>(g) * p.M + m] = scale;
-                uint8_t* const qbase = p.outq + static_cast<int64_t>(g) * p.strideO + static_cast<int64_t>((s - s_base) * 32) * p.N;
 #pragma unroll
                 for (int nbp = 0; nbp < NB / 2; ++nbp) {
 #pragma unroll
@@ -399,8 +510,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                         const int r = 16 * j + t_row;
                         const u32x4 ck = *reinterpret_cast<const u32x4*>(tbuf + r * 64 + ((t_c ^ ((r >> 2) & 3)) << 4));
                         const int ccol = nbp * 64 + t_c * 16;
-                        if ((s - s_base) * 32 + r < p.M && ccol < p.N)
-                            *reinterpret_cast<u32x4*>(qbase + static_cast<int64_t>(r) * p.N + ccol) = ck;
+                        put(ck, r, ccol);
                     }
                     after_block(2 * nbp);
                     after_block(2 * nbp + 1);
@@ -408,9 +518,13 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             };
             // (an instantiation of its own: in one kernel with the bf16 form the larger shapes spill more)
             if (FP8OUT) {
-                if (affine) normalize_store_fp8(std::true_type{}); else normalize_store_fp8(std::false_type{});
+                if (affine) { normalize_store_fp8(std::true_type{}); if (LEAN) asm volatile("; stored, affine"); }
+                else { normalize_store_fp8(std::false_type{}); if (LEAN) asm volatile("; stored"); }
             } else {
-                if (affine) normalize_store(std::true_type{}); else normalize_store(std::false_type{});
+                // (each path ends in a line of its own: their last stores would be merged into one tail, behind which the
+                // compiler knows of these alone, and waits for all others with the next operands)
+                if (affine) { normalize_store(std::true_type{}); if (LEAN) asm volatile("; stored, affine"); }
+                else { normalize_store(std::false_type{}); if (LEAN) asm volatile("; stored"); }
             }
         };
 
@@ -424,14 +538,23 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             // side: the next strip is then requested piece by piece from inside the epilogue, each piece into the
             // registers of a column block that has just been stored (LATE); the wave waits for it afterwards, and the
             // other seven cover.
-            constexpr bool LATE = NWV == 8 && !(NB == 4 && KS <= 4);
+            constexpr bool LATE = NWV == 8 && !(NB == 4 && KS <= 4) && !RAWLDS;
             u32x4 raw[KS][4];
             int s = t + wave;
-            if (s < seg_end) load_raw(s, raw);
+            if (s < seg_end) {
+                if (RAWLDS) request_raw(s);
+                load_raw(s, raw, KL);
+            }
+            if (RAWLDS) wait_vmcnt<0>();
             while (s < seg_end) {
-                convert(s, raw, x, sxm);
                 const bool more = s + NWV < seg_end;
-                if (!LATE && more) load_raw(s + NWV, raw);
+                if (RAWLDS) {
+                    read_raw(raw);
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the strip has been read: its place is free
+                    if (more) request_raw(s + NWV);
+                }
+                convert(s, raw, x, sxm);
+                if (!LATE && more) load_raw(s + NWV, raw, KL);
                 __builtin_amdgcn_sched_barrier(0);
                 v16f acc[NB];
 #pragma unroll
@@ -442,13 +565,19 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                 epilogue(s, sxm, acc, [&](int nb) __attribute__((always_inline)) {
                     if (LATE && more) load_raw_part(s + NWV, raw, nb * (KS * 4) / NB, (nb + 1) * (KS * 4) / NB);
                 });
+                // the next strip is there: of this wave's operations only the epilogue's 2 NB stores are younger
+                if (RAWLDS) wait_vmcnt<2 * NB>();
                 s += NWV;
             }
         } else if (NPH == 1) {
             // W is complete in LDS: the waves run on their own.  The next strip's operands are requested into the
             // same registers right after the last MFMA (x is dead then) and arrive during the epilogue.
+            // (requested whether or not there is one - past the end beyond the descriptor, which reads zeros - and awaited by
+            // count: of this wave's operations only the epilogue's stores are younger.  On conditional paths the compiler
+            // does not know the counts, and waits for the stores as well.)
             int s = t + wave;
-            if (s < seg_end) load_x(s, 0, x, sxm);
+            if (s < seg_end) load_x(s, 0, x, sxm, true);
+            if constexpr (SHORT_ROWS) wait_vmcnt<0>();
             while (s < seg_end) {
                 v16f acc[NB];
 #pragma unroll
@@ -457,9 +586,11 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                     for (int i = 0; i < 16; ++i) acc[nb][i] = 0.f;
                 mma(x, acc);
                 const float sx_cur = sxm;
-                if (s + NWV < seg_end) load_x(s + NWV, 0, x, sxm);
+                if constexpr (SHORT_ROWS) load_x(s + NWV, 0, x, sxm, s + NWV < seg_end);
+                else if (s + NWV < seg_end) load_x(s + NWV, 0, x, sxm, true);
                 __builtin_amdgcn_sched_barrier(0);
                 epilogue(s, sx_cur, acc, [](int) {});
+                if constexpr (SHORT_ROWS) wait_vmcnt<FP8OUT ? NB : 2 * NB>();
                 s += NWV;
             }
         } else {
@@ -477,7 +608,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                 for (int ph = 0; ph < NPH; ++ph) {
                     __syncthreads();                            // every wave has read the previous slab (and the tables are written)
                     load_w(ph);
-                    if (active) load_x(s, ph, x, sxm);
+                    if (active) load_x(s, ph, x, sxm, true);
                     wait_vmcnt<0>();
                     __syncthreads();
                     if (active) mma(x, acc);
@@ -497,20 +628,20 @@ struct StripInst {
     const void* fn;
     const void* fn_fused;      // bf16 X, quantization fused (single-phase instances only)
     const void* fn_q;          // e4m3 output
-    size_t lds;
+    size_t lds, lds_fused;
     void (*launch)(const GemmParams&, int, dim3, hipStream_t);
 };
 
 // waves of a fused-quantization instance: 8 where accumulators, the raw strip and the operands fit 256 registers
 // (N <= 128 with K <= 256; N = 256 with K = 128 and the piecewise request), else 4 with up to 512 each (measured:
 // the 8-wave forms that spill are slower than the 4-wave ones, 94 against 71-81 us at 64 x (4096 x 256 x 256))
-constexpr int fused_waves(int nb, int ks) { return ((nb == 4 && ks <= 4) || (nb == 8 && ks == 2)) ? 8 : 4; }
+constexpr int fused_waves(int nb, int ks) { return ks <= 4 ? 8 : 4; }
 
 template <int NB, int KS, int NPH>
 void launch_strip(const GemmParams& p, int spp, dim3 grid, hipStream_t s) {
     if (p.xb) {
         if constexpr (NPH == 1 && KS <= 8)                      // (K = 1024: the raw strip alone would be 256 registers)
-            gemm_strip_kernel<NB, KS, NPH, fused_waves(NB, KS), true, false><<<grid, fused_waves(NB, KS) * 64, StripCfg<NB, KS, NPH>::LDS, s>>>(p, spp);
+            gemm_strip_kernel<NB, KS, NPH, fused_waves(NB, KS), true, false><<<grid, fused_waves(NB, KS) * 64, StripCfg<NB, KS, NPH>::lds_fused(fused_waves(NB, KS)), s>>>(p, spp);
     } else if (p.outq) {
         gemm_strip_kernel<NB, KS, NPH, 8, false, true><<<grid, 512, StripCfg<NB, KS, NPH>::LDS, s>>>(p, spp);
     } else {
@@ -526,7 +657,7 @@ const void* strip_fused_fn() {
 
 #define LOKA_STRIP(NB, KS, NPH)                                                                                     \
     {NB, KS, NPH, reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, 8, false, false>), strip_fused_fn<NB, KS, NPH>(), \
-     reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, 8, false, true>), StripCfg<NB, KS, NPH>::LDS,          \
+     reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, 8, false, true>), StripCfg<NB, KS, NPH>::LDS, StripCfg<NB, KS, NPH>::lds_fused(fused_waves(NB, KS)), \
      &launch_strip<NB, KS, NPH>}
 
 // column blocks, K steps per phase, phases (K = 64 KS NPH; one phase when W fits the LDS)
@@ -558,7 +689,7 @@ int strip_plan(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool bf1
     const StripInst* w = strip_pick(N, K);
     if (!w || (bf16_in && (!w->fn_fused || fp8_out))) return 0;
     *fn = bf16_in ? w->fn_fused : fp8_out ? w->fn_q : w->fn;
-    *lds = w->lds;
+    *lds = bf16_in ? w->lds_fused : w->lds;
     const int64_t strips = batch * ((M + 31) / 32);
     // (one strip per workgroup while CUs are free, though only one wave of it then works: measured with fused quantization,
     // M x N x K: 1311 x 112 x 256 10.4 -> 7.2 us, 9815 x 112 x 128 8.6 -> 6.8, 32 x (1348 x 128 x 256) 17.9 -> 13.2)

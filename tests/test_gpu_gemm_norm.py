@@ -1184,3 +1184,21 @@ def test_streaming_fp8_output_is_the_quantized_bf16_output(shape, norm, gamma):
     assert torch.isnan(so[5]) and torch.isnan(out[5].float()).all()
     assert torch.equal(so[rows], s[rows])
     assert torch.equal(oq.view(torch.uint8)[rows], q.view(torch.uint8)[rows])
+
+
+# fused quantization on the strip kernel (a strip's bf16 rows through LDS for N > 128 and K <= 256, in registers else): the same
+# bits as quantize + GEMM on that kernel; one row, rows that do not fill a strip, more strips than waves, several problems
+@pytest.mark.parametrize("M,batch", [(1, 1), (33, 3), (1000, 1), (20011, 2)])
+@pytest.mark.parametrize("K,N", [(128, 256), (256, 144), (256, 256), (256, 128), (512, 240)])
+@pytest.mark.parametrize("norm", ["layernorm", "rmsnorm"])
+def test_fused_strip_is_quantize_then_gemm(M, batch, K, N, norm):
+    x = synth.student_t4(batch * M, K, seed=91).to(DEV)
+    ws = [B.loka_quantize(synth.weight(K, N, seed=92 + b).to(DEV), B.SCALE_COL, transpose_out=True) for b in range(batch)]
+    wq, sw = torch.cat([q for q, _ in ws]), torch.cat([s for _, s in ws])
+    d = B.make_desc(M, N, K, batch, norm=B.NORMS[norm], variant=B.variant_id("strip32"))
+    xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+    ref, y_ref = B.loka_fp8_gemm_norm(d, xq, sx, wq, sw, want_y=True)
+    out, y, s = B.loka_fp8_linear_norm(d, x, wq, sw, want_y=True, want_sx=True)
+    plain, _, _ = B.loka_fp8_linear_norm(d, x, wq, sw)
+    assert torch.equal(s, sx) and torch.equal(y, y_ref)
+    assert torch.equal(out, ref) and torch.equal(plain, ref)
