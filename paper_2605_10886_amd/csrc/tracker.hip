@@ -11,11 +11,11 @@
 //
 //   tracker_scatter_kernel   one workgroup per (tile pair ti <= tj of 256 x 256 outputs, one of S row ranges of
 //                            the batch): raw partial scatter -> workspace (fp32); workgroups on diagonal
-//                            tiles also write fp64 column sums of their 256 columns
-//   tracker_mean_kernel      folds the column sums of the S ranges in a fixed order: mu_b, delta (fp64,
-//                            workspace), mu' in place
-//   tracker_merge_kernel     folds the partial scatters in a fixed order, forms S_b and the rank-1 term and
-//                            updates Sigma (both triangles; the mirror image goes through an LDS transpose)
+//                            tiles also write fp64 column sums of their 256 columns, those of the first range
+//                            a copy of the old mean
+//   tracker_merge_kernel     folds the column sums (mu_b, delta in fp64) and the partial scatters in a fixed order,
+//                            forms S_b and the rank-1 term and updates mu and Sigma in place (both triangles; the
+//                            mirror image goes through an LDS transpose)
 //
 // The contraction runs over the rows of a row-major matrix, i.e. over the strided dimension of both MFMA
 // operands: an MFMA lane needs 8 consecutive batch rows of ONE column.  Each 8 x 8 block of X is transposed
@@ -44,7 +44,7 @@ constexpr int TRK_PLAN_SLOTS = 256;             // cost model only: workgroups a
 struct TrackerPlan {
     int T, pairs, splits;
     int64_t rows_per_split;
-    size_t off_colsum, off_mub, off_delta, bytes;
+    size_t off_colsum, off_mu, bytes;
 };
 
 TrackerPlan tracker_plan(int64_t B, int64_t K) {
@@ -70,9 +70,8 @@ TrackerPlan tracker_plan(int64_t B, int64_t K) {
     const size_t slots = static_cast<size_t>(pl.splits) * pl.pairs;
     const size_t kp = static_cast<size_t>(pl.T) * TRK_T;
     pl.off_colsum = slots * TRK_T * TRK_T * sizeof(float);
-    pl.off_mub = pl.off_colsum + slots * TRK_T * sizeof(double);
-    pl.off_delta = pl.off_mub + kp * sizeof(double);
-    pl.bytes = pl.off_delta + kp * sizeof(double);
+    pl.off_mu = pl.off_colsum + slots * TRK_T * sizeof(double);
+    pl.bytes = pl.off_mu + kp * sizeof(float);
     return pl;
 }
 
@@ -82,6 +81,8 @@ struct TrackerParams {
     int K, T, pairs, splits;
     float* partial;      // [splits][pairs][256][256]
     double* colsum;      // [splits][pairs][256] (written for diagonal pairs only)
+    const float* mu;     // [K]: the mean before this call, copied to
+    float* mu_old;       // the workspace by the diagonal pairs of the first range
 };
 
 __device__ __forceinline__ void pair_to_tiles(int pair, int T, int& ti, int& tj) {
@@ -280,38 +281,28 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
         const int pos = tid & 255, col = 8 * (pos & 31) + (pos >> 5);
         red[(tid >> 8) * TRK_T + col] = cs;
         __syncthreads();
-        if (tid < TRK_T) p.colsum[static_cast<int64_t>(id) * TRK_T + tid] = red[tid] + red[TRK_T + tid];
+        if (tid < TRK_T) {
+            p.colsum[static_cast<int64_t>(id) * TRK_T + tid] = red[tid] + red[TRK_T + tid];
+            const int k = ti * TRK_T + tid;
+            if (id < p.pairs && k < p.K) p.mu_old[k] = p.mu[k];          // id = range * pairs + pair
+        }
     }
-}
-
-__global__ __launch_bounds__(256) void tracker_mean_kernel(const double* __restrict__ colsum, int T, int pairs, int splits,
-                                                           int K, int64_t B, int64_t n_old, float* __restrict__ mu,
-                                                           double* __restrict__ mub, double* __restrict__ delta) {
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= T * TRK_T) return;
-    if (k >= K) { mub[k] = 0.0; delta[k] = 0.0; return; }
-    const int t = k / TRK_T;
-    const double* src = colsum + static_cast<int64_t>(diag_pair(t, T)) * TRK_T + (k - t * TRK_T);
-    const int64_t stride = static_cast<int64_t>(pairs) * TRK_T;
-    double s = 0.0;
-#pragma unroll 8
-    for (int sp = 0; sp < splits; ++sp) s += src[sp * stride];
-    const double mb = s / static_cast<double>(B);
-    const double m0 = static_cast<double>(mu[k]);
-    const double d = mb - m0;
-    const double n_new = static_cast<double>(n_old) + static_cast<double>(B);
-    mub[k] = mb;
-    delta[k] = d;
-    mu[k] = static_cast<float>(m0 + static_cast<double>(B) / n_new * d);
 }
 
 // grid (pairs, 64): workgroup y handles the 32 x 32 block (y / 8, y % 8) of its pair's tile, one run of four
 // columns per thread, and, for an off-diagonal pair, the mirrored block of the lower triangle (through a
 // transposing LDS tile, so both triangles are written in full 128-byte runs).
-__global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restrict__ partial, int T, int pairs, int splits,
-                                                            int K, int64_t B, double coef, const double* __restrict__ mub,
-                                                            const double* __restrict__ delta, float* __restrict__ sigma) {
+// The workgroup folds the column sums of its 64 columns by itself (wave q takes the ranges q, q + 4, ..., then the four
+// waves' sums in order: the same bits in every workgroup), with the first loads in flight together with those of the
+// partial tiles.  A kernel of its own for the means ran a few workgroups for 4.7 us between the two large ones (whole
+// call before and after: 65536 x 256 42.0 -> 36.8 us, 4096 x 512 23.7 -> 22.0, 32768 x 1024 64.6 -> 62.0).  The
+// old mean is the scatter kernel's copy, because the workgroups of the diagonal blocks overwrite mu here.
+__global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restrict__ partial, const double* __restrict__ colsum,
+                                                            const float* __restrict__ mu_old, int T, int pairs, int splits,
+                                                            int K, int64_t B, double ratio, double coef,
+                                                            float* __restrict__ mu, float* __restrict__ sigma) {
     __shared__ double tr[32][33];
+    __shared__ double part[4][64], mub[64], delta[64];                   // columns: 32 of the i block, 32 of the j block
     const int tid = threadIdx.x, tq = tid & 7, ty = tid >> 3;            // 8 runs of four columns x 32 rows
     const int pair = blockIdx.x, bi = blockIdx.y >> 3, bj = blockIdx.y & 7;
     int ti, tj;
@@ -321,25 +312,57 @@ __global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restr
     const int64_t tile_elems = TRK_T * TRK_T, stride = static_cast<int64_t>(pairs) * tile_elems;
     const int il = bi * 32 + ty, jl = bj * 32 + 4 * tq;
     const int i = ti * TRK_T + il, j = tj * TRK_T + jl;                  // K % 8 == 0: a run is inside or outside
-    double c[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i < K && j < K) {
+    const bool live = i < K && j < K;
+    const int fc = tid & 63, fq = tid >> 6;                              // folding: column, first range
+    const int ft = fc < 32 ? ti : tj, fl = (fc < 32 ? bi : bj) * 32 + (fc & 31), fk = ft * TRK_T + fl;
+    const double* fsrc = colsum + static_cast<int64_t>(diag_pair(ft, T)) * TRK_T + fl;
+    const int64_t fstride = static_cast<int64_t>(pairs) * TRK_T;
+    double cv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) cv[u] = fq + 4 * u < splits ? fsrc[(fq + 4 * u) * fstride] : 0.0;
+    const double m0 = fk < K ? static_cast<double>(mu_old[fk]) : 0.0;
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+    float* dst = sigma + static_cast<int64_t>(i) * K + j;
+    // mirrored block: row jl2 of the lower triangle takes column jl2 of this block
+    const int jl2 = bj * 32 + ty, il2 = bi * 32 + 4 * tq;
+    const int i2 = ti * TRK_T + il2, j2 = tj * TRK_T + jl2;
+    const bool live2 = !diag && i2 < K && j2 < K;
+    float* dst2 = sigma + static_cast<int64_t>(j2) * K + i2;
+    v4f old{}, old2{};
+    if (live2) old2 = *reinterpret_cast<const v4f*>(dst2);
+    if (live) {
+        old = *reinterpret_cast<const v4f*>(dst);
         const float* src = partial + static_cast<int64_t>(pair) * tile_elems + il * TRK_T + jl;
-        double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
 #pragma unroll 8
         for (int sp = 0; sp < splits; ++sp) {
             const v4f v = *reinterpret_cast<const v4f*>(src + sp * stride);
             s0 += static_cast<double>(v[0]); s1 += static_cast<double>(v[1]);
             s2 += static_cast<double>(v[2]); s3 += static_cast<double>(v[3]);
         }
+    }
+    double cs = 0.0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) cs += cv[u];
+#pragma unroll 4
+    for (int sp = fq + 32; sp < splits; sp += 4) cs += fsrc[sp * fstride];
+    part[fq][fc] = cs;
+    __syncthreads();
+    if (tid < 64) {
+        const double mb = ((part[0][fc] + part[1][fc]) + (part[2][fc] + part[3][fc])) / Bd;
+        mub[fc] = mb;
+        delta[fc] = mb - m0;
+        if (diag && bi == bj && fc < 32 && fk < K) mu[fk] = static_cast<float>(m0 + ratio * (mb - m0));
+    }
+    __syncthreads();
+    double c[4] = {0.0, 0.0, 0.0, 0.0};
+    if (live) {
         const double sv[4] = {s0, s1, s2, s3};
-        float* dst = sigma + static_cast<int64_t>(i) * K + j;
-        const v4f old = *reinterpret_cast<const v4f*>(dst);
         v4f nw;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             // products of the two columns first: (i, j) and (j, i) then give identical bits
-            const double sb = sv[e] - Bd * (mub[i] * mub[j + e]);
-            c[e] = sb + coef * (delta[i] * delta[j + e]);
+            const double sb = sv[e] - Bd * (mub[ty] * mub[32 + 4 * tq + e]);
+            c[e] = sb + coef * (delta[ty] * delta[32 + 4 * tq + e]);
             nw[e] = static_cast<float>(static_cast<double>(old[e]) + c[e]);
         }
         *reinterpret_cast<v4f*>(dst) = nw;
@@ -348,16 +371,11 @@ __global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restr
 #pragma unroll
         for (int e = 0; e < 4; ++e) tr[ty][4 * tq + e] = c[e];
         __syncthreads();
-        // mirrored block: row jl2 of the lower triangle takes column jl2 of the block just computed
-        const int jl2 = bj * 32 + ty, il2 = bi * 32 + 4 * tq;
-        const int i2 = ti * TRK_T + il2, j2 = tj * TRK_T + jl2;
-        if (i2 < K && j2 < K) {
-            float* dst = sigma + static_cast<int64_t>(j2) * K + i2;
-            const v4f old = *reinterpret_cast<const v4f*>(dst);
+        if (live2) {
             v4f nw;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) nw[e] = static_cast<float>(static_cast<double>(old[e]) + tr[4 * tq + e][ty]);
-            *reinterpret_cast<v4f*>(dst) = nw;
+            for (int e = 0; e < 4; ++e) nw[e] = static_cast<float>(static_cast<double>(old2[e]) + tr[4 * tq + e][ty]);
+            *reinterpret_cast<v4f*>(dst2) = nw;
         }
     }
 }
@@ -369,23 +387,19 @@ loka_status tracker_update_launch(const void* x, int64_t B, int64_t K, int64_t l
     const TrackerPlan pl = tracker_plan(B, K);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
     double* colsum = reinterpret_cast<double*>(ws + pl.off_colsum);
-    double* mub = reinterpret_cast<double*>(ws + pl.off_mub);
-    double* delta = reinterpret_cast<double*>(ws + pl.off_delta);
     TrackerParams p{};
     p.x = static_cast<const uint16_t*>(x); p.B = B; p.ld = ld; p.K = static_cast<int>(K);
     p.T = pl.T; p.pairs = pl.pairs; p.splits = pl.splits; p.rows_per_split = pl.rows_per_split;
     p.partial = reinterpret_cast<float*>(ws); p.colsum = colsum;
+    p.mu = mu; p.mu_old = reinterpret_cast<float*>(ws + pl.off_mu);
     // set on every call (a host-side table write): no process-wide state, and correct on whichever device is current
     LOKA_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(&tracker_scatter_kernel),
                                      hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(TRK_LDS)));
     tracker_scatter_kernel<<<dim3(pl.pairs * pl.splits), 512, TRK_LDS, s>>>(p);
-    const int KP = pl.T * TRK_T;
-    tracker_mean_kernel<<<dim3((KP + 255) / 256), 256, 0, s>>>(colsum, pl.T, pl.pairs, pl.splits, static_cast<int>(K), B, n_old,
-                                                               mu, mub, delta);
     const double n_new = static_cast<double>(n_old) + static_cast<double>(B);
-    const double coef = static_cast<double>(n_old) * static_cast<double>(B) / n_new;
-    tracker_merge_kernel<<<dim3(pl.pairs, 64), 256, 0, s>>>(p.partial, pl.T, pl.pairs, pl.splits, static_cast<int>(K), B, coef,
-                                                            mub, delta, sigma);
+    const double ratio = static_cast<double>(B) / n_new, coef = static_cast<double>(n_old) * static_cast<double>(B) / n_new;
+    tracker_merge_kernel<<<dim3(pl.pairs, 64), 256, 0, s>>>(p.partial, colsum, p.mu_old, pl.T, pl.pairs, pl.splits,
+                                                            static_cast<int>(K), B, ratio, coef, mu, sigma);
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }
 

@@ -63,6 +63,17 @@ def test_single_update_from_a_given_state(orc, shape):
     assert np.array_equal(g[1], g[1].T), "symmetric state in, symmetric state out (bit for bit)"
 
 
+@pytest.mark.parametrize("shape", [(33000, 8), (9000, 72), (40000, 264), (70000, 64)])
+def test_many_row_ranges(orc, shape):
+    # few tiles and many rows: more than 32 row ranges, whose column sums and partial scatters the merge folds
+    rows, K = shape
+    x = synth.correlated(rows, K, seed=rows + K)
+    n_old, mu, sigma = _state(K, K)
+    o, g = _step_both(orc, x, n_old, mu, sigma)
+    _check(x, sigma.astype(np.float64), o, g)
+    assert np.array_equal(g[1], g[1].T)
+
+
 def test_first_batch_and_constant_columns(orc):
     # from the empty state; a constant column has zero scatter: its own sum of squares is exact in fp32 and cancels
     # exactly against B mu^2 (its products with other columns round in fp32 and stay within the bound)
