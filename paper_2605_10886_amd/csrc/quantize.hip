@@ -288,17 +288,19 @@ __global__ __launch_bounds__(256) void amax_col_kernel(const uint16_t* __restric
 //   G_COL128:  every column of the tile is a group (BLOCK_128x1); scales [cols][rows/128]
 //   G_COL:     a group is a whole column (COL), G_TENSOR: the whole matrix: the workgroup folds the partial maxima of
 //              its groups that the amax pass left (parts[nparts][groups]); the first row of tiles writes the scales
+//   G_COL_ALL: COL with few rows: the workgroup reads the other tiles of its columns itself (a second read from L2 in
+//              place of the amax pass, whose launch costs more than the reads)
 //   TRANSPOSE: codes leave as [cols, rows] through an LDS tile (128-byte runs per output row)
 // rows % 128 == 0 for G_TILE and G_COL128; rows % 16 == 0 with TRANSPOSE; any rows else.  cols % 16 == 0 (% 128 for G_TILE).
 // Measured (us, whole call with the amax pass; before: clearing, atomics, scales and a cast through a byte-wise LDS tile,
-// four kernels): COL transposed 256 x 1024 22.5 -> 7.9, 4096 x 4096 44.8 -> 19.3, 123200 x 1024 423 -> 129; TENSOR
+// four kernels): COL transposed 1024 x 1024 7.4, 4096 x 4096 44.8 -> 19.3, 123200 x 1024 423 -> 129; TENSOR
 // 16384 x 512 57 -> 10.4, 65536 x 1024 95 -> 58, 32768 x 4096 136 -> 120.
-enum { G_TILE, G_COL128, G_COL, G_TENSOR };
+enum { G_TILE, G_COL128, G_COL_ALL, G_COL, G_TENSOR };
 template <int GROUPS, bool TRANSPOSE>
 __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                             int64_t ld, uint8_t* __restrict__ q, float* __restrict__ scales,
                                                             const int pow2, const float* __restrict__ parts, const int nparts) {
-    constexpr bool ROW_TAIL = GROUPS == G_COL || GROUPS == G_TENSOR;   // rows need not fill the last tile
+    constexpr bool ROW_TAIL = GROUPS == G_COL || GROUPS == G_COL_ALL || GROUPS == G_TENSOR;   // rows need not fill the last tile
     __shared__ float red[4 * 128];                      // per wave: column maxima (G_COL128) or one value
     __shared__ float inv_s[128];
     __shared__ __attribute__((aligned(16))) uint8_t tile[TRANSPOSE ? 128 * (128 + 16) : 16];   // [c][r], rows padded to 144 bytes
@@ -316,15 +318,31 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
             w[sw] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + (r0 + rr * 8 + sw) * ld + c0 + cc * 8));
     }
     float inv8[8];
-    if (GROUPS == G_COL128) {
+    if (GROUPS == G_COL128 || GROUPS == G_COL_ALL) {
         float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        auto column_maxima = [&](const u32x4 (&v)[8]) __attribute__((always_inline)) {
 #pragma unroll
-        for (int sw = 0; sw < 8; ++sw) {
-            a[0] = fmaxf(a[0], fabsf(bf16_lo(w[sw].x))); a[1] = fmaxf(a[1], fabsf(bf16_hi(w[sw].x)));
-            a[2] = fmaxf(a[2], fabsf(bf16_lo(w[sw].y))); a[3] = fmaxf(a[3], fabsf(bf16_hi(w[sw].y)));
-            a[4] = fmaxf(a[4], fabsf(bf16_lo(w[sw].z))); a[5] = fmaxf(a[5], fabsf(bf16_hi(w[sw].z)));
-            a[6] = fmaxf(a[6], fabsf(bf16_lo(w[sw].w))); a[7] = fmaxf(a[7], fabsf(bf16_hi(w[sw].w)));
+            for (int sw = 0; sw < 8; ++sw) {
+                a[0] = fmaxf(a[0], fabsf(bf16_lo(v[sw].x))); a[1] = fmaxf(a[1], fabsf(bf16_hi(v[sw].x)));
+                a[2] = fmaxf(a[2], fabsf(bf16_lo(v[sw].y))); a[3] = fmaxf(a[3], fabsf(bf16_hi(v[sw].y)));
+                a[4] = fmaxf(a[4], fabsf(bf16_lo(v[sw].z))); a[5] = fmaxf(a[5], fabsf(bf16_hi(v[sw].z)));
+                a[6] = fmaxf(a[6], fabsf(bf16_lo(v[sw].w))); a[7] = fmaxf(a[7], fabsf(bf16_hi(v[sw].w)));
+            }
+        };
+        if (GROUPS == G_COL_ALL) {
+            for (int64_t rb = 0; rb < rows; rb += 128) {
+                if (rb == r0) continue;
+                u32x4 v[8];
+#pragma unroll
+                for (int sw = 0; sw < 8; ++sw) {
+                    v[sw] = u32x4{0u, 0u, 0u, 0u};
+                    if (live && rb + rr * 8 + sw < rows)
+                        v[sw] = *reinterpret_cast<const u32x4*>(x + (rb + rr * 8 + sw) * ld + c0 + cc * 8);
+                }
+                column_maxima(v);
+            }
         }
+        column_maxima(w);
         // lanes l, l ^ 16, l ^ 32, l ^ 48 of a wave hold the same columns (rows rr differ); then the 4 waves through LDS
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -341,7 +359,11 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
             float sc, iv;
             group_scale_any(pow2 != 0, am, sc, iv);
             inv_s[t] = iv;
-            if (c0 + t < cols) scales[(c0 + t) * (rows >> 7) + by] = sc;
+            if (GROUPS == G_COL_ALL) {
+                if (by == 0 && c0 + t < cols) scales[c0 + t] = sc;
+            } else if (c0 + t < cols) {
+                scales[(c0 + t) * (rows >> 7) + by] = sc;
+            }
         }
         __syncthreads();
 #pragma unroll
@@ -475,6 +497,12 @@ static void launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t l
 }
 
 // Row ranges of a COL amax pass: 128 rows each (four rows per thread) as long as the cast has few partials to fold.
+// COL in one kernel (G_COL_ALL) instead of two: every workgroup reads all row tiles of its columns, so the time grows with
+// their number where the amax pass costs a launch.  Measured (us, two kernels -> one): 256 x 1024 7.3 -> 4.8, 256 x 65536
+// 18.3 -> 11.5, 256 x 262144 60.9 -> 51.8; 512 x 1024 7.3 -> 5.9, 512 x 16384 11.2 -> 8.1, but 512 x 65536 31.6 -> 40.7 and
+// 1024 x 1024 7.4 -> 8.5.
+static bool col_in_one(int64_t rows, int64_t cols) { return rows <= 256 || (rows <= 512 && cols <= 16384); }
+
 static int64_t col_rows_per_part(int64_t rows) {
     const int64_t per = (rows + kMaxParts - 1) / kMaxParts;
     return ((per < 128 ? 128 : per) + 31) / 32 * 32;
@@ -519,6 +547,9 @@ loka_status quantize_launch(const void* x_bf16, int64_t rows, int64_t cols, int6
         amax_tensor_kernel<<<dim3(static_cast<unsigned>(n)), 256, 0, s>>>(x, rows, cols, ld, parts);
         if (transpose_out) quant_tile128_kernel<G_TENSOR, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
         else quant_tile128_kernel<G_TENSOR, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
+    } else if (col_in_one(rows, cols)) {
+        if (transpose_out) quant_tile128_kernel<G_COL_ALL, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, nullptr, 0);
+        else quant_tile128_kernel<G_COL_ALL, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, nullptr, 0);
     } else {
         const int64_t per = col_rows_per_part(rows);
         const int n = static_cast<int>((rows + per - 1) / per);

@@ -53,6 +53,18 @@ def test_modes_and_shapes(orc, mode_name, shape):
     _cmp_quant(orc, x, mode, what=f"{mode_name} {shape}")
 
 
+@pytest.mark.parametrize("transpose_out", [False, True])
+@pytest.mark.parametrize("shape", [(16, 16), (112, 144), (128, 16400), (144, 272), (256, 128), (496, 400), (512, 16384),
+                                   (512, 16400), (528, 144)])
+def test_column_groups_of_few_rows(orc, shape, transpose_out):
+    # both sides of the line between one kernel and two (256 rows; 512 rows up to 16384 columns), tails of rows and columns
+    rows, cols = shape
+    x = synth.student_t4(rows, cols, seed=rows + cols)
+    x[rows - 1, 3] = 3.0e4            # a column's maximum in its last row
+    x[:, 5] = 0
+    _cmp_quant(orc, x, B.SCALE_COL, transpose_out=transpose_out, what=f"COL {shape}")
+
+
 @pytest.mark.parametrize("mode_name", ["TENSOR", "COL", "BLOCK_128x128", "BLOCK_128x128_POW2"])
 def test_weight_layout_transposed(orc, mode_name):
     mode = getattr(B, "SCALE_" + mode_name)
