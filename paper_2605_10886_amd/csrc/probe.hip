@@ -92,35 +92,47 @@ __global__ __launch_bounds__(256) void probe_kernel(const float* __restrict__ y,
     }
 }
 
-// One workgroup; thread t sums partials t, t+256, ... in order, then a fixed tree.
+// One workgroup; thread t sums partials t, t+256, ... in order (all of them in flight at once: kProbeBlocks / 256), then a
+// fixed tree: the upper half onto the lower, through LDS down to one wave, there by lane exchange.
+// Latency bound and alone on the chip; with eight rounds of loads and a tree of eight barriers 2.4 us more (call of the
+// statistics behind its two GEMMs, 16384 x 1024 x 1024: 116.7 -> 114.4 us).
 __global__ __launch_bounds__(256) void probe_finalize_kernel(const ProbePartial* __restrict__ partials, int n,
                                                              int64_t M, int64_t N,
                                                              loka_probe_stats* __restrict__ stats) {
-    __shared__ double s0[256], s1[256], s2[256];
-    __shared__ float s3[256];
-    double sse = 0.0, ssr = 0.0, rel = 0.0;
-    float mx = 0.f;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        sse += partials[i].sse; ssr += partials[i].ssr; rel += partials[i].rel; mx = fmaxf(mx, partials[i].mx);
+    static_assert(kProbeBlocks % 256 == 0 && sizeof(ProbePartial) == 32, "two 16-byte loads per partial");
+    __shared__ ProbePartial red[256];
+    const int t = static_cast<int>(threadIdx.x);
+    ProbePartial v[kProbeBlocks / 256];
+#pragma unroll
+    for (int u = 0; u < kProbeBlocks / 256; ++u) {
+        v[u] = ProbePartial{0.0, 0.0, 0.0, 0.f, 0.f};
+        if (t + 256 * u < n) v[u] = partials[t + 256 * u];
     }
-    s0[threadIdx.x] = sse; s1[threadIdx.x] = ssr; s2[threadIdx.x] = rel; s3[threadIdx.x] = mx;
+    ProbePartial p{0.0, 0.0, 0.0, 0.f, 0.f};
+    auto add = [&](const ProbePartial& o) __attribute__((always_inline)) {
+        p.sse += o.sse; p.ssr += o.ssr; p.rel += o.rel; p.mx = fmaxf(p.mx, o.mx);
+    };
+#pragma unroll
+    for (int u = 0; u < kProbeBlocks / 256; ++u) add(v[u]);
+    red[t] = p;
     __syncthreads();
-    for (unsigned w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) {
-            s0[threadIdx.x] += s0[threadIdx.x + w];
-            s1[threadIdx.x] += s1[threadIdx.x + w];
-            s2[threadIdx.x] += s2[threadIdx.x + w];
-            s3[threadIdx.x] = fmaxf(s3[threadIdx.x], s3[threadIdx.x + w]);
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double e = s0[0], r = s1[0];
+    if (t >= 64) return;
+    // (t + 128) onto t and (t + 192) onto t + 64, then t + 64 onto t
+    add(red[t + 128]);
+    ProbePartial q = red[t + 64];
+    const ProbePartial& r = red[t + 192];
+    q.sse += r.sse; q.ssr += r.ssr; q.rel += r.rel; q.mx = fmaxf(q.mx, r.mx);
+    add(q);
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1)
+        add(ProbePartial{__shfl_down(p.sse, w, 64), __shfl_down(p.ssr, w, 64), __shfl_down(p.rel, w, 64), __shfl_down(p.mx, w, 64), 0.f});
+    if (t == 0) {
+        const double e = p.sse, r = p.ssr;
         stats->sum_sq_err = e;
         stats->sum_sq_ref = r;
         stats->rel_fro = r > 0.0 ? sqrt(e) / sqrt(r) : (e > 0.0 ? __builtin_inf() : 0.0);
-        stats->max_abs = static_cast<double>(s3[0]);
-        stats->mere = s2[0] / (static_cast<double>(M) * static_cast<double>(N));
+        stats->max_abs = static_cast<double>(p.mx);
+        stats->mere = p.rel / (static_cast<double>(M) * static_cast<double>(N));
     }
 }
 

@@ -39,6 +39,16 @@ def test_probe_shapes(orc, shape):
     _cmp_probe(orc, y, yref)
 
 
+@pytest.mark.parametrize("blocks", [63, 65, 129, 193, 256, 257, 2047, 2048, 2300])
+def test_probe_partial_counts(orc, blocks):
+    # four rows of 256 columns per workgroup; the error sits in the last row, i.e. in the last partial alone
+    rng = np.random.default_rng(blocks)
+    yref = rng.standard_normal((4 * blocks, 256)).astype(np.float32)
+    y = yref.copy()
+    y[-1, 100:] += 0.5
+    _cmp_probe(orc, y, yref)
+
+
 def test_probe_identical_inputs_and_repeatability(orc):
     rng = np.random.default_rng(0)
     yref = rng.standard_normal((4096, 512)).astype(np.float32)
