@@ -50,8 +50,9 @@ struct StripCfg {
 // NWV waves per workgroup; BF16IN: X arrives as bf16 and is quantized per row (amax, scale, e4m3 cast: the
 // arithmetic of the quantize kernel, bit for bit) on its way into the MFMA operand registers, so the FP8 copy of X
 // never exists in memory (Section 3.2: quantization fused with the layer).  A strip's 32 x K bf16 values are a
-// second set of 16 KS registers per lane that must stay live through the previous strip's epilogue: those
-// instances run with 4 waves of up to 512 registers instead of 8 of 256.
+// second set of 16 KS registers per lane that must stay live through the previous strip's epilogue: with more than 128
+// columns it waits in LDS, all or half of it (raw_steps), with K = 512 four waves of up to 512 registers run instead of
+// eight of 256.
 template <int NB, int KS, int NPH, int NWV, bool BF16IN, bool FP8OUT>
 __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p, const int strips_per_problem) {
     using C = StripCfg<NB, KS, NPH>;
@@ -162,19 +163,6 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                     raw[j][q] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xbr, off + 16u * q, 0, 0));
             }
         };
-        // loads i0 <= i < i1 of the KS * 4 that make up a raw strip (i = 4 j + q)
-        auto load_raw_part = [&](int s, u32x4 (&raw)[KS][4], int i0, int i1) __attribute__((always_inline)) {
-            int lane_o = lane;
-            asm volatile("; per-strip lane id" : "+v"(lane_o));
-            const int m = (s - s_base) * 32 + (lane_o & 31);
-#pragma unroll
-            for (int i = 0; i < KS * 4; ++i)
-                if (i >= i0 && i < i1) {
-                    const unsigned off = static_cast<unsigned>(m) * (KBT * 2u) +
-                                         static_cast<unsigned>((64 * (i / 4) + 32 * (lane_o >> 5)) * 2 + 16 * (i % 4));
-                    raw[i / 4][i % 4] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(xbr, off, 0, 0));
-                }
-        };
         // Where LDS has room the raw strip comes through it: loads straight into LDS move whole rows (1 KB runs; 16-byte chunk c
         // of row r at c ^ (r % 16)), each lane then takes its pieces from there.  Requested straight into the lanes that
         // need them a load instruction touches 64 lines for 16 bytes each, and four waves' strips do not stay in the CU's
@@ -277,8 +265,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
         };
 
         // scales, row statistics, normalization and store of one strip, from registers
-        // (after_block(nb) runs when column block nb has been stored and its 16 accumulators are dead)
-        auto epilogue = [&](int s, const float sxm, v16f (&acc)[NB], auto after_block) __attribute__((always_inline)) {
+        auto epilogue = [&](int s, const float sxm, v16f (&acc)[NB]) __attribute__((always_inline)) {
             int lane_o = lane;
             asm volatile("; per-strip lane id" : "+v"(lane_o));
             const int l32 = lane_o & 31, hk = lane_o >> 5;
@@ -442,7 +429,6 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                         const int ccol = nb * 32 + t_c * 8;
                         put(pk, r, ccol);
                     }
-                    after_block(nb);
                 }
             };
             // FP8 output for the next layer (Section 3.2: quantization fused before the output is written): the
@@ -512,8 +498,6 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                         const int ccol = nbp * 64 + t_c * 16;
                         put(ck, r, ccol);
                     }
-                    after_block(2 * nbp);
-                    after_block(2 * nbp + 1);
                 }
             };
             // (an instantiation of its own: in one kernel with the bf16 form the larger shapes spill more)
@@ -534,11 +518,6 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
         if (NPH == 1 && BF16IN) {
             // as below, with the raw strip in a register set of its own: requested right after the previous strip's
             // values have been cast, in flight through that strip's MFMAs and epilogue
-            // With 8 waves and the larger shapes the raw strip and the accumulators do not fit 256 registers side by
-            // side: the next strip is then requested piece by piece from inside the epilogue, each piece into the
-            // registers of a column block that has just been stored (LATE); the wave waits for it afterwards, and the
-            // other seven cover.
-            constexpr bool LATE = NWV == 8 && !(NB == 4 && KS <= 4) && !RAWLDS;
             u32x4 raw[KS][4];
             int s = t + wave;
             if (s < seg_end) {
@@ -554,7 +533,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                     if (more) request_raw(s + NWV);
                 }
                 convert(s, raw, x, sxm);
-                if (!LATE && more) load_raw(s + NWV, raw, KL);
+                if (more) load_raw(s + NWV, raw, KL);
                 __builtin_amdgcn_sched_barrier(0);
                 v16f acc[NB];
 #pragma unroll
@@ -562,9 +541,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
 #pragma unroll
                     for (int i = 0; i < 16; ++i) acc[nb][i] = 0.f;
                 mma(x, acc);
-                epilogue(s, sxm, acc, [&](int nb) __attribute__((always_inline)) {
-                    if (LATE && more) load_raw_part(s + NWV, raw, nb * (KS * 4) / NB, (nb + 1) * (KS * 4) / NB);
-                });
+                epilogue(s, sxm, acc);
                 // the next strip is there: of this wave's operations only the epilogue's 2 NB stores are younger
                 if (RAWLDS) wait_vmcnt<2 * NB>();
                 s += NWV;
@@ -589,7 +566,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                 if constexpr (SHORT_ROWS) load_x(s + NWV, 0, x, sxm, s + NWV < seg_end);
                 else if (s + NWV < seg_end) load_x(s + NWV, 0, x, sxm, true);
                 __builtin_amdgcn_sched_barrier(0);
-                epilogue(s, sx_cur, acc, [](int) {});
+                epilogue(s, sx_cur, acc);
                 if constexpr (SHORT_ROWS) wait_vmcnt<FP8OUT ? NB : 2 * NB>();
                 s += NWV;
             }
@@ -613,7 +590,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                     __syncthreads();
                     if (active) mma(x, acc);
                 }
-                if (active) epilogue(s, sxm, acc, [](int) {});
+                if (active) epilogue(s, sxm, acc);
             }
         }
         t = seg_end;
@@ -632,16 +609,16 @@ struct StripInst {
     void (*launch)(const GemmParams&, int, dim3, hipStream_t);
 };
 
-// waves of a fused-quantization instance: 8 where accumulators, the raw strip and the operands fit 256 registers
-// (N <= 128 with K <= 256; N = 256 with K = 128 and the piecewise request), else 4 with up to 512 each (measured:
-// the 8-wave forms that spill are slower than the 4-wave ones, 94 against 71-81 us at 64 x (4096 x 256 x 256))
-constexpr int fused_waves(int nb, int ks) { return ks <= 4 ? 8 : 4; }
+// waves of a fused-quantization instance: 8 where accumulators, the raw strip (or the half of it that is not in LDS) and the
+// operands fit 256 registers, K <= 256; else 4 with up to 512 each (eight that spill were slower: 64 x (4096 x 256 x 256),
+// M x N x K, 94 us where four took 65 and eight with half the strip in LDS take 63)
+constexpr int fused_waves(int ks) { return ks <= 4 ? 8 : 4; }
 
 template <int NB, int KS, int NPH>
 void launch_strip(const GemmParams& p, int spp, dim3 grid, hipStream_t s) {
     if (p.xb) {
         if constexpr (NPH == 1 && KS <= 8)                      // (K = 1024: the raw strip alone would be 256 registers)
-            gemm_strip_kernel<NB, KS, NPH, fused_waves(NB, KS), true, false><<<grid, fused_waves(NB, KS) * 64, StripCfg<NB, KS, NPH>::lds_fused(fused_waves(NB, KS)), s>>>(p, spp);
+            gemm_strip_kernel<NB, KS, NPH, fused_waves(KS), true, false><<<grid, fused_waves(KS) * 64, StripCfg<NB, KS, NPH>::lds_fused(fused_waves(KS)), s>>>(p, spp);
     } else if (p.outq) {
         gemm_strip_kernel<NB, KS, NPH, 8, false, true><<<grid, 512, StripCfg<NB, KS, NPH>::LDS, s>>>(p, spp);
     } else {
@@ -651,13 +628,13 @@ void launch_strip(const GemmParams& p, int spp, dim3 grid, hipStream_t s) {
 
 template <int NB, int KS, int NPH>
 const void* strip_fused_fn() {
-    if constexpr (NPH == 1 && KS <= 8) return reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, fused_waves(NB, KS), true, false>);
+    if constexpr (NPH == 1 && KS <= 8) return reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, fused_waves(KS), true, false>);
     else return nullptr;
 }
 
 #define LOKA_STRIP(NB, KS, NPH)                                                                                     \
     {NB, KS, NPH, reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, 8, false, false>), strip_fused_fn<NB, KS, NPH>(), \
-     reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, 8, false, true>), StripCfg<NB, KS, NPH>::LDS, StripCfg<NB, KS, NPH>::lds_fused(fused_waves(NB, KS)), \
+     reinterpret_cast<const void*>(&gemm_strip_kernel<NB, KS, NPH, 8, false, true>), StripCfg<NB, KS, NPH>::LDS, StripCfg<NB, KS, NPH>::lds_fused(fused_waves(KS)), \
      &launch_strip<NB, KS, NPH>}
 
 // column blocks, K steps per phase, phases (K = 64 KS NPH; one phase when W fits the LDS)
