@@ -496,13 +496,13 @@ static void launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t l
 #undef LOKA_QR
 }
 
-// Row ranges of a COL amax pass: 128 rows each (four rows per thread) as long as the cast has few partials to fold.
 // COL in one kernel (G_COL_ALL) instead of two: every workgroup reads all row tiles of its columns, so the time grows with
 // their number where the amax pass costs a launch.  Measured (us, two kernels -> one): 256 x 1024 7.3 -> 4.8, 256 x 65536
 // 18.3 -> 11.5, 256 x 262144 60.9 -> 51.8; 512 x 1024 7.3 -> 5.9, 512 x 16384 11.2 -> 8.1, but 512 x 65536 31.6 -> 40.7 and
 // 1024 x 1024 7.4 -> 8.5.
 static bool col_in_one(int64_t rows, int64_t cols) { return rows <= 256 || (rows <= 512 && cols <= 16384); }
 
+// Row ranges of a COL amax pass: 128 rows each (four rows per thread) as long as the cast has few partials to fold.
 static int64_t col_rows_per_part(int64_t rows) {
     const int64_t per = (rows + kMaxParts - 1) / kMaxParts;
     return ((per < 128 ? 128 : per) + 31) / 32 * 32;

@@ -24,6 +24,8 @@
 // rows in the same order.
 #include "gemm_common.h"
 
+#include <type_traits>
+
 namespace loka {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
@@ -102,6 +104,10 @@ __host__ __device__ __forceinline__ int diag_pair(int t, int T) { return t * T -
 // write 512 consecutive bytes, and MFMA block t (positions 32 t .. 32 t + 31) is the set of columns 8 m + t,
 // m = 0..31 = the block's MFMA row (or column) index.  Which tile column lands on which MFMA row is free as
 // long as the epilogue knows: wave (wi, wj) owns blocks 4 wi .. 4 wi + 3 on the i side, 2 wj, 2 wj + 1 on the j side.
+// A diagonal pair needs only the MFMA blocks (a, b) with a <= b, block (b, a) being the transpose of (a, b): 36 of 64.  Its
+// waves 0..5 own the four blocks of one pair of 2-block groups each, waves 6 and 7 the three blocks within each of two groups;
+// a SIMD (waves w, w + 4) then issues 8 or 10 MFMAs per k step instead of 16.  The blocks below the diagonal are filled in from
+// the same registers when the tile leaves through LDS.  (Ranges of few stages: all 64 blocks, like any other pair.)
 // Waves 0..3 stage the i tile, waves 4..7 the j tile (nothing on a diagonal pair, where both operands are
 // the i tile).  The loads of stage s + 1 are in flight while stage s is multiplied (registers), two LDS
 // buffers, one barrier per stage.
@@ -173,120 +179,191 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
 #pragma unroll
         for (int e = 0; e < 2; ++e) fb[e] = __builtin_bit_cast(v8bf, *reinterpret_cast<const u32x4*>(Bt + b_off + e * 512 + kk * 8192));
     };
-    v16f acc[4][2];
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[t][e][r] = 0.f;
-    auto mma = [&](const v8bf (&fa)[4], const v8bf (&fb)[2]) __attribute__((always_inline)) {
+    auto run = [&](auto diag_c) __attribute__((always_inline)) {
+        constexpr bool DIAG = decltype(diag_c)::value;
+        v16f acc[4][2];
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int e = 0; e < 2; ++e)
-                acc[t][e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t], fb[e], acc[t][e], 0, 0, 0);
-    };
-    // issue order of one k step: an MFMA, then one LDS read of the next step's fragments, six times over
-    auto interleave = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
-    };
-    // column sums (diagonal pairs): thread = (position tid % 256, row groups 4 (tid / 256) .. + 3), fp64
-    double cs = 0.0;
-    const int cs_off = (tid >> 8) * 4 * 4096 + (tid & 255) * 16;
+                for (int r = 0; r < 16; ++r) acc[t][e][r] = 0.f;
+        auto mma = [&](const v8bf (&fa)[4], const v8bf (&fb)[2]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    acc[t][e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t], fb[e], acc[t][e], 0, 0, 0);
+        };
+        // issue order of one k step: an MFMA, then one LDS read of the next step's fragments, six times over
+        auto interleave = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        };
+        // diagonal pairs: groups (2 blocks each) of this wave; waves 0..5 multiply the two, waves 6, 7 each with itself
+        const int g0 = (0x20102100u >> (4 * wave)) & 3, g1 = (0x31223331u >> (4 * wave)) & 3;
+        const bool self = wave >= 6;
+        auto read_diag = [&](const uint8_t* At, int kk, v8bf (&f)[4]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                f[t] = __builtin_bit_cast(v8bf, *reinterpret_cast<const u32x4*>(At + fr_off + (2 * (t < 2 ? g0 : g1) + (t & 1)) * 512 + kk * 8192));
+        };
+        auto mma_diag = [&](const v8bf (&f)[4]) __attribute__((always_inline)) {
+            if (self) {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+#pragma unroll
+                    for (int e = t & 1; e < 2; ++e)
+                        acc[t][e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[t], f[(t & 2) + e], acc[t][e], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int e = 0; e < 2; ++e)
+                        acc[t][e] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[t], f[2 + e], acc[t][e], 0, 0, 0);
+            }
+        };
+        // column sums (diagonal pairs): thread = (position tid % 256, row groups 4 (tid / 256) .. + 3), fp64
+        double cs = 0.0;
+        const int cs_off = (tid >> 8) * 4 * 4096 + (tid & 255) * 16;
 
-    fetch(0);
-    stage(0);
-    __syncthreads();
-    for (int s = 0; s < nst; ++s) {
-        const uint8_t* At = smem + (s & 1) * TRK_STAGEB;
-        const uint8_t* Bt = diag ? At : At + TRK_TILEB;
-        // the two waves of a SIMD (w, w + 4) request their blocks of the next stage at different times: a wave
-        // sits in the load issue until the memory pipeline has taken its requests, and should not do so together
-        // with the wave that shares its matrix pipe.  (Measured: both groups at the start of the stage 750 us
-        // at B = 32768, K = 4096; staggered 690 us; the eight loads spread over the stage, two per k step, with
-        // a second register set so that they have a whole stage to land: 955 us.)
-        if (s + 1 < nst && wave < 4) fetch(s + 1);
-        v8bf fa0[4], fb0[2], fa1[4], fb1[2];
-        read_frags(At, Bt, 0, fa0, fb0);
-        read_frags(At, Bt, 1, fa1, fb1);
-        mma(fa0, fb0);
-        interleave();
-        if (s + 1 < nst && wave >= 4) fetch(s + 1);
-        read_frags(At, Bt, 2, fa0, fb0);
-        mma(fa1, fb1);
-        interleave();
-        read_frags(At, Bt, 3, fa1, fb1);
-        mma(fa0, fb0);
-        interleave();
-        mma(fa1, fb1);
-        if (diag) {
+        fetch(0);
+        stage(0);
+        __syncthreads();
+        for (int s = 0; s < nst; ++s) {
+            const uint8_t* At = smem + (s & 1) * TRK_STAGEB;
+            const uint8_t* Bt = diag ? At : At + TRK_TILEB;
+            // the two waves of a SIMD (w, w + 4) request their blocks of the next stage at different times: a wave
+            // sits in the load issue until the memory pipeline has taken its requests, and should not do so together
+            // with the wave that shares its matrix pipe.  (Measured: both groups at the start of the stage 750 us
+            // at B = 32768, K = 4096; staggered 690 us; the eight loads spread over the stage, two per k step, with
+            // a second register set so that they have a whole stage to land: 955 us.)
+            if (s + 1 < nst && wave < 4) fetch(s + 1);
+            if constexpr (!DIAG) {
+                v8bf fa0[4], fb0[2], fa1[4], fb1[2];
+                read_frags(At, Bt, 0, fa0, fb0);
+                read_frags(At, Bt, 1, fa1, fb1);
+                mma(fa0, fb0);
+                interleave();
+                if (s + 1 < nst && wave >= 4) fetch(s + 1);
+                read_frags(At, Bt, 2, fa0, fb0);
+                mma(fa1, fb1);
+                interleave();
+                read_frags(At, Bt, 3, fa1, fb1);
+                mma(fa0, fb0);
+                interleave();
+                mma(fa1, fb1);
+            } else {
+                v8bf f0[4], f1[4];
+                read_diag(At, 0, f0);
+                read_diag(At, 1, f1);
+                mma_diag(f0);
+                read_diag(At, 2, f0);
+                mma_diag(f1);
+                read_diag(At, 3, f1);
+                mma_diag(f0);
+                mma_diag(f1);
+            }
+            if (diag) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const u32x4 v = *reinterpret_cast<const u32x4*>(At + cs_off + g * 4096);
+                for (int g = 0; g < 4; ++g) {
+                    const u32x4 v = *reinterpret_cast<const u32x4*>(At + cs_off + g * 4096);
 #pragma unroll
-                for (int w = 0; w < 4; ++w) {
-                    cs += static_cast<double>(bf16_lo(v[w]));
-                    cs += static_cast<double>(bf16_hi(v[w]));
+                    for (int w = 0; w < 4; ++w) {
+                        cs += static_cast<double>(bf16_lo(v[w]));
+                        cs += static_cast<double>(bf16_hi(v[w]));
+                    }
                 }
             }
+            if (s + 1 < nst) stage((s + 1) & 1);
+            __syncthreads();
         }
-        if (s + 1 < nst) stage((s + 1) & 1);
-        __syncthreads();
-    }
 
-    // raw partial scatter: element r of a lane is MFMA row R = 8 (r / 4) + 4 h + r % 4, MFMA column C = lane % 32 of its
-    // block; block (ta, tb) row R is tile row 8 R + 4 wi + ta, column C is tile column 8 C + 2 wj + tb: a lane holds
-    // pairs of columns 32 bytes apart.  Stored straight from registers every instruction would scatter 8-byte pieces
-    // over 64 cache lines (measured: 70 us of the 780 us at B = 32768, K = 4096); the tile goes through the stage
-    // buffers instead, 128 rows at a time (R < 16, then R >= 16 = elements r < 8, then r >= 8), and leaves as whole
-    // 1 KB rows.  LDS row: the four waves' columns side by side, position 64 wj + ((2 C + tb) ^ (wj >= 2 ? 32 : 0)), so
-    // that the writes of 32 lanes are 256 consecutive bytes and the two 8-byte reads of the 32 lanes that share a
-    // row half fall on different banks.
-    // (offsets recomputed from an opaque copy of the lane id: derived from a loop invariant, the compiler
-    // would keep the addresses alive across the main loop, in registers the accumulators need)
-    int lane_o = lane, tid_o = tid;
-    asm volatile("" : "+v"(lane_o), "+v"(tid_o));
-    float* const stg = reinterpret_cast<float*>(smem);
-    const int st_w = (8 * 4 * (lane_o >> 5) + 4 * wi) * 256 + wj * 64 + ((2 * (lane_o & 31)) ^ ((wj >> 1) * 32));
-    const int q4 = tid_o & 63, cq = q4 >> 1, uq = q4 & 1;
-    const int st_r = (tid_o >> 6) * 256 + (2 * uq) * 64 + ((2 * cq) ^ (uq * 32));
-    float* const out = p.partial + static_cast<int64_t>(id) * (TRK_T * TRK_T) + (tid_o >> 6) * TRK_T + 4 * q4;
+        // raw partial scatter: element r of a lane is MFMA row R = 8 (r / 4) + 4 h + r % 4, MFMA column C = lane % 32 of its
+        // block; block (ta, tb) row R is tile row 8 R + 4 wi + ta, column C is tile column 8 C + 2 wj + tb: a lane holds
+        // pairs of columns 32 bytes apart.  Stored straight from registers every instruction would scatter 8-byte pieces
+        // over 64 cache lines (measured: 70 us of the 780 us at B = 32768, K = 4096); the tile goes through the stage
+        // buffers instead, 128 rows at a time (R < 16, then R >= 16 = elements r < 8, then r >= 8), and leaves as whole
+        // 1 KB rows.  LDS row: the four waves' columns side by side, position 64 wj + ((2 C + tb) ^ (wj >= 2 ? 32 : 0)), so
+        // that the writes of 32 lanes are 256 consecutive bytes and the two 8-byte reads of the 32 lanes that share a
+        // row half fall on different banks.
+        // (offsets recomputed from an opaque copy of the lane id: derived from a loop invariant, the compiler
+        // would keep the addresses alive across the main loop, in registers the accumulators need)
+        int lane_o = lane, tid_o = tid;
+        asm volatile("" : "+v"(lane_o), "+v"(tid_o));
+        float* const stg = reinterpret_cast<float*>(smem);
+        // Diagonal pairs: acc[t][e] is block (a, b) = (2 ga + t % 2, 2 gb + e); rows 8 R .. 8 R + 7 of the half are rotated by
+        // an XOR of 2 R, so that the transposed writes (lanes = rows 8 C + b) spread over the banks as well.
+        const int h_o = lane_o >> 5, c_o = lane_o & 31;
+        auto grp_a = [&](int t) __attribute__((always_inline)) { return t < 2 ? g0 : g1; };
+        auto grp_b = [&](int t) __attribute__((always_inline)) { return DIAG ? (self ? grp_a(t) : g1) : wj; };
+        const int q4 = tid_o & 63, cq = q4 >> 1, uq = q4 & 1;
+        const int st_r = (tid_o >> 6) * 256 + (2 * uq) * 64, pos_r = (2 * cq) ^ (uq * 32);
+        float* const out = p.partial + static_cast<int64_t>(id) * (TRK_T * TRK_T) + (tid_o >> 6) * TRK_T + 4 * q4;
 #pragma unroll
-    for (int ps = 0; ps < 2; ++ps) {
-        if (ps) __syncthreads();                                        // the first half has been read out of LDS
+        for (int ps = 0; ps < 2; ++ps) {
+            if (ps) __syncthreads();                                        // the first half has been read out of LDS
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+            for (int t = 0; t < 4; ++t) {
+                if (DIAG && !self && t >= 2) continue;
+                const int gb = grp_b(t), row = 32 * h_o + (DIAG ? 2 * grp_a(t) + (t & 1) : 4 * wi + t);
+                const int pos = (2 * c_o) ^ ((gb >> 1) * 32) ^ (DIAG ? 8 * h_o : 0);
+                float* const st = stg + row * 256 + gb * 64;
 #pragma unroll
-            for (int r8 = 0; r8 < 8; ++r8) {
-                const int r = 8 * ps + r8;
-                // local row 8 R' + 4 wi + t with R' = 8 (r8 / 4) + 4 h + r8 % 4
-                *reinterpret_cast<f32x2_t*>(stg + st_w + (64 * (r8 >> 2) + 8 * (r8 & 3) + t) * 256) = f32x2_t{acc[t][0][r], acc[t][1][r]};
+                for (int r8 = 0; r8 < 8; ++r8) {
+                    const int r = 8 * ps + r8, key = DIAG ? 16 * (r8 >> 2) + 2 * (r8 & 3) : 0;
+                    // local row 8 R' + a with R' = 8 (r8 / 4) + 4 h + r8 % 4
+                    *reinterpret_cast<f32x2_t*>(st + (64 * (r8 >> 2) + 8 * (r8 & 3)) * 256 + (pos ^ key)) = f32x2_t{acc[t][0][r], acc[t][1][r]};
+                }
             }
-        __syncthreads();
+            if constexpr (DIAG) {
+                // block (b, a): element (R, C) at row 8 C + b, column 8 R + a
+                if ((c_o >> 4) == ps) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        if (self ? (t & 1) != 0 : t >= 2) continue;
+                        const int ga = grp_a(t), gb = grp_b(t);
+                        const int pos = (t & 1) ^ ((ga >> 1) * 32) ^ (8 * h_o) ^ (2 * (c_o & 15));
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            if (self && e == 0) continue;                   // (a, a) is its own mirror image
+                            float* const st = stg + (8 * (c_o & 15) + 2 * gb + e) * 256 + ga * 64;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) st[pos ^ (16 * (r >> 2) + 2 * (r & 3))] = acc[t][e][r];
+                        }
+                    }
+                }
+            }
+            __syncthreads();
 #pragma unroll 4
-        for (int it = 0; it < 16; ++it) {
-            const f32x2_t lo = *reinterpret_cast<const f32x2_t*>(stg + st_r + it * 8 * 256);
-            const f32x2_t hi = *reinterpret_cast<const f32x2_t*>(stg + st_r + it * 8 * 256 + 64);
-            *reinterpret_cast<v4f*>(out + (128 * ps + it * 8) * TRK_T) = v4f{lo[0], lo[1], hi[0], hi[1]};
+            for (int it = 0; it < 16; ++it) {
+                const float* const src = stg + st_r + it * 8 * 256 + (pos_r ^ (DIAG ? 2 * it : 0));
+                const f32x2_t lo = *reinterpret_cast<const f32x2_t*>(src);
+                const f32x2_t hi = *reinterpret_cast<const f32x2_t*>(src + 64);
+                *reinterpret_cast<v4f*>(out + (128 * ps + it * 8) * TRK_T) = v4f{lo[0], lo[1], hi[0], hi[1]};
+            }
         }
-    }
-    if (diag) {
-        // position pos holds column 8 (pos % 32) + pos / 32
-        const int pos = tid & 255, col = 8 * (pos & 31) + (pos >> 5);
-        red[(tid >> 8) * TRK_T + col] = cs;
-        __syncthreads();
-        if (tid < TRK_T) {
-            p.colsum[static_cast<int64_t>(id) * TRK_T + tid] = red[tid] + red[TRK_T + tid];
-            const int k = ti * TRK_T + tid;
-            if (id < p.pairs && k < p.K) p.mu_old[k] = p.mu[k];          // id = range * pairs + pair
+        if (diag) {
+            // position pos holds column 8 (pos % 32) + pos / 32
+            const int pos = tid & 255, col = 8 * (pos & 31) + (pos >> 5);
+            red[(tid >> 8) * TRK_T + col] = cs;
+            __syncthreads();
+            if (tid < TRK_T) {
+                p.colsum[static_cast<int64_t>(id) * TRK_T + tid] = red[tid] + red[TRK_T + tid];
+                const int k = ti * TRK_T + tid;
+                if (id < p.pairs && k < p.K) p.mu_old[k] = p.mu[k];          // id = range * pairs + pair
+            }
         }
-    }
+    };
+    // Short ranges do not pay for the transposed writes (us, all blocks -> a <= b, ranges in stages: 2000 x 64, 2, 13.4 -> 14.2;
+    // 4096 x 512, 4, 22.0 -> 22.4; 1593 x 1168, 5, 24.3 -> 24.3; 18786 x 456, 9, 29.9 -> 29.6; 30000 x 768, 17, 46.0 -> 44.5;
+    // 32768 x 1024, 27, 61.6 -> 59.3; 65536 x 1024, 41, 98.2 -> 91.0; 32768 x 4096, 103, 620.8 -> 609.1)
+    if (diag && nst >= 6) run(std::true_type{});
+    else run(std::false_type{});
 }
 
 // grid (pairs, 64): workgroup y handles the 32 x 32 block (y / 8, y % 8) of its pair's tile, one run of four

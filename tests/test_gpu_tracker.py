@@ -63,9 +63,10 @@ def test_single_update_from_a_given_state(orc, shape):
     assert np.array_equal(g[1], g[1].T), "symmetric state in, symmetric state out (bit for bit)"
 
 
-@pytest.mark.parametrize("shape", [(33000, 8), (9000, 72), (40000, 264), (70000, 64)])
+@pytest.mark.parametrize("shape", [(33000, 8), (9000, 72), (40000, 264), (70000, 64), (16384, 392)])
 def test_many_row_ranges(orc, shape):
-    # few tiles and many rows: more than 32 row ranges, whose column sums and partial scatters the merge folds
+    # few tiles and many rows: more than 32 row ranges, whose column sums and partial scatters the merge folds; ranges of 6
+    # stages and more, where a diagonal tile's lower blocks are the transposes of the upper ones
     rows, K = shape
     x = synth.correlated(rows, K, seed=rows + K)
     n_old, mu, sigma = _state(K, K)
