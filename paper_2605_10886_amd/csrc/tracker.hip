@@ -23,6 +23,7 @@
 // single 16-byte LDS read.  The MFMA's k order is irrelevant here because both operands come from the same
 // rows in the same order.
 #include "gemm_common.h"
+#include "tracker_stage.h"
 
 #include <type_traits>
 
@@ -205,8 +206,8 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
             __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
         };
         // diagonal pairs: groups (2 blocks each) of this wave; waves 0..5 multiply the two, waves 6, 7 each with itself
-        const int g0 = (0x20102100u >> (4 * wave)) & 3, g1 = (0x31223331u >> (4 * wave)) & 3;
-        const bool self = wave >= 6;
+        const int g0 = trk_group(wave, 0), g1 = trk_group(wave, 1);
+        const bool self = trk_self(wave);
         auto read_diag = [&](const uint8_t* At, int kk, v8bf (&f)[4]) __attribute__((always_inline)) {
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -288,16 +289,13 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
         // pairs of columns 32 bytes apart.  Stored straight from registers every instruction would scatter 8-byte pieces
         // over 64 cache lines (measured: 70 us of the 780 us at B = 32768, K = 4096); the tile goes through the stage
         // buffers instead, 128 rows at a time (R < 16, then R >= 16 = elements r < 8, then r >= 8), and leaves as whole
-        // 1 KB rows.  LDS row: the four waves' columns side by side, position 64 wj + ((2 C + tb) ^ (wj >= 2 ? 32 : 0)), so
-        // that the writes of 32 lanes are 256 consecutive bytes and the two 8-byte reads of the 32 lanes that share a
-        // row half fall on different banks.
+        // 1 KB rows (tracker_stage.h: the writes of 32 lanes are 256 consecutive bytes).
         // (offsets recomputed from an opaque copy of the lane id: derived from a loop invariant, the compiler
         // would keep the addresses alive across the main loop, in registers the accumulators need)
         int lane_o = lane, tid_o = tid;
         asm volatile("" : "+v"(lane_o), "+v"(tid_o));
         float* const stg = reinterpret_cast<float*>(smem);
-        // Diagonal pairs: acc[t][e] is block (a, b) = (2 ga + t % 2, 2 gb + e); rows 8 R .. 8 R + 7 of the half are rotated by
-        // an XOR of 2 R, so that the transposed writes (lanes = rows 8 C + b) spread over the banks as well.
+        // Diagonal pairs: acc[t][e] is block (a, b) = (2 ga + t % 2, 2 gb + e).
         const int h_o = lane_o >> 5, c_o = lane_o & 31;
         auto grp_a = [&](int t) __attribute__((always_inline)) { return t < 2 ? g0 : g1; };
         auto grp_b = [&](int t) __attribute__((always_inline)) { return DIAG ? (self ? grp_a(t) : g1) : wj; };
@@ -309,31 +307,31 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
             if (ps) __syncthreads();                                        // the first half has been read out of LDS
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                if (DIAG && !self && t >= 2) continue;
-                const int gb = grp_b(t), row = 32 * h_o + (DIAG ? 2 * grp_a(t) + (t & 1) : 4 * wi + t);
-                const int pos = (2 * c_o) ^ ((gb >> 1) * 32) ^ (DIAG ? 8 * h_o : 0);
-                float* const st = stg + row * 256 + gb * 64;
+                if (DIAG && !self && !trk_pair_holds(t)) continue;
+                const TrkAddr ad = trk_direct(DIAG, DIAG ? 2 * grp_a(t) + (t & 1) : 4 * wi + t, 2 * grp_b(t), h_o, c_o);
+                float* const st = stg + ad.row;
+                if (DIAG && self && !trk_self_stores(t, 0)) {
 #pragma unroll
-                for (int r8 = 0; r8 < 8; ++r8) {
-                    const int r = 8 * ps + r8, key = DIAG ? 16 * (r8 >> 2) + 2 * (r8 & 3) : 0;
-                    // local row 8 R' + a with R' = 8 (r8 / 4) + 4 h + r8 % 4
-                    *reinterpret_cast<f32x2_t*>(st + (64 * (r8 >> 2) + 8 * (r8 & 3)) * 256 + (pos ^ key)) = f32x2_t{acc[t][0][r], acc[t][1][r]};
+                    for (int r8 = 0; r8 < 8; ++r8) st[trk_direct_step(r8) + (ad.pos ^ trk_direct_key(DIAG, r8)) + 1] = acc[t][1][8 * ps + r8];
+                } else {
+#pragma unroll
+                    for (int r8 = 0; r8 < 8; ++r8)
+                        *reinterpret_cast<f32x2_t*>(st + trk_direct_step(r8) + (ad.pos ^ trk_direct_key(DIAG, r8))) =
+                            f32x2_t{acc[t][0][8 * ps + r8], acc[t][1][8 * ps + r8]};
                 }
             }
             if constexpr (DIAG) {
-                // block (b, a): element (R, C) at row 8 C + b, column 8 R + a
                 if ((c_o >> 4) == ps) {
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        if (self ? (t & 1) != 0 : t >= 2) continue;
-                        const int ga = grp_a(t), gb = grp_b(t);
-                        const int pos = (t & 1) ^ ((ga >> 1) * 32) ^ (8 * h_o) ^ (2 * (c_o & 15));
+                        if (self ? !trk_self_mirrors(t, 1) : !trk_pair_holds(t)) continue;
 #pragma unroll
                         for (int e = 0; e < 2; ++e) {
-                            if (self && e == 0) continue;                   // (a, a) is its own mirror image
-                            float* const st = stg + (8 * (c_o & 15) + 2 * gb + e) * 256 + ga * 64;
+                            if (self && !trk_self_mirrors(t, e)) continue;         // (a, a) is its own mirror image
+                            const TrkAddr ad = trk_mirror(2 * grp_a(t) + (t & 1), 2 * grp_b(t) + e, h_o, c_o);
+                            float* const st = stg + ad.row;
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) st[pos ^ (16 * (r >> 2) + 2 * (r & 3))] = acc[t][e][r];
+                            for (int r = 0; r < 16; ++r) st[ad.pos ^ trk_mirror_key(r)] = acc[t][e][r];
                         }
                     }
                 }

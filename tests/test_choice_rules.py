@@ -147,6 +147,51 @@ int main() {
                 sent += [f"W{k + 2}"] * 4
 
 
+def test_every_word_of_a_diagonal_tracker_tile_has_one_writer(tmp_path):
+    # A diagonal pair's tile on its way out, half by half: every LDS word is written once, by the lane that holds its element or
+    # the mirror image of it; two lanes' writes to one word have no order that the kernel may rely on.
+    src = tmp_path / "stage.hip"
+    src.write_text("""#include "tracker_stage.h"
+#include <cstdio>
+#include <vector>
+using namespace loka;
+int main() {
+    int bad = 0;
+    for (int ps = 0; ps < 2; ++ps) {
+        std::vector<int> writers(128 * 256), held(128 * 256, -1);               // held: 256 * tile row + tile column
+        auto put = [&](int word, int row, int col) { ++writers.at(word); held[word] = 256 * row + col; };
+        for (int wave = 0; wave < 8; ++wave)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int t = 0; t < 4; ++t)
+                    for (int e = 0; e < 2; ++e) {
+                        const bool self = trk_self(wave);
+                        const int h = lane >> 5, c = lane & 31, ga = trk_group(wave, t < 2 ? 0 : 1), gb = self ? ga : trk_group(wave, 1);
+                        const int a = 2 * ga + (t & 1), b = 2 * gb;
+                        const bool stores = self ? trk_self_stores(t, e) : trk_pair_holds(t), mirrors = self ? trk_self_mirrors(t, e) : trk_pair_holds(t);
+                        for (int r = 0; r < 16; ++r) {
+                            const int R = 8 * (r >> 2) + 4 * h + (r & 3), row = 8 * R + a, col = 8 * c + b + e;
+                            const TrkAddr d = trk_direct(true, a, b, h, c), m = trk_mirror(a, b + e, h, c);
+                            if (stores && r / 8 == ps) put(d.row + trk_direct_step(r & 7) + (d.pos ^ trk_direct_key(true, r & 7)) + e, row, col);
+                            if (mirrors && c / 16 == ps) put(m.row + (m.pos ^ trk_mirror_key(r)), col, row);
+                        }
+                    }
+        for (int row = 0; row < 128; ++row)
+            for (int col = 0; col < 256; ++col) {
+                const int R = row / 8, w = row * 256 + ((col & 7) >> 1) * 64 + ((2 * (col / 8)) ^ (((col & 7) >> 2) * 32) ^ (2 * R)) + (col & 1);
+                if (writers[w] != 1 || held[w] != 256 * (128 * ps + row) + col)
+                    if (++bad < 20) std::printf("half %d row %d column %d: %d writers, element %d\\n", ps, row, col, writers[w], held[w]);
+            }
+    }
+    return bad ? 1 : 0;
+}
+""")
+    exe = str(tmp_path / "stage")
+    subprocess.run([build._hipcc(), "--cuda-host-only", "-O1", "-std=c++17", "-I", os.path.join(build.HERE, "csrc"), str(src), "-o", exe],
+                   check=True, capture_output=True)
+    r = subprocess.run([exe], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
+
+
 def _chosen(form, M, N, K, norm=B.NORM_LAYERNORM, batch=1):
     """Name of the kernel behind variant = -1 for a call of that form (the library's own rule, a C++ function of the descriptor)."""
     fn = B.lib().loka_default_variant if form == "bf16" else getattr(B.lib(), {"fp8out": "_ZN4loka22variant_fp8out_defaultEPK14loka_gemm_desc",
