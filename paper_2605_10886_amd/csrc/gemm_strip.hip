@@ -58,11 +58,16 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
     using C = StripCfg<NB, KS, NPH>;
     static_assert(!BF16IN || NPH == 1, "fused quantization needs the whole row of X in one pass");
     constexpr int NT = C::NT, KB = C::KB, KBT = C::KBT, KEYMASK = C::SWIN - 1;
-    // Up to rows of 256: statistics and stores without branches, and the next strip's operands awaited by count; with fused
-    // quantization the stores everywhere.  Longer rows' operands leave no registers for it: the kernel spills more (M x N x K:
-    // 65536 x 128 x 1024 21.5 -> 23.2 us, with FP8 output 23.9 -> 25.3 and 64 x (4096 x 256 x 512) 62.6 -> 64.8; but
-    // 64 x (4096 x 256 x 256) 38.9 -> 37.6 and, with FP8 output, 48.6 -> 45.6).
+    // Up to rows of 256: statistics and stores without branches; with fused quantization the stores everywhere.  Longer rows'
+    // operands leave no registers for it: the kernel spills more (M x N x K: 65536 x 128 x 1024 21.5 -> 23.2 us, with FP8
+    // output 23.9 -> 25.3 and 64 x (4096 x 256 x 512) 62.6 -> 64.8; but 64 x (4096 x 256 x 256) with FP8 output 48.6 -> 45.6).
     constexpr bool SHORT_ROWS = KS < 8 && NPH == 1, LEAN = SHORT_ROWS || BF16IN;
+    // One sequence of stores for layers with and without gamma and beta, so that the next strip's operands, requested before
+    // it, can be awaited by count and the stores stay in flight.  With a sequence on each side of a branch the compiler
+    // sees a path without any, on which the count does not cover the operands, and drains every store at the next use.
+    // (Geometric mean over 160 layers, two sequences -> one: 1.4 % faster; 66481 x 240 x 256, M x N x K, 16.4 -> 15.6 us.)  Not
+    // where the branches and registers cost more than that: FP8 output 1.4 to 14 % slower, fused with N <= 128 2.5 to 4 %.
+    constexpr bool ONE_PATH = SHORT_ROWS && !FP8OUT && !BF16IN;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
 
     const int lane = threadIdx.x & 63;
@@ -375,8 +380,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             const int t_wr = l32 * 64, t_key = (l32 >> 2) & 3;
             const int t_row = lane_o >> 2, t_c = lane_o & 3;                   // store side: row (+ 16 j), chunk
             // (buffer stores relative to the strip's first row: the descriptor ends with the last row that exists, columns past
-            // N get an offset beyond it.  Every strip issues the same stores, no branch among them, so that a wait for the
-            // next strip's operands, requested before them, leaves them in flight.)
+            // N get an offset beyond it; every strip issues the same stores, no branch among them.)
             const int row0 = (s - s_base) * 32, rows_here = p.M - row0 < 32 ? p.M - row0 : 32;
             const __amdgpu_buffer_rsrc_t orsrc =
                 FP8OUT ? __builtin_amdgcn_make_buffer_rsrc(p.outq + static_cast<int64_t>(g) * p.strideO + static_cast<int64_t>(row0) * p.N, 0,
@@ -396,30 +400,33 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                     }
                 }
             };
-            // (without gamma and beta the affine step is x * 1 + 0: skipped, same bits, no table reads)
-            auto normalize_store = [&](auto affine_tag) __attribute__((always_inline)) {
-                constexpr bool AFFINE = decltype(affine_tag)::value;
+            // The affine step (without gamma and beta it is x * 1 + 0: skipped, same bits, no table reads)
+            auto affine_step = [&](float (&o)[8], int nb, int half) __attribute__((always_inline)) {
+                const int col = nb * 32 + hk * 16;
+                const v4f* g4 = reinterpret_cast<const v4f*>(smem + C::OFF_GM + col * 4);
+                const v4f* b4 = reinterpret_cast<const v4f*>(smem + C::OFF_BT + col * 4);
+                const v4f gq0 = g4[2 * half], gq1 = g4[2 * half + 1], bq0 = b4[2 * half], bq1 = b4[2 * half + 1];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    o[e] = __builtin_fmaf(o[e], gq0[e], bq0[e]);
+                    o[4 + e] = __builtin_fmaf(o[4 + e], gq1[e], bq1[e]);
+                }
+            };
+            // (affine: a compile-time constant per path, or (ONE_PATH) the run-time flag)
+            auto normalize_store = [&](auto affine) __attribute__((always_inline)) {
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) {
-                    const int col = nb * 32 + hk * 16;
-                    const v4f* g4 = reinterpret_cast<const v4f*>(smem + C::OFF_GM + col * 4);
-                    const v4f* b4 = reinterpret_cast<const v4f*>(smem + C::OFF_BT + col * 4);
+                    float o[2][8];
+#pragma unroll
+                    for (int half = 0; half < 2; ++half)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) o[half][e] = __builtin_fmaf(acc[nb][8 * half + e], rstd, nmr);
+                    if (affine) { affine_step(o[0], nb, 0); affine_step(o[1], nb, 1); }
 #pragma unroll
                     for (int half = 0; half < 2; ++half) {
-                        float o[8];
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) o[e] = __builtin_fmaf(acc[nb][8 * half + e], rstd, nmr);
-                        if (AFFINE) {
-                            const v4f gq0 = g4[2 * half], gq1 = g4[2 * half + 1], bq0 = b4[2 * half], bq1 = b4[2 * half + 1];
-#pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                o[e] = __builtin_fmaf(o[e], gq0[e], bq0[e]);
-                                o[4 + e] = __builtin_fmaf(o[4 + e], gq1[e], bq1[e]);
-                            }
-                        }
                         u32x4 pk;
-                        pk.x = pack_bf16x2(o[0], o[1]); pk.y = pack_bf16x2(o[2], o[3]);
-                        pk.z = pack_bf16x2(o[4], o[5]); pk.w = pack_bf16x2(o[6], o[7]);
+                        pk.x = pack_bf16x2(o[half][0], o[half][1]); pk.y = pack_bf16x2(o[half][2], o[half][3]);
+                        pk.z = pack_bf16x2(o[half][4], o[half][5]); pk.w = pack_bf16x2(o[half][6], o[half][7]);
                         *reinterpret_cast<u32x4*>(tbuf + t_wr + (((2 * hk + half) ^ t_key) << 4)) = pk;
                     }
 #pragma unroll
@@ -436,23 +443,12 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             // tensor.  The whole row lives in this lane and lane ^ 32, so the row amax needs one exchange; the values
             // are then computed a second time (keeping 128 packed values would not fit beside the accumulators),
             // cast, and leave through the same staging buffer, two column blocks (64 codes per row) at a time.
-            auto normalize_store_fp8 = [&](auto affine_tag) __attribute__((always_inline)) {
-                constexpr bool AFFINE = decltype(affine_tag)::value;
+            auto normalize_store_fp8 = [&](auto affine) __attribute__((always_inline)) {
                 auto packed8 = [&](int nb, int half) __attribute__((always_inline)) {
-                    const int col = nb * 32 + hk * 16;
                     float o[8];
 #pragma unroll
                     for (int e = 0; e < 8; ++e) o[e] = __builtin_fmaf(acc[nb][8 * half + e], rstd, nmr);
-                    if (AFFINE) {
-                        const v4f* g4 = reinterpret_cast<const v4f*>(smem + C::OFF_GM + col * 4);
-                        const v4f* b4 = reinterpret_cast<const v4f*>(smem + C::OFF_BT + col * 4);
-                        const v4f gq0 = g4[2 * half], gq1 = g4[2 * half + 1], bq0 = b4[2 * half], bq1 = b4[2 * half + 1];
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            o[e] = __builtin_fmaf(o[e], gq0[e], bq0[e]);
-                            o[4 + e] = __builtin_fmaf(o[4 + e], gq1[e], bq1[e]);
-                        }
-                    }
+                    if (affine) affine_step(o, nb, half);
                     u32x4 pk;
                     pk.x = pack_bf16x2(o[0], o[1]); pk.y = pack_bf16x2(o[2], o[3]);
                     pk.z = pack_bf16x2(o[4], o[5]); pk.w = pack_bf16x2(o[6], o[7]);
@@ -502,13 +498,10 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
             };
             // (an instantiation of its own: in one kernel with the bf16 form the larger shapes spill more)
             if (FP8OUT) {
-                if (affine) { normalize_store_fp8(std::true_type{}); if (LEAN) asm volatile("; stored, affine"); }
-                else { normalize_store_fp8(std::false_type{}); if (LEAN) asm volatile("; stored"); }
+                if (affine) normalize_store_fp8(std::true_type{}); else normalize_store_fp8(std::false_type{});
             } else {
-                // (each path ends in a line of its own: their last stores would be merged into one tail, behind which the
-                // compiler knows of these alone, and waits for all others with the next operands)
-                if (affine) { normalize_store(std::true_type{}); if (LEAN) asm volatile("; stored, affine"); }
-                else { normalize_store(std::false_type{}); if (LEAN) asm volatile("; stored"); }
+                if constexpr (ONE_PATH) normalize_store(affine);
+                else if (affine) normalize_store(std::true_type{}); else normalize_store(std::false_type{});
             }
         };
 
@@ -549,9 +542,8 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
         } else if (NPH == 1) {
             // W is complete in LDS: the waves run on their own.  The next strip's operands are requested into the
             // same registers right after the last MFMA (x is dead then) and arrive during the epilogue.
-            // (requested whether or not there is one - past the end beyond the descriptor, which reads zeros - and awaited by
-            // count: of this wave's operations only the epilogue's stores are younger.  On conditional paths the compiler
-            // does not know the counts, and waits for the stores as well.)
+            // (short rows: requested whether or not there is one - past the end beyond the descriptor, which reads zeros - and,
+            // ONE_PATH, awaited by count: of this wave's operations only the epilogue's stores are younger)
             int s = t + wave;
             if (s < seg_end) load_x(s, 0, x, sxm, true);
             if constexpr (SHORT_ROWS) wait_vmcnt<0>();
@@ -567,7 +559,7 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                 else if (s + NWV < seg_end) load_x(s + NWV, 0, x, sxm, true);
                 __builtin_amdgcn_sched_barrier(0);
                 epilogue(s, sx_cur, acc);
-                if constexpr (SHORT_ROWS) wait_vmcnt<FP8OUT ? NB : 2 * NB>();
+                if constexpr (ONE_PATH) wait_vmcnt<2 * NB>();
                 s += NWV;
             }
         } else {

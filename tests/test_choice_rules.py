@@ -2,6 +2,7 @@
 import ctypes
 import os
 import random
+import re
 import subprocess
 
 import pytest
@@ -190,6 +191,49 @@ int main() {
                    check=True, capture_output=True)
     r = subprocess.run([exe], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout
+
+
+def _device_assembly(src, out):
+    """gfx950 assembly of one of the library's sources, by the flags that the library is built with: {kernel: its lines}."""
+    subprocess.run([build._hipcc(), *build.HIPCC_FLAGS, *build.EXTRA_FLAGS.get(src, []), "-S", "--cuda-device-only",
+                    os.path.join(build.CSRC, src), "-o", str(out)], check=True, capture_output=True)
+    kernels, name = {}, None
+    for line in out.read_text().splitlines():
+        m = re.match(r"(_Z\w+):", line)
+        if m:
+            name = m.group(1)
+            kernels[name] = []
+        elif name:
+            kernels[name].append(line)
+            if "s_endpgm" in line:
+                name = None
+    return kernels
+
+
+def test_strips_are_awaited_without_the_stores_behind_them(tmp_path):
+    # The strip kernel's loop, rows of up to 256, bf16 output: the operands of the next strip are older than the epilogue's 2 NB
+    # stores, which the wait for them leaves in flight; nothing in the loop waits for more than that.
+    kernels = _device_assembly("gemm_strip.hip", tmp_path / "strip.s")
+    def strip_loop(nb, ks, fused):
+        lines = next(v for k, v in kernels.items() if f"gemm_strip_kernelILi{nb}ELi{ks}ELi1ELi8ELb{fused}ELb0E" in k)
+        # (the listing names the header of the innermost loop of every block)
+        loops, header = {}, None
+        for l in lines:
+            if re.match(r"\.LBB\w+:|; %bb", l):
+                m = re.search(r"Header=(BB\w+)", l)
+                header = l[2:l.index(":")] if l.startswith(".LBB") and "Parent Loop" in l else m.group(1) if m else header if l.startswith("; %bb") else None
+            loops.setdefault(header, []).append(l)
+        loop = next(b for h, b in loops.items() if h and any(f"vmcnt({2 * nb})" in l for l in b))
+        assert any("v_mfma" in l for l in loop)
+        return loop
+
+    def wait(line):
+        m = re.search(r"s_waitcnt.*vmcnt\((\d+)\)", line)
+        return int(m.group(1)) if m else None
+
+    for nb, ks in ((4, 2), (4, 4), (8, 2), (8, 4)):
+        waits = [wait(l) for l in strip_loop(nb, ks, 0) if wait(l) is not None]
+        assert waits and min(waits) == 2 * nb, (nb, ks, waits)
 
 
 def _chosen(form, M, N, K, norm=B.NORM_LAYERNORM, batch=1):
