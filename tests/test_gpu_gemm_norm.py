@@ -1202,3 +1202,38 @@ def test_fused_strip_is_quantize_then_gemm(M, batch, K, N, norm):
     plain, _, _ = B.loka_fp8_linear_norm(d, x, wq, sw)
     assert torch.equal(s, sx) and torch.equal(y, y_ref)
     assert torch.equal(out, ref) and torch.equal(plain, ref)
+
+
+def _same_bits(a, b):
+    """Equal bits, any NaN being equal to any other."""
+    na, nb = torch.isnan(a.float()), torch.isnan(b.float())
+    return torch.equal(na, nb) and torch.equal(torch.where(na, torch.zeros_like(a), a), torch.where(nb, torch.zeros_like(b), b))
+
+
+# an infinite value of X takes its row (and, in the strip kernel's cast, its wave) another way than finite rows: the same codes,
+# scales and outputs as quantize + GEMM, in waves with none, one and several such rows.  A NaN in X is outside the
+# contract of either call (a row's amax is NaN here, and does not see it there); it leaves the other rows of its wave alone.
+@pytest.mark.parametrize("form,variant,K,N", [("fused", "strip32", 128, 256), ("fused", "strip32", 256, 240), ("fused", "strip32", 256, 128),
+                                              ("fused", "strip32", 512, 256), ("fused", "wreg32", 256, 512), ("fused", "wreg32", 128, 1024),
+                                              ("xq", "wreg32", 256, 256), ("xq", "wreg32", 512, 512), ("xq", "panel32_256x256", 512, 256)])
+@pytest.mark.parametrize("norm", ["layernorm", "none"])
+def test_one_launch_forms_with_infinite_rows(form, variant, K, N, norm):
+    M = 700
+    x = synth.student_t4(M, K, seed=111)
+    x[3, 5] = float("inf"); x[40, K - 1] = float("-inf"); x[300, 7] = float("inf"); x[300, 8] = float("-inf")
+    x[512:544, 64] = float("inf"); x[M - 1] = float("-inf")
+    nan = torch.zeros(M, dtype=torch.bool, device=DEV)
+    nan[41] = nan[600] = True
+    x[41, 0] = x[600, 9] = float("nan"); x[600, 8] = float("inf")
+    x = x.to(DEV)
+    wq, sw = B.loka_quantize(synth.weight(K, N, seed=112).to(DEV), B.SCALE_COL, transpose_out=True)
+    d = B.make_desc(M, N, K, 1, norm=B.NORMS[norm], variant=B.variant_id(variant))
+    xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+    ref, _ = B.loka_fp8_gemm_norm(d, xq, sx, wq, sw)
+    if form == "fused":
+        out, _, s = B.loka_fp8_linear_norm(d, x, wq, sw, want_sx=True)
+    else:
+        out, _, q, s = B.loka_fp8_linear_norm_xq(d, x, wq, sw)
+        assert torch.equal(q.view(torch.uint8)[~nan], xq.view(torch.uint8)[~nan])
+    assert _same_bits(s[~nan], sx[~nan]) and _same_bits(out[~nan], ref[~nan])
+    assert int(torch.isinf(s).sum()) == 3 + 32 + 1 and not torch.isnan(out[~torch.isinf(s) & ~nan].float()).any()
