@@ -1215,54 +1215,60 @@ static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Na
 // ---- expected time of a variant, in microseconds: what the static choice compares.
 // A launch is `start` plus, per round of workgroups (tiles over the slots of 256 CUs), `round` plus K steps of `step` +
 // `full` * (share of the slots in use: the last level caches and the power budget are shared), `lng` more from the 17th
-// step on and `ragged` more where K is no multiple of a step, plus `ln` for the row statistics (RMSNorm: 0.4 of it); plus X, W
-// and the output at `x`, `w` and `out` per million elements, `out32` more where rows of the output are no whole number of 64-byte lines (the panel kernels' streaming stores).  Kernels that exchange or re-read for a row norm
-// add `norm` (per round; two-pass: per problem), two-pass also `once` and `norm_out` per million outputs.  Fitted
-// (non-negative least squares on relative error, variants far from the fastest of a shape counting less) to every variant's
-// time at 24182 shapes, M 64 - 131072, N 64 - 16384, K 64 - 131072; fitted to one half of them, the choice is within 1.1 % of
-// the fastest variant in the geometric mean over the other (block scales 0.5 %; the table before the branch-free epilogue
-// 1.5 % and 1.0 %: 5013 x 720 x 1008, M x N x K, 17.5 us on 32 x 256 tiles, 14.3 on 128 x 128).
-// profiles/variant_times.csv has the times of 2000 of them.  (A first fit without `lng`, `ragged`, `x`, `w`, `ln` and `out32`
-// was at 2.1 %, worst 2.9: 101163 x 240 x 512 54 us on the 256 x 256 kernel, strip 30.  By tile width and row count alone 25 %:
-// 2048 x 768 x 256 17.5 us on 64-row tiles, 8.6 on 16-row tiles; 4096 x 1024 x 8192 143 us, split K 52.)
+// step on and `ragged` more where K is no multiple of a step, plus `ln` for the row statistics (RMSNorm: 0.4 of it); plus, per
+// million elements, X, W and the output at `x`, `w` and `out`, X and W once more for every column or row of tiles that reads
+// them at `xr` and `wr` (16 problems of 1066 x 128 x 7248, M x N x K: 65.7 us on 32-row tiles, which read W twice as often as
+// 64-row tiles, 46.9), the output beyond 64 million at `far`, and `out32` more where rows of the output are no whole
+// number of 64-byte lines (the panel kernels' streaming stores).  Kernels that exchange or re-read for a row norm
+// add `norm` (per round; two-pass: per problem) and `rec` per million records that a row's tiles read of each other (1439 x
+// 46544 x 96: 317.6 us on 182 tiles of 64 x 256 a row, 182.3 on tiles of 256 x 256), two-pass also `once` and `norm_out` per
+// million outputs.
+// Fitted to every variant's time at 30099 shapes, M 64 - 131072, N 64 - 16384, K 64 - 131072, 1 to 64 problems, and, counting half, at
+// 3398 beyond (M 1 - 4 million, N to 65536, K to 2 million, 4096 problems): non-negative least squares on relative error first,
+// then by gradient on what the choice loses (the time of the expected-fastest variant over the fastest one's, smoothed; losses
+// against two former sets of figures counted four times), so that the figures are best where variants compete, and a third
+// off where they do not.  Fitted to one half, over the other: 0.6 % over the fastest variant in the geometric mean and 13.9 %
+// at the 99th percentile (beyond the range 1.1 and 23); the two former sets 1.2 and 20.9 (3.6 and 61), with weights and a rule
+// for the strip kernel on top, and 1.55 and 24.5 (3.8 and 63).  Of 14991 choices 136 and 125 are more than 5 % slower
+// than theirs, 597 and 962 more than 5 % faster.  profiles/variant_times.csv has the times of 1997 shapes.
 // Fixed figures for an MI355X, not the running device's: workspace sizes follow from the choice.
-struct CostRow { float start, round, step, full, lng, ragged, x, w, out, ln, norm, out32, once, norm_out; };
+struct CostRow { float start, round, step, full, lng, ragged, x, w, out, ln, norm, out32, once, norm_out, xr, wr, far, rec; };
 struct VariantCost { const char* name; int per_cu; CostRow plain, block; };
 constexpr int kPlanCus = 256;
 static const VariantCost kCosts[] = {
-    {"row32x128", 3, {2.82f, .327f, .264f, 0.f, .0607f, .0117f, .131f, 0.f, .417f, .551f},
-     {2.97f, .0418f, .376f, .112f, .017f, 0.f, .125f, 0.f, .378f, .497f}},
-    {"row64x128", 3, {2.33f, 1.27f, .27f, 0.f, .113f, .0324f, .118f, 0.f, .309f, .733f},
-     {2.75f, .801f, .479f, .121f, .0668f, 0.f, .0989f, 0.f, .306f, .617f}},
-    {"row64x256", 2, {2.72f, 1.86f, .431f, .0809f, .139f, .0551f, .122f, .0257f, .309f, 1.41f},
-     {2.84f, 1.26f, .861f, 0.f, .0461f, 0.f, .166f, .656f, .292f, 1.27f}},
-    {"row128x256", 1, {2.32f, 2.85f, .81f, .0533f, .06f, .035f, .0313f, .0698f, .318f, 1.53f},
-     {1.99f, 2.62f, .943f, .21f, .155f, 0.f, 0.f, 4.33f, .272f, 1.49f}},
-    {"row64x512", 1, {2.26f, 2.51f, .766f, .208f, .129f, .0268f, 0.f, .0752f, .337f, 1.75f},
-     {1.97f, 2.48f, 1.17f, .126f, .191f, 0.f, 0.f, 2.72f, .281f, 1.72f}},
-    {"row64x1024", 1, {2.59f, 4.83f, .779f, 0.f, 0.f, .115f, .426f, .0893f, .148f, 2.69f},
-     {1.94f, 5.01f, .713f, 0.f, 0.f, 0.f, .582f, 6.66f, .067f, 2.49f}},
-    {"row16x256", 2, {2.02f, 1.43f, .381f, .0232f, .0235f, .0184f, .197f, .0215f, .468f, .423f},
-     {2.07f, 1.33f, .428f, 0.f, 0.f, 0.f, .254f, .762f, .429f, .391f}},
-    {"row32x256", 2, {2.13f, 1.73f, .361f, .0962f, .0621f, .0242f, .135f, .021f, .324f, .715f},
-     {2.44f, 1.25f, .581f, 0.f, .0356f, 0.f, .172f, .0771f, .354f, .66f}},
-    {"row16x512", 1, {1.66f, 2.01f, .597f, 0.f, .0287f, .0247f, .114f, .0389f, .425f, .584f},
-     {1.41f, 2.13f, .684f, .00668f, .0501f, 0.f, .119f, .713f, .248f, .562f}},
-    {"row32x512", 1, {1.72f, 2.43f, .628f, .0629f, .0841f, .0207f, .0713f, .0457f, .337f, 1.01f},
-     {1.43f, 2.38f, .781f, .0564f, .156f, 0.f, .0844f, 1.17f, .237f, .997f}},
-    {"row16x1024", 1, {1.89f, 2.97f, .599f, 0.f, 0.f, .0282f, 1.26f, 0.f, 0.f, .79f},
-     {1.81f, 2.87f, .699f, 0.f, .0113f, 0.f, 1.09f, .195f, 0.f, .789f}},
-    {"twopass128x128", 2, {3.59f, .713f, .418f, .402f, .131f, .0464f, .0335f, .0245f, .351f, .431f, 2.78f, 0.f, 2.2f, 1.53f},
-     {3.86f, .0412f, .809f, .423f, .0655f, 0.f, .0489f, .328f, .351f, .554f, 5.78f, 0.f, 0.f, 1.39f}},
-    {"panel32x256", 2, {3.87f, .387f, .347f, .309f, .102f, .0658f, .0483f, .223f, .395f, 1.43f, 2.09f, .149f},
-     {4.04f, 0.f, .582f, .234f, .113f, 0.f, .0502f, .148f, .465f, 1.11f, 2.24f}},
-    {"panel64x256", 2, {4.63f, .162f, .55f, .37f, .108f, .0861f, .0313f, .158f, .387f, 1.67f, 2.3f, .23f},
-     {4.62f, 0.f, .871f, .392f, .0876f, 0.f, .0514f, .281f, .348f, 1.39f, 2.48f}},
-    {"panel128x128", 1, {3.66f, 1.23f, .482f, .0953f, 0.f, .0277f, .0134f, .0382f, .316f, 1.3f, 2.83f, .0413f},
-     {3.67f, 1.14f, .569f, .0915f, 0.f, 0.f, .014f, .138f, .249f, 1.2f, 2.85f}},
-    {kPanel32Name, 1, {2.76f, 5.39f, .936f, .445f, 0.f, 0.f, 0.f, 0.f, .178f, 1.87f, 3.23f, .562f},
-     {3.13f, 5.15f, 1.14f, .502f, .0411f, 0.f, 0.f, .0807f, .144f, 2.02f, 3.12f}},
-    {kPanel32RaggedName, 1, {3.6f, 4.53f, .944f, .524f, 0.f, 0.f, 0.f, .0115f, .199f, 1.51f, 3.57f, .515f},
+    {"row32x128", 3, {.9f, 1.65f, .125f, 0.f, .248f, .0292f, .186f, .0073f, .196f, .342f, 0.f, 0.f, 0.f, 0.f, 0.f, .0132f, .127f, 12.7f},
+     {1.38f, .939f, .274f, 0.f, .251f, 0.f, 0.f, .0298f, .302f, .181f, 0.f, 0.f, 0.f, 0.f, 0.f, .0584f, .122f, 7.06f}},
+    {"row64x128", 3, {1.12f, 2.35f, .246f, .0794f, .385f, .0396f, .0834f, 0.f, .0625f, .825f, 0.f, 0.f, 0.f, 0.f, 0.f, .0049f, .396f, .146f},
+     {1.37f, 2.44f, .361f, 0.f, .477f, 0.f, 0.f, .0486f, .00663f, .474f, 0.f, 0.f, 0.f, 0.f, .0502f, .0347f, .222f, 5.58f}},
+    {"row64x256", 2, {2.22f, 2.84f, .456f, .000775f, .205f, .116f, .152f, .0712f, .103f, .846f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, .282f, 21.4f},
+     {3.95f, .989f, .813f, 0.f, .269f, 0.f, .162f, .0563f, .212f, 1.55f, 0.f, 0.f, 0.f, 0.f, 0.f, .0135f, .493f}},
+    {"row128x256", 1, {1.1f, 4.08f, .809f, 0.f, .177f, 0.f, .000936f, 0.f, .291f, 1.61f, 0.f, 0.f, 0.f, 0.f, 0.f, .0357f, 0.f, 19.1f},
+     {.21f, 4.02f, 1.15f, 0.f, .265f, 0.f, 0.f, 0.f, .171f, 1.54f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 15.8f}},
+    {"row64x512", 1, {1.86f, 3.19f, .732f, 0.f, .0516f, .146f, .082f, .0653f, .201f, 1.51f, .00386f, 0.f, 0.f, 0.f, 0.f, .0184f, .222f, 30.8f},
+     {.983f, 4.02f, 1.3f, 0.f, .0771f, 0.f, .00556f, .0381f, .166f, 1.2f, 0.f, 0.f, 0.f, 0.f, 0.f, .0119f, .156f, 9.16f}},
+    {"row64x1024", 1, {1.86f, 5.55f, 1.21f, 0.f, 0.f, 0.f, .333f, .146f, .036f, 2.64f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, .313f, 13.5f},
+     {1.86f, 4.51f, 1.53f, 0.f, 0.f, 0.f, .333f, .11f, 0.f, 2.83f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, .438f}},
+    {"row16x256", 2, {1.42f, 1.53f, .211f, .09f, .302f, .0893f, 0.f, .0415f, .516f, .283f, .00105f, 0.f, 0.f, 0.f, .306f, .0141f, 0.f, 29.6f},
+     {1.41f, 1.31f, .406f, 0.f, 0.f, 0.f, .476f, .114f, .141f, .133f, 0.f, 0.f, 0.f, 0.f, 0.f, .00442f, .473f, 66.6f}},
+    {"row32x256", 2, {.817f, 3.12f, .239f, .101f, .226f, .0658f, .168f, .0647f, 0.f, .761f, 0.f, 0.f, 0.f, 0.f, 0.f, .0144f, .0357f, 8.07f},
+     {.958f, 2.89f, .535f, 0.f, .221f, 0.f, .0944f, .021f, .0791f, .6f, 0.f, 0.f, 0.f, 0.f, 0.f, .0255f, .0258f}},
+    {"row16x512", 1, {.981f, 2.36f, .503f, 0.f, .26f, .0605f, 0.f, .0869f, .301f, .335f, 0.f, 0.f, 0.f, 0.f, .12f, .0125f, 0.f, 65.9f},
+     {.624f, 2.26f, .703f, 0.f, .0713f, 0.f, 0.f, .093f, .217f, .261f, 0.f, 0.f, 0.f, 0.f, .349f, .000633f, 0.f, 58.9f}},
+    {"row32x512", 1, {.815f, 3.63f, .573f, 0.f, .24f, .0832f, 0.f, .115f, .158f, .894f, 0.f, 0.f, 0.f, 0.f, .00994f, .0195f, 0.f, 3.07f},
+     {.591f, 3.13f, .854f, 0.f, .183f, 0.f, 0.f, .0757f, .0871f, .804f, 0.f, 0.f, 0.f, 0.f, 0.f, .0197f, 0.f, 56.f}},
+    {"row16x1024", 1, {.422f, 3.72f, .713f, 0.f, .236f, .0406f, 1.3f, .12f, 0.f, .699f},
+     {0.f, 3.59f, .841f, 0.f, .21f, 0.f, 1.26f, .111f, 0.f, .502f}},
+    {"twopass128x128", 2, {1.81f, 2.74f, .431f, .144f, .231f, .0116f, .0384f, .0604f, .00609f, 1.61f, 2.67f, 0.f, 2.91f, 1.76f, .0122f, .0101f, 0.f, 2.94f},
+     {2.79f, 2.36f, .797f, 0.f, .375f, 0.f, 0.f, .0746f, 0.f, 0.f, 3.02f, 0.f, 2.46f, 1.72f, .0735f, 0.f, .256f, 2.04f}},
+    {"panel32x256", 2, {3.14f, .949f, .238f, .0611f, .352f, .105f, .128f, .412f, .288f, 1.16f, 2.46f, .262f, 0.f, 0.f, .131f, .0112f, .135f, 1.3f},
+     {3.22f, .442f, .56f, 0.f, .186f, 0.f, .102f, .138f, .374f, .604f, 2.39f, 0.f, 0.f, 0.f, .131f, .0174f, 0.f, 2.72f}},
+    {"panel64x256", 2, {3.74f, 2.44f, .538f, 0.f, .124f, .0969f, .104f, .237f, .111f, 1.48f, 2.11f, .2f, 0.f, 0.f, .0737f, .00733f, .282f, 2.18f},
+     {3.87f, 1.37f, .878f, 0.f, .267f, 0.f, .118f, .14f, .0907f, 1.39f, 2.52f, 0.f, 0.f, 0.f, .0979f, .0113f, .227f, 2.54f}},
+    {"panel128x128", 1, {3.53f, 2.38f, .516f, 0.f, 0.f, 0.f, .024f, .0601f, 0.f, 1.71f, 2.33f, 0.f, 0.f, 0.f, 0.f, .0114f, 0.f, 3.68f},
+     {2.19f, 2.99f, .645f, 0.f, 0.f, 0.f, 0.f, .024f, 0.f, 1.47f, 2.67f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 3.29f}},
+    {kPanel32Name, 1, {1.71f, 6.91f, 1.07f, .133f, 0.f, 0.f, .000689f, 0.f, 0.f, 2.57f, 3.68f, .709f, 0.f, 0.f, 0.f, 0.f, 0.f, .568f},
+     {1.64f, 6.57f, 1.45f, .0388f, 0.f, 0.f, .00625f, 0.f, 0.f, 2.61f, 3.4f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, .841f}},
+    {kPanel32RaggedName, 1, {2.45f, 6.42f, 1.02f, .0882f, 0.f, 0.f, 0.f, 0.f, 0.f, 2.f, 4.47f, .685f, 0.f, 0.f, 0.f, 0.f, 0.f, .177f},
      {}},
 };
 // BlockNorm's choice between the large tile and the row tiles of its width (blocknorm_form), where rows are wider than a tile:
@@ -1276,12 +1282,13 @@ static const VariantCost kBlocknormCosts[] = {
 };
 // split K: a launch is `start` plus, per round, K steps as above, plus `part` per million partial sums and `out` per
 // million outputs; rows of more than 2048 add `wide` and `wide_out`.  Tile 128 on the ring and on two stages, tile 256; plain
-// and block scales.
+// and block scales.  The two forms compete like any other variants (a rule between them, the ring form up to 128 steps per
+// range, lost 0.16 % in the geometric mean over all shapes; 390 x 3712 x 27776 with block scales 95.3 us where the other takes 71.0).
 struct SplitkCost { float start, step, full, part, out, wide, wide_out; };
 static const SplitkCost kSplitkCosts[3][2] = {
-    {{8.57f, .429f, .0372f, 2.05f, .0325f, 1.84f, 4.13f}, {9.4f, .336f, .285f, 1.77f, 0.f, 1.24f, 4.08f}},
-    {{8.63f, .351f, .685f, 1.6f, .249f, 1.56f, 4.62f}, {9.77f, .438f, .95f, 1.61f, 0.f, 1.36f, 3.41f}},
-    {{13.f, .568f, .805f, .941f, .71f, 1.13f, 4.19f}, {13.9f, .878f, .883f, .805f, .437f, 0.f, 4.34f}}};
+    {{9.2f, .54f, 0.f, 1.94f, 0.f, 2.79f, 3.22f}, {6.81f, .626f, .0134f, 2.75f, 0.f, 1.21f, 4.11f}},
+    {{5.63f, .641f, .558f, 2.97f, .826f, 4.05f, 2.12f}, {7.17f, 1.17f, .344f, 2.72f, 0.f, 2.41f, 2.65f}},
+    {{19.2f, 1.02f, 0.f, .731f, 1.42f, 2.78f, 4.16f}, {15.f, 1.36f, .0879f, .977f, .417f, 0.f, 5.41f}}};
 // ... and what decides between tiles of 128 and 256 on the long-range form.  An earlier fit, kept: a caller that names the
 // variant gets the same tiles (the two fits differ at 8 of 364 shapes).
 static const SplitkCost kSplitkTileCosts[2][2] = {{{10.7f, 0.f, .79f, 1.78f}, {12.f, .12f, 1.13f, 1.37f, .66f}},
@@ -1340,21 +1347,6 @@ static double splitk_time(const loka_gemm_desc* d, int v) {
 }
 
 bool variant_supports(const loka_gemm_desc* d, int v);
-// the split-K form for the shape: the ring form unless its ranges would be long (measured: 65536 x 256 x 1024 as a weight
-// gradient, 32 steps per range, 36.6 us against 41 us for the two-stage form; 2048 x 123200 x 1024, 482 steps per range:
-// 128 x 128 tiles 346 us, 256 x 256 tiles 242) or 256 x 256 tiles are expected to be faster; the other form where only one
-// of them splits K at all
-static int splitk_choice(const loka_gemm_desc* d) {
-    int ring = -1, two = -1;
-    for (int v = 0; v < kNumVariants; ++v) {
-        if (kVariants[v].epi != EPI_SPLITK || !variant_supports(d, v)) continue;
-        if (splitk_is_ring(kVariants[v])) ring = v; else two = v;
-    }
-    if (ring < 0 || two < 0) return ring >= 0 ? ring : two;
-    const bool large = splitk_plan(d, two).tile == 256;
-    return splitk_plan(d, ring).per <= 128 && !(large && splitk_time(d, two) < splitk_time(d, ring)) ? ring : two;
-}
-
 // The two kernels that keep W on the CU (fitted like the table, with terms of their own): strips of 32 rows, W in LDS by 128 or
 // 256 columns in one piece or (K * 128 or K * 256 above 128 KB) in slabs; blocks of 32 rows, W in registers, loaded once
 // per workgroup and problem.
@@ -1362,13 +1354,13 @@ static double strip_time(const loka_gemm_desc* d, double ln) {
     const double wide = d->N > 128 ? 1.0 : 0.0, w = d->K * (128 + 128 * wide) / 65536.0;
     const double strips = static_cast<double>((d->M + 31) / 32) * d->batch / 2048, rounds = std::max(1.0, strips);
     const double x = 1e-6 * d->M * d->K * d->batch, out = 1e-6 * d->M * d->N * d->batch;
-    if (w > 2.0) return rounds * (8.8 + 1.09 * ln) + w * (.496 + .0163 * d->batch) + .229 * x + .374 * out;
-    return 4.17 + 1.05 * wide + w * (1.42 + 2.35 * strips + .018 * d->batch) + .706 * rounds * ln + .1 * x + .275 * out;
+    if (w > 2.0) return 9.9 * rounds + .508 * rounds * ln + .366 * w + .0213 * w * d->batch + .159 * x + .744 * out;
+    return 3.27 + .00847 * wide + 2.74 * w + 4.54 * w * strips + .0256 * w * d->batch + 1.1 * rounds * ln + .00894 * x + .095 * out;
 }
 static double wreg_time(const loka_gemm_desc* d, double ln) {
     const double w = d->K * d->N / 65536.0, rounds = std::max(1.0, static_cast<double>((d->M + 31) / 32) * d->batch / kPlanCus);
     const double x = 1e-6 * d->M * d->K * d->batch, out = 1e-6 * d->M * d->N * d->batch;
-    return 6.36 + w * (.361 + .0239 * d->batch) + rounds * (.0688 + .0314 * w + .722 * ln) + .199 * x + .277 * out;
+    return 5.12 + 1.27 * w + .0301 * w * d->batch + .186 * rounds + .904 * rounds * ln + .18 * x + .0325 * out;
 }
 
 // Expected time of variant v; negative where the static choice does not consider it (no figures above).
@@ -1384,7 +1376,7 @@ static double variant_cost(const loka_gemm_desc* d, int v) {
     const CostRow& c = scale_mode_is_block(d->x_mode) ? vc->block : vc->plain;
     const double problems = static_cast<double>(d->batch), out = 1e-6 * d->M * d->N * problems;
     const bool panel = vi.epi == EPI_PANEL_SYNC;
-    const int64_t tiles_n = (d->N + vi.bn - 1) / vi.bn, tiles = ((d->M + vi.bm - 1) / vi.bm) * tiles_n * d->batch;
+    const int64_t tiles_m = (d->M + vi.bm - 1) / vi.bm, tiles_n = (d->N + vi.bn - 1) / vi.bn, tiles = tiles_m * tiles_n * d->batch;
     int64_t slots = kPlanCus * vc->per_cu;
     if (panel) slots = slots / tiles_n * tiles_n;        // whole row panels at a time
     // (one-tile workgroups: past a few rounds they drift apart and the last round no longer stands out)
@@ -1393,9 +1385,9 @@ static double variant_cost(const loka_gemm_desc* d, int v) {
     const double steps = static_cast<double>((d->K + 127) / 128) * (vi.bn > 512 ? (d->N + 511) / 512 : 1);
     const double step = c.step + c.full * std::min(1.0, static_cast<double>(tiles) / slots) + (d->K % 128 ? c.ragged : 0.f);
     double t = c.start + rounds * (c.round + steps * step + c.lng * std::max(0.0, steps - 16) + c.ln * ln) +
-               1e-6 * d->K * (d->M * problems * c.x + d->N * (d->strideW ? problems : 1.0) * c.w) +
-               out * (c.out + (panel && d->N % 32 ? c.out32 : 0.f));
-    if (row_norm) t += panel ? c.norm * rounds * (tiles_n > 1 ? 1.0 : 0.3) : c.norm * problems + c.once + out * c.norm_out;
+               1e-6 * d->K * (d->M * problems * (c.x + tiles_n * c.xr) + d->N * ((d->strideW ? problems : 1.0) * c.w + tiles_m * problems * c.wr)) +
+               out * (c.out + (panel && d->N % 32 ? c.out32 : 0.f)) + c.far * std::max(0.0, out - 64.0);
+    if (row_norm) t += 1e-6 * d->M * problems * tiles_n * tiles_n * c.rec + (panel ? c.norm * rounds * (tiles_n > 1 ? 1.0 : 0.3) : c.norm * problems + c.once + out * c.norm_out);
     return t;
 }
 
@@ -1466,37 +1458,19 @@ int variant_fp8out_default(const loka_gemm_desc* d) {
 }
 
 size_t variant_workspace(const loka_gemm_desc* d, int v, bool fp8out);
-// What the expected times are weighed with in the choice, without block scales: where two are close, the one whose fit is off by
-// less.  With LayerNorm or RMSNorm the 256 x 256 kernel, whose time varies least (16 x (2939 x 464 x 4272), M x N x K, takes 135 us there;
-// 64-row tiles, expected to be 3 % below it, take 184); the small panel tiles of several problems and the 32 x 128 tile are the
-// ones expected too fast most often.  5000 shapes, time over the fastest variant's, without -> with: several problems 1.26 ->
-// 1.15 % in the mean, 22.5 -> 19.3 % at the 99th percentile; one problem 0.95 -> 0.92 and 16.3 -> 15.7.  Without a norm the
-// first weight would lose 2 % at the shapes that it changes.
-static double choice_margin(const loka_gemm_desc* d, const VariantInfo& vi) {
-    if (scale_mode_is_block(d->x_mode)) return 1.0;
-    if (panel32_layout(vi)) return d->norm == LOKA_NORM_LAYERNORM || d->norm == LOKA_NORM_RMSNORM ? 0.95 : 1.0;
-    if (vi.epi == EPI_PANEL_SYNC && vi.bm <= 64) return d->batch > 1 ? 1.04 : 1.0;
-    return vi.epi == EPI_ROW_IN_TILE && vi.bm == 32 && vi.bn == 128 ? 1.03 : 1.0;
-}
-
 // The static choice among the variants whose workspace fits `max_ws`: the least expected time.  The streaming kernel only
-// from 4096 rows on (below, its set-up is most of the launch and the fit does not describe it).  A tile that is less
-// than 5 % below the strip kernel does not displace it, so that the call keeps its last bits (36 of the 1360 shapes that it
-// takes: it is the faster one at 8 of them, the other by 4 % in the mean).   -1: none.
+// from 4096 rows on (below, its set-up is most of the launch and the fit does not describe it).  -1: none.
 int variant_cheapest(const loka_gemm_desc* d, size_t max_ws) {
-    const int split = splitk_choice(d);
-    int best = -1, strip = -1;
-    double best_cost = 0.0, strip_cost = 0.0;
+    int best = -1;
+    double best_cost = 0.0;
     for (int v = 0; v < kNumVariants; ++v) {
-        if (!variant_supports(d, v) || (kVariants[v].epi == EPI_SPLITK && v != split)) continue;
+        if (!variant_supports(d, v)) continue;
         if (kVariants[v].name == kWregName && d->M * d->batch < 4096) continue;
-        const double c = variant_cost(d, v) * choice_margin(d, kVariants[v]);
-        if (kVariants[v].name == kStripName) { strip = v; strip_cost = c; }
+        const double c = variant_cost(d, v);
         if (c < 0.0 || (best >= 0 && c >= best_cost) || (max_ws != SIZE_MAX && variant_workspace(d, v, false) > max_ws)) continue;
         best = v;
         best_cost = c;
     }
-    if (strip >= 0 && kVariants[best].name != kWregName && 0.95 * strip_cost < best_cost) best = strip;
     return best;
 }
 

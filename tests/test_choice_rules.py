@@ -1,5 +1,7 @@
 """Host rules of the library: which kernel a call takes, and how much scratch it accepts (no GPU needed)."""
+import csv
 import ctypes
+import math
 import os
 import random
 import re
@@ -278,3 +280,22 @@ def test_fp8_output_without_a_row_norm_takes_a_kernel_that_has_it():
     (31021, 688, 384, 1, "rmsnorm", "row64x1024"), (8616, 64, 2048, 8, "none", "row64x128"), (9214, 128, 128, 1, "none", "row32x128")])
 def test_bf16_output_chooses_by_measured_times(M, N, K, batch, norm, want):
     assert _chosen("bf16", M, N, K, B.NORMS[norm], batch) == want
+
+
+def test_static_choice_over_measured_times():
+    # Every variant's time at 1997 shapes: what the choice loses to the fastest variant, in the mean and at its worst shapes, and
+    # against what two former sets of figures chose there (the mean alone hides layers that a new set sends to a slower kernel).
+    with open(os.path.join(build.ROOT, "profiles", "variant_times.csv")) as f:
+        rows = list(csv.DictReader(line for line in f if not line.startswith("#")))
+    over, against = [], []
+    for r in rows:
+        modes = (B.SCALE_BLOCK_1x128, B.SCALE_BLOCK_128x128) if r["scales"] == "block" else (B.SCALE_ROW, B.SCALE_COL)
+        d = B.make_desc(int(r["M"]), int(r["N"]), int(r["K"]), int(r["batch"]), *modes, B.NORMS[r["norm"]], 1e-5)
+        name = B.loka_variant_name(B.lib().loka_default_variant(ctypes.byref(d)))
+        times = {k: float(v) for k, v in r.items() if k not in ("M", "N", "K", "batch", "scales", "norm", "former") and v}
+        over.append(math.log(times[name] / min(times.values())))
+        against.append(times[name] / times[r["former"].split("/")[0]])
+    assert len(rows) == 1997
+    assert math.exp(sum(over) / len(over)) < 1.006
+    assert math.exp(sorted(over)[int(0.99 * len(over))]) < 1.12
+    assert sum(x > 1.05 for x in against) < 0.013 * len(against) and sum(x > 1.2 for x in against) < 0.002 * len(against)
