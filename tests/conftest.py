@@ -1,4 +1,3 @@
-import gc
 import os
 import sys
 
@@ -11,13 +10,6 @@ if ROOT not in sys.path:
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu)")
-
-
-@pytest.fixture(scope="module", autouse=True)
-def _no_garbage_of_other_modules():
-    # tracebacks kept by pytest.raises hold the failed call's tensors in reference cycles; collected in the middle of a
-    # later module, they change the allocator's counts that test_zz_no_alloc.py compares
-    gc.collect()
 
 
 @pytest.fixture(scope="session")
