@@ -1272,8 +1272,8 @@ static const VariantCost kCosts[] = {
      {}},
 };
 // BlockNorm's choice between the large tile and the row tiles of its width (blocknorm_form), where rows are wider than a tile:
-// an earlier fit, of the first four terms and the output (taken from the table above, the choice was 4 % slower in the
-// geometric mean over 80 layers, 107 x 2048 x 256 in 4 problems 5.3 -> 12.0 us).
+// an earlier fit, of the first four terms and the output.  It is from before the row tiles' statistics went by sums (1 - 2 us of
+// a launch), so it may take the large tile for layers that they are as fast for.
 static const VariantCost kBlocknormCosts[] = {
     {"row16x256", 2, {2.05f, 1.74f, .41f, .19f, 0.f, 0.f, 0.f, 0.f, .63f}, {.56f, 2.86f, .58f, .21f, 0.f, 0.f, 0.f, 0.f, .09f}},
     {"row32x256", 2, {2.04f, 2.31f, .41f, .25f, 0.f, 0.f, 0.f, 0.f, .44f}, {2.82f, 1.13f, .76f, .22f, 0.f, 0.f, 0.f, 0.f, .63f}},
@@ -1422,11 +1422,13 @@ bool variant_supports_fp8out(const loka_gemm_desc* d, int v) {
     if (name == kPanel32Name) return d->norm != LOKA_NORM_NONE && !scale_mode_is_block(d->x_mode);
     return name == kWregName || name == kStripName;
 }
-// Expected time of that form, microseconds, N <= 256: fitted (as above) to its times at 252 shapes, M 512 - 131072, N 64 - 256,
-// K 128 - 2048; the choice is within 0.1 % of the fastest of the three in the geometric mean over them (worst 1.04), where
-// following the bf16 choice (and the streaming kernel where that has no such form) was at 17 % (worst 2.2).  W in LDS
-// (strip) costs by 128 or 256 columns, and only one phase of it is considered; the streaming kernel's blocks are taller for
-// K <= 256.
+// Expected time of that form, microseconds, N <= 256: fitted (least squares) to its times at 252 shapes, M 512 - 131072, N 64 -
+// 256, K 128 - 2048.  The streaming and the strip kernel have become faster since (65536 x 256 x 1024, M x K x N, 50 -> 43 us;
+// 64 x (4096 x 256 x 256) 48.6 -> 45.3): over 2313 shapes as they are now, the choice is 0.24 % over the fastest of the three in
+// the geometric mean (worst 1.18), with gamma, which the descriptor does not tell, 0.44 % (worst 1.27: 4 x (15938 x 240 x 128), M x N x
+// K, 17.9 us on the large-tile kernel, strip 14.1).  Following the bf16 choice (and the streaming kernel where that has no
+// such form) was at 17 % (worst 2.2).  W in LDS (strip) costs by 128 or 256 columns, and only one phase of it is
+// considered; the streaming kernel's blocks are taller for K <= 256.
 static double fp8out_cost(const loka_gemm_desc* d, int v) {
     const double x = 1e-6 * d->M * d->K * d->batch, out = 1e-6 * d->M * d->N * d->batch;
     const double strips = static_cast<double>((d->M + 31) / 32) * d->batch;
