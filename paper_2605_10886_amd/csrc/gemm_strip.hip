@@ -501,7 +501,10 @@ __global__ __launch_bounds__(NWV * 64) void gemm_strip_kernel(const GemmParams p
                 if (affine) normalize_store_fp8(std::true_type{}); else normalize_store_fp8(std::false_type{});
             } else {
                 if constexpr (ONE_PATH) normalize_store(affine);
-                else if (affine) normalize_store(std::true_type{}); else normalize_store(std::false_type{});
+                // (fused: each path ends in a line of its own; with their last stores merged into one tail 64 x (4096 x 256 x 256),
+                // M x N x K, takes 65.2 us instead of 65.0)
+                else if (affine) { normalize_store(std::true_type{}); if (BF16IN) asm volatile("; stored, affine"); }
+                else { normalize_store(std::false_type{}); if (BF16IN) asm volatile("; stored"); }
             }
         };
 
