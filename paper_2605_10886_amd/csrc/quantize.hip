@@ -10,17 +10,68 @@
 // cast, and write plain or transposed (the layout used for weights).
 #include "common.h"
 
+#include <type_traits>
+
 namespace loka {
+
+__device__ __forceinline__ float chunk_amax(const u32x4 w) {
+    float a = fmaxf(fabsf(bf16_lo(w.x)), fabsf(bf16_hi(w.x)));
+    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y))));
+    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))));
+    return fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
+}
+
+// one chunk of 8 elements, past the caches or through them
+template <bool STREAMED>
+__device__ __forceinline__ u32x4 load_chunk(const uint16_t* p) {
+    const u32x4* v = reinterpret_cast<const u32x4*>(p);
+    if (STREAMED) return __builtin_nontemporal_load(v);
+    return *v;
+}
+
+// Maximum over groups of GL consecutive lanes (16, 32 or 64), in all of them: moves within 16 lanes, row and half swaps.
+template <int GL>
+__device__ __forceinline__ float lanes_max(float a) {
+    auto moved = [&](auto ctrl) __attribute__((always_inline)) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(a), decltype(ctrl)::value, 0xF, 0xF, true));
+    };
+    a = fmaxf(a, moved(std::integral_constant<int, 0xB1>{}));       // lane ^ 1
+    a = fmaxf(a, moved(std::integral_constant<int, 0x4E>{}));       // lane ^ 2
+    a = fmaxf(a, moved(std::integral_constant<int, 0x141>{}));      // the other quad of 8
+    a = fmaxf(a, moved(std::integral_constant<int, 0x140>{}));      // the other half of 16
+    typedef unsigned u32_pair __attribute__((ext_vector_type(2)));
+    if (GL >= 32) {
+        const u32_pair r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+        a = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+    }
+    if (GL >= 64) {
+        const u32_pair r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(a), false, false);
+        a = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
+    }
+    return a;
+}
+// out[k] = v of lane k of the lane's 16, k < T
+template <int T, int K = 0>
+__device__ __forceinline__ void row_broadcasts(float v, float (&out)[T]) {
+    if constexpr (T == 1) out[0] = v;
+    else if constexpr (K < T) {
+        out[K] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xF, 0xF, true));
+        row_broadcasts<T, K + 1>(v, out);
+    }
+}
 
 // ---------------------------------------------------------------------------------
 // Single pass: TPR lanes share one row (TPR = 16, 32 or 64); each lane holds CPL
 // chunks of 8 consecutive bf16 (one 16-byte load each); a wave works on RU row sets at
-// once so that enough loads are in flight.  GW = lanes per scale group: TPR for ROW
+// once so that enough loads are in flight.  Lanes per scale group: TPR for ROW
 // scaling (one group per row), 16 for 1x128 blocks (16 lanes x 8 elements).
+// Bound by HBM, and where all of it is one round of workgroups by what a wave does between its loads and its stores (rows x
+// columns, exchanges by LDS shuffles and divisions in every lane -> as here, us, streamed loads: 65536 x 256 11.5 -> 10.6,
+// 16384 x 1024 11.6 -> 10.4; in 1 x 128 blocks 8192 x 2048 12.1 -> 10.6, 65536 x 512 20.5 -> 18.8, 2048 x 8192 16.4 -> 14.4).
 template <int TPR, int CPL, int RU, bool BLOCK128>
 __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                          int64_t ld, uint8_t* __restrict__ q,
-                                                         float* __restrict__ scales, const int pow2) {
+                                                         float* __restrict__ scales, const int pow2, const bool streamed) {
     constexpr int ROWS_PER_WAVE = (64 / TPR) * RU;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -30,70 +81,68 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restr
     const int64_t row0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * ROWS_PER_WAVE;
 
     u32x4 v[RU][CPL];
+    auto load = [&](auto streamed_c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const int64_t r = row0 + u * (64 / TPR) + sub;
+#pragma unroll
+            for (int j = 0; j < CPL; ++j) {
+                const int64_t c = lr + static_cast<int64_t>(j) * TPR;
+                v[u][j] = u32x4{0u, 0u, 0u, 0u};
+                if (r < rows && c < chunks) v[u][j] = load_chunk<decltype(streamed_c)::value>(x + r * ld + c * 8);
+            }
+        }
+    };
+    if (streamed) load(std::true_type{}); else load(std::false_type{});
+    // The groups of a 16-lane row: T.  Every lane has the maxima of all of them after the exchanges (in the vector unit, no LDS
+    // round trips); lane k takes group k's two divisions, and the factors go round by broadcasts: the divisions of all
+    // groups in every lane were a third of the 1 x 128 form's instructions.
+    constexpr int T = BLOCK128 ? RU * CPL : RU;
+    float am[T];
 #pragma unroll
     for (int u = 0; u < RU; ++u) {
-        const int64_t r = row0 + u * (64 / TPR) + sub;
+        if (!BLOCK128) am[u] = chunk_amax(v[u][0]);
 #pragma unroll
-        for (int j = 0; j < CPL; ++j) {
-            const int64_t c = lr + static_cast<int64_t>(j) * TPR;
-            if (r < rows && c < chunks)
-                v[u][j] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + r * ld + c * 8));
-            else
-                v[u][j] = u32x4{0u, 0u, 0u, 0u};
+        for (int j = BLOCK128 ? 0 : 1; j < CPL; ++j) {
+            if (BLOCK128) am[u * CPL + j] = chunk_amax(v[u][j]);
+            else am[u] = fmaxf(am[u], chunk_amax(v[u][j]));
         }
     }
 #pragma unroll
+    for (int k = 0; k < T; ++k) am[k] = lanes_max<BLOCK128 ? 16 : TPR>(am[k]);
+    const int k16 = lane & 15;
+    float mine = am[0], scale, inv_mine;
+#pragma unroll
+    for (int k = 1; k < T; ++k) mine = k16 == k ? am[k] : mine;
+    group_scale_any(BLOCK128 && pow2, mine, scale, inv_mine);
+    if (BLOCK128) {
+        const int u = k16 / CPL, j = k16 % CPL;
+        const int64_t r = row0 + u * (64 / TPR) + sub, c = (lr & ~15) + static_cast<int64_t>(j) * TPR;
+        if (k16 < T && r < rows && c < chunks) scales[r * (cols >> 7) + (c >> 4)] = scale;
+    } else {
+        const int64_t r = row0 + k16 * (64 / TPR) + sub;
+        if (lr < T && r < rows) scales[r] = scale;
+    }
+    float inv[T];
+    row_broadcasts<T>(inv_mine, inv);
+#pragma unroll
     for (int u = 0; u < RU; ++u) {
         const int64_t r = row0 + u * (64 / TPR) + sub;
-        float am[CPL];
-#pragma unroll
-        for (int j = 0; j < CPL; ++j) {
-            const u32x4 w = v[u][j];
-            float a = fmaxf(fabsf(bf16_lo(w.x)), fabsf(bf16_hi(w.x)));
-            a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y))));
-            a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))));
-            a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
-            am[j] = a;
-        }
-        if (!BLOCK128) {
-#pragma unroll
-            for (int j = 1; j < CPL; ++j) am[0] = fmaxf(am[0], am[j]);
-#pragma unroll
-            for (int m = 1; m < TPR; m <<= 1) am[0] = fmaxf(am[0], wave_shfl_xor(am[0], m));
-        } else {
-#pragma unroll
-            for (int j = 0; j < CPL; ++j)
-#pragma unroll
-                for (int m = 1; m < 16; m <<= 1) am[j] = fmaxf(am[j], wave_shfl_xor(am[j], m));
-        }
 #pragma unroll
         for (int j = 0; j < CPL; ++j) {
             const int64_t c = lr + static_cast<int64_t>(j) * TPR;
-            float scale, inv;
-            group_scale_any(BLOCK128 && pow2, BLOCK128 ? am[j] : am[0], scale, inv);
             if (r < rows && c < chunks) {
                 const u32x4 w = v[u][j];
+                const float f = inv[BLOCK128 ? u * CPL + j : u];
                 u32x2 o;
-                o.x = e4m3x4(bf16_lo(w.x) * inv, bf16_hi(w.x) * inv, bf16_lo(w.y) * inv, bf16_hi(w.y) * inv);
-                o.y = e4m3x4(bf16_lo(w.z) * inv, bf16_hi(w.z) * inv, bf16_lo(w.w) * inv, bf16_hi(w.w) * inv);
+                o.x = e4m3x4(bf16_lo(w.x) * f, bf16_hi(w.x) * f, bf16_lo(w.y) * f, bf16_hi(w.y) * f);
+                o.y = e4m3x4(bf16_lo(w.z) * f, bf16_hi(w.z) * f, bf16_lo(w.w) * f, bf16_hi(w.w) * f);
                 // plain store: the GEMM that follows reads the codes from the last-level cache (measured at
                 // 32768 x 4096: the GEMM runs 3 % faster than after a streaming store, this kernel no slower)
                 *reinterpret_cast<u32x2*>(q + r * cols + c * 8) = o;
-                if (BLOCK128) {
-                    if ((c & 15) == 0) scales[r * (cols >> 7) + (c >> 4)] = scale;
-                } else if (j == 0 && lr == 0) {
-                    scales[r] = scale;
-                }
             }
         }
     }
-}
-
-__device__ __forceinline__ float chunk_amax(const u32x4 w) {
-    float a = fmaxf(fabsf(bf16_lo(w.x)), fabsf(bf16_hi(w.x)));
-    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y))));
-    a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))));
-    return fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
 }
 
 // Rows too long for one wave (8192 < cols <= 131072): a workgroup of 16 waves holds the whole row in registers (CPL chunks
@@ -128,13 +177,10 @@ __global__ __launch_bounds__(1024) void quant_wide_rows_kernel(const uint16_t* _
         float a = chunk_amax(v[0]);
 #pragma unroll
         for (int j = 1; j < CPL; ++j) a = fmaxf(a, chunk_amax(v[j]));
-#pragma unroll
-        for (int m = 1; m < 64; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+        a = lanes_max<64>(a);
         if ((t & 63) == 0) red[it][t >> 6] = a;
         __syncthreads();
-        a = red[it][t & 15];
-#pragma unroll
-        for (int m = 1; m < 16; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+        a = lanes_max<16>(red[it][t & 15]);
         float scale, inv;
         group_scale(a, scale, inv);
         if (t == 0) scales[r] = scale;
@@ -195,7 +241,7 @@ __global__ __launch_bounds__(256) void quant_long_rows_kernel(const uint16_t* __
             a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y))));
             a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))));
             a = fmaxf(a, fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w))));
-            for (int m = 1; m < 16; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+            a = lanes_max<16>(a);
             float scale;
             group_scale_any(pow2, a, scale, inv);
             if (ok && (c & 15) == 0) scales[r * (cols >> 7) + (c >> 4)] = scale;
@@ -237,7 +283,7 @@ __global__ __launch_bounds__(256) void amax_tensor_kernel(const uint16_t* __rest
 #pragma unroll
         for (int u = 0; u < 4; ++u) a = fmaxf(a, chunk_amax(w[u]));
     }
-    for (int m = 1; m < 64; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+    a = lanes_max<64>(a);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
     if (threadIdx.x == 0) parts[blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
@@ -299,7 +345,8 @@ enum { G_TILE, G_COL128, G_COL_ALL, G_COL, G_TENSOR };
 template <int GROUPS, bool TRANSPOSE>
 __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __restrict__ x, int64_t rows, int64_t cols,
                                                             int64_t ld, uint8_t* __restrict__ q, float* __restrict__ scales,
-                                                            const int pow2, const float* __restrict__ parts, const int nparts) {
+                                                            const int pow2, const bool streamed, const float* __restrict__ parts,
+                                                            const int nparts) {
     constexpr bool ROW_TAIL = GROUPS == G_COL || GROUPS == G_COL_ALL || GROUPS == G_TENSOR;   // rows need not fill the last tile
     __shared__ float red[4 * 128];                      // per wave: column maxima (G_COL128) or one value
     __shared__ float inv_s[128];
@@ -311,12 +358,15 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
     const int64_t r0 = static_cast<int64_t>(by) * 128, c0 = static_cast<int64_t>(bx) * 128;
     const bool live = c0 + cc * 8 < cols;
     u32x4 w[8];
+    auto load = [&](auto streamed_c) __attribute__((always_inline)) {
 #pragma unroll
-    for (int sw = 0; sw < 8; ++sw) {
-        w[sw] = u32x4{0u, 0u, 0u, 0u};
-        if (live && (!ROW_TAIL || r0 + rr * 8 + sw < rows))
-            w[sw] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(x + (r0 + rr * 8 + sw) * ld + c0 + cc * 8));
-    }
+        for (int sw = 0; sw < 8; ++sw) {
+            w[sw] = u32x4{0u, 0u, 0u, 0u};
+            if (live && (!ROW_TAIL || r0 + rr * 8 + sw < rows))
+                w[sw] = load_chunk<decltype(streamed_c)::value>(x + (r0 + rr * 8 + sw) * ld + c0 + cc * 8);
+        }
+    };
+    if (streamed) load(std::true_type{}); else load(std::false_type{});
     float inv8[8];
     if (GROUPS == G_COL128 || GROUPS == G_COL_ALL) {
         float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -401,7 +451,7 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
 #pragma unroll
             for (int sw = 0; sw < 8; ++sw) a = fmaxf(a, chunk_amax(w[sw]));
         }
-        for (int m = 1; m < 64; m <<= 1) a = fmaxf(a, wave_shfl_xor(a, m));
+        a = lanes_max<64>(a);
         if (lane == 0) red[wave] = a;
         __syncthreads();
         float sc, iv;
@@ -465,15 +515,25 @@ __global__ void e4m3_from_f32_kernel(const float* __restrict__ t, uint8_t* __res
 }
 
 // ---------------------------------------------------------------------------------
+// Whether X is read past the caches.  A plain read is the faster one by itself until X and its codes outgrow the last-level cache
+// (rows x columns, streamed -> plain, us: 16384 x 512 6.8 -> 6.1, 8192 x 2048 in 1 x 128 blocks 10.6 -> 10.3, 2048 x 8192 14.4 ->
+// 12.5; 65536 x 1024 33.4 -> 32.4, but 32768 x 3072 46.9 -> 49.6 and 32768 x 4096 60.3 -> 72.4), but X then stays in that
+// cache in the place of what the GEMM behind it reads and writes: a training step of 65536 x 256 x 1024 (M x K x N) takes 204 us
+// with X (32 MB) and dY (128 MB) streamed, 208 with X plain, 226 with both plain; the layer 8192 x 2048 x 2048 (X 32 MB) 54.8
+// streamed and 52.0 plain, the probe on 16384 x 1024 x 1024 111.0 and 108.0.  So streamed from 64 MB, and from 16 MB where rows are
+// short: such layers write more than they read.
+static bool read_streamed(int64_t rows, int64_t cols) { return rows * cols >= int64_t(1) << (cols <= 256 ? 23 : 25); }
+
 template <bool B128>
 static void launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld, uint8_t* q, float* scales,
                         int pow2, hipStream_t s) {
     const int64_t chunks = cols / 8;
+    const bool streamed = read_streamed(rows, cols);
     auto grid = [&](int rows_per_wave) {
         return dim3(static_cast<unsigned>((rows + 4 * rows_per_wave - 1) / (4 * rows_per_wave)));
     };
 #define LOKA_QR(TPR, CPL, RU) \
-    quant_rows_kernel<TPR, CPL, RU, B128><<<grid((64 / TPR) * RU), 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2)
+    quant_rows_kernel<TPR, CPL, RU, B128><<<grid((64 / TPR) * RU), 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, streamed)
     // Rows per wave: enough loads in flight per lane when the launch has many waves per SIMD anyway, fewer rows
     // per wave (more waves) when the whole tensor would otherwise be a handful of waves per SIMD.
     const bool few = rows * chunks < (int64_t(1) << 21);      // under 32 MB of bf16 (measured: 16384 x 512 8.8 -> 6.7 us)
@@ -533,30 +593,31 @@ loka_status quantize_launch(const void* x_bf16, int64_t rows, int64_t cols, int6
         else launch_rows<true>(x, rows, cols, ld, q, scales, pow2, s);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
+    const bool streamed = read_streamed(rows, cols);
     const dim3 tiles(static_cast<unsigned>(((cols + 127) / 128) * ((rows + 127) / 128)));
     if (mode == LOKA_SCALE_BLOCK_128x128 || mode == LOKA_SCALE_BLOCK_128x1) {
         // groups that fit a workgroup: one pass
-        if (mode == LOKA_SCALE_BLOCK_128x1) quant_tile128_kernel<G_COL128, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, nullptr, 0);
-        else if (transpose_out) quant_tile128_kernel<G_TILE, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, nullptr, 0);
-        else quant_tile128_kernel<G_TILE, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, nullptr, 0);
+        if (mode == LOKA_SCALE_BLOCK_128x1) quant_tile128_kernel<G_COL128, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, nullptr, 0);
+        else if (transpose_out) quant_tile128_kernel<G_TILE, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, streamed, nullptr, 0);
+        else quant_tile128_kernel<G_TILE, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, pow2, streamed, nullptr, 0);
         return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
     }
     float* parts = static_cast<float*>(workspace);
     if (mode == LOKA_SCALE_TENSOR) {
         const int n = static_cast<int>(tensor_parts(rows, cols));
         amax_tensor_kernel<<<dim3(static_cast<unsigned>(n)), 256, 0, s>>>(x, rows, cols, ld, parts);
-        if (transpose_out) quant_tile128_kernel<G_TENSOR, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
-        else quant_tile128_kernel<G_TENSOR, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
+        if (transpose_out) quant_tile128_kernel<G_TENSOR, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, parts, n);
+        else quant_tile128_kernel<G_TENSOR, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, parts, n);
     } else if (col_in_one(rows, cols)) {
-        if (transpose_out) quant_tile128_kernel<G_COL_ALL, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, nullptr, 0);
-        else quant_tile128_kernel<G_COL_ALL, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, nullptr, 0);
+        if (transpose_out) quant_tile128_kernel<G_COL_ALL, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, nullptr, 0);
+        else quant_tile128_kernel<G_COL_ALL, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, nullptr, 0);
     } else {
         const int64_t per = col_rows_per_part(rows);
         const int n = static_cast<int>((rows + per - 1) / per);
         const dim3 g(static_cast<unsigned>((cols + 63) / 64), static_cast<unsigned>(n));
         amax_col_kernel<<<g, 256, 0, s>>>(x, rows, cols, ld, per, parts);
-        if (transpose_out) quant_tile128_kernel<G_COL, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
-        else quant_tile128_kernel<G_COL, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, parts, n);
+        if (transpose_out) quant_tile128_kernel<G_COL, true><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, parts, n);
+        else quant_tile128_kernel<G_COL, false><<<tiles, 256, 0, s>>>(x, rows, cols, ld, q, scales, 0, streamed, parts, n);
     }
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }

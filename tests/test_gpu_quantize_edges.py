@@ -45,3 +45,28 @@ def test_rows_longer_than_a_wave_holds(orc, rows, cols):
     if rows > 1:
         x[1] = 0
     _check(orc, x, B.SCALE_ROW, ld=cols + 8 if rows < 4 else None)
+
+
+# every share of a row (lanes, chunks per lane, rows per wave) of the one-pass kernel, whose groups' scales are taken by different
+# lanes: rows that do not fill a wave's share, a row of zeros, the maximum at the end of the first group and the start of the last
+@pytest.mark.parametrize("rows,cols", [(1, 128), (7, 128), (11, 256), (70003, 256), (5, 512), (33001, 512), (9, 1024), (17003, 1024),
+                                       (6, 2048), (9, 4096), (3, 8192)])
+@pytest.mark.parametrize("mode", [B.SCALE_ROW, B.SCALE_BLOCK_1x128, B.SCALE_BLOCK_1x128_POW2])
+def test_groups_whose_scales_other_lanes_take(orc, rows, cols, mode):
+    x = synth.student_t4(rows, cols, seed=cols + rows)
+    x[:, 127] *= 64
+    x[-1, cols - 128] = -500.0
+    if rows > 2:
+        x[1] = 0
+    _check(orc, x, mode, ld=cols + 8 if rows < 8 else None)
+
+
+# tensors that are read past the caches give what their parts, which are not, give
+@pytest.mark.parametrize("rows,cols", [(32768, 256), (65536, 512), (8192, 4096)])
+@pytest.mark.parametrize("mode", [B.SCALE_ROW, B.SCALE_BLOCK_128x128, B.SCALE_TENSOR])
+def test_streamed_reads_change_nothing(rows, cols, mode):
+    x = synth.student_t4(rows // 8, cols, seed=7).to("cuda:0").repeat(8, 1)
+    q, s = B.loka_quantize(x, mode)
+    q1, s1 = B.loka_quantize(x[:rows // 8], mode)
+    assert torch.equal(q.view(8, rows // 8, cols), q1.expand(8, -1, -1))
+    assert torch.equal(s if mode == B.SCALE_TENSOR else s.view(8, -1), s1 if mode == B.SCALE_TENSOR else s1.reshape(1, -1).expand(8, -1))
