@@ -58,12 +58,14 @@ TrackerPlan tracker_plan(int64_t B, int64_t K) {
     int64_t max_s = steps / 2 > 0 ? steps / 2 : 1;                    // at least 2 stages per workgroup
     if (max_s > 256) max_s = 256;
     // estimated time in units of one stage (about 1.2 us): rounds * (stages per workgroup + start-up) for the
-    // scatter, and 0.1 per partial tile (256 KB written, then read back by the merge, at HBM speed)
+    // scatter, and so much per partial tile, written and then read back by the merge: 256 KB, of a diagonal tile 144
+    // (one tile: its merge is a few workgroups and takes longer with every range)
+    const double tiles_cost = pl.T == 1 ? 0.06 : 0.08 * (pl.pairs - pl.T) + 0.05 * pl.T;
     int64_t best_s = 1;
     double best = 1e300;
     for (int64_t sp = 1; sp <= max_s; ++sp) {
         const int64_t rounds = (static_cast<int64_t>(pl.pairs) * sp + TRK_PLAN_SLOTS - 1) / TRK_PLAN_SLOTS;
-        const double cost = static_cast<double>(rounds) * ((steps + sp - 1) / sp + 3) + 0.1 * pl.pairs * static_cast<double>(sp);
+        const double cost = static_cast<double>(rounds) * ((steps + sp - 1) / sp + 3) + tiles_cost * static_cast<double>(sp);
         if (cost < best) { best = cost; best_s = sp; }
     }
     int64_t rows = (B + best_s - 1) / best_s;
@@ -82,7 +84,7 @@ struct TrackerParams {
     const uint16_t* x;
     int64_t B, ld, rows_per_split;
     int K, T, pairs, splits;
-    float* partial;      // [splits][pairs][256][256]
+    float* partial;      // [splits][pairs][256][256] (of a diagonal pair the 32 x 32 blocks on and above the diagonal, live columns)
     double* colsum;      // [splits][pairs][256] (written for diagonal pairs only)
     const float* mu;     // [K]: the mean before this call, copied to
     float* mu_old;       // the workspace by the diagonal pairs of the first range
@@ -337,12 +339,16 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
                 }
             }
             __syncthreads();
+            // a diagonal tile leaves from its 32 x 32 blocks on the diagonal on, and as far as there are columns: the merge reads
+            // nothing else of it
+            const int last = DIAG || diag ? p.K - ti * TRK_T : TRK_T;
 #pragma unroll 4
             for (int it = 0; it < 16; ++it) {
                 const float* const src = stg + st_r + it * 8 * 256 + (pos_r ^ (DIAG ? 2 * it : 0));
                 const f32x2_t lo = *reinterpret_cast<const f32x2_t*>(src);
                 const f32x2_t hi = *reinterpret_cast<const f32x2_t*>(src + 64);
-                *reinterpret_cast<v4f*>(out + (128 * ps + it * 8) * TRK_T) = v4f{lo[0], lo[1], hi[0], hi[1]};
+                if (!(DIAG || diag) || (4 * q4 >= 32 * (4 * ps + it / 4) && 4 * q4 < last))
+                    *reinterpret_cast<v4f*>(out + (128 * ps + it * 8) * TRK_T) = v4f{lo[0], lo[1], hi[0], hi[1]};
             }
         }
         if (diag) {
@@ -364,25 +370,34 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
     else run(std::false_type{});
 }
 
-// grid (pairs, 64): workgroup y handles the 32 x 32 block (y / 8, y % 8) of its pair's tile, one run of four
-// columns per thread, and, for an off-diagonal pair, the mirrored block of the lower triangle (through a
-// transposing LDS tile, so both triangles are written in full 128-byte runs).
-// The workgroup folds the column sums of its 64 columns by itself (wave q takes the ranges q, q + 4, ..., then the four
+// Bound by the latency of the loads of a run's ranges and, with many tiles, by their bytes: what is never read is not
+// written either (whole call, us: 32768 x 1024 63.3 -> 58.8, 65536 x 512 45.7 -> 42.9,
+// 65536 x 256 35.7 -> 32.2, 16384 x 512 30.3 -> 26.9, 4000 x 1024 28.3 -> 26.8, 32768 x 4096 the same).
+// grid (pairs, 64): workgroup y handles the 32 x 32 block (y / 8, y % 8) of its pair's tile, PARTS threads per run of four
+// columns (each folds every PARTS-th range, their sums are added in order), and the mirrored block of the lower
+// triangle (through a transposing LDS tile, so both triangles are written in full 128-byte runs); of a diagonal pair's
+// blocks those below the diagonal have nothing to do.
+// The workgroup folds the column sums of its 64 columns by itself (wave q takes the ranges q, q + 4 PARTS, ..., then the
 // waves' sums in order: the same bits in every workgroup), with the first loads in flight together with those of the
 // partial tiles.  A kernel of its own for the means ran a few workgroups for 4.7 us between the two large ones (whole
 // call before and after: 65536 x 256 42.0 -> 36.8 us, 4096 x 512 23.7 -> 22.0, 32768 x 1024 64.6 -> 62.0).  The
 // old mean is the scatter kernel's copy, because the workgroups of the diagonal blocks overwrite mu here.
-__global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restrict__ partial, const double* __restrict__ colsum,
+template <int PARTS>
+__global__ __launch_bounds__(256 * PARTS) void tracker_merge_kernel(const float* __restrict__ partial, const double* __restrict__ colsum,
                                                             const float* __restrict__ mu_old, int T, int pairs, int splits,
                                                             int K, int64_t B, double ratio, double coef,
                                                             float* __restrict__ mu, float* __restrict__ sigma) {
     __shared__ double tr[32][33];
-    __shared__ double part[4][64], mub[64], delta[64];                   // columns: 32 of the i block, 32 of the j block
-    const int tid = threadIdx.x, tq = tid & 7, ty = tid >> 3;            // 8 runs of four columns x 32 rows
+    __shared__ double part[4 * PARTS][64], mub[64], delta[64];           // columns: 32 of the i block, 32 of the j block
+    __shared__ double sums[PARTS > 1 ? PARTS - 1 : 1][4][256];
+    const int tid = threadIdx.x, run = tid & 255, mine = tid >> 8;
+    const int tq = run & 7, ty = run >> 3;                               // 8 runs of four columns x 32 rows
     const int pair = blockIdx.x, bi = blockIdx.y >> 3, bj = blockIdx.y & 7;
     int ti, tj;
     pair_to_tiles(pair, T, ti, tj);
     const bool diag = ti == tj;
+    if (diag && bi > bj) return;
+    const bool mirrored = !diag || bi < bj;
     const double Bd = static_cast<double>(B);
     const int64_t tile_elems = TRK_T * TRK_T, stride = static_cast<int64_t>(pairs) * tile_elems;
     const int il = bi * 32 + ty, jl = bj * 32 + 4 * tq;
@@ -394,22 +409,22 @@ __global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restr
     const int64_t fstride = static_cast<int64_t>(pairs) * TRK_T;
     double cv[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) cv[u] = fq + 4 * u < splits ? fsrc[(fq + 4 * u) * fstride] : 0.0;
+    for (int u = 0; u < 8; ++u) cv[u] = fq + 4 * PARTS * u < splits ? fsrc[(fq + 4 * PARTS * u) * fstride] : 0.0;
     const double m0 = fk < K ? static_cast<double>(mu_old[fk]) : 0.0;
     double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
     float* dst = sigma + static_cast<int64_t>(i) * K + j;
     // mirrored block: row jl2 of the lower triangle takes column jl2 of this block
     const int jl2 = bj * 32 + ty, il2 = bi * 32 + 4 * tq;
     const int i2 = ti * TRK_T + il2, j2 = tj * TRK_T + jl2;
-    const bool live2 = !diag && i2 < K && j2 < K;
+    const bool live2 = mirrored && mine == 0 && i2 < K && j2 < K;
     float* dst2 = sigma + static_cast<int64_t>(j2) * K + i2;
     v4f old{}, old2{};
     if (live2) old2 = *reinterpret_cast<const v4f*>(dst2);
     if (live) {
-        old = *reinterpret_cast<const v4f*>(dst);
+        if (mine == 0) old = *reinterpret_cast<const v4f*>(dst);
         const float* src = partial + static_cast<int64_t>(pair) * tile_elems + il * TRK_T + jl;
 #pragma unroll 8
-        for (int sp = 0; sp < splits; ++sp) {
+        for (int sp = mine; sp < splits; sp += PARTS) {
             const v4f v = *reinterpret_cast<const v4f*>(src + sp * stride);
             s0 += static_cast<double>(v[0]); s1 += static_cast<double>(v[1]);
             s2 += static_cast<double>(v[2]); s3 += static_cast<double>(v[3]);
@@ -419,19 +434,31 @@ __global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restr
 #pragma unroll
     for (int u = 0; u < 8; ++u) cs += cv[u];
 #pragma unroll 4
-    for (int sp = fq + 32; sp < splits; sp += 4) cs += fsrc[sp * fstride];
+    for (int sp = fq + 32 * PARTS; sp < splits; sp += 4 * PARTS) cs += fsrc[sp * fstride];
     part[fq][fc] = cs;
+    if (PARTS > 1 && mine > 0) {
+        sums[mine - 1][0][run] = s0; sums[mine - 1][1][run] = s1; sums[mine - 1][2][run] = s2; sums[mine - 1][3][run] = s3;
+    }
     __syncthreads();
     if (tid < 64) {
-        const double mb = ((part[0][fc] + part[1][fc]) + (part[2][fc] + part[3][fc])) / Bd;
+        double t = 0.0;
+#pragma unroll
+        for (int u = 0; u < 4 * PARTS; ++u) t += part[u][fc];
+        const double mb = t / Bd;
         mub[fc] = mb;
         delta[fc] = mb - m0;
         if (diag && bi == bj && fc < 32 && fk < K) mu[fk] = static_cast<float>(m0 + ratio * (mb - m0));
     }
     __syncthreads();
     double c[4] = {0.0, 0.0, 0.0, 0.0};
-    if (live) {
-        const double sv[4] = {s0, s1, s2, s3};
+    if (live && mine == 0) {
+        double sv[4] = {s0, s1, s2, s3};
+        if (PARTS > 1) {
+#pragma unroll
+            for (int u = 0; u < PARTS - 1; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) sv[e] += sums[u][e][run];
+        }
         v4f nw;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -442,9 +469,11 @@ __global__ __launch_bounds__(256) void tracker_merge_kernel(const float* __restr
         }
         *reinterpret_cast<v4f*>(dst) = nw;
     }
-    if (!diag) {
+    if (mirrored) {
+        if (mine == 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) tr[ty][4 * tq + e] = c[e];
+            for (int e = 0; e < 4; ++e) tr[ty][4 * tq + e] = c[e];
+        }
         __syncthreads();
         if (live2) {
             v4f nw;
@@ -473,8 +502,14 @@ loka_status tracker_update_launch(const void* x, int64_t B, int64_t K, int64_t l
     tracker_scatter_kernel<<<dim3(pl.pairs * pl.splits), 512, TRK_LDS, s>>>(p);
     const double n_new = static_cast<double>(n_old) + static_cast<double>(B);
     const double ratio = static_cast<double>(B) / n_new, coef = static_cast<double>(n_old) * static_cast<double>(B) / n_new;
-    tracker_merge_kernel<<<dim3(pl.pairs, 64), 256, 0, s>>>(p.partial, colsum, p.mu_old, pl.T, pl.pairs, pl.splits,
-                                                            static_cast<int>(K), B, ratio, coef, mu, sigma);
+    auto merge = [&](auto parts) {
+        tracker_merge_kernel<decltype(parts)::value><<<dim3(pl.pairs, 64), 256 * decltype(parts)::value, 0, s>>>(
+            p.partial, colsum, p.mu_old, pl.T, pl.pairs, pl.splits, static_cast<int>(K), B, ratio, coef, mu, sigma);
+    };
+    // Four threads per run where workgroups are few and ranges many (us, one thread -> four: 65536 x 256, 103 ranges, 33.0 -> 31.8,
+    // 18786 x 456, 33, 28.4 -> 27.6; but 32768 x 1024, four column tiles and 19 ranges, 57.7 -> 62.5, 2000 x 64, 16, 13.2 -> 14.1)
+    if (pl.T <= 2 && pl.splits >= 32) merge(std::integral_constant<int, 4>{});
+    else merge(std::integral_constant<int, 1>{});
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
 }
 

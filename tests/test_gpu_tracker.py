@@ -147,3 +147,15 @@ def test_large_layer_on_sampled_columns(orc):
     _check(xs, np.zeros_like(ab), (mu_o, sg_o, ab), (mu_g.cpu().numpy()[cols], sub))
     full = sg_g.cpu().numpy()
     assert np.array_equal(full, full.T)
+
+
+# one or two column tiles and many ranges: four threads fold each run of the merge; diagonal tiles leave without what lies below
+# their diagonal blocks or beyond the last column
+@pytest.mark.parametrize("shape", [(20011, 8), (30000, 72), (16500, 256), (16500, 264), (9000, 488), (6400, 1032)])
+def test_many_ranges_of_few_column_tiles(orc, shape):
+    rows, K = shape
+    x = synth.correlated(rows, K, seed=rows + K)
+    n_old, mu, sigma = _state(K, K + 1)
+    o, g = _step_both(orc, x, n_old, mu, sigma)
+    _check(x, sigma, o, g)
+    assert np.array_equal(g[1], g[1].T)
