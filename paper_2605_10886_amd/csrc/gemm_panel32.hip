@@ -502,12 +502,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // lane: rows m(mi) = m0 + 128 wave_m + 32 mi + l32; columns ncol(ni) + [0, 16), ncol = n0 + 64 wave_n + 32 ni + 16 hk
     const bool tensor_x = p.x_mode == LOKA_SCALE_TENSOR, tensor_w = p.w_mode == LOKA_SCALE_TENSOR;
     int ncol[NI];
-    float cnt_lane = 0.f;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-        ncol[ni] = n0 + wave_n * WN + ni * 32 + hk * 16;
-        if (ncol[ni] < p.N) cnt_lane += 16.f;               // N % 16 == 0: a run of 16 is all in or all out
-    }
+    for (int ni = 0; ni < NI; ++ni) ncol[ni] = n0 + wave_n * WN + ni * 32 + hk * 16;     // N % 16 == 0: a run of 16 is all in or all out
     v4f s4[NI][4];
     float sxm[MI];
 #pragma unroll
@@ -540,8 +536,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     }
 
     // ------------------------------------------------------------------ epilogue
-    float* red = reinterpret_cast<float*>(smem);                                   // [BM][4][3]
-    float2* fin = reinterpret_cast<float2*>(smem) + BM * 4 * 3 / 2 + 8;            // [BM] (mean, rstd)
+    float2* red = reinterpret_cast<float2*>(smem);                                 // [4][BM] (mean, M2) of a wave's columns
+    float2* fin = red + BM * 4;                                                    // [BM] (mean, rstd)
     float* finq = reinterpret_cast<float*>(fin + BM);                              // [BM] 448 / amax of the output row (FP8OUT)
     float* red2 = reinterpret_cast<float*>(smem + 16384);                          // [BM][4][2] (min, max) (FP8OUT); the
                                                                                    // transpose buffers take its place later
@@ -592,48 +588,42 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) { mean_r[mi] = 0.f; rstd_r[mi] = 1.f; iq_r[mi] = 1.f; }
     } else {
+        // In every wave per row: mean and centred squares of its 64 columns (LayerNorm) or the sum of squares.  Without branches and
+        // LDS exchanges: columns past N hold zeros, which add nothing to the sums (their centred value is taken as
+        // zero), and the two lanes of a row add up by half swaps.  The counts of the waves' columns add up to the tile's,
+        // so the tile's mean is the plain sum of n_w mean_w over n, its centred squares that of m2_w + n_w (mean_w - mean)^2.
+        // (M x N x K, us, with branches, shuffles and pairwise merges before: 16384 x 3072 x 1024 100.1 -> 98.3, 8192 x 2048 x 2048
+        // 36.0 -> 35.7, 65536 x 256 x 512 20.5 -> 20.2, 32768 x 4096 x 4096 477 -> 474)
+        const int n_tile = n_o - n0 < BN ? n_o - n0 : BN;
+        auto cols_of = [&](int w) __attribute__((always_inline)) {
+            const int c = n_tile - w * WN;
+            return static_cast<float>(c < 0 ? 0 : c < WN ? c : WN);
+        };
+        const float n_wave = cols_of(wave_n), rn_wave = n_wave > 0.f ? __builtin_amdgcn_rcpf(n_wave) : 0.f;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) {
-            float n_ = cnt_lane, mean = 0.f, m2 = 0.f;
+            float mean = 0.f, q[4] = {0.f, 0.f, 0.f, 0.f};
             if (ln) {
-                float s = 0.f;
+                float t[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
-                    if (ncol[ni] < p.N) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) s += acc[mi][ni][i];
-                    }
-                mean = n_ > 0.f ? s * __builtin_amdgcn_rcpf(n_) : 0.f;
+                    for (int i = 0; i < 16; ++i) t[i & 3] += acc[mi][ni][i];
+                mean = half_lanes_sum((t[0] + t[1]) + (t[2] + t[3])) * rn_wave;
 #pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
-                    if (ncol[ni] < p.N) {
+                for (int ni = 0; ni < NI; ++ni) {
+                    const float mean_in = ncol[ni] < n_o ? mean : 0.f;
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) { const float d = acc[mi][ni][i] - mean; m2 = __builtin_fmaf(d, d, m2); }
-                    }
-                // lanes l and l ^ 32 hold the same row: symmetric merge, identical bits on both
-                const float nb = wave_shfl_xor(n_, 32), mb = wave_shfl_xor(mean, 32), m2b = wave_shfl_xor(m2, 32);
-                const float nn = n_ + nb;
-                if (nn > 0.f) {
-                    const float d = mb - mean;
-                    const float rn = __builtin_amdgcn_rcpf(nn);
-                    const float newmean = (n_ * mean + nb * mb) * rn;
-                    m2 = m2 + m2b + d * d * (n_ * nb * rn);
-                    mean = newmean;
+                    for (int i = 0; i < 16; ++i) { const float d = acc[mi][ni][i] - mean_in; q[i & 3] = __builtin_fmaf(d, d, q[i & 3]); }
                 }
-                n_ = nn;
             } else {
 #pragma unroll
                 for (int ni = 0; ni < NI; ++ni)
-                    if (ncol[ni] < p.N) {
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) m2 = __builtin_fmaf(acc[mi][ni][i], acc[mi][ni][i], m2);
-                    }
-                m2 += wave_shfl_xor(m2, 32);
+                    for (int i = 0; i < 16; ++i) q[i & 3] = __builtin_fmaf(acc[mi][ni][i], acc[mi][ni][i], q[i & 3]);
             }
-            if (hk == 0) {
-                float* r3 = red + ((wave_m * WM + mi * 32 + l32) * 4 + wave_n) * 3;
-                r3[0] = n_; r3[1] = mean; r3[2] = m2;
-            }
+            const float m2 = half_lanes_sum((q[0] + q[1]) + (q[2] + q[3]));
+            if (hk == 0) red[wave_n * BM + wave_m * WM + mi * 32 + l32] = make_float2(mean, m2);
             if (FP8OUT && !affine_q) {
                 float lo = __builtin_inff(), hi = -__builtin_inff();
 #pragma unroll
@@ -645,8 +635,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                             hi = __builtin_fmaxf(hi, acc[mi][ni][i]);
                         }
                     }
-                lo = __builtin_fminf(lo, wave_shfl_xor(lo, 32));
-                hi = __builtin_fmaxf(hi, wave_shfl_xor(hi, 32));
+                lo = -half_lanes_max(-lo);
+                hi = half_lanes_max(hi);
                 if (hk == 0) {
                     float* r2 = red2 + ((wave_m * WM + mi * 32 + l32) * 4 + wave_n) * 2;
                     r2[0] = lo; r2[1] = hi;
@@ -654,15 +644,20 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
             }
         }
         __syncthreads();
-        // tile statistics per row: thread r < 256 merges the four column waves in order
+        // tile statistics per row: thread r < 256 folds the four column waves in order
         float t_mean = 0.f, t_m2 = 0.f, t_lo = __builtin_inff(), t_hi = -__builtin_inff();
         if (tid < BM) {
-            float n_ = 0.f;
+            float2 part[4];
 #pragma unroll
             for (int w = 0; w < 4; ++w) {
-                const float* r3 = red + (tid * 4 + w) * 3;
-                if (ln) merge_stats(n_, t_mean, t_m2, r3[0], r3[1], r3[2]);
-                else t_m2 += r3[2];
+                part[w] = red[w * BM + tid];
+                t_mean = __builtin_fmaf(cols_of(w), part[w].x, t_mean);
+            }
+            t_mean *= __builtin_amdgcn_rcpf(static_cast<float>(n_tile));
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const float d = part[w].x - t_mean;
+                t_m2 += __builtin_fmaf(cols_of(w) * d, d, part[w].y);
                 if (FP8OUT && !affine_q) {
                     t_lo = __builtin_fminf(t_lo, red2[(tid * 4 + w) * 2]);
                     t_hi = __builtin_fmaxf(t_hi, red2[(tid * 4 + w) * 2 + 1]);
@@ -737,7 +732,11 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                         }
                     }
                 }
-                const float nb = wave_shfl_xor(n_, 1), mb = wave_shfl_xor(mean, 1), m2b = wave_shfl_xor(m2, 1);
+                // (the other thread's, by a move within the quad)
+                auto other = [](float v) __attribute__((always_inline)) {
+                    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, true));
+                };
+                const float nb = other(n_), mb = other(mean), m2b = other(m2);
                 if (ln) {
                     const float nn = n_ + nb;
                     if (nn > 0.f) {
@@ -751,8 +750,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                     m2 = m2 + m2b;
                 }
                 if (FP8OUT && !affine_q) {
-                    lo = __builtin_fminf(lo, wave_shfl_xor(lo, 1));
-                    hi = __builtin_fmaxf(hi, wave_shfl_xor(hi, 1));
+                    lo = __builtin_fminf(lo, other(lo));
+                    hi = __builtin_fmaxf(hi, other(hi));
                 }
                 if (sub == 0) {
                     // (a wait that ran out: the statistics are not to be trusted; the tile's rows leave as NaN, their
