@@ -737,7 +737,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64) void gemm_kernel(const GemmP
             }
         }
         int* lds_word = reinterpret_cast<int*>(smem) + BM * RS * 4 + 4;                        // between `red` and `fin`
-        const bool arrived = panel_publish_and_wait(p, p.flags + static_cast<int64_t>(panel) * p.tiles_n, tn, p.tiles_n, lds_word);
+        const bool arrived = panel_publish_and_wait(p, p.flags + static_cast<int64_t>(panel) * p.tiles_n, tn, p.tiles_n, lds_word, wave == 0);
         // Merge: the workgroup's BM rows are spread over its threads (TPR threads per row, each folding a
         // contiguous share of the row's tiles_n entries in order, read with device-coherent 8-byte loads
         // that bypass stale cache lines); shares are combined like the parts of a tile, the row's final

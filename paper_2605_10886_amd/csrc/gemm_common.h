@@ -144,6 +144,13 @@ __device__ __forceinline__ void merge_stats(float& n, float& mean, float& m2, fl
     }
 }
 
+// The lane's number, made where it is asked for: neither the thread id is kept in a register for it nor what is derived from it.
+__device__ __forceinline__ int lane_id() {
+    int l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
 // The exchange between the tiles_n workgroups that share a row panel (Section 3.2, Case 2: a row wider than a
 // workgroup's tile).  Called by every thread of the workgroup after its per-row records have been STORED with
 // device-coherent (agent-scope atomic, write-through) stores:
@@ -161,14 +168,13 @@ __device__ __forceinline__ void merge_stats(float& n, float& mean, float& m2, fl
 // or uninitialised word never equals a fresh 64-bit nonce.
 // Returns false when the wait ran out (never when all tiles_n workgroups are resident, which the launch arranges):
 // the launch's nonce is then recorded in header[1] and the caller poisons the rows of its tile.
-// `lds_word` is one LDS word the workgroup does not otherwise use during the call.
+// `lds_word` is one LDS word the workgroup does not otherwise use during the call; first_wave: this is wave 0.
 __device__ __forceinline__ bool panel_publish_and_wait(const GemmParams& p, unsigned long long* words, int tn, int tiles_n,
-                                                       int* lds_word) {
+                                                       int* lds_word, bool first_wave) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (with the clobber the record stores stay in front of it)
     __syncthreads();
-    if (threadIdx.x < 64) {
-        int lane = static_cast<int>(threadIdx.x);
-        asm volatile("; lane id" : "+v"(lane));           // (an opaque copy: addresses derived from it are not hoisted out of the tile loop)
+    if (first_wave) {
+        const int lane = lane_id();                       // (opaque: addresses derived from it are not hoisted out of the tile loop)
         // (the two 64-bit values restart from the scalar registers here: taken from the parameter block directly, the
         // compiler moves them into vector registers once, before the tile loop, and spills them through the main loop)
         unsigned n_lo = static_cast<unsigned>(p.nonce), n_hi = static_cast<unsigned>(p.nonce >> 32);

@@ -1,17 +1,21 @@
-// Large-tile FP8 GEMM with the row norm fused across workgroups: 256 x 256 tiles, 8 waves,
-// v_mfma_f32_32x32x64_f8f6f4, persistent panel-synchronous schedule (see gemm.hip for the schedule's
-// description; this file is its throughput-oriented instantiation).
+// Large-tile FP8 GEMM with the row norm fused across workgroups: 256 x 256 tiles, 8 waves, persistent
+// panel-synchronous schedule (see gemm.hip for the schedule's description; this file is its throughput-oriented
+// instantiation).
 //
-// Why a second kernel: measured on MI355X, back-to-back 16x16x128 MFMAs issued by ONE wave reach ~70-80 %
-// of the FP8 rate (each instruction reads 16 operand registers for 32 cycles of work), while 32x32x64
-// reaches 98 % (same operand registers, 64 cycles of work).  In the ping-pong main loop only one wave
-// per SIMD computes at a time, so the 32x32x64 form is the one that keeps the matrix pipe full.
+// Matrix instruction: v_mfma_f32_16x16x128_f8f6f4 where the accumulators take nothing but products (one scale per row,
+// column or tensor), v_mfma_f32_32x32x64_f8f6f4 with block scales (which want one row per lane), 32x32x16 for the BF16
+// reference.  From registers the 32 x 32 form issues back to back at 98 % of the FP8 rate in one wave where the
+// 16 x 16 form reaches 70 - 80 %, but only while the operands do not change: on changing operands the chip holds the first to
+// 2.3 - 2.5 PFLOP/s and the second to 3.7 - 4.0.  Whole launches, M x N x K, us, 32 x 32 x 64 -> 16 x 16 x 128 (with the
+// main loop below): 32768 x 4096 x 4096 472 -> 451, without a norm 460 -> 434, with FP8 output 468 -> 446; 16384 x 2048 x 8192
+// 213 -> 202; 2048 x 1024 x 123200 in K ranges 245 -> 230; 12000 x 2560 x 3072 93.7 -> 90.8; 8192 x 2048 x 2048 36.5 -> 35.7;
+// K = 256 and 512 the same within 1 %.
 //
 // Work split: waves 0..3 own rows 0..127 of the tile, waves 4..7 rows 128..255; wave w % 4 owns columns
-// [64 (w % 4), +64).  Per K step of 128 bytes a wave runs 4 (row tiles of 32) x 2
-// (column tiles of 32) x 2 (K halves of 64) = 16 MFMAs from 12 operand fragments of 8 registers.
+// [64 (w % 4), +64).  Per K step of 128 bytes a wave runs 8 (row tiles of 16) x 4 (column tiles of 16) = 32 MFMAs, or
+// 4 x 2 tiles of 32 x 2 K halves of 64 = 16, from 12 operand fragments of 8 registers.
 //
-// Operand roles are swapped as in gemm.hip (W rows -> MFMA rows, X rows -> MFMA columns).  MFMA row
+// Operand roles are swapped as in gemm.hip (W rows -> MFMA rows, X rows -> MFMA columns).  In the 32 x 32 form MFMA row
 // rho = 8a + 4h + b (a = 0..3, h = lane / 32, b = 0..3) is fed W row 16h + 4a + b of the 32-row tile, so a
 // lane ends with 16 CONSECUTIVE output columns (accumulator element i <-> column 16h + i) of one output
 // row m = lane % 32, and the two lanes that share a row cover 32 consecutive columns.
@@ -149,6 +153,8 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     constexpr bool SPLITK = EPI == EPI_SPLITK, PART = SPLITK || BF16;
     static_assert(!PART || (!FP8OUT && !QPRO), "partial sums and the reference GEMM leave as fp32");
     constexpr bool BLOCKWISE = BW != 0;
+    // Matrix instruction: 16 x 16 x 128 where the accumulators take nothing but products (see LOKA_PAIR)
+    constexpr bool SQ16 = BW == 0 && !BF16;
     constexpr int BM = 256, BN = 256, NW = 8, WM = 128, WN = 64, MI = 4, NI = 2;
     constexpr int ES = 256 * 128;           // one ring entry: 256 rows x 128 bytes of X or of W
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -238,17 +244,23 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     if (!prefetched) set_rsrc(tile);
     // this wave's share of one ring entry (the X or the W rows of K step kb / 128) is four loads of 1 KB:
     // row groups wave, wave + 8, wave + 16, wave + 24; load j of an entry
+    // (ragged rows: the offset is chosen per load from an opaque copy, or the choices of the first steps are kept from tile to
+    // tile and spilled)
     auto issue_x1 = [&](int slot, int kb, int j) __attribute__((always_inline)) {
         const int grp = wave + j * NW;
+        int x_lane = x_lane_off;
+        if (RAGK) asm volatile("; lane offset" : "+v"(x_lane));
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             x_rsrc, (__attribute__((address_space(3))) void*)(smem + slot * ES + grp * 1024), 16,
-            !RAGK || kb + kb0 + 128 <= p.KB || x_in ? x_lane_off : 0x7FFFFFFF, grp * 8 * p.KB + kb + kb0, 0, 0);
+            !RAGK || kb + kb0 + 128 <= p.KB || x_in ? x_lane : 0x7FFFFFFF, grp * 8 * p.KB + kb + kb0, 0, 0);
     };
     auto issue_w1 = [&](int slot, int kb, int j) __attribute__((always_inline)) {
         const int grp = wave + j * NW;
+        int w_lane = w_lane_off;
+        if (RAGK) asm volatile("; lane offset" : "+v"(w_lane));
         __builtin_amdgcn_raw_ptr_buffer_load_lds(
             w_rsrc, (__attribute__((address_space(3))) void*)(smem + slot * ES + grp * 1024), 16,
-            !RAGK || kb + kb0 + 128 <= p.KB || w_in ? w_lane_off : 0x7FFFFFFF, grp * 8 * p.KB + kb + kb0, 0, 0);
+            !RAGK || kb + kb0 + 128 <= p.KB || w_in ? w_lane : 0x7FFFFFFF, grp * 8 * p.KB + kb + kb0, 0, 0);
     };
     auto issue_x = [&](int slot, int kb) __attribute__((always_inline)) {
 #pragma unroll
@@ -419,6 +431,68 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
         __builtin_amdgcn_sched_barrier(0);                                           \
     } while (0)
 
+    // The same by 16 x 16 x 128 instructions, which sustain 3.7 - 4.0 PFLOP/s on changing operands from registers where the 32 x 32 x 64
+    // form sustains 2.3 - 2.5.  A K step is four pairs of X fragments (16 rows each; pair = row tile mi), a pair eight
+    // instructions: the step's four W fragments (32 registers) against both.  A pair's two X fragments are read while the
+    // pair before it is multiplied (two sets of 16 registers); a W fragment is replaced by the next step's behind its
+    // last instruction, in the step's last pair, and used again six instructions later.  So the last pair of a step reads
+    // of the next one only, and the step's barrier stands in front of it.
+    // acc16[mi][ni][2 t + x]: X rows 32 mi + 16 x + [0, 16), W rows of fragment (ni, t); lane (l16, q) holds the rows 4 q + r.  W row
+    // 16 hk + 8 t + 4 s + r of the 32 is row 4 (2 hk + s) + r of fragment t: exchanging the odd rows of 16 lanes of x = 0 with the
+    // even ones of x = 1 afterwards (one swap per two registers) leaves what the 32 x 32 form leaves, 16 consecutive
+    // columns of row l % 32 in every lane, and one epilogue serves both.
+    v4f acc16[MI][NI][4];
+    v8i xf[2][2], wf[4];
+    // Lane (l16, kg) takes the chunks kg and kg + 4 of its row, X row l16 (+ 16 per fragment), W row w16 (+ 8 and + 32 per
+    // fragment; neither changes the swizzle).  (From an opaque copy of the lane id: not kept from tile to tile.)
+    const int lane16 = lane_id();
+    const int l16 = lane16 & 15, kg = lane16 >> 4, w16 = wave_n * WN + 16 * (l16 >> 3) + 4 * ((l16 >> 2) & 1) + (l16 & 3);
+    const int x_at = (wave_m * WM + l16) * 128 + ((kg ^ ((l16 >> 1) & 7)) << 4);
+    const int w_at = w16 * 128 + ((kg ^ (((w16 >> 1) & 1) | (((w16 >> 2) & 1) << 1) | (((w16 >> 4) & 1) << 2))) << 4);
+    if constexpr (SQ16) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc16[mi][ni][u] = v4f{0.f, 0.f, 0.f, 0.f};
+    }
+    auto read16 = [&](const uint8_t* entry, int off) __attribute__((always_inline)) {
+        const v4i lo = *reinterpret_cast<const v4i*>(entry + off);
+        const v4i hi = *reinterpret_cast<const v4i*>(entry + (off ^ 64));
+        return v8i{lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    };
+    auto read_x16 = [&](int slot, int pair, int x) __attribute__((always_inline)) {
+        xf[pair & 1][x] = read16(smem + slot * ES + (32 * pair + 16 * x) * 128, x_at);
+    };
+    auto read_w16 = [&](int slot, int j) __attribute__((always_inline)) {
+        wf[j] = read16(smem + slot * ES + (32 * (j >> 1) + 8 * (j & 1)) * 128, w_at);
+    };
+    auto mfma16 = [&](int mi, int x, int j) __attribute__((always_inline)) {
+        v4f& a = acc16[mi][j >> 1][2 * (j & 1) + x];
+        a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf[j], xf[mi & 1][x], a, 0, 0, 0, 0, 0, 0);
+    };
+    // Pair MI_ of a step; reads pair RP (-1: none) of the entry in slot RX and, NEXT, the W fragments of the entry in slot RW; this
+    // wave's four loads LD as in LOKA_HALF_STEP.
+#define LOKA_PAIR(MI_, RX, RP, NEXT, RW, LD)                                               \
+    do {                                                                             \
+        _Pragma("unroll") for (int j = 0; j < 4; ++j) {                              \
+            __builtin_amdgcn_sched_barrier(0);                                       \
+            mfma16(MI_, 0, j);                                                       \
+            __builtin_amdgcn_sched_barrier(0);                                       \
+            if ((LD) == 1 && ld_x && !grp_b) issue_x1(ld_x_slot, ld_x_kb, j);        \
+            if ((LD) == 2 && ld_w && !grp_b) issue_w1(ld_w_slot, ld_w_kb, j);        \
+            if ((RP) >= 0 && (j & 1) == 0) read_x16(RX, RP, j >> 1);                 \
+            __builtin_amdgcn_sched_barrier(0);                                       \
+            mfma16(MI_, 1, j);                                                       \
+            __builtin_amdgcn_sched_barrier(0);                                       \
+            if (NEXT) read_w16(RW, j);                                               \
+            if ((LD) == 1 && ld_x && grp_b) issue_x1(ld_x_slot, ld_x_kb, j);         \
+            if ((LD) == 2 && ld_w && grp_b) issue_w1(ld_w_slot, ld_w_kb, j);         \
+        }                                                                            \
+        __builtin_amdgcn_sched_barrier(0);                                           \
+    } while (0)
+
     // ---- main loop.  LDS holds a ring of five 32 KB entries X(0) W(0) X(1) W(1) X(2) ...; entry e lives in
     // slot e % 5.  One barrier per K step, in its middle, when every wave has read X(k) and W(k) completely and
     // every wave's share of X(k + 1), W(k + 1) has landed.  The slot of X(k) then takes W(k + 2) (loads issued
@@ -451,9 +525,16 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
         __builtin_amdgcn_s_waitcnt(0x0F70);
     }
     lds_barrier();
-    read_w(2, 0, 0);
+    if constexpr (SQ16) {
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) read_x(1, 0, mi);
+        for (int j = 0; j < 4; ++j) read_w16(2, j);
+        read_x16(1, 0, 0);
+        read_x16(1, 0, 1);
+    } else {
+        read_w(2, 0, 0);
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) read_x(1, 0, mi);
+    }
     int e5 = 1;                                                 // slot of X(k)
     // (the last K step is peeled: MFMAs under a condition inside the loop make the compiler copy accumulators)
     for (int k = 0; k + 1 < ksteps; ++k) {
@@ -469,28 +550,43 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
         const int ld_w_slot = e5, ld_w_kb = (k + 2) * 128;              // W(k + 2) -> the slot X(k) leaves
         if (BLOCKWISE) limit_rsrc(more);
         bw_fetch(k);
-        LOKA_HALF_STEP(e5, sw_cur, 1, 0, 1, 1);
+        if constexpr (SQ16) {
+            LOKA_PAIR(0, e5, 1, false, 0, 0);
+            LOKA_PAIR(1, e5, 2, false, 0, 1);
+            LOKA_PAIR(2, e5, 3, false, 0, 0);
+        } else {
+            LOKA_HALF_STEP(e5, sw_cur, 1, 0, 1, 1);
+        }
         // all but this step's newest loads: X(k + 2) (4) and, blockwise, the scales of block k + 1 (1 or MI + 1)
         if (!ld_w) __builtin_amdgcn_s_waitcnt(0x0F70);
         else if (!BLOCKWISE) __builtin_amdgcn_s_waitcnt(0x0F74);
         else if (panel32_scale_loads(QUAD, k) == 1) __builtin_amdgcn_s_waitcnt(0x0F75);
         else __builtin_amdgcn_s_waitcnt(0x0F79);
         lds_barrier();                                          // (also waits for this wave's LDS reads)
-        LOKA_HALF_STEP(sx_nxt, sw_nxt, 0, 1, 2, 0);
+        if constexpr (SQ16) {
+            LOKA_PAIR(3, sx_nxt, 0, true, sw_nxt, 2);
+        } else {
+            LOKA_HALF_STEP(sx_nxt, sw_nxt, 0, 1, 2, 0);
+        }
         bw_use(k);
         e5 = sx_nxt;
     }
     {
         const bool ld_x = false, ld_w = false;
         const int ld_x_slot = 0, ld_x_kb = 0, ld_w_slot = 0, ld_w_kb = 0;
-        LOKA_HALF_STEP(e5, mod5(e5 + 1), 1, 0, 0, 1);
+        if constexpr (SQ16) {
+            LOKA_PAIR(0, e5, 1, false, 0, 0);
+            LOKA_PAIR(1, e5, 2, false, 0, 0);
+            LOKA_PAIR(2, e5, 3, false, 0, 0);
+        } else {
+            LOKA_HALF_STEP(e5, mod5(e5 + 1), 1, 0, 0, 1);
+        }
         (void)ld_x; (void)ld_w; (void)ld_x_slot; (void)ld_x_kb; (void)ld_w_slot; (void)ld_w_kb;
     }
     {   // Epilogue scope.  Lane- and thread-derived offsets restart from opaque copies of the ids: derived from
         // loop-invariant values the compiler would compute them once before the tile loop and keep dozens of
         // registers live through the main loop.
-    int lane_o = static_cast<int>(threadIdx.x) & 63, tid_o = static_cast<int>(threadIdx.x);
-    asm volatile("; epilogue ids" : "+v"(lane_o), "+v"(tid_o));
+    const int lane_o = lane_id(), tid_o = wave * 64 + lane_o;
     const int lane = lane_o, l32 = lane & 31, hk = lane >> 5;
     const unsigned tid = static_cast<unsigned>(tid_o);
     (void)lane;
@@ -506,24 +602,49 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     for (int ni = 0; ni < NI; ++ni) ncol[ni] = n0 + wave_n * WN + ni * 32 + hk * 16;     // N % 16 == 0: a run of 16 is all in or all out
     v4f s4[NI][4];
     float sxm[MI];
+    v4f s4q[NI][2];                                         // SQ16: columns 4 q .. of fragment (ni, t), row l16 of (mi, x): 24
+    float sxq[MI][2];                                       // registers, 36 in the layout behind the exchange
+    if constexpr (SQ16) {
+        // (buffer loads: one 32-bit offset per lane; columns and rows past the last read as zeros)
+        const int q = lane >> 4, r16 = lane & 15;
+        const __amdgpu_buffer_rsrc_t sw_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(swg), 0, tensor_w ? 4 : n_o * 4, 0x00020000);
+        const float sw_all = swg[0];
+        const __amdgpu_buffer_rsrc_t sx_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(sxg), 0, tensor_x ? 4 : p.M * 4, 0x00020000);
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            if (BLOCKWISE || BF16) s4[ni][a] = v4f{1.f, 1.f, 1.f, 1.f};
-            else if (tensor_w) { const float s = swg[0]; s4[ni][a] = v4f{s, s, s, s}; }
-            else s4[ni][a] = ncol[ni] < p.N ? *reinterpret_cast<const v4f*>(swg + ncol[ni] + 4 * a) : v4f{0.f, 0.f, 0.f, 0.f};
-        }
+            for (int t = 0; t < 2; ++t) {
+                const int c = n0 + wave_n * WN + ni * 32 + 16 * (q >> 1) + 8 * t + 4 * (q & 1);
+                s4q[ni][t] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(sw_rsrc, c * 4, 0, 0));
+                s4q[ni][t] = tensor_w ? v4f{sw_all, sw_all, sw_all, sw_all} : s4q[ni][t];
+            }
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
-        int m = m0 + wave_m * WM + mi * 32 + l32;
-        m = m < p.M ? m : p.M - 1;
-        sxm[mi] = BW == 1 ? s_cur[mi] : BW == 2 || BF16 ? 1.f : tensor_x ? sxg[0] : sxg[m];
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const int m = m0 + wave_m * WM + mi * 32 + 16 * x + r16;
+                sxq[mi][x] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sx_rsrc, tensor_x ? 0 : m * 4, 0, 0));
+            }
+    } else {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) s4[ni][a] = v4f{1.f, 1.f, 1.f, 1.f};          // (BLOCKWISE, BF16)
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) sxm[mi] = BW == 1 ? s_cur[mi] : 1.f;
     }
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (SQ16) {
+        const bool ld_x = false, ld_w = false;
+        const int ld_x_slot = 0, ld_x_kb = 0, ld_w_slot = 0, ld_w_kb = 0;
+        LOKA_PAIR(3, 0, -1, false, 0, 0);
+        (void)ld_x; (void)ld_w; (void)ld_x_slot; (void)ld_x_kb; (void)ld_w_slot; (void)ld_w_kb;
+    } else {
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) mfma_row(mi, 1);
+        for (int mi = 0; mi < MI; ++mi) mfma_row(mi, 1);
+    }
 #undef LOKA_HALF_STEP
+#undef LOKA_PAIR
     if (BLOCKWISE) wait_vmcnt<0>();                         // (the zeros requested past the last K step are in)
     __syncthreads();                                        // LDS is free for the epilogue
     // the next tile's first four ring entries stream in while this tile's statistics are exchanged
@@ -542,7 +663,22 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     float* red2 = reinterpret_cast<float*>(smem + 16384);                          // [BM][4][2] (min, max) (FP8OUT); the
                                                                                    // transpose buffers take its place later
     const int64_t obase = static_cast<int64_t>(g) * p.strideO;
-    if (!BF16) {
+    if constexpr (SQ16) {
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float v0 = acc16[mi][ni][2 * t][r] * (s4q[ni][t][r] * sxq[mi][0]);
+                        const float v1 = acc16[mi][ni][2 * t + 1][r] * (s4q[ni][t][r] * sxq[mi][1]);
+                        const u32_pair sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+                        acc[mi][ni][8 * t + r] = __uint_as_float(sw.x);
+                        acc[mi][ni][8 * t + 4 + r] = __uint_as_float(sw.y);
+                    }
+    } else if (!BF16) {
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
@@ -699,7 +835,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                                                          (static_cast<unsigned long long>(__float_as_uint(t_hi)) << 32),
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            arrived = panel_publish_and_wait(p, p.flags + static_cast<int64_t>(panel) * p.tiles_n, tn, p.tiles_n, lds_word);
+            arrived = panel_publish_and_wait(p, p.flags + static_cast<int64_t>(panel) * p.tiles_n, tn, p.tiles_n, lds_word, wave == 0);
             // two threads per row, each folds a contiguous half of the row's tiles in order (device-coherent
             // 8-byte loads), symmetric merge of the halves: identical bits in every workgroup of the panel
             {
@@ -882,7 +1018,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                 // (the second set of arrival words of the panel)
                 const bool arrived2 = panel_publish_and_wait(
                     p, p.flags + (static_cast<int64_t>(p.batch) * p.tiles_m + panel) * p.tiles_n, tn, p.tiles_n,
-                    reinterpret_cast<int*>(smem + 16000));
+                    reinterpret_cast<int*>(smem + 16000), wave == 0);
                 amax_ok = arrived2;
                 {
                     const int r = static_cast<int>(tid) >> 1, sub = static_cast<int>(tid) & 1;
