@@ -93,7 +93,10 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restr
             }
         }
     };
-    if (streamed) load(std::true_type{}); else load(std::false_type{});
+    // (each kind of read ends in a line of its own: the compiler merges the ends of the two branches otherwise, and an eighth of
+    // what is to be streamed went through the caches: training step 57472 x 896 x 1664, M x K x N, 522 -> 540 us)
+    if (streamed) { load(std::true_type{}); asm volatile("; streamed"); }
+    else { load(std::false_type{}); asm volatile("; through the caches"); }
     // The groups of a 16-lane row: T.  Every lane has the maxima of all of them after the exchanges (in the vector unit, no LDS
     // round trips); lane k takes group k's two divisions, and the factors go round by broadcasts: the divisions of all
     // groups in every lane were a third of the 1 x 128 form's instructions.
@@ -366,7 +369,8 @@ __global__ __launch_bounds__(256) void quant_tile128_kernel(const uint16_t* __re
                 w[sw] = load_chunk<decltype(streamed_c)::value>(x + (r0 + rr * 8 + sw) * ld + c0 + cc * 8);
         }
     };
-    if (streamed) load(std::true_type{}); else load(std::false_type{});
+    if (streamed) { load(std::true_type{}); asm volatile("; streamed"); }         // (as in quant_rows_kernel)
+    else { load(std::false_type{}); asm volatile("; through the caches"); }
     float inv8[8];
     if (GROUPS == G_COL128 || GROUPS == G_COL_ALL) {
         float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -516,12 +520,12 @@ __global__ void e4m3_from_f32_kernel(const float* __restrict__ t, uint8_t* __res
 
 // ---------------------------------------------------------------------------------
 // Whether X is read past the caches.  A plain read is the faster one by itself until X and its codes outgrow the last-level cache
-// (rows x columns, streamed -> plain, us: 16384 x 512 6.8 -> 6.1, 8192 x 2048 in 1 x 128 blocks 10.6 -> 10.3, 2048 x 8192 14.4 ->
-// 12.5; 65536 x 1024 33.4 -> 32.4, but 32768 x 3072 46.9 -> 49.6 and 32768 x 4096 60.3 -> 72.4), but X then stays in that
-// cache in the place of what the GEMM behind it reads and writes: a training step of 65536 x 256 x 1024 (M x K x N) takes 204 us
-// with X (32 MB) and dY (128 MB) streamed, 208 with X plain, 226 with both plain; the layer 8192 x 2048 x 2048 (X 32 MB) 54.8
-// streamed and 52.0 plain, the probe on 16384 x 1024 x 1024 111.0 and 108.0.  So streamed from 64 MB, and from 16 MB where rows are
-// short: such layers write more than they read.
+// (rows x columns, streamed -> plain, us: 65536 x 128 6.6 -> 6.1, 16384 x 512 6.9 -> 6.4, 8192 x 2048 10.3 -> 10.1; 65536 x 1024
+// 33.2 -> 32.4, but 32768 x 4096 61 -> 72), but X then stays in that cache in the place of what the calls behind it
+// read: a training step of 65536 x 256 x 1024 (M x K x N) takes 198.6 us with all streamed, 198.1 with X (32 MB) plain and 223 with
+// dY (128 MB) plain too, one of 57472 x 896 x 1664 516, 518 and 554; the layer 8192 x 2048 x 2048 (X 32 MB) 53.9 streamed and 51.6
+// plain, the probe on 16384 x 1024 x 1024 109.2 and 107.  So streamed from 64 MB, and from 16 MB where rows are short: such layers
+// write more than they read (on inputs new in every pass, the mlp 65536 x 256 x 1024 x 256 90.4 plain and 88.9 streamed).
 static bool read_streamed(int64_t rows, int64_t cols) { return rows * cols >= int64_t(1) << (cols <= 256 ? 23 : 25); }
 
 template <bool B128>

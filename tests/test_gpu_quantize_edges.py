@@ -62,7 +62,7 @@ def test_groups_whose_scales_other_lanes_take(orc, rows, cols, mode):
 
 
 # tensors that are read past the caches give what their parts, which are not, give
-@pytest.mark.parametrize("rows,cols", [(32768, 256), (65536, 512), (8192, 4096)])
+@pytest.mark.parametrize("rows,cols", [(131072, 256), (65536, 512), (8192, 4096)])
 @pytest.mark.parametrize("mode", [B.SCALE_ROW, B.SCALE_BLOCK_128x128, B.SCALE_TENSOR])
 def test_streamed_reads_change_nothing(rows, cols, mode):
     x = synth.student_t4(rows // 8, cols, seed=7).to("cuda:0").repeat(8, 1)
