@@ -3,13 +3,13 @@
 // instantiation).
 //
 // Matrix instruction: v_mfma_f32_16x16x128_f8f6f4 where the accumulators take nothing but products (one scale per row,
-// column or tensor), v_mfma_f32_32x32x64_f8f6f4 with block scales (which want one row per lane), 32x32x16 for the BF16
-// reference.  From registers the 32 x 32 form issues back to back at 98 % of the FP8 rate in one wave where the
+// column or tensor, power-of-two block scales), v_mfma_f32_32x32x64_f8f6f4 where block scales rescale them, 32x32x16 for the
+// BF16 reference.  From registers the 32 x 32 form issues back to back at 98 % of the FP8 rate in one wave where the
 // 16 x 16 form reaches 70 - 80 %, but only while the operands do not change: on changing operands the chip holds the first to
 // 2.3 - 2.5 PFLOP/s and the second to 3.7 - 4.0.  Whole launches, M x N x K, us, 32 x 32 x 64 -> 16 x 16 x 128 (with the
 // main loop below): 32768 x 4096 x 4096 472 -> 451, without a norm 460 -> 434, with FP8 output 468 -> 446; 16384 x 2048 x 8192
 // 213 -> 202; 2048 x 1024 x 123200 in K ranges 245 -> 230; 12000 x 2560 x 3072 93.7 -> 90.8; 8192 x 2048 x 2048 36.5 -> 35.7;
-// K = 256 and 512 the same within 1 %.
+// K = 256 and 512 the same within 1 %.  Power-of-two block scales 32768 x 4096 x 4096 511 -> 488, 8192 x 2048 x 2048 38.5 -> 36.6.
 //
 // Work split: waves 0..3 own rows 0..127 of the tile, waves 4..7 rows 128..255; wave w % 4 owns columns
 // [64 (w % 4), +64).  Per K step of 128 bytes a wave runs 8 (row tiles of 16) x 4 (column tiles of 16) = 32 MFMAs, or
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     static_assert(!PART || (!FP8OUT && !QPRO), "partial sums and the reference GEMM leave as fp32");
     constexpr bool BLOCKWISE = BW != 0;
     // Matrix instruction: 16 x 16 x 128 where the accumulators take nothing but products (see LOKA_PAIR)
-    constexpr bool SQ16 = BW == 0 && !BF16;
+    constexpr bool SQ16 = BW != 1 && !BF16;
     constexpr int BM = 256, BN = 256, NW = 8, WM = 128, WN = 64, MI = 4, NI = 2;
     constexpr int ES = 256 * 128;           // one ring entry: 256 rows x 128 bytes of X or of W
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -391,10 +391,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                                                                   __builtin_bit_cast(v8bf, v4i{b[0], b[1], b[2], b[3]}), acc[mi][ni], 0, 0, 0);
             acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, v4i{a[4], a[5], a[6], a[7]}),
                                                                   __builtin_bit_cast(v8bf, v4i{b[4], b[5], b[6], b[7]}), acc[mi][ni], 0, 0, 0);
-        } else if (BW == 2)
-            acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(aw[set][ni], bx[mi], acc[mi][ni], 0, 0, 0, sc_w, 0,
-                                                                         sc_x[mi]);
-        else
+        } else
             acc[mi][ni] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(aw[set][ni], bx[mi], acc[mi][ni], 0, 0, 0, 0, 0, 0);
     };
     auto mfma_row = [&](int mi, int set) __attribute__((always_inline)) {
@@ -443,6 +440,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     // columns of row l % 32 in every lane, and one epilogue serves both.
     v4f acc16[MI][NI][4];
     v8i xf[2][2], wf[4];
+    int sc_pair[2] = {127, 127};                             // (BW == 2) exponents of the pair's two row blocks
     // Lane (l16, kg) takes the chunks kg and kg + 4 of its row, X row l16 (+ 16 per fragment), W row w16 (+ 8 and + 32 per
     // fragment; neither changes the swizzle).  (From an opaque copy of the lane id: not kept from tile to tile.)
     const int lane16 = lane_id();
@@ -470,25 +468,39 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     };
     auto mfma16 = [&](int mi, int x, int j) __attribute__((always_inline)) {
         v4f& a = acc16[mi][j >> 1][2 * (j & 1) + x];
-        a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf[j], xf[mi & 1][x], a, 0, 0, 0, 0, 0, 0);
+        if constexpr (BW == 2) a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf[j], xf[mi & 1][x], a, 0, 0, 0, sc_w, 0, sc_pair[x]);
+        else a = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(wf[j], xf[mi & 1][x], a, 0, 0, 0, 0, 0, 0);
+    };
+    // Power-of-two block scales: a lane holds those of row l % 32 of every row tile, and needs those of rows l16 and 16 + l16: a
+    // swap.  (Scales of any value multiply the accumulators between the instructions.  So did the 16 x 16 form, at most two
+    // instructions ahead: 32768 x 4096 x 4096 555 -> 554 us, 2048 x 1024 x 32768 84.7 -> 84.0, but 16384 x 1024 x 1024 26.3 -> 27.0
+    // and 65536 x 256 x 512 20.5 -> 21.1.)
+    auto pair_scales = [&](int mi) __attribute__((always_inline)) {
+        if constexpr (BW == 2) {
+            const u32_pair r = __builtin_amdgcn_permlane16_swap(static_cast<unsigned>(sc_x[mi]), static_cast<unsigned>(sc_x[mi]), false, false);
+            sc_pair[0] = static_cast<int>(r.x);
+            sc_pair[1] = static_cast<int>(r.y);
+        }
     };
     // Pair MI_ of a step; reads pair RP (-1: none) of the entry in slot RX and, NEXT, the W fragments of the entry in slot RW; this
     // wave's four loads LD as in LOKA_HALF_STEP.
 #define LOKA_PAIR(MI_, RX, RP, NEXT, RW, LD)                                               \
     do {                                                                             \
+        __builtin_amdgcn_sched_barrier(0);                                           \
+        pair_scales(MI_);                                                            \
         _Pragma("unroll") for (int j = 0; j < 4; ++j) {                              \
             __builtin_amdgcn_sched_barrier(0);                                       \
             mfma16(MI_, 0, j);                                                       \
             __builtin_amdgcn_sched_barrier(0);                                       \
-            if ((LD) == 1 && ld_x && !grp_b) issue_x1(ld_x_slot, ld_x_kb, j);        \
-            if ((LD) == 2 && ld_w && !grp_b) issue_w1(ld_w_slot, ld_w_kb, j);        \
+            if ((LD) == 1 && ld_x && (BLOCKWISE || !grp_b)) issue_x1(ld_x_slot, ld_x_kb, j);        \
+            if ((LD) == 2 && ld_w && (BLOCKWISE || !grp_b)) issue_w1(ld_w_slot, ld_w_kb, j);        \
             if ((RP) >= 0 && (j & 1) == 0) read_x16(RX, RP, j >> 1);                 \
             __builtin_amdgcn_sched_barrier(0);                                       \
             mfma16(MI_, 1, j);                                                       \
             __builtin_amdgcn_sched_barrier(0);                                       \
             if (NEXT) read_w16(RW, j);                                               \
-            if ((LD) == 1 && ld_x && grp_b) issue_x1(ld_x_slot, ld_x_kb, j);         \
-            if ((LD) == 2 && ld_w && grp_b) issue_w1(ld_w_slot, ld_w_kb, j);         \
+            if ((LD) == 1 && ld_x && !BLOCKWISE && grp_b) issue_x1(ld_x_slot, ld_x_kb, j);         \
+            if ((LD) == 2 && ld_w && !BLOCKWISE && grp_b) issue_w1(ld_w_slot, ld_w_kb, j);         \
         }                                                                            \
         __builtin_amdgcn_sched_barrier(0);                                           \
     } while (0)
@@ -600,11 +612,9 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     int ncol[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni) ncol[ni] = n0 + wave_n * WN + ni * 32 + hk * 16;     // N % 16 == 0: a run of 16 is all in or all out
-    v4f s4[NI][4];
-    float sxm[MI];
     v4f s4q[NI][2];                                         // SQ16: columns 4 q .. of fragment (ni, t), row l16 of (mi, x): 24
     float sxq[MI][2];                                       // registers, 36 in the layout behind the exchange
-    if constexpr (SQ16) {
+    if constexpr (SQ16 && !BLOCKWISE) {
         // (buffer loads: one 32-bit offset per lane; columns and rows past the last read as zeros)
         const int q = lane >> 4, r16 = lane & 15;
         const __amdgpu_buffer_rsrc_t sw_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(swg), 0, tensor_w ? 4 : n_o * 4, 0x00020000);
@@ -625,13 +635,6 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                 const int m = m0 + wave_m * WM + mi * 32 + 16 * x + r16;
                 sxq[mi][x] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sx_rsrc, tensor_x ? 0 : m * 4, 0, 0));
             }
-    } else {
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) s4[ni][a] = v4f{1.f, 1.f, 1.f, 1.f};          // (BLOCKWISE, BF16)
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) sxm[mi] = BW == 1 ? s_cur[mi] : 1.f;
     }
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (SQ16) {
@@ -672,19 +675,20 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
-                        const float v0 = acc16[mi][ni][2 * t][r] * (s4q[ni][t][r] * sxq[mi][0]);
-                        const float v1 = acc16[mi][ni][2 * t + 1][r] * (s4q[ni][t][r] * sxq[mi][1]);
+                        const float v0 = BLOCKWISE ? acc16[mi][ni][2 * t][r] : acc16[mi][ni][2 * t][r] * (s4q[ni][t][r] * sxq[mi][0]);
+                        const float v1 = BLOCKWISE ? acc16[mi][ni][2 * t + 1][r] : acc16[mi][ni][2 * t + 1][r] * (s4q[ni][t][r] * sxq[mi][1]);
                         const u32_pair sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
                         acc[mi][ni][8 * t + r] = __uint_as_float(sw.x);
                         acc[mi][ni][8 * t + 4 + r] = __uint_as_float(sw.y);
                     }
-    } else if (!BF16) {
+    }
+    if (BW == 1) {
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
             for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[mi][ni][i] *= s4[ni][i >> 2][i & 3] * sxm[mi];
+                for (int i = 0; i < 16; ++i) acc[mi][ni][i] *= s_cur[mi];
     }
     // fp32 tile: split K's share of this range (its scales are factors of every term), the reference's Y, or the pre-norm Y
     // a caller asked for.  Each wave passes a 32 x 32 sub-tile through 4 KB of its own LDS (128-byte rows, 16-byte chunk c
