@@ -97,4 +97,29 @@ __device__ __forceinline__ void group_scale_any(bool pow2, float amax, float& sc
 
 __device__ __forceinline__ float wave_shfl_xor(float v, int mask) { return __shfl_xor(v, mask, 64); }
 
+// out[k] = v of lane k of the lane's 16, k < T
+template <int T, int K = 0>
+__device__ __forceinline__ void row_broadcasts(float v, float (&out)[T]) {
+    if constexpr (T == 1) out[0] = v;
+    else if constexpr (K < T) {
+        out[K] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xF, 0xF, true));
+        row_broadcasts<T, K + 1>(v, out);
+    }
+}
+
+// Maximum of unsigned values over groups of GL consecutive lanes (16, 32 or 64), in all of them: moves within 16 lanes, row and
+// half swaps, no LDS round trip.
+typedef unsigned u32_pair __attribute__((ext_vector_type(2)));
+template <int GL>
+__device__ __forceinline__ unsigned lanes_max_bits(unsigned a) {
+    unsigned o;
+    o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0xB1, 0xF, 0xF, false)); a = a > o ? a : o;      // lane ^ 1
+    o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x4E, 0xF, 0xF, false)); a = a > o ? a : o;      // lane ^ 2
+    o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x141, 0xF, 0xF, false)); a = a > o ? a : o;     // the other quad of 8
+    o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x140, 0xF, 0xF, false)); a = a > o ? a : o;     // the other half of 16
+    if (GL >= 32) { const u32_pair r = __builtin_amdgcn_permlane16_swap(a, a, false, false); a = r.x > r.y ? r.x : r.y; }
+    if (GL >= 64) { const u32_pair r = __builtin_amdgcn_permlane32_swap(a, a, false, false); a = r.x > r.y ? r.x : r.y; }
+    return a;
+}
+
 }  // namespace loka

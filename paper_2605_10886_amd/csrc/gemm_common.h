@@ -118,7 +118,6 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // Sums over lanes l, l ^ 32 and over l, l ^ 16, l ^ 32, l ^ 48 (identical bits on all of them), by the half and row swaps of the
 // vector unit: no LDS round trip, which a shuffle is.
-typedef unsigned u32_pair __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ float half_lanes_sum(float v) {
     const u32_pair r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     return __uint_as_float(r.x) + __uint_as_float(r.y);

@@ -87,8 +87,7 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
         locate(q, g, m0);
         uint8_t* const xq = const_cast<uint8_t*>(p.X) + static_cast<int64_t>(g) * p.strideX;
         float* const sxo = const_cast<float*>(p.sx) + static_cast<int64_t>(g) * p.strideSx;
-        // row amax: packed 16-bit maxima of the magnitudes (exact), the 16 lanes of a DPP row by four data-parallel
-        // moves, the four rows of lanes by two xor shuffles
+        // row amax: packed 16-bit maxima of the magnitudes (exact)
         unsigned mine = 0u;
 #pragma unroll
         for (int rr = 0; rr < RG; ++rr) {
@@ -97,21 +96,18 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
             for (int i = 0; i < LPR; ++i)
 #pragma unroll
                 for (int e = 0; e < 4; ++e) a2 = __builtin_elementwise_max(a2, __builtin_bit_cast(us2, src[rr][i][e] & 0x7FFF7FFFu));
-            unsigned a = a2[0] > a2[1] ? a2[0] : a2[1], o;
-            o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0xB1, 0xF, 0xF, false)); a = a > o ? a : o;
-            o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x4E, 0xF, 0xF, false)); a = a > o ? a : o;
-            o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x141, 0xF, 0xF, false)); a = a > o ? a : o;
-            o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x140, 0xF, 0xF, false)); a = a > o ? a : o;
-            o = static_cast<unsigned>(__shfl_xor(static_cast<int>(a), 16, 64)); a = a > o ? a : o;
-            o = static_cast<unsigned>(__shfl_xor(static_cast<int>(a), 32, 64)); a = a > o ? a : o;
-            mine = lv == rr ? a : mine;          // lane rr keeps row rr's amax: one division pair per lane, not per row and lane
+            const unsigned a = lanes_max_bits<64>(a2[0] > a2[1] ? a2[0] : a2[1]);
+            mine = (lv & 15) == rr ? a : mine;   // lane rr of 16 keeps row rr's amax: one division pair per lane, not per row and lane
         }
         float scale_l, inv_l;
         group_scale(__uint_as_float(mine << 16), scale_l, inv_l);
         if (lv < RG && m0 + lv < p.M) sxo[m0 + lv] = scale_l;
+        static_assert(RG <= 16, "one row per lane of 16");
+        float inv_b[RG];
+        row_broadcasts<RG>(inv_l, inv_b);
 #pragma unroll
         for (int rr = 0; rr < RG; ++rr) {
-            const float inv = __shfl(inv_l, rr, 64);
+            const float inv = inv_b[rr];
             const bool live = m0 + rr < p.M;
 #pragma unroll
             for (int i = 0; i < LPR; ++i) {

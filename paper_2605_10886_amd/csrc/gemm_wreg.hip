@@ -114,9 +114,7 @@ struct QuantPrologue {
         static_assert(QB * NRG <= 16, "one row per lane of a 16-lane group");
         int lv = static_cast<int>(threadIdx.x) & 63;
         asm volatile("; lane id" : "+v"(lv));
-        // row amax: integer max of the 15-bit magnitudes (exact), lanes of the row by xor shuffles
-        // (a lane's 8 or 16 magnitudes as packed 16-bit maxima; the 16 lanes of a row of the data-parallel primitives by
-        // four of those, with no LDS round trip; rows of lanes by xor shuffles)
+        // row amax: integer max of the 15-bit magnitudes (exact; a lane's 8 or 16 as packed 16-bit maxima)
         typedef unsigned short us2 __attribute__((ext_vector_type(2)));
         unsigned am[QB][NRG];
 #pragma unroll
@@ -136,21 +134,7 @@ struct QuantPrologue {
                     for (int e = 0; e < 4; ++e) a2 = __builtin_elementwise_max(a2, __builtin_bit_cast(us2, w[e] & 0x7FFF7FFFu));
                 }
                 unsigned a = a2[0] > a2[1] ? a2[0] : a2[1];
-                unsigned o;
-                o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0xB1, 0xF, 0xF, false));   // lane ^ 1
-                a = a > o ? a : o;
-                o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x4E, 0xF, 0xF, false));   // lane ^ 2
-                a = a > o ? a : o;
-                o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x141, 0xF, 0xF, false));  // the other quad of 8
-                a = a > o ? a : o;
-                o = static_cast<unsigned>(__builtin_amdgcn_update_dpp(0, static_cast<int>(a), 0x140, 0xF, 0xF, false));  // the other half of 16
-                a = a > o ? a : o;
-#pragma unroll
-                for (int msk = 16; msk < (CH_ROW < 64 ? CH_ROW : 64); msk <<= 1) {
-                    o = static_cast<unsigned>(__shfl_xor(static_cast<int>(a), msk, 64));
-                    a = a > o ? a : o;
-                }
-                am[u][rg] = a;
+                am[u][rg] = lanes_max_bits<CH_ROW < 64 ? CH_ROW : 64>(a);
             }
         }
         unsigned mine = am[0][0];
@@ -160,7 +144,9 @@ struct QuantPrologue {
             for (int rg = 0; rg < NRG; ++rg) mine = (lv & 15) == u * NRG + rg ? am[u][rg] : mine;
         float scale_l, inv_l;
         group_scale(__uint_as_float(mine << 16), scale_l, inv_l);
-        const int grp_base = IPR == 1 ? (lv / CH_ROW) * CH_ROW : 0;         // first lane of this lane's row group
+        float scale_b[QB * NRG], inv_b[QB * NRG];                           // (a row's lanes are whole groups of 16)
+        row_broadcasts<QB * NRG>(scale_l, scale_b);
+        row_broadcasts<QB * NRG>(inv_l, inv_b);
 #pragma unroll
         for (int u = 0; u < QB; ++u) {
             if (bb + u >= b1) continue;                                     // (uniform)
@@ -174,7 +160,7 @@ struct QuantPrologue {
             float* const sxl = reinterpret_cast<float*>(smem + C::OFF_SX + (b % C::NBUF) * 4 * C::SXL * 256);
 #pragma unroll
             for (int rg = 0; rg < NRG; ++rg) {
-                const float scale = __shfl(scale_l, grp_base + u * NRG + rg, 64), inv = __shfl(inv_l, grp_base + u * NRG + rg, 64);
+                const float scale = scale_b[u * NRG + rg], inv = inv_b[u * NRG + rg];
                 const int row = wave * RW + rg * RPI + (IPR == 1 ? lv / CH_ROW : 0);
                 const bool live = !dead && m0 + row < p.M;
 #pragma unroll
@@ -291,7 +277,7 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
         float* const sxl = reinterpret_cast<float*>(smem + C::OFF_SX + (b % NBUF) * 4 * SXL * 256);
         int lv = lane;
         asm volatile("; lane id" : "+v"(lv));
-        // row amax: integer max of the 15-bit magnitudes (exact), lanes of the row by xor shuffles
+        // row amax: integer max of the 15-bit magnitudes (exact)
         unsigned am[NRG];
 #pragma unroll
         for (int rg = 0; rg < NRG; ++rg) {
@@ -306,12 +292,7 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
                     a = a > hi ? a : hi;
                 }
             }
-#pragma unroll
-            for (int msk = 1; msk < (CH_ROW < 64 ? CH_ROW : 64); msk <<= 1) {
-                const unsigned o = static_cast<unsigned>(__shfl_xor(static_cast<int>(a), msk, 64));
-                a = a > o ? a : o;
-            }
-            am[rg] = a;
+            am[rg] = lanes_max_bits<CH_ROW < 64 ? CH_ROW : 64>(a);
         }
         // lane (lv % 16) = rg of each row's lane group computes that row's scale and factor
         unsigned mine = am[0];
@@ -319,10 +300,12 @@ __global__ __launch_bounds__(512) void gemm_wreg_kernel(const GemmParams p, cons
         for (int rg = 1; rg < NRG; ++rg) mine = (lv & 15) == rg ? am[rg] : mine;
         float scale_l, inv_l;
         group_scale(__uint_as_float(mine << 16), scale_l, inv_l);
-        const int grp_base = IPR == 1 ? (lv / CH_ROW) * CH_ROW : 0;         // first lane of this lane's row group
+        float scale_b[NRG], inv_b[NRG];                                     // (a row's lanes are whole groups of 16)
+        row_broadcasts<NRG>(scale_l, scale_b);
+        row_broadcasts<NRG>(inv_l, inv_b);
 #pragma unroll
         for (int rg = 0; rg < NRG; ++rg) {
-            const float scale = __shfl(scale_l, grp_base + rg, 64), inv = __shfl(inv_l, grp_base + rg, 64);
+            const float scale = scale_b[rg], inv = inv_b[rg];
             const int row = wave * RW + rg * RPI + (IPR == 1 ? lv / CH_ROW : 0);
 #pragma unroll
             for (int i = 0; i < IPR; ++i) {

@@ -39,7 +39,6 @@ __device__ __forceinline__ float lanes_max(float a) {
     a = fmaxf(a, moved(std::integral_constant<int, 0x4E>{}));       // lane ^ 2
     a = fmaxf(a, moved(std::integral_constant<int, 0x141>{}));      // the other quad of 8
     a = fmaxf(a, moved(std::integral_constant<int, 0x140>{}));      // the other half of 16
-    typedef unsigned u32_pair __attribute__((ext_vector_type(2)));
     if (GL >= 32) {
         const u32_pair r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(a), false, false);
         a = fmaxf(__uint_as_float(r.x), __uint_as_float(r.y));
@@ -50,16 +49,6 @@ __device__ __forceinline__ float lanes_max(float a) {
     }
     return a;
 }
-// out[k] = v of lane k of the lane's 16, k < T
-template <int T, int K = 0>
-__device__ __forceinline__ void row_broadcasts(float v, float (&out)[T]) {
-    if constexpr (T == 1) out[0] = v;
-    else if constexpr (K < T) {
-        out[K] = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x150 + K, 0xF, 0xF, true));
-        row_broadcasts<T, K + 1>(v, out);
-    }
-}
-
 // ---------------------------------------------------------------------------------
 // Single pass: TPR lanes share one row (TPR = 16, 32 or 64); each lane holds CPL
 // chunks of 8 consecutive bf16 (one 16-byte load each); a wave works on RU row sets at
