@@ -1134,7 +1134,7 @@ static const VariantInfo kVariants[] = {
     // persistent, panel-synchronous: the tiles_n workgroups of a row panel exchange row statistics
     // through a few words of global memory and normalize their own tile in registers
     LOKA_VARIANT("panel256x256w8", 256, 256, 1, 2, 4, EPI_PANEL_SYNC),
-    // the same schedule on 32x32x64 MFMAs: the throughput variant
+    // the same schedule with the large-tile kernel's main loop: the throughput variant
     {kPanel32Name, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32, panel32_fn(0, false, false), panel32_fn(1, false, false)},
     // (an id is the place in this table, and callers keep ids: new entries go to the end)
     // fewer rows per tile, for layers with few rows
@@ -1148,7 +1148,7 @@ static const VariantInfo kVariants[] = {
     LOKA_VARIANT("panel32x256", 32, 256, 1, 1, 4, EPI_PANEL_SYNC),
     LOKA_VARIANT("panel64x256", 64, 256, 1, 1, 4, EPI_PANEL_SYNC),
     LOKA_VARIANT("panel128x128", 128, 128, 1, 2, 4, EPI_PANEL_SYNC),
-    // the 32x32x64 kernel for a K that is no multiple of the 128-byte step (non-blockwise recipes, bf16 output)
+    // the large-tile kernel for a K that is no multiple of the 128-byte step (non-blockwise recipes, bf16 output)
     {kPanel32RaggedName, 256, 256, 512, EPI_PANEL_SYNC, panel32_lds(), &launch_panel32_ragged, panel32_ragged_fn(), nullptr},
 };
 constexpr int kMaxRowTiles = 256;     // shape limit of the panel-synchronous schedule (a row's tiles must be co-resident:
@@ -1209,7 +1209,7 @@ int variant_fused_default(const loka_gemm_desc* d) {
     return wreg;
 }
 bool variant_is_streaming(int v) { return kVariants[v].name == kWregName; }
-// (the two instantiations of the 32 x 32 x 64 kernel that lay out the workspace its way)
+// (the two instantiations of the large-tile kernel that lay out the workspace its way)
 static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Name || vi.name == kPanel32RaggedName; }
 
 // ---- expected time of a variant, in microseconds: what the static choice compares.
@@ -1391,7 +1391,7 @@ static double variant_cost(const loka_gemm_desc* d, int v) {
     return t;
 }
 
-// BlockNorm where the static choice is the 32 x 32 x 64 kernel (a caller that names it gets its bits, which its FP8-output form
+// BlockNorm where the static choice is the large-tile kernel (a caller that names it gets its bits, which its FP8-output form
 // quantizes, and so does a shape for which loka_dispatch timed and probed it): the groups are tiles of 256 columns, so a
 // layer with few rows also runs on the 256-column row tiles, one workgroup per group and 16, 32 or 64 rows (no exchange, no
 // scratch in either).  By expected time (bf16 output; M x N x K: 222 x 256 x 768 in 4 problems 16.1 -> 6.7 us,

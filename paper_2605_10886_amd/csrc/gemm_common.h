@@ -84,7 +84,7 @@ __host__ __device__ constexpr int panel_per_xcd(int b, int G, int tiles_n) {
     return ((i / tiles_n) * 8 + (b & 7)) * tiles_n + i % tiles_n;
 }
 
-// Loads of block scales that a wave of the 32 x 32 x 64 kernel requests at the start of K step k, for step k + 1: W's scale and
+// Loads of block scales that a wave of the large-tile kernel requests at the start of K step k, for step k + 1: W's scale and
 // X's four, or (quad: a lane holds four K blocks' scales of X) W's alone in three steps of four.  What may stay in flight
 // where the step needs X(k + 1) and W(k + 1) is these and the 4 loads of X(k + 2), the only ones requested behind W(k + 1).
 __host__ __device__ constexpr int panel32_scale_loads(bool quad, int k) { return quad && ((k + 1) & 3) != 0 ? 1 : 5; }

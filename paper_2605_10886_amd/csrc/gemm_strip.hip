@@ -13,7 +13,7 @@
 // X does not pass through LDS: the MFMA operand of a lane is 32 consecutive K bytes of one row, which two
 // 16-byte loads fetch directly (two lanes cover a 64-byte run of the row); the next strip's operands are
 // requested before the current strip is multiplied.  Roles and the W row permutation are those of the other
-// 32 x 32 x 64 kernels: W rows -> MFMA rows, X rows -> MFMA columns, so a lane ends with 16 consecutive output
+// streaming kernel: W rows -> MFMA rows, X rows -> MFMA columns, so a lane ends with 16 consecutive output
 // columns per column block of one output row (= lane % 32).
 #include "gemm_common.h"
 
