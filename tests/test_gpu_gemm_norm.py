@@ -1237,3 +1237,34 @@ def test_one_launch_forms_with_infinite_rows(form, variant, K, N, norm):
         assert torch.equal(q.view(torch.uint8)[~nan], xq.view(torch.uint8)[~nan])
     assert _same_bits(s[~nan], sx[~nan]) and _same_bits(out[~nan], ref[~nan])
     assert int(torch.isinf(s).sum()) == 3 + 32 + 1 and not torch.isnan(out[~torch.isinf(s) & ~nan].float()).any()
+
+
+# The large-tile kernel's operand mapping, every element: codes of 0, +-0.5, +-1, +-2 and power-of-two scales, whose sums are exact in
+# fp32, so that Y equals the product in fp64 bit for bit.  Rows, columns and K that end inside a tile, a fragment or a K step, one to
+# several K steps (the ring's start and end), several tiles per row and several rounds of tiles.
+@pytest.mark.parametrize("M,N,K", [(1, 16, 128), (17, 48, 256), (255, 240, 384), (257, 272, 512), (300, 512, 640), (70, 304, 1040),
+                                   (513, 96, 208), (33000, 256, 128)])
+@pytest.mark.parametrize("recipe", ["row", "tensor", "pow2"])
+def test_large_tile_products_are_exact_where_sums_are(M, N, K, recipe):
+    if recipe == "pow2" and (K % 128 or N % 128):
+        pytest.skip("block recipes need whole blocks")
+    g = torch.Generator().manual_seed(M + N + K)
+    codes = torch.tensor([0x00, 0x30, 0x38, 0x40, 0xB0, 0xB8, 0xC0], dtype=torch.uint8)
+    values = torch.tensor([0.0, 0.5, 1.0, 2.0, -0.5, -1.0, -2.0], dtype=torch.float64)
+    xi, wi = torch.randint(0, 7, (M, K), generator=g), torch.randint(0, 7, (N, K), generator=g)
+    pow2 = lambda *s: torch.pow(2.0, torch.randint(-3, 4, s, generator=g).double())
+    xm, wm = {"row": (B.SCALE_ROW, B.SCALE_COL), "tensor": (B.SCALE_TENSOR, B.SCALE_TENSOR),
+              "pow2": (B.SCALE_BLOCK_1x128_POW2, B.SCALE_BLOCK_128x128_POW2)}[recipe]
+    xv, wv = values[xi].to(DEV), values[wi].to(DEV)
+    if recipe == "pow2":
+        sx, sw = pow2(M, K // 128), pow2(K // 128, N // 128)
+        ref = (xv * sx.to(DEV).repeat_interleave(128, 1)) @ (wv * sw.to(DEV).repeat_interleave(128, 0).repeat_interleave(128, 1).T).T
+    else:
+        sx, sw = (pow2(M), pow2(N)) if recipe == "row" else (pow2(1), pow2(1))
+        ref = (xv @ wv.T) * sx.to(DEV)[:, None] * sw.to(DEV)[None, :]
+    v = B.variant_id("panel32_256x256_ragged" if K % 128 else "panel32_256x256")
+    d = B.make_desc(M, N, K, 1, xm, wm, B.NORM_NONE, 1e-5, v)
+    out, y = B.loka_fp8_gemm_norm(d, codes[xi].to(DEV), sx.float().to(DEV), codes[wi].to(DEV), sw.float().to(DEV), want_y=True)
+    plain, _ = B.loka_fp8_gemm_norm(d, codes[xi].to(DEV), sx.float().to(DEV), codes[wi].to(DEV), sw.float().to(DEV))
+    assert torch.equal(y.double(), ref)
+    assert torch.equal(out, ref.float().to(torch.bfloat16)) and torch.equal(plain, out)
