@@ -1268,3 +1268,48 @@ def test_large_tile_products_are_exact_where_sums_are(M, N, K, recipe):
     plain, _ = B.loka_fp8_gemm_norm(d, codes[xi].to(DEV), sx.float().to(DEV), codes[wi].to(DEV), sw.float().to(DEV))
     assert torch.equal(y.double(), ref)
     assert torch.equal(out, ref.float().to(torch.bfloat16)) and torch.equal(plain, out)
+
+
+# More rows than a 32-bit byte offset of their scales reaches, on the large-tile kernel: exact products as above, looked at where the
+# offset leaves the positive range, where it wraps, and at the ends.
+def test_large_tile_row_scales_past_32_bit_offsets():
+    M, N, K = (1 << 30) + 2348, 16, 16
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < 64 << 30:
+        pytest.skip("needs 64 GiB of free device memory")
+    g = torch.Generator(device=DEV).manual_seed(30)
+    codes = torch.tensor([0x00, 0x30, 0x38, 0x40, 0xB0, 0xB8, 0xC0], dtype=torch.uint8, device=DEV)
+    values = torch.tensor([0.0, 0.5, 1.0, 2.0, -0.5, -1.0, -2.0], dtype=torch.float64, device=DEV)
+    R = 1 << 20                                   # X repeats every R rows, the scales do not
+    xi, wi = torch.randint(0, 7, (R, K), generator=g, device=DEV), torch.randint(0, 7, (N, K), generator=g, device=DEV)
+    x = torch.empty(M, K, dtype=torch.uint8, device=DEV)
+    x[:M // R * R].view(-1, R, K)[:] = codes[xi]
+    x[M // R * R:] = codes[xi[:M % R]]
+    sx = torch.exp2(torch.randint(-3, 4, (M,), dtype=torch.int8, generator=g, device=DEV).float())
+    sw = torch.exp2(torch.randint(-3, 4, (N,), generator=g, device=DEV).float())
+    v = B.variant_id("panel32_256x256_ragged")
+    d = B.make_desc(M, N, K, 1, norm=B.NORM_NONE, variant=v)
+    assert B.loka_variant_supports(d, v)
+    out, _ = B.loka_fp8_gemm_norm(d, x, sx, codes[wi], sw)
+    y = values[xi] @ values[wi].T
+    for r0 in (0, (1 << 28) - 512, (1 << 29) - 512, (1 << 30) - 512, M - 1024):
+        assert 0 <= r0 and r0 + 1024 <= M
+        r = torch.arange(r0, r0 + 1024, device=DEV)
+        ref = y[r % R] * sx[r].double()[:, None] * sw.double()[None, :]
+        assert torch.equal(out[r0:r0 + 1024], ref.float().to(torch.bfloat16)), f"rows from {r0}"
+    del x, sx, out
+    torch.cuda.empty_cache()
+
+
+# ... and where the FP8-output form moves on to its next descriptor of row scales (every 2^20 rows): the quantized bf16 output, all rows
+def test_large_tile_fp8_output_past_one_descriptor_of_row_scales():
+    M, N, K = (1 << 20) + 300, 64, 128
+    g = torch.Generator(device=DEV).manual_seed(20)
+    x = torch.randn(M, K, generator=g, device=DEV).mul_(torch.exp2(torch.randint(-6, 7, (M, 1), generator=g, device=DEV).float())).to(torch.bfloat16)
+    xq, sx = B.loka_quantize(x, B.SCALE_ROW)
+    wq, sw = B.loka_quantize(synth.weight(K, N, seed=21).to(DEV), B.SCALE_COL, transpose_out=True)
+    d = B.make_desc(M, N, K, 1, norm=B.NORM_LAYERNORM, variant=B.variant_id("panel32_256x256"), eps=1.0)      # (eps: the row scale counts)
+    out, _ = B.loka_fp8_gemm_norm(d, xq, sx, wq, sw)
+    oq, so, _ = B.loka_fp8_gemm_norm_fp8out(d, xq, sx, wq, sw)
+    q, s = B.loka_quantize(out, B.SCALE_ROW)
+    assert torch.equal(oq, q) and torch.equal(so, s)
