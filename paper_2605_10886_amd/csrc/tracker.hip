@@ -353,12 +353,15 @@ __global__ __launch_bounds__(512) void tracker_scatter_kernel(const TrackerParam
         }
         if (diag) {
             // position pos holds column 8 (pos % 32) + pos / 32
-            const int pos = tid & 255, col = 8 * (pos & 31) + (pos >> 5);
-            red[(tid >> 8) * TRK_T + col] = cs;
+            // (from a copy of its own: the ids' parts would be kept across the main loop, in two registers that are spilled)
+            int tid_e = tid;
+            asm volatile("" : "+v"(tid_e));
+            const int pos = tid_e & 255, col = 8 * (pos & 31) + (pos >> 5);
+            red[(tid_e >> 8) * TRK_T + col] = cs;
             __syncthreads();
-            if (tid < TRK_T) {
-                p.colsum[static_cast<int64_t>(id) * TRK_T + tid] = red[tid] + red[TRK_T + tid];
-                const int k = ti * TRK_T + tid;
+            if (tid_e < TRK_T) {
+                p.colsum[static_cast<int64_t>(id) * TRK_T + tid_e] = red[tid_e] + red[TRK_T + tid_e];
+                const int k = ti * TRK_T + tid_e;
                 if (id < p.pairs && k < p.K) p.mu_old[k] = p.mu[k];          // id = range * pairs + pair
             }
         }

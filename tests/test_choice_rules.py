@@ -238,6 +238,13 @@ def test_strips_are_awaited_without_the_stores_behind_them(tmp_path):
         assert waits and min(waits) == 2 * nb, (nb, ks, waits)
 
 
+def test_tracker_contraction_keeps_its_values_in_registers(tmp_path):
+    # 128 accumulators, a stage in flight and two sets of fragments fill a wave's 256 registers: nothing of it goes to scratch
+    _device_assembly("tracker.hip", tmp_path / "tracker.s")
+    m = re.search(r"\.amdhsa_kernel \w*tracker_scatter_kernel\w*\n(.*?)\.end_amdhsa_kernel", (tmp_path / "tracker.s").read_text(), re.S)
+    assert re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", m.group(1)).group(1) == "0"
+
+
 def _chosen(form, M, N, K, norm=B.NORM_LAYERNORM, batch=1):
     """Name of the kernel behind variant = -1 for a call of that form (the library's own rule, a C++ function of the descriptor)."""
     fn = B.lib().loka_default_variant if form == "bf16" else getattr(B.lib(), {"fp8out": "_ZN4loka22variant_fp8out_defaultEPK14loka_gemm_desc",
