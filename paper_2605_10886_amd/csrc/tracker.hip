@@ -59,8 +59,10 @@ TrackerPlan tracker_plan(int64_t B, int64_t K) {
     if (max_s > 256) max_s = 256;
     // estimated time in units of one stage (about 1.2 us): rounds * (stages per workgroup + start-up) for the
     // scatter, and so much per partial tile, written and then read back by the merge: 256 KB, of a diagonal tile 144
-    // (one tile: its merge is a few workgroups and takes longer with every range)
-    const double tiles_cost = pl.T == 1 ? 0.06 : 0.08 * (pl.pairs - pl.T) + 0.05 * pl.T;
+    // (one tile: its merge is a few workgroups and takes longer with every range).  More from 8 column tiles on, where the
+    // partial tiles are 100 MB and more and the plans' estimates lie close together (ranges by 0.08 and 0.05, by 0.1, us:
+    // 65536 x 2560 9 473, 4 455; 8000 x 2048 7 60.4, 6 59.7; 65536 x 4096 7 1180, 250 MB, 5 1180, 178 MB).
+    const double tiles_cost = pl.T == 1 ? 0.06 : pl.T >= 8 ? 0.1 * pl.pairs : 0.08 * (pl.pairs - pl.T) + 0.05 * pl.T;
     int64_t best_s = 1;
     double best = 1e300;
     for (int64_t sp = 1; sp <= max_s; ++sp) {

@@ -245,6 +245,14 @@ def test_tracker_contraction_keeps_its_values_in_registers(tmp_path):
     assert re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", m.group(1)).group(1) == "0"
 
 
+@pytest.mark.parametrize("batch,features,ranges", [(65536, 4096, 5), (65536, 2560, 4), (8000, 2048, 6), (32768, 1024, 25), (65536, 256, 128)])
+def test_tracker_ranges(batch, features, ranges):
+    # scratch: a 256 KB partial tile and its column sums per pair of column tiles and range, and the mean
+    tiles = (features + 255) // 256
+    want = ranges * tiles * (tiles + 1) // 2 * 256 * (256 * 4 + 8) + tiles * 256 * 4
+    assert B.lib().loka_tracker_update_workspace(batch, features) == want
+
+
 def _chosen(form, M, N, K, norm=B.NORM_LAYERNORM, batch=1):
     """Name of the kernel behind variant = -1 for a call of that form (the library's own rule, a C++ function of the descriptor)."""
     fn = B.lib().loka_default_variant if form == "bf16" else getattr(B.lib(), {"fp8out": "_ZN4loka22variant_fp8out_defaultEPK14loka_gemm_desc",
