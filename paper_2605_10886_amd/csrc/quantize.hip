@@ -508,14 +508,16 @@ __global__ void e4m3_from_f32_kernel(const float* __restrict__ t, uint8_t* __res
 }
 
 // ---------------------------------------------------------------------------------
-// Whether X is read past the caches.  A plain read is the faster one by itself until X and its codes outgrow the last-level cache
-// (rows x columns, streamed -> plain, us: 65536 x 128 6.6 -> 6.1, 16384 x 512 6.9 -> 6.4, 8192 x 2048 10.3 -> 10.1; 65536 x 1024
-// 33.2 -> 32.4, but 32768 x 4096 61 -> 72), but X then stays in that cache in the place of what the calls behind it
-// read: a training step of 65536 x 256 x 1024 (M x K x N) takes 198.6 us with all streamed, 198.1 with X (32 MB) plain and 223 with
-// dY (128 MB) plain too, one of 57472 x 896 x 1664 516, 518 and 554; the layer 8192 x 2048 x 2048 (X 32 MB) 53.9 streamed and 51.6
-// plain, the probe on 16384 x 1024 x 1024 109.2 and 107.  So streamed from 64 MB, and from 16 MB where rows are short: such layers
-// write more than they read (on inputs new in every pass, the mlp 65536 x 256 x 1024 x 256 90.4 plain and 88.9 streamed).
-static bool read_streamed(int64_t rows, int64_t cols) { return rows * cols >= int64_t(1) << (cols <= 256 ? 23 : 25); }
+// Whether X is read past the caches.  Under 64 MB a plain read is as fast or faster whatever is in the last-level cache: a pass, us,
+// streamed -> plain, on one X in every pass | on an X that no cache holds | on an X that the kernel before has written (with that
+// kernel): quantization alone 65536 x 512 19.3 -> 17.6 | 19.2 -> 19.0 | 42.4 -> 42.0, 16384 x 1024 9.1 -> 9.1 | 10.6 -> 10.8 | 24.5 -> 23.6,
+// 65536 x 256 9.1 -> 9.0 | 10.6 -> 10.5 | 24.5 -> 23.2; layers (M x K x N) 8192 x 2048 x 2048 in block scales 58.5 -> 56.5 | 55.7 -> 54.2 |
+// 66.3 -> 66.3, 65536 x 384 x 384 55.6 -> 52.0 | 53.6 -> 51.8 | 69.6 -> 69.2, 65536 x 256 x 1024 57.9 -> 54.9 | 55.1 -> 53.3 | 67.2 -> 65.9;
+// training step 16384 x 512 x 512 81.8 -> 79.0 | 81.8 -> 81.2 | 90.0 -> 88.6; probe 16384 x 1024 x 1024 120 -> 118 | 115 -> 113 | 127 -> 125.
+// (The other way: 65536 x 128 x 512 32.0 -> 31.7 | 31.2 -> 31.7 | 35.4 -> 35.1, the mlp 65536 x 128 x 512 x 128 51.7 -> 52.6 | 51.7 -> 53.0 |
+// 60.2 -> 60.0, the mlp 65536 x 256 x 1024 x 256 91.2 -> 90.8 | 90.7 -> 91.2 | 104.0 -> 104.1.)  From 64 MB on X stays in that cache in the place of what the calls behind it read: a training step of 57472 x 896 x 1664 takes 551 us
+// with X (103 MB) and dY (191 MB) streamed and 569 with both plain, one of 65536 x 256 x 1024 (dY 128 MB) 207 and 225.
+static bool read_streamed(int64_t rows, int64_t cols) { return rows * cols >= int64_t(1) << 25; }
 
 template <bool B128>
 static void launch_rows(const uint16_t* x, int64_t rows, int64_t cols, int64_t ld, uint8_t* q, float* scales,
