@@ -611,18 +611,19 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     v4f s4q[NI][2];                                         // SQ16: columns 4 q .. of fragment (ni, t), row l16 of (mi, x): 24
     float sxq[MI][2];                                       // registers, 36 in the layout behind the exchange
     if constexpr (SQ16 && !BLOCKWISE) {
-        // (buffer loads: one 32-bit offset per lane; columns and rows past the last read as zeros)
+        // (buffer loads: one 32-bit offset per lane; columns past the last read as zeros)
         const int q = lane >> 4, r16 = lane & 15;
         const __amdgpu_buffer_rsrc_t sw_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(swg), 0, tensor_w ? 4 : n_o * 4, 0x00020000);
         const float sw_all = swg[0];
-        // (the rows' descriptor starts at the tile: the scales of all of X can be more bytes than 32 bits count.  With FP8 output, at
-        // a multiple of 2^20 rows, in which the tile lies: 8192 x 1024 x 2048 31.2 us, from the tile on 31.7; bf16 output
-        // 16384 x 3072 x 1024 99.7 and 98.3)
+        // (the rows' descriptor starts at the tile: the scales of all of X can be more bytes than 32 bits count.  Rows past the last
+        // take the first one's scale: a bound that follows from M costs one more round of argument loads at the start, 2 % of
+        // a launch of one round.  With FP8 output it starts at a multiple of 2^20 rows, in which the tile lies, and ends with M:
+        // 8192 x 1024 x 2048 31.2 us, from the tile on 31.6.)
         constexpr int kScaleRows = FP8OUT ? 1 << 20 : BM;
         static_assert(kScaleRows % BM == 0, "a tile's rows have one descriptor");
         const int m_at = FP8OUT ? m0 & (kScaleRows - 1) : 0, m_base = m0 - m_at, m_left = p.M - m_base;
-        const __amdgpu_buffer_rsrc_t sx_rsrc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(tensor_x ? sxg : sxg + m_base), 0, tensor_x ? 4 : (m_left < kScaleRows ? m_left : kScaleRows) * 4, 0x00020000);
+        const int sx_bytes = !FP8OUT ? BM * 4 : tensor_x ? 4 : (m_left < kScaleRows ? m_left : kScaleRows) * 4;
+        const __amdgpu_buffer_rsrc_t sx_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(tensor_x ? sxg : sxg + m_base), 0, sx_bytes, 0x00020000);
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
@@ -636,7 +637,7 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
 #pragma unroll
             for (int x = 0; x < 2; ++x) {
                 const int r = m_at + wave_m * WM + mi * 32 + 16 * x + r16;
-                sxq[mi][x] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sx_rsrc, tensor_x ? 0 : r * 4, 0, 0));
+                sxq[mi][x] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(sx_rsrc, tensor_x || (!FP8OUT && r >= m_left) ? 0 : r * 4, 0, 0));
             }
     }
     __builtin_amdgcn_sched_barrier(0);
