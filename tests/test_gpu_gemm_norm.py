@@ -1313,3 +1313,30 @@ def test_large_tile_fp8_output_past_one_descriptor_of_row_scales():
     oq, so, _ = B.loka_fp8_gemm_norm_fp8out(d, xq, sx, wq, sw)
     q, s = B.loka_quantize(out, B.SCALE_ROW)
     assert torch.equal(oq, q) and torch.equal(so, s)
+
+
+# The same with block scales, which need whole blocks, powers of two in both recipes: scales fetched block by block and (K a multiple of
+# 512) four blocks at a time, one to several K steps, a last row tile of one row to a full one, several rounds of tiles, and K in
+# ranges (on tiles of 256: 16 ranges of 16 K steps, four blocks at a time and, with a last range of 10, one).  Products are multiples
+# of 2^-4 and |sums| at most 2^4 K < 2^20: exact in fp32 in any order, in units of any of the scales.
+@pytest.mark.parametrize("variant,M,N,K", [("panel32_256x256", M, N, K) for M, N, K in (
+    (1, 128, 128), (17, 256, 256), (255, 128, 384), (257, 256, 512), (300, 512, 1024), (513, 384, 640), (256, 640, 2048),
+    (33000, 256, 128), (33000, 256, 512), (33000, 384, 384))] + [("splitk128x128s2", 1000, 1024, 32768), ("splitk128x128s2", 1000, 1024, 32000)])
+@pytest.mark.parametrize("recipe", ["block", "block_pow2"])
+def test_large_tile_products_with_block_scales_are_exact(variant, M, N, K, recipe):
+    g = torch.Generator(device=DEV).manual_seed(M + N + K)
+    codes = torch.tensor([0x00, 0x30, 0x38, 0x40, 0xB0, 0xB8, 0xC0], dtype=torch.uint8, device=DEV)
+    values = torch.tensor([0.0, 0.5, 1.0, 2.0, -0.5, -1.0, -2.0], dtype=torch.float64, device=DEV)
+    xi, wi = torch.randint(0, 7, (M, K), generator=g, device=DEV), torch.randint(0, 7, (N, K), generator=g, device=DEV)
+    pow2 = lambda *s: torch.exp2(torch.randint(-1, 2, s, generator=g, device=DEV).float())
+    sx, sw = pow2(M, K // 128), pow2(K // 128, N // 128)
+    ref = (values[xi] * sx.double().repeat_interleave(128, 1)) @ (values[wi] * sw.double().repeat_interleave(128, 0).repeat_interleave(128, 1).T).T
+    v = B.variant_id(variant)
+    d = B.make_desc(M, N, K, 1, *RECIPES[recipe], B.NORM_NONE, 1e-5, v)
+    assert B.loka_variant_supports(d, v)
+    if variant == "splitk128x128s2":        # (16 ranges; tiles of 128 have 8)
+        assert B.lib().loka_fp8_gemm_norm_workspace(ctypes.byref(d)) == 16 * M * N * 4
+    out, y = B.loka_fp8_gemm_norm(d, codes[xi], sx, codes[wi], sw, want_y=True)
+    plain, _ = B.loka_fp8_gemm_norm(d, codes[xi], sx, codes[wi], sw)
+    assert torch.equal(y.double(), ref)
+    assert torch.equal(out, ref.float().to(torch.bfloat16)) and torch.equal(plain, out)
