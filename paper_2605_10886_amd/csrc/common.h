@@ -108,7 +108,7 @@ __device__ __forceinline__ void row_broadcasts(float v, float (&out)[T]) {
 }
 
 // Maximum of unsigned values over groups of GL consecutive lanes (16, 32 or 64), in all of them: moves within 16 lanes, row and
-// half swaps, no LDS round trip.
+// half swaps, no LDS round trip.  (Of magnitudes' bits: a NaN is the largest, in place of fmaxf's rule in quantize.hip's lanes_max.)
 typedef unsigned u32_pair __attribute__((ext_vector_type(2)));
 template <int GL>
 __device__ __forceinline__ unsigned lanes_max_bits(unsigned a) {

@@ -1231,6 +1231,11 @@ static bool panel32_layout(const VariantInfo& vi) { return vi.name == kPanel32Na
 // at the 99th percentile (beyond the range 1.1 and 23); the two former sets 1.2 and 20.9 (3.6 and 61), with weights and a rule
 // for the strip kernel on top, and 1.55 and 24.5 (3.8 and 63).  Of 14991 choices 136 and 125 are more than 5 % slower
 // than theirs, 597 and 962 more than 5 % faster.  profiles/variant_times.csv has the times of 1997 shapes.
+// The large-tile kernel, and the split K of 256-tiles, took the 16 x 16 x 128 instruction afterwards (plain and power-of-two scales):
+// with plain scales 0.3 - 0.6 us (2 - 5 %) longer in one round of few K steps, 0 - 5 % shorter in two rounds or over 32 steps.  The
+// figures below are those of the former instruction, and kept: at the 1997 shapes, every variant timed again, the choice is 0.47 % over the fastest in the
+// geometric mean and 11 % at the 99th percentile, and at the 609 of them with block scales, timed with power-of-two scales,
+// which share the block figures, 0.38 and 10 %.
 // Fixed figures for an MI355X, not the running device's: workspace sizes follow from the choice.
 struct CostRow { float start, round, step, full, lng, ragged, x, w, out, ln, norm, out32, once, norm_out, xr, wr, far, rec; };
 struct VariantCost { const char* name; int per_cu; CostRow plain, block; };
@@ -1290,7 +1295,8 @@ static const SplitkCost kSplitkCosts[3][2] = {
     {{5.63f, .641f, .558f, 2.97f, .826f, 4.05f, 2.12f}, {7.17f, 1.17f, .344f, 2.72f, 0.f, 2.41f, 2.65f}},
     {{19.2f, 1.02f, 0.f, .731f, 1.42f, 2.78f, 4.16f}, {15.f, 1.36f, .0879f, .977f, .417f, 0.f, 5.41f}}};
 // ... and what decides between tiles of 128 and 256 on the long-range form.  An earlier fit, kept: a caller that names the
-// variant gets the same tiles (the two fits differ at 8 of 364 shapes).
+// variant gets the same tiles (the two fits differ at 8 of 364 shapes).  On the kernels as they are its tile is, over 489 shapes, 0.6 %
+// slower than the better one in the geometric mean, 9 % at the 99th percentile (block scales, 231 shapes: 0.6 and 7 %).
 static const SplitkCost kSplitkTileCosts[2][2] = {{{10.7f, 0.f, .79f, 1.78f}, {12.f, .12f, 1.13f, 1.37f, .66f}},
                                                   {{15.8f, .2f, 1.08f, 1.06f, .27f}, {14.8f, .66f, 1.38f, .85f, .63f}}};
 

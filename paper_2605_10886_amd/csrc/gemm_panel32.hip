@@ -9,7 +9,10 @@
 // 2.3 - 2.5 PFLOP/s and the second to 3.7 - 4.0.  Whole launches, M x N x K, us, 32 x 32 x 64 -> 16 x 16 x 128 (with the
 // main loop below): 32768 x 4096 x 4096 472 -> 451, without a norm 460 -> 434, with FP8 output 468 -> 446; 16384 x 2048 x 8192
 // 213 -> 202; 2048 x 1024 x 123200 in K ranges 245 -> 230; 12000 x 2560 x 3072 93.7 -> 90.8; 8192 x 2048 x 2048 36.5 -> 35.7;
-// K = 256 and 512 the same within 1 %.  Power-of-two block scales 32768 x 4096 x 4096 511 -> 488, 8192 x 2048 x 2048 38.5 -> 36.6.
+// K = 256 and 512 the same within 1 % where a workgroup has several tiles.  The exchange into the 32 x 32 layout costs 0.3 - 0.6 us a
+// tile: a launch of one round of few K steps is 2 - 5 % longer (over 496 shapes beside the former form, medians: one round to 4 K steps
+// 1.04, to 16 1.02, more 0.99; two rounds 1.02, 0.98, 0.96; more 1.00, 0.98, 0.97).  Power-of-two block scales 32768 x 4096 x 4096
+// 511 -> 488, 8192 x 2048 x 2048 38.5 -> 36.6.
 //
 // Work split: waves 0..3 own rows 0..127 of the tile, waves 4..7 rows 128..255; wave w % 4 owns columns
 // [64 (w % 4), +64).  Per K step of 128 bytes a wave runs 8 (row tiles of 16) x 4 (column tiles of 16) = 32 MFMAs, or
@@ -140,8 +143,8 @@ __device__ __forceinline__ void panel32_quantize_own_rows(const GemmParams& p, i
 // bytes per fragment and the same matrix-pipe time per K step of 128 bytes, so the same main loop keeps the pipe full).
 // RAGK: K need not be a multiple of the 128-byte step: in the last step the lanes whose 16-byte chunk lies past the end
 // of the row read zeros, in both operands.
-// YOUT false: the caller wants no fp32 Y, and the code that would store it is left out (244 instead of 249 registers;
-// quantize + GEMM at 32768 x 4096 x 4096, beside a kernel that stored Y straight from registers: 1.1 and 0.5 % slower with the code in, 0.3 and
+// YOUT false: the caller wants no fp32 Y, and the code that would store it is left out (230 instead of 242 registers;
+// in the 32 x 32 form, quantize + GEMM at 32768 x 4096 x 4096, beside a kernel that stored Y straight from registers: 1.1 and 0.5 % slower with the code in, 0.3 and
 // 0.4 % without it).
 template <int EPI, int BW, int F8, bool QPRO = false, bool BF16 = false, bool RAGK = (EPI == EPI_SPLITK || BF16) && BW == 0, bool YOUT = true, bool QUAD = false>
 __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
@@ -502,11 +505,12 @@ __global__ __launch_bounds__(512) void gemm_panel32_kernel(const GemmParams p) {
     } while (0)
 
     // ---- main loop.  LDS holds a ring of five 32 KB entries X(0) W(0) X(1) W(1) X(2) ...; entry e lives in
-    // slot e % 5.  One barrier per K step, in its middle, when every wave has read X(k) and W(k) completely and
-    // every wave's share of X(k + 1), W(k + 1) has landed.  The slot of X(k) then takes W(k + 2) (loads issued
-    // in the second half of step k), the slot of W(k) takes X(k + 3) (first half of step k + 1): an X entry is
-    // requested 1.5 steps before its first read, a W entry one step (half the bytes of a stage: the round
-    // trip through L2 under load is ~1 us for 64 KB, ~0.6 us for 32 KB; a step is ~1.2 us).
+    // slot e % 5.  One barrier per K step, when every wave has read X(k) and W(k) completely and every wave's share of
+    // X(k + 1), W(k + 1) has landed: in the step's middle in the 32 x 32 form, which reads a half step ahead; in front of its last
+    // quarter in the 16 x 16 form, whose pairs read one pair ahead and whose last pair reads X(k + 1) and W(k + 1).
+    // The slot of X(k) then takes W(k + 2) (requested behind the barrier), the slot of W(k) takes X(k + 3) (first half, or
+    // second quarter, of step k + 1): an X entry is requested 1.5 steps before its first read, a W entry one step (half the
+    // bytes of a stage: the round trip through L2 under load is ~1 us for 64 KB, ~0.6 us for 32 KB; a step is ~1.2 us).
     // All of a wave's loads return in issue order, so "vmcnt(4)" = everything but the newest entry's share.
     auto mod5 = [](int v) { return v >= 5 ? v - 5 : v; };
     // entry e of a tile lives in slot (e + 1) % 5: slot 0, which the epilogue uses as scratch, is the last to fill

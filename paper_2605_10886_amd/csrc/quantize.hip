@@ -30,6 +30,7 @@ __device__ __forceinline__ u32x4 load_chunk(const uint16_t* p) {
 }
 
 // Maximum over groups of GL consecutive lanes (16, 32 or 64), in all of them: moves within 16 lanes, row and half swaps.
+// (lanes_max_bits is the same on the bits of magnitudes: there a NaN is the largest value, here fmaxf leaves it out.)
 template <int GL>
 __device__ __forceinline__ float lanes_max(float a) {
     auto moved = [&](auto ctrl) __attribute__((always_inline)) {
@@ -49,6 +50,7 @@ __device__ __forceinline__ float lanes_max(float a) {
     }
     return a;
 }
+
 // ---------------------------------------------------------------------------------
 // Single pass: TPR lanes share one row (TPR = 16, 32 or 64); each lane holds CPL
 // chunks of 8 consecutive bf16 (one 16-byte load each); a wave works on RU row sets at
@@ -82,8 +84,8 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const uint16_t* __restr
             }
         }
     };
-    // (each kind of read ends in a line of its own: the compiler merges the ends of the two branches otherwise, and an eighth of
-    // what is to be streamed went through the caches: training step 57472 x 896 x 1664, M x K x N, 522 -> 540 us)
+    // (each kind of read ends in a line of its own: the compiler merges the ends of the two branches otherwise, and a lane's last
+    // load, an eighth to a quarter of what is to be streamed, went through the caches: training step 57472 x 896 x 1664, M x K x N, 522 -> 540 us)
     if (streamed) { load(std::true_type{}); asm volatile("; streamed"); }
     else { load(std::false_type{}); asm volatile("; through the caches"); }
     // The groups of a 16-lane row: T.  Every lane has the maxima of all of them after the exchanges (in the vector unit, no LDS
@@ -508,15 +510,24 @@ __global__ void e4m3_from_f32_kernel(const float* __restrict__ t, uint8_t* __res
 }
 
 // ---------------------------------------------------------------------------------
-// Whether X is read past the caches.  Under 64 MB a plain read is as fast or faster whatever is in the last-level cache: a pass, us,
+// Whether X is read past the caches.  Under 64 MB a plain read is as fast or faster whatever the last-level cache holds.  A pass, us,
 // streamed -> plain, on one X in every pass | on an X that no cache holds | on an X that the kernel before has written (with that
-// kernel): quantization alone 65536 x 512 19.3 -> 17.6 | 19.2 -> 19.0 | 42.4 -> 42.0, 16384 x 1024 9.1 -> 9.1 | 10.6 -> 10.8 | 24.5 -> 23.6,
-// 65536 x 256 9.1 -> 9.0 | 10.6 -> 10.5 | 24.5 -> 23.2; layers (M x K x N) 8192 x 2048 x 2048 in block scales 58.5 -> 56.5 | 55.7 -> 54.2 |
-// 66.3 -> 66.3, 65536 x 384 x 384 55.6 -> 52.0 | 53.6 -> 51.8 | 69.6 -> 69.2, 65536 x 256 x 1024 57.9 -> 54.9 | 55.1 -> 53.3 | 67.2 -> 65.9;
-// training step 16384 x 512 x 512 81.8 -> 79.0 | 81.8 -> 81.2 | 90.0 -> 88.6; probe 16384 x 1024 x 1024 120 -> 118 | 115 -> 113 | 127 -> 125.
-// (The other way: 65536 x 128 x 512 32.0 -> 31.7 | 31.2 -> 31.7 | 35.4 -> 35.1, the mlp 65536 x 128 x 512 x 128 51.7 -> 52.6 | 51.7 -> 53.0 |
-// 60.2 -> 60.0, the mlp 65536 x 256 x 1024 x 256 91.2 -> 90.8 | 90.7 -> 91.2 | 104.0 -> 104.1.)  From 64 MB on X stays in that cache in the place of what the calls behind it read: a training step of 57472 x 896 x 1664 takes 551 us
-// with X (103 MB) and dY (191 MB) streamed and 569 with both plain, one of 65536 x 256 x 1024 (dY 128 MB) 207 and 225.
+// kernel):
+//   quantization alone        49152 x 512                14.9 -> 13.8 | 16.0 -> 15.9 | 33.3 -> 32.6
+//                             16384 x 1024                9.1 ->  9.1 | 10.6 -> 10.8 | 24.5 -> 23.6
+//                             65536 x 256                 9.1 ->  9.0 | 10.6 -> 10.5 | 24.5 -> 23.2
+//   layer (M x K x N)         65536 x 256 x 768          54.5 -> 51.7 | 52.5 -> 51.1 | 65.1 -> 63.0
+//                             65536 x 384 x 384          55.6 -> 52.0 | 53.6 -> 51.8 | 69.6 -> 69.2
+//                             65536 x 128 x 512          32.0 -> 31.7 | 31.2 -> 31.7 | 35.4 -> 35.1
+//   ... in block scales       8192 x 2048 x 2048         58.5 -> 56.5 | 55.7 -> 54.2 | 66.3 -> 66.3
+//                             65536 x 256 x 256          37.3 -> 28.5 | 36.8 -> 28.8 | 42.3 -> 41.0
+//   two layers                65536 x 256 x 512 x 256    66.4 -> 64.2 | 66.2 -> 65.5 | 80.1 -> 78.2
+//                             65536 x 256 x 1024 x 256   93.7 -> 91.5 | 93.3 -> 92.6 | 105.4 -> 104.2 (three X in turn 91.6 -> 92.5)
+//                             65536 x 128 x 512 x 128    51.7 -> 52.6 | 51.7 -> 53.0 | 60.2 -> 60.0
+//   training step             16384 x 512 x 512          81.8 -> 79.0 | 81.8 -> 81.2 | 90.0 -> 88.6
+//   probe                     16384 x 1024 x 1024         120 -> 118  |  115 -> 113  |  127 -> 125
+// From 64 MB on X stays in that cache in the place of what the calls behind it read: a training step of 57472 x 896 x 1664 takes
+// 551 us with X (103 MB) and dY (191 MB) streamed and 569 with both plain, one of 65536 x 256 x 1024 (dY 128 MB) 207 and 225.
 static bool read_streamed(int64_t rows, int64_t cols) { return rows * cols >= int64_t(1) << 25; }
 
 template <bool B128>

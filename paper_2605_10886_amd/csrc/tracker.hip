@@ -511,8 +511,9 @@ loka_status tracker_update_launch(const void* x, int64_t B, int64_t K, int64_t l
         tracker_merge_kernel<decltype(parts)::value><<<dim3(pl.pairs, 64), 256 * decltype(parts)::value, 0, s>>>(
             p.partial, colsum, p.mu_old, pl.T, pl.pairs, pl.splits, static_cast<int>(K), B, ratio, coef, mu, sigma);
     };
-    // Four threads per run where workgroups are few and ranges many (us, one thread -> four: 65536 x 256, 103 ranges, 33.0 -> 31.8,
-    // 18786 x 456, 33, 28.4 -> 27.6; but 32768 x 1024, four column tiles and 19 ranges, 57.7 -> 62.5, 2000 x 64, 16, 13.2 -> 14.1)
+    // Four threads per run where workgroups are few and ranges many (us, one thread -> four: 65536 x 256, 128 ranges, 33.8 -> 32.5,
+    // 16384 x 512, 37, 28.1 -> 27.1, 18786 x 456, 42, 28.2 -> 27.7; but 12000 x 512, 32, 28.7 -> 29.1, 8000 x 512, 25, 24.8 -> 25.2,
+    // 2000 x 64, 16, 13.5 -> 14.4, and with three column tiles and more 65536 x 768, 41, 64.8 -> 66.8, 32768 x 1024, 25, 56.2 -> 61.5)
     if (pl.T <= 2 && pl.splits >= 32) merge(std::integral_constant<int, 4>{});
     else merge(std::integral_constant<int, 1>{});
     return hipGetLastError() == hipSuccess ? LOKA_OK : LOKA_ERR_HIP;
