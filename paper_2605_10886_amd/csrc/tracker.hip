@@ -43,7 +43,7 @@ constexpr int TRK_PLAN_SLOTS = 256;             // cost model only: workgroups a
 // Work decomposition: workgroup = (tile pair ti <= tj, one of S equal row ranges of the batch).  All
 // workgroups in flight walk their rows at the same pace, so the workgroups of an XCD that share a column
 // tile find it in that XCD's L2.  S trades the rounding of pairs * S to whole rounds of 256 workgroups
-// against the fp32 partial tile every workgroup leaves in the workspace (256 KB written and read back).
+// against the fp32 partial tile every workgroup leaves in the workspace (256 KB written and read back, 144 of a diagonal one).
 struct TrackerPlan {
     int T, pairs, splits;
     int64_t rows_per_split;
